@@ -88,6 +88,12 @@ void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y
                        int Cout, int H, int W, int k, int stride);
 void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* x, float* part,
                        float* G, int N, int Cin, int Cout, int H, int W, int k, int stride);
+// The LDS-staged kernels behind the calls above (kernels_f32_conv_lds.hip); false / 0 where no block shape fits.
+bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
+                      const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S);
+int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S);
+void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const float* x, float* part, int N, int Cin, int Cout,
+                    int H, int W, int KS, int S);
 // 7x7 dense conv with fewer than 8 input channels (ResNet's stem) on the matrix cores: the contraction index is
 // the flattened (ci, u, v); Wp = pw_pack of W as the [Cout][Cin*49] matrix.  Forward and weight gradient
 // (partials [chunk][Cout][Cin*49] in `part`, G may be NULL: the caller reduces).

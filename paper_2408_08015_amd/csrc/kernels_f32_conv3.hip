@@ -561,6 +561,7 @@ bool conv_mfma_supported(int Cin, int Cout, int k, int stride, int pad, int grou
 size_t conv_mfma_pack_floats(int Mdim, int Kdim, int k) { return (size_t)k * k * pw_pack_floats(Mdim, Kdim); }
 
 int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride) {
+  if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride)) return lp;
   const int HWo = out_dim(H, k, stride) * out_dim(W, k, stride);
   return N * cdiv(HWo, 4 * c3_pxw(N, Cin, Cout, HWo));
 }
@@ -571,6 +572,7 @@ size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int str
 
 void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y, const float* bias, int N, int Cin,
                        int Cout, int H, int W, int k, int stride) {
+  if (conv_lds_product(st, product_name(k, stride), false, Wp, x, y, bias, N, Cin, Cout, H, W, k, stride)) return;
   const int Ho = out_dim(H, k, stride), Wo = out_dim(W, k, stride);
   if (k == 3) launch_product<3, false>(st, product_name(k, stride), Wp, x, y, bias, N, Cin, Cout, Ho, Wo, H, W, stride);
   else launch_product<1, false>(st, product_name(k, stride), Wp, x, y, bias, N, Cin, Cout, Ho, Wo, H, W, stride);
@@ -579,9 +581,16 @@ void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y
 void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* x, float* part,
                        float* G, int N, int Cin, int Cout, int H, int W, int k, int stride) {
   const int Ho = out_dim(H, k, stride), Wo = out_dim(W, k, stride);
-  if (dx) {
+  if (dx && !conv_lds_product(st, product_name(k, stride), true, Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, k, stride)) {
     if (k == 3) launch_product<3, true>(st, product_name(k, stride), Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, Ho, Wo, stride);
     else launch_product<1, true>(st, product_name(k, stride), Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, Ho, Wo, stride);
+  }
+  const size_t n = (size_t)Cin * Cout * k * k;
+  if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride)) {
+    conv_lds_wgrad(st, k == 3 ? "conv3x3_wgrad_mfma_f32_kernel" : "conv1x1s2_wgrad_mfma_f32_kernel", g, x, part, N, Cin, Cout, H, W,
+                   k, stride);
+    if (G) KLAUNCH(conv3x3_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, part, G, n, lp);
+    return;
   }
   C3WgArgs w;
   w.g = g; w.x = x; w.part = part;
@@ -592,7 +601,6 @@ void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float*
   if (k == 3 && stride == 1 && W % 4 == 0) KLAUNCH(conv3x3_wgrad_vec_mfma_f32_kernel, grid, dim3(256), 0, st, w);
   else if (k == 3) KLAUNCH_NAMED("conv3x3_wgrad_mfma_f32_kernel", (conv_wgrad_mfma_f32_kernel<3>), grid, dim3(256), 0, st, w);
   else KLAUNCH_NAMED("conv1x1s2_wgrad_mfma_f32_kernel", (conv_wgrad_mfma_f32_kernel<1>), grid, dim3(256), 0, st, w);
-  const size_t n = (size_t)Cin * Cout * k * k;
   if (G) KLAUNCH(conv3x3_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, part, G, n, (int)grid.x);
 }
 

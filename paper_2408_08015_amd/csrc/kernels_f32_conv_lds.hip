@@ -1,0 +1,580 @@
+// fp32 dense convolutions on the matrix cores with the pixels staged in LDS: 3x3 pad 1 (stride 1 or 2) and 1x1
+// stride 2, forward, input gradient and weight gradient.
+//
+// v_mfma_f32_32x32x2 takes 64 cycles for 2 + 2 operand words per lane, so the matrix cores are the bound as soon as
+// operands arrive with few instructions: nine taps are nine shifted reads of one LDS copy of the pixels.
+//
+// LDS copy: "virtual rows".  Row h of sample n of the operand tensor is virtual row n*(XH+1) + h + 1; the rows
+// between two samples and around the first and last one are zero, and every row has a zero on either side (pitch
+// XW + 2).  A tile of consecutive result pixels needs a contiguous range of virtual rows, whatever samples it
+// touches, and a tap is one constant offset from a pixel's position: no border test in the product loop.
+#include <algorithm>
+#include <array>
+#include <cmath>
+#include <map>
+
+#include "device_utils.h"
+#include "kernels.h"
+#include "prof.h"
+
+namespace ast {
+
+namespace {
+
+inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
+__host__ __device__ constexpr int round_up64(int v) { return (v + 63) & ~63; }
+// floor(n / d) = mulhi(n, reciprocal(d)) while n * d < 2^32
+inline unsigned reciprocal(unsigned d) { return d == 1 ? 0xffffffffu : (unsigned)(((1ull << 32) + d - 1) / d); }
+constexpr size_t kProductLds = 128 * 1024, kWgradLds = 156 * 1024;
+
+// ------------------------------------------------------------------ product (forward / input gradient)
+// One class of result pixels: all of them, or (input gradient of a stride-2 conv) those of one row / column
+// parity, which are reached by the same taps.  The taps are the product of a row list and a column list: entry k of
+// `rows` is the byte (tap row u << 4) | (dr + 1), with dr the shift of the operand row in [-1, 1].
+struct LdsClass {
+  int PH, PW, oy, ox;     // pixels of the class, first result row / column
+  unsigned npix;          // N * PH * PW
+  unsigned rows, cols;
+  int nr, nc;
+};
+struct LdsArgs {
+  const float4* Wp;       // packed weight copies (pw_pack layout), one per tap, tap_stride words apart
+  const float* X;         // operand tensor [N][Kdim][XH][XW], or every XS-th row and column of a larger one
+  float* Y;               // result tensor  [N][Mdim][OH][OW]
+  const float* bias;
+  LdsClass cls[4];
+  unsigned tap_stride, x_bytes, XHW;  // XHW: words of an operand plane in memory; XRW of a row
+  int N, XH, XW, XS, XRW, OH, OW, SI, SO, Kdim, Mdim, KG, KS;
+  int WN, WK, rows, RW, NP, PL, CH;
+  unsigned rRW, rXH1;
+};
+
+typedef __attribute__((address_space(3))) void lds_void;
+constexpr unsigned kOutside = 0x80000000u;  // buffer offset beyond every extent: the copy writes zeros
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t r, float* dst, unsigned voff, unsigned soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 4, voff, soff, 0, 0);
+}
+// byte offset (without the channel part) of position `pos` of the virtual rows vr0, vr0 + 1, ... (pitch XW + 2), or kOutside for the zeros between samples, beside the rows and past the last row.
+// rRW, rXH1: reciprocal() of XW + 2 and XH + 1.
+__device__ __forceinline__ unsigned virtual_offset(int pos, int vr0, int rows, unsigned rRW, unsigned rXH1, int N, int XH, int XW,
+                                                   int XRW, int XS, unsigned sample_words) {
+  // (an integer division is about 40 vector instructions; 840 of a stage's 9200 cycles this way, 4200 with them)
+  const int r = (int)__umulhi((unsigned)pos, rRW), x = pos - r * (XW + 2) - 1;
+  const int v = vr0 + r, n = (int)__umulhi((unsigned)v, rXH1), h = v - n * (XH + 1) - 1;
+  const bool in = r < rows && (unsigned)x < (unsigned)XW && h >= 0 && n < N;
+  return in ? ((unsigned)n * sample_words + (unsigned)((h * XRW + x) * XS)) * 4u : kOutside;
+}
+
+// Block: WN pixel groups of 32 x WK shares of the contraction, one wavefront each, and MT 32-row tiles of result
+// channels.  A chunk of CH = 8*WK operand channels is copied to LDS (buffer_load ... lds: no registers, zeros
+// from the descriptor's bounds check) while the previous chunk is multiplied; wavefront (wn, wk) multiplies the
+// wk-th group of eight channels for every tap.  The weights of a wavefront's taps stay one chunk ahead in registers: their loads are issued behind the copies of the next chunk, and vector-memory results
+// return in order, so a weight load waited for in the same chunk would wait for the copies too.  The WK partial
+// tiles are added through LDS in fixed order.
+template <int MT, int NT>
+__device__ __forceinline__ void conv_lds_body(const LdsArgs& a, const LdsClass& c, float* lds, int tile0, unsigned q0) {
+  const int tid = threadIdx.x, lane = tid & 63, T = blockDim.x, waves = T >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
+  const int col = lane & 31, half = lane >> 5;
+  const int WN = a.WN, WK = a.WK, wn = wave % WN, wk = wave / WN;
+  const int XH1 = a.XH + 1, RW = a.RW, PL = a.PL, KG = a.KG, NP = a.NP, CH = a.CH;
+  const unsigned PHW = (unsigned)(c.PH * c.PW);
+  const unsigned n0 = q0 / PHW;
+  const int vr0 = (int)n0 * XH1 + a.SI * (int)((q0 - n0 * PHW) / (unsigned)c.PW);
+  unsigned* const tabv = reinterpret_cast<unsigned*>(lds);  // [NP * 64] operand offsets of the staged positions
+  float* const buf0 = lds + NP * 64;
+  const int bufsz = CH * PL;
+  for (int pos = tid; pos < NP * 64; pos += T)
+    tabv[pos] = virtual_offset(pos, vr0, a.rows, a.rRW, a.rXH1, a.N, a.XH, a.XW, a.XRW, a.XS, (unsigned)a.Kdim * a.XHW);
+  const __amdgpu_buffer_rsrc_t rx = rsrc_of(a.X, a.x_bytes);
+  auto stage = [&](int k0, float* dst) __attribute__((always_inline)) {
+    int cc = wave / NP, i = wave - cc * NP;
+    const int dc = waves / NP, di = waves - dc * NP;
+    while (cc < CH) {
+      const unsigned k = (unsigned)min(k0 + cc, a.Kdim - 1);  // rows past Kdim meet zero weights
+      copy_to_lds(rx, dst + cc * PL + i * 64, tabv[i * 64 + lane], k * a.XHW * 4u);
+      cc += dc;
+      i += di;
+      if (i >= NP) { i -= NP; ++cc; }
+    }
+  };
+  const unsigned q = q0 + wn * 32 + col;
+  const bool qv = q < c.npix;
+  const unsigned qc = qv ? q : c.npix - 1;
+  const unsigned qn = qc / PHW;
+  const int qp = (int)(qc - qn * PHW), qi = qp / c.PW, qj = qp - qi * c.PW;
+  const int base = ((int)qn * XH1 + a.SI * qi - vr0) * RW + a.SI * qj;
+
+  unsigned woff[NT];   // tap t: offset of its weight copy, and of its shift in LDS (uniform)
+  int boff[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int ri = t / c.nc, ci = t - ri * c.nc;
+    const unsigned rc = c.rows >> (8 * ri), cc = c.cols >> (8 * ci);
+    woff[t] = ((rc >> 4 & 15) * (unsigned)a.KS + (cc >> 4 & 15)) * a.tap_stride;
+    boff[t] = (int)(rc & 15) * RW + (int)(cc & 15);
+  }
+  const float4* wl = a.Wp + (size_t)tile0 * KG * 64 + lane;
+  const unsigned t1 = (tile0 + 1) * 32 < a.Mdim ? (unsigned)KG * 64u : 0u;  // the second tile, where it exists
+  float4 A[NT][MT];
+  auto ldA = [&](int i, int ch) __attribute__((always_inline)) {
+    const int g = min(ch * WK + wk, KG - 1);  // groups past KG are not multiplied
+    const float4* w = wl + (woff[i] + (unsigned)g * 64u);
+    A[i][0] = w[0];
+    if (MT > 1) A[i][MT - 1] = w[t1];
+  };
+#pragma unroll
+  for (int i = 0; i < NT; ++i) ldA(i, 0);
+  floatx16 acc[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
+  __syncthreads();
+  stage(0, buf0);
+  __syncthreads();  // (waits for the copies)
+  const int nchunk = (KG + WK - 1) / WK;
+  for (int ch = 0; ch < nchunk; ++ch) {
+    const bool more = ch + 1 < nchunk;
+    if (more) stage((ch + 1) * CH, buf0 + ((ch + 1) & 1) * bufsz);
+    const float* lb = buf0 + (ch & 1) * bufsz + (8 * wk + half) * PL + base;
+    const bool live = ch * WK + wk < KG;  // uniform per wavefront
+    float b[2][4];
+    auto ldB = [&](int i) __attribute__((always_inline)) {
+      const float* p = lb + boff[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[i & 1][e] = p[2 * e * PL];
+    };
+    ldB(0);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      if (i + 1 < NT) ldB(i + 1);
+      if (live) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            const float av = e == 0 ? A[i][m].x : e == 1 ? A[i][m].y : e == 2 ? A[i][m].z : A[i][m].w;
+            acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b[i & 1][e], acc[m], 0, 0, 0);
+          }
+      }
+      if (more) ldA(i, ch + 1);
+    }
+    __syncthreads();
+  }
+
+  float* yq = a.Y + (size_t)qn * a.Mdim * a.OH * a.OW + (size_t)(a.SO * qi + c.oy) * a.OW + a.SO * qj + c.ox;
+  const size_t OHW = (size_t)a.OH * a.OW;
+  if (WK == 1) {
+    if (!qv) return;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = (tile0 + mt) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (m < a.Mdim) yq[(size_t)m * OHW] = acc[mt][r] + (a.bias ? a.bias[m] : 0.f);
+      }
+    return;
+  }
+  const int rpw = 16 / WK;  // accumulator rows that each of the WK wavefronts finishes
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    if (mt) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) lds[(wave * 16 + r) * 64 + lane] = acc[mt][r];
+    __syncthreads();
+    for (int rr = 0; rr < rpw; ++rr) {
+      const int r = wk * rpw + rr;
+      const int m = (tile0 + mt) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+      float v = 0.f;
+      for (int k = 0; k < WK; k += 2)  // fixed order
+        v += lds[((k * WN + wn) * 16 + r) * 64 + lane] + lds[(((k + 1) * WN + wn) * 16 + r) * 64 + lane];
+      if (qv && m < a.Mdim) yq[(size_t)m * OHW] = v + (a.bias ? a.bias[m] : 0.f);
+    }
+  }
+}
+
+// ALL: one class reached by all nine taps; else the class decides (1, 2 or 4 taps, or none: zeros)
+template <int MT, bool ALL>
+__global__ __launch_bounds__((MT == 2 && ALL) ? 512 : 1024) void conv_lds_f32_kernel(LdsArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const LdsClass& c = a.cls[blockIdx.z];
+  const unsigned id = xcd_grouped(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  const int tile0 = (int)(id % gridDim.y) * MT;      // the channel tiles of one pixel block share an L2
+  const unsigned q0 = (id / gridDim.y) * (unsigned)(32 * a.WN);
+  if (q0 >= c.npix) return;  // uniform: a smaller parity class
+  if constexpr (ALL) {
+    conv_lds_body<MT, 9>(a, c, lds, tile0, q0);
+  } else {
+    const int nt = c.nr * c.nc;
+    if (nt == 4) conv_lds_body<MT, 4>(a, c, lds, tile0, q0);
+    else if (nt == 2) conv_lds_body<MT, 2>(a, c, lds, tile0, q0);
+    else if (nt == 1) conv_lds_body<MT, 1>(a, c, lds, tile0, q0);
+    else {
+      const unsigned PHW = (unsigned)(c.PH * c.PW);
+      for (unsigned i = threadIdx.x; i < 32u * a.WN * 32u * MT; i += blockDim.x) {
+        const unsigned q = q0 + i % (32u * a.WN), m = tile0 * 32 + i / (32u * a.WN);
+        if (q >= c.npix || m >= (unsigned)a.Mdim) continue;
+        const unsigned n = q / PHW, p = q - n * PHW, r = p / (unsigned)c.PW;
+        a.Y[((size_t)n * a.Mdim + m) * a.OH * a.OW + (size_t)(a.SO * r + c.oy) * a.OW + a.SO * (p - r * c.PW) + c.ox] = 0.f;
+      }
+    }
+  }
+}
+
+// virtual rows that P consecutive pixels of a PH x PW class can need
+int tile_rows(int P, int PH, int PW, int SI, int XH) {
+  const int r = cdiv(P - 1, PW) + 1;
+  return SI * (r - 1) + cdiv(r - 1, PH) * std::max(0, XH + 1 - SI * PH) + 3;
+}
+struct LdsPick { int MT, WN, WK, CH, rows, NP, PL; size_t lds; double cost; };
+
+// The block shape with the least modelled time (cycles of the busiest SIMD): matrix cycles of the waves it is dealt,
+// at least the latency of a chunk, plus staging and the reduction over WK.  Wide tiles read less per product; splitting the
+// contraction is what fills the chip when there are few pixels.
+bool search_product(const LdsArgs& a, int ncls, LdsPick& best) {
+  best.cost = 1e30;
+  const bool all = ncls == 1 && a.cls[0].nr * a.cls[0].nc == 9;
+  for (int MT = 1; MT <= (a.Mdim > 32 ? 2 : 1); ++MT)
+    for (int WK = 1; WK <= 16; WK *= 2)
+      for (int WN = 1; WN * WK <= (MT == 2 && all ? 8 : 16) && WN <= 8; ++WN) {
+        if (WK > 1 && WK > a.KG) continue;
+        const int waves = WN * WK, P = 32 * WN;
+        LdsPick p;
+        p.MT = MT; p.WN = WN; p.WK = WK; p.CH = 8 * WK;
+        p.rows = 0;
+        for (int i = 0; i < ncls; ++i) p.rows = std::max(p.rows, tile_rows(P, a.cls[i].PH, a.cls[i].PW, a.SI, a.XH));
+        p.NP = cdiv(p.rows * a.RW, 64);
+        p.PL = p.NP * 64 + 32;
+        p.lds = std::max((size_t)2 * p.CH * p.PL + p.NP * 64, WK > 1 ? (size_t)waves * 1024 : (size_t)0) * 4;
+        if (p.lds > kProductLds) continue;
+        double blocks = 0, mfma = 0;
+        for (int i = 0; i < ncls; ++i) {
+          if (a.cls[i].nr * a.cls[i].nc == 0) continue;  // zeros only
+          const double b = (double)cdiv(a.cls[i].npix, P) * cdiv(a.Mdim, 32 * MT);
+          blocks += b;
+          mfma += b * a.cls[i].nr * a.cls[i].nc;  // taps, averaged over the blocks below
+        }
+        const double taps = mfma / blocks;
+        const int nchunk = cdiv(a.KG, WK);
+        const double per_cu = std::ceil(blocks / 256.0);
+        const double simd_waves = std::ceil(per_cu * waves / 4.0);
+        const double chunk_mfma = taps * 4 * MT * 64;
+        // bytes through L2 per compute unit: staged pixels (with their halo) and weights
+        const double traffic = per_cu * ((double)a.KG * 8 * p.NP * 256 + (double)MT * taps * a.KG * 1024);
+        const double resident = std::min(std::floor(160.0 * 1024 / p.lds), std::max(1.0, std::floor((MT == 2 ? 12.0 : 16.0) / waves)));
+        const double rounds = std::ceil(per_cu / resident);
+        const double stage = 600 + (double)p.CH * p.NP / waves * 30.0;   // not hidden while a block is alone on its CU
+        p.cost = simd_waves * nchunk * chunk_mfma + (per_cu > 1 ? 0.3 : 0.6) * rounds * nchunk * stage +
+                 rounds * (4000 + (WK > 1 ? MT * (600.0 + WK * 60) : 0)) + simd_waves * nchunk * taps * 4 * 8 + traffic / 40;
+        if (p.cost < best.cost) best = p;
+      }
+  return best.cost < 1e30;
+}
+
+// (the choice depends on the sizes alone: looked up after a thread's first call with them)
+bool pick_product(const LdsArgs& a, int ncls, LdsPick& p) {
+  static thread_local std::map<std::array<int, 9>, LdsPick> seen;
+  const std::array<int, 9> key = {a.N, a.XH, a.XW, a.OH, a.OW, a.SI * 2 + a.SO, a.Kdim, a.Mdim, a.KS};
+  auto it = seen.find(key);
+  if (it == seen.end()) {
+    LdsPick q;
+    search_product(a, ncls, q);
+    if (seen.size() >= 1024) seen.clear();
+    it = seen.emplace(key, q).first;
+  }
+  p = it->second;
+  return p.cost < 1e30;
+}
+
+template <int MT, bool ALL>
+void launch_one(hipStream_t st, const char* name, const LdsArgs& a, const LdsPick& p, dim3 grid) {
+  if (p.lds > 64 * 1024)  // more than the default dynamic limit
+    (void)hipFuncSetAttribute((const void*)conv_lds_f32_kernel<MT, ALL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+  KLAUNCH_NAMED(name, (conv_lds_f32_kernel<MT, ALL>), grid, dim3(64 * p.WN * p.WK), p.lds, st, a);
+}
+
+}  // namespace
+
+// Y = conv of X (dgrad: gradient of a conv's input from its output gradient X).  H, W: the conv's INPUT size.
+// false: no block shape fits (very wide rows); the caller's direct kernel runs instead.
+bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
+                      const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S) {
+  const int pad = KS / 2, Ho = (H + 2 * pad - KS) / S + 1, Wo = (W + 2 * pad - KS) / S + 1;
+  LdsArgs a = {};
+  a.Wp = reinterpret_cast<const float4*>(Wp);
+  a.X = X; a.Y = Y; a.bias = bias;
+  a.N = N; a.Kdim = Kdim; a.Mdim = Mdim; a.KG = cdiv(Kdim, 8); a.KS = KS;
+  a.tap_stride = (unsigned)(pw_pack_floats(Mdim, Kdim) / 4);
+  if (dgrad) { a.XH = Ho; a.XW = Wo; a.OH = H; a.OW = W; a.SI = 1; a.SO = S; }
+  else { a.XH = H; a.XW = W; a.OH = Ho; a.OW = Wo; a.SI = S; a.SO = 1; }
+  a.XS = 1; a.XRW = a.XW; a.XHW = (unsigned)(a.XH * a.XW);
+  if ((size_t)N * (a.XH + 2) * (a.XH + 1) >= ((size_t)1 << 32)) return false;  // reciprocals
+  const size_t x_bytes = (size_t)N * Kdim * a.XHW * 4;
+  if (x_bytes >= kOutside || (size_t)a.tap_stride * KS * KS >= kOutside) return false;  // 32-bit offsets
+  a.x_bytes = (unsigned)x_bytes;
+  if (!dgrad && KS == 1 && S > 1) {  // only the pixels a strided 1x1 conv reads: its operand is the subsampled tensor
+    a.XH = Ho; a.XW = Wo; a.SI = 1; a.XS = S;
+  }
+  int ncls = 0;
+  auto code = [](int u, int d) { return (unsigned)((u << 4) | (d + 1)); };
+  // row (or column) taps of a parity class: input row r = S*i + u - pad
+  auto taps = [&](int par, unsigned& list) {
+    int n = 0;
+    list = 0;
+    for (int u = 0; u < KS; ++u) {
+      int d;
+      if (!dgrad) d = u - pad;
+      else if (S == 1) d = pad - u;
+      else if ((par + pad - u) & 1) continue;
+      else d = (par + pad - u) / 2;
+      list |= code(u, d) << (8 * n++);
+    }
+    return n;
+  };
+  for (int pr = 0; pr < a.SO; ++pr)
+    for (int pc = 0; pc < a.SO; ++pc) {
+      LdsClass& c = a.cls[ncls];
+      c.PH = (a.OH - pr + a.SO - 1) / a.SO;
+      c.PW = (a.OW - pc + a.SO - 1) / a.SO;
+      if (c.PH <= 0 || c.PW <= 0) continue;
+      c.oy = pr; c.ox = pc;
+      c.npix = (unsigned)N * c.PH * c.PW;
+      c.nr = taps(pr, c.rows);
+      c.nc = taps(pc, c.cols);
+      ++ncls;
+    }
+  a.RW = a.XW + 2;
+  LdsPick p;
+  if (!pick_product(a, ncls, p)) return false;
+  a.rRW = reciprocal(a.RW); a.rXH1 = reciprocal(a.XH + 1);
+  a.WN = p.WN; a.WK = p.WK; a.rows = p.rows; a.NP = p.NP; a.PL = p.PL; a.CH = p.CH;
+  unsigned most = 0;
+  for (int i = 0; i < ncls; ++i) most = std::max(most, a.cls[i].npix);
+  const dim3 grid((unsigned)cdiv(most, 32 * p.WN), (unsigned)cdiv(Mdim, 32 * p.MT), (unsigned)ncls);
+  const bool all = ncls == 1 && a.cls[0].nr * a.cls[0].nc == 9;
+  if (p.MT == 2) all ? launch_one<2, true>(st, name, a, p, grid) : launch_one<2, false>(st, name, a, p, grid);
+  else all ? launch_one<1, true>(st, name, a, p, grid) : launch_one<1, false>(st, name, a, p, grid);
+  return true;
+}
+
+// ------------------------------------------------------------------ weight gradient
+namespace {
+
+struct LdsWgArgs {
+  const float* g;   // [N][Cout][Ho][Wo]
+  const float* x;   // [N][Cin][H][W], or every XS-th row and column of a larger one
+  float* part;      // [chunk][Cout][Cin][KS*KS]
+  int N, Cin, Cout, H, W, Ho, Wo, S, XS, XRW;
+  unsigned XHW, x_bytes, g_bytes;
+  int rows, RW, NP, PT, per, nstage, nbuf;
+  unsigned rRW, rH1, rWo;
+  unsigned npix;
+};
+
+// Block of eight wavefronts, one per compute unit: a 32 x 32 tile of (cout, cin), all taps (1x1: 64 x 64), over a run of stages of
+// PT consecutive output pixels, whatever samples they lie in.  A stage copies g [32][PT] and the virtual rows of x
+// under it to LDS with coalesced loads (lanes along the pixels: a load per lane and channel row would touch 64 cache
+// lines instead of 2 to 4) while the stage before is multiplied; the products read one word of g and one of x per
+// tap for a pair of pixels.  Wavefront w takes the w-th eighth of every stage's pixels; the eight tiles are added
+// through LDS and leave as whole rows of the partial.  Pitches are 2 modulo 64: the 32 channel rows and the two
+// neighbouring pixels of a pair hit 64 different banks.
+template <int KS>
+__global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
+  constexpr int KK = KS * KS, TI = KS == 1 ? 2 : 1, TJ = TI, NA = KK * TI * TJ;  // 32 x 32 tiles of (cout, cin)
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
+  const int PT = w.PT, PG = round_up64(PT) + 2, PL = w.NP * 64 + 2, RW = w.RW, H1 = w.H + 1, HWo = w.Ho * w.Wo;
+  const int XO = 32 * TI * PG, TO = XO + 32 * TJ * PL, bufsz = TO + PT;  // g [32*TI][PG], x [32*TJ][PL], [PT] position of an output pixel's tap (0, 0)
+  const unsigned tiles_ci = (unsigned)(w.Cin + 32 * TJ - 1) / (32 * TJ), tiles = tiles_ci * (unsigned)((w.Cout + 32 * TI - 1) / (32 * TI));
+  const unsigned id = xcd_grouped(blockIdx.x, gridDim.x);
+  const int chunk = (int)(id / tiles), tile = (int)(id % tiles);
+  const int ci_base = (tile % (int)tiles_ci) * 32 * TJ, co_base = (tile / (int)tiles_ci) * 32 * TI;
+  const __amdgpu_buffer_rsrc_t rx = rsrc_of(w.x, w.x_bytes), rg = rsrc_of(w.g, w.g_bytes);
+  floatx16 acc[NA];
+#pragma unroll
+  for (int t = 0; t < NA; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+  const int s_begin = chunk * w.per, s_end = min(s_begin + w.per, w.nstage);
+  auto stage = [&](int s, float* buf) __attribute__((always_inline)) {
+    const unsigned q0 = (unsigned)s * PT;
+    const unsigned n0 = q0 / (unsigned)HWo;
+    const int vr0 = (int)n0 * H1 + w.S * (int)((q0 - n0 * (unsigned)HWo) / (unsigned)w.Wo);
+    for (int p0 = 0; p0 < PT; p0 += 64) {  // a pixel past the last one: zeros (its x words then do not matter)
+      const unsigned q = q0 + p0 + lane, qc = min(q, w.npix - 1), n = qc / (unsigned)HWo;
+      const int p = (int)(qc - n * (unsigned)HWo);
+      const unsigned voff = (q < w.npix && p0 + lane < PT) ? (n * (unsigned)(w.Cout * HWo) + (unsigned)p) * 4u : kOutside;
+#pragma unroll
+      for (int k = 0; k < 4 * TI; ++k) {
+        const int c = wave + 8 * k;
+        copy_to_lds(rg, buf + c * PG + p0, voff, (unsigned)min(co_base + c, w.Cout - 1) * (unsigned)HWo * 4u);
+      }
+      if (wave == 0 && p0 + lane < PT) {
+        const int i = w.Wo > 1 ? (int)__umulhi((unsigned)p, w.rWo) : p, j = p - i * w.Wo;
+        reinterpret_cast<int*>(buf + TO)[p0 + lane] = ((int)n * H1 + w.S * i - vr0) * RW + w.S * j;
+      }
+    }
+    for (int i = 0; i < w.NP; ++i) {
+      const unsigned voff = virtual_offset(i * 64 + lane, vr0, w.rows, w.rRW, w.rH1, w.N, w.H, w.W, w.XRW, w.XS, (unsigned)w.Cin * w.XHW);
+#pragma unroll
+      for (int k = 0; k < 4 * TJ; ++k) {
+        const int c = wave + 8 * k;
+        copy_to_lds(rx, buf + XO + c * PL + i * 64, voff, (unsigned)min(ci_base + c, w.Cin - 1) * w.XHW * 4u);
+      }
+    }
+  };
+  stage(s_begin, lds);
+  __syncthreads();  // (waits for the copies)
+  for (int s = s_begin; s < s_end; ++s) {
+    const float* buf = lds + (w.nbuf == 2 ? ((s - s_begin) & 1) * bufsz : 0);
+    if (w.nbuf == 2 && s + 1 < s_end) stage(s + 1, lds + ((s + 1 - s_begin) & 1) * bufsz);
+    const int p0 = wave * (PT / 8) + half;
+    const float* ga = buf + row * PG + p0;
+    const int* ta = reinterpret_cast<const int*>(buf + TO) + p0;
+    const float* xa = buf + XO + row * PL;
+    float av[2][TI], b[2][KK * TJ];
+    const int ks = PT / 16;  // pairs of pixels per wavefront: even
+    int pos = ta[0];         // one pair ahead of its use
+    auto ld = [&](int k, float (&a)[TI], float (&bb)[KK * TJ]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) a[i] = ga[2 * k + i * 32 * PG];
+      const float* xb = xa + pos;
+      pos = ta[2 * min(k + 1, ks - 1)];
+#pragma unroll
+      for (int t = 0; t < KK * TJ; ++t) bb[t] = KS == 1 ? xb[RW + 1 + t * 32 * PL] : xb[(t / 3) * RW + t % 3];
+    };
+    auto mma = [&](const float (&a)[TI], const float (&bb)[KK * TJ]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int t = 0; t < KK * TJ; ++t)
+          acc[i * KK * TJ + t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], bb[t], acc[i * KK * TJ + t], 0, 0, 0);
+    };
+    ld(0, av[0], b[0]);
+    for (int k = 0; k < ks; k += 2) {  // operands one pair ahead of the products
+      ld(k + 1, av[1], b[1]);
+      mma(av[0], b[0]);
+      if (k + 2 < ks) ld(k + 2, av[0], b[0]);
+      mma(av[1], b[1]);
+    }
+    __syncthreads();
+    if (w.nbuf == 1 && s + 1 < s_end) {
+      stage(s + 1, lds);
+      __syncthreads();
+    }
+  }
+  // [32*TI co][32*TJ ci][KK] of the tile, then rows of 32*TJ*KK floats
+  constexpr int RO = 32 * TJ * KK;
+  float* sR = lds;               // [8][16][64]
+  float* so = lds + 8 * 1024;    // [32*TI][RO]
+#pragma unroll
+  for (int t = 0; t < NA; ++t) {
+    if (t) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sR[(wave * 16 + r) * 64 + lane] = acc[t][r];
+    __syncthreads();
+    const int ti = t / (KK * TJ), tj = KS == 1 ? t % TJ : 0, tap = KS == 1 ? 0 : t;
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr) {
+      const int r = 2 * wave + rr, co = ti * 32 + 8 * (r >> 2) + 4 * half + (r & 3), o = r * 64 + lane;
+      so[co * RO + (tj * 32 + row) * KK + tap] = ((sR[o] + sR[o + 1024]) + (sR[o + 2048] + sR[o + 3072])) +
+                                                 ((sR[o + 4096] + sR[o + 5120]) + (sR[o + 6144] + sR[o + 7168]));
+    }
+  }
+  __syncthreads();
+  const int nci = min(32 * TJ, w.Cin - ci_base) * KK, nco = min(32 * TI, w.Cout - co_base);
+  float* out = w.part + (((size_t)chunk * w.Cout + co_base) * w.Cin + ci_base) * KK;
+  for (int co = wave; co < nco; co += 8)
+    for (int i = lane; i < nci; i += 64) out[(size_t)co * w.Cin * KK + i] = so[co * RO + i];
+}
+
+struct LdsWgPick { int PT = 0, per, chunks, rows, NP, nbuf; size_t lds; };
+
+LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
+  LdsWgPick best;
+  const int pad = KS / 2, Ho = (H + 2 * pad - KS) / S + 1, Wo = (W + 2 * pad - KS) / S + 1;
+  if (KS == 1) { H = Ho; W = Wo; S = 1; }
+  const long npix = (long)N * Ho * Wo, tw = KS == 1 ? 64 : 32, tiles = (long)cdiv(Cin, tw) * cdiv(Cout, tw);
+  if ((size_t)N * std::max((size_t)Cin * H * S * (W + 1) * S, (size_t)Cout * Ho * Wo) * 4 >= kOutside) return best;  // 32-bit offsets
+  if ((size_t)N * (H + 2) * (H + 1) >= ((size_t)1 << 32) || (size_t)Ho * Wo * Wo >= ((size_t)1 << 32)) return best;  // reciprocals
+  double cost = 1e30;
+  for (int PT = 32; PT <= 128; PT *= 2) {
+    LdsWgPick p;
+    p.PT = PT;
+    p.rows = tile_rows(PT, Ho, Wo, S, H);
+    p.NP = cdiv(p.rows * (W + 2), 64);
+    const size_t buf = ((size_t)tw * (round_up64(PT) + 2 + p.NP * 64 + 2) + PT) * 4;
+    p.nbuf = 2 * buf <= kWgradLds ? 2 : 1;
+    p.lds = std::max(p.nbuf * buf, (size_t)(8192 + tw * tw * KS * KS) * 4);
+    if (p.lds > kWgradLds) continue;
+    const int nstage = cdiv(npix, PT);
+    for (int per = 1; per <= nstage; per = per < 8 ? per + 1 : per + per / 4) {
+      const int chunks = cdiv(nstage, per);
+      if (chunks * tiles > 8192 && per < nstage) continue;
+      const double mfma = PT / 8 * (KS == 1 ? 4 : 9) * 64.0, bytes = tw * 256.0 * (p.NP + cdiv(PT, 64));
+      const double stage = 2000 + bytes / 20;
+      const double one = p.nbuf == 2 ? std::max(mfma, stage) + bytes / 40 + 800 : mfma + stage;
+      const double c = std::ceil(chunks * tiles / 256.0) * (cdiv(nstage, chunks) * one + stage + 3000 + KS * KS * 500) +
+                       (double)chunks * tiles * KS * KS * tw * tw * 8 / 1500;  // writing and reducing the partials
+      if (c < cost) {
+        cost = c;
+        p.per = cdiv(nstage, chunks);
+        p.chunks = cdiv(nstage, p.per);
+        best = p;
+      }
+    }
+  }
+  return best;
+}
+
+bool pick_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S, LdsWgPick& p) {
+  static thread_local std::map<std::array<int, 7>, LdsWgPick> seen;
+  const std::array<int, 7> key = {N, Cin, Cout, H, W, KS, S};
+  auto it = seen.find(key);
+  if (it == seen.end()) {
+    if (seen.size() >= 1024) seen.clear();
+    it = seen.emplace(key, search_wgrad(N, Cin, Cout, H, W, KS, S)).first;
+  }
+  p = it->second;
+  return p.PT > 0;
+}
+
+}  // namespace
+
+int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S) {
+  LdsWgPick p;
+  return pick_wgrad(N, Cin, Cout, H, W, KS, S, p) ? p.chunks : 0;
+}
+
+void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const float* x, float* part, int N, int Cin, int Cout,
+                    int H, int W, int KS, int S) {
+  LdsWgPick p;
+  if (!pick_wgrad(N, Cin, Cout, H, W, KS, S, p)) return;
+  LdsWgArgs w;
+  w.g = g; w.x = x; w.part = part;
+  w.N = N; w.Cin = Cin; w.Cout = Cout; w.H = H; w.W = W; w.S = S;
+  w.Ho = (H + 2 * (KS / 2) - KS) / S + 1;
+  w.Wo = (W + 2 * (KS / 2) - KS) / S + 1;
+  w.XS = 1; w.XRW = W; w.XHW = (unsigned)(H * W);
+  if (KS == 1 && S > 1) { w.H = w.Ho; w.W = w.Wo; w.S = 1; w.XS = S; }
+  w.x_bytes = (unsigned)N * Cin * w.XHW * 4u;
+  w.g_bytes = (unsigned)N * Cout * w.Ho * w.Wo * 4u;
+  w.npix = (unsigned)N * w.Ho * w.Wo;
+  w.rRW = reciprocal(w.W + 2); w.rH1 = reciprocal(w.H + 1); w.rWo = reciprocal(w.Wo);
+  w.rows = p.rows; w.RW = w.W + 2; w.NP = p.NP; w.PT = p.PT; w.per = p.per; w.nbuf = p.nbuf;
+  w.nstage = cdiv(w.npix, p.PT);
+  const int tw = KS == 1 ? 64 : 32;
+  const dim3 grid((unsigned)(p.chunks * cdiv(Cin, tw) * cdiv(Cout, tw)));
+  if (p.lds > 64 * 1024)
+    (void)hipFuncSetAttribute(KS == 3 ? (const void*)conv_lds_wgrad_f32_kernel<3> : (const void*)conv_lds_wgrad_f32_kernel<1>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+  if (KS == 3) KLAUNCH_NAMED(name, (conv_lds_wgrad_f32_kernel<3>), grid, dim3(512), p.lds, st, w);
+  else KLAUNCH_NAMED(name, (conv_lds_wgrad_f32_kernel<1>), grid, dim3(512), p.lds, st, w);
+}
+
+}  // namespace ast
