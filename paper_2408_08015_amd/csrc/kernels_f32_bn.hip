@@ -23,7 +23,10 @@ static inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 // samples (small planes) or one chunk of one plane (large planes) of one channel, so it
 // streams contiguous memory with no index arithmetic per element; P = groups * chunks
 // partial pairs per channel.
-struct BnSplit { int spb, groups, nchunks, chunk, P; };
+struct BnSplit {
+  int spb, groups, nchunks, chunk, P;
+  unsigned rq;  // reciprocal of a sample's elements: floor(i / HW) = mulhi(i, rq) for i < 4096
+};
 static inline BnSplit bn_split(int N, int HW) {
   BnSplit b;
   b.nchunks = cdiv(HW, 4096);
@@ -34,8 +37,11 @@ static inline BnSplit bn_split(int N, int HW) {
   if (b.spb > N) b.spb = N;
   b.groups = cdiv(N, b.spb);
   b.P = b.groups * b.nchunks;
+  const unsigned q = b.nchunks > 1 ? 1u << 31 : (unsigned)HW;  // one chunk of one plane: quotient 0
+  b.rq = q == 1 ? 0 : (unsigned)(((1ull << 32) + q - 1) / q);
   return b;
 }
+__device__ __forceinline__ int bn_sample_of(int i, unsigned rq) { return rq ? (int)__umulhi((unsigned)i, rq) : i; }
 size_t bn_ws_doubles(int C, int N, int HW) { return (size_t)C * bn_split(N, HW).P * 2; }
 
 // both sums of a block in one pass; the result is valid in thread 0
@@ -81,12 +87,24 @@ __global__ __launch_bounds__(256) void bn_stats_partial_kernel(const float* __re
       }
     }
   } else {
+    // planes that are no multiple of 16 bytes: 16 words in flight per thread, unconditional (the last one again past
+    // the end, counted as zero).  One load per trip behind an integer division took 7.3 us where this takes
+    // 3.9 (32 channels, 13 x 27x27).
     const int total = (n1 - n0) * len;
-    for (int idx = threadIdx.x; idx < total; idx += 256) {
-      const int nl = idx / len, e = e0 + idx - nl * len;
-      const float v = x[((size_t)(n0 + nl) * C + c) * HW + e];
-      s1 += v;
-      s2 += v * v;
+    for (int i0 = threadIdx.x; i0 < total; i0 += 4096) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int idx = min(i0 + 256 * u, total - 1);
+        const int nl = bn_sample_of(idx, b.rq), e = e0 + idx - nl * len;
+        v[u] = x[((size_t)(n0 + nl) * C + c) * HW + e];
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const float w = i0 + 256 * u < total ? v[u] : 0.f;
+        s1 += w;
+        s2 += w * w;
+      }
     }
   }
   double d1, d2;
@@ -252,14 +270,23 @@ __global__ __launch_bounds__(256) void bn_bwd_partial_kernel(const float* __rest
       }
     }
   } else {
-    const int total = (n1 - n0) * len;
-    for (int idx = threadIdx.x; idx < total; idx += 256) {
-      const int nl = idx / len, e = e0 + idx - nl * len;
-      const size_t off = ((size_t)(n0 + nl) * C + c) * HW + e;
-      float xv = x[off];
-      float gv = g[off] * act_slope_sw<SW>(xv * sc + sf, act);
-      s1 += gv;
-      s2 += gv * ((xv - mean) * istd);
+    const int total = (n1 - n0) * len;  // as above: 2 x 8 words in flight (192 channels, 13 x 27x27: 10.8 -> 5.6 us)
+    for (int i0 = threadIdx.x; i0 < total; i0 += 2048) {
+      float xq[8], gq[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int idx = min(i0 + 256 * u, total - 1);
+        const int nl = bn_sample_of(idx, b.rq), e = e0 + idx - nl * len;
+        const size_t off = ((size_t)(n0 + nl) * C + c) * HW + e;
+        xq[u] = x[off];
+        gq[u] = g[off];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float gv = i0 + 256 * u < total ? gq[u] * act_slope_sw<SW>(xq[u] * sc + sf, act) : 0.f;
+        s1 += gv;
+        s2 += gv * ((xq[u] - mean) * istd);
+      }
     }
   }
   double d1, d2;

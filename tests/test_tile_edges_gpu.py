@@ -3,7 +3,7 @@ smallest and largest of a range, both sides of a rule.  Oracle and tolerances of
 activations, 1e-3 for gradients; sums of a few thousand fp32 terms differ by about 1e-6)."""
 import pytest
 
-from asteroid_workloads.configs import conv
+from asteroid_workloads.configs import bn, conv, simple
 from test_parity_gpu import A, check, one  # noqa: F401  (A: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -24,3 +24,13 @@ pytestmark = pytest.mark.gpu
 ])
 def test_dense_conv_tiles(A, cin, cout, k, stride, h, w, B):
     check(one([conv(cin, cout, k, stride, k // 2)], (cin, h, w), B=B), rounds=1)
+
+
+@pytest.mark.parametrize("c,h,w,B", [
+    (8, 27, 27, 13),    # planes of 729 words: five samples per block, 16 words per thread in flight
+    (6, 67, 67, 3),     # 4489 words: two chunks per plane
+    (5, 1, 3, 2900),    # 1365 samples per block
+    (3, 1, 1, 9001),    # one-word planes
+])
+def test_batchnorm_planes_not_a_multiple_of_16_bytes(A, c, h, w, B):
+    check(one([bn(c), simple("relu6")], (c, h, w), B=B), rounds=1)
