@@ -11,6 +11,7 @@
 // Depthwise 3x3: a block stages whole (n, c) planes (they are contiguous) with a zero halo
 // in LDS; the backward kernel produces the input gradient and the nine weight-gradient
 // sums of each plane from one read of g and x.
+#include <algorithm>
 #include "bn_common.h"
 #include "device_utils.h"
 #include "kernels.h"
@@ -41,8 +42,9 @@ struct WgArgs {  // one pointwise-conv weight-gradient launch (partials only)
   const float* g;
   const float* x;
   float* part;
-  int Cin, Cout, HW, cps, pxw;
-  int tile_order;  // 1: the (ci, co) tiles of one pixel chunk run side by side on one XCD
+  long NQ;
+  int Cin, Cout, HW, splits;
+  int tile_order;  // 1: the (ci, co) tiles of one pixel range run side by side on one XCD
 };
 
 // Block coordinates of a product grid of gx pixel blocks x gy channel tiles from the flat block id:
@@ -474,107 +476,154 @@ void pw_conv_f32(hipStream_t st, const float* Wp, const float* X, float* Y, cons
 }
 
 // ============================================================== pointwise conv wgrad
-// Block = one 32(co) x 32(ci) tile of dW over 4*pxw pixels of one sample; each wavefront
-// contracts pxw pixels (lane (m = l%32, h = l/32) loads eight consecutive pixels of row m
-// and feeds eight MFMAs; both operands use the same pixel per slot), the four accumulators
-// are added through LDS and written as one partial.  A second kernel adds the partials in a
-// fixed order and performs G += (in-place gradient accumulation).
-template <bool VEC>
-__device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int bx, int by, int bz, float (*sR)[16][64]) {
-  const float* __restrict__ g = w.g;
-  const float* __restrict__ x = w.x;
-  float* __restrict__ part = w.part;
-  const int Cin = w.Cin, Cout = w.Cout, HW = w.HW, cps = w.cps, pxw = w.pxw;
+// dW[co][ci] = sum over the pixels q of all samples of g[co][q] x[ci][q].  A block owns TCO x TCI tiles of
+// 32 x 32 weights (KS wavefronts per tile share its pixels) and the pixels of one of `splits` equal ranges of the
+// flattened (sample, pixel) index, in steps of PX.  Each step copies PX pixels of the block's rows of g and x to LDS
+// once, in whole 128 / 256-byte runs and one step ahead through registers, and the wavefronts read their operands
+// there: lane (m = l%32, h = l/32) takes the four pixels of 16-byte chunk 2k + h of row m from either matrix and
+// feeds four MFMAs.  Chunk j of a row sits at position j ^ f(row), so the sixteen lanes of one LDS access hit
+// all 64 banks.  The partials of the splits are added to G in a fixed order by a later launch.
+//
+// The kernel before this one loaded the operands of a 32 x 32 tile from global memory, sixteen bytes per lane from 32
+// different rows: every instruction touched 64 cache lines, and a chunk of pixels ended with its sample (49 pixels of
+// a 7x7 plane occupied two of four wavefronts).
+template <int TCO, int TCI, int KS>
+struct WgTile {
+  static constexpr int PX = KS == 4 ? 64 : 32, CH = PX / 4, ROWS = (TCO + TCI) * 32;
+  static constexpr int LDS = 2 * ROWS * PX;  // floats, two steps
+  static __device__ __forceinline__ int swz(int row) { return PX == 64 ? (row & 15) : ((row >> 1) & 7); }
+};
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int TCO, int TCI, int KS, bool VEC>
+__device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bci, int bco, float* __restrict__ lds) {
+  using T = WgTile<TCO, TCI, KS>;
+  constexpr int PX = T::PX, CH = T::CH, ROWS = T::ROWS;
+  static_assert(TCO * TCI * KS == 4, "four wavefronts");
+  const int Cin = w.Cin, Cout = w.Cout, HW = w.HW;
+  const unsigned Q = (unsigned)w.NQ;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int row = lane & 31, half = lane >> 5;
-  const int chunk = bx;
-  const int n = chunk / cps;
-  const int p0 = ((chunk - n * cps) * 4 + wave) * pxw;
-  const int p1 = min(p0 + pxw, HW);
-  const int ci_base = by * 32, co_base = bz * 32;
-  const bool av = co_base + row < Cout, bv = ci_base + row < Cin;
-  const float* ga = g + ((size_t)n * Cout + (av ? co_base + row : 0)) * HW;
-  const float* xb = x + ((size_t)n * Cin + (bv ? ci_base + row : 0)) * HW;
+  const int co_base = bco * (TCO * 32), ci_base = bci * (TCI * 32);
+  const int steps = (int)((Q + PX - 1) / PX);
+  const int s0 = (int)((long)steps * split / w.splits), s1 = (int)((long)steps * (split + 1) / w.splits);
+
+  // Staging: LPR threads per row and pass, RP rows per pass.  16-byte words (VEC: HW % 4 == 0, so a word never
+  // leaves its sample) or single pixels.  Rows past Cout / Cin read the last row: their products are never stored.
+  constexpr int LPR = VEC ? CH : PX, RP = 256 / LPR, NL = ROWS / RP;
+  const int lp = t % LPR, lr = t / LPR;
+  const int px = VEC ? 4 * (lp ^ T::swz(lr)) : lp;  // VEC: RP keeps swz(row) the same for all rows of a thread
+  float4 rv[VEC ? NL : 1];
+  float rs[VEC ? 1 : NL];
+  auto load = [&](int s) {
+    unsigned q = (unsigned)s * PX + px;
+    const bool ok = q < Q;
+    if (!ok) q = 0;
+    const unsigned n = q / (unsigned)HW;
+    const unsigned p = q - n * (unsigned)HW;
+    const float* gp = w.g + (size_t)n * Cout * HW + p;
+    const float* xp = w.x + (size_t)n * Cin * HW + p;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const bool isg = RP * i < TCO * 32;  // RP divides 32
+      const int r = lr + RP * i;
+      const float* src = isg ? gp + (size_t)min(co_base + r, Cout - 1) * HW
+                             : xp + (size_t)min(ci_base + r - TCO * 32, Cin - 1) * HW;
+      if constexpr (VEC) {
+        const float4 v = *reinterpret_cast<const float4*>(src);
+        rv[i] = ok ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+      } else {
+        const float v = *src;
+        rs[i] = ok ? v : 0.f;
+      }
+    }
+  };
+  auto store = [&](int buf) {
+    float* o = lds + buf * (ROWS * PX);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int r = lr + RP * i;
+      if constexpr (VEC) *reinterpret_cast<float4*>(o + r * PX + 4 * lp) = rv[i];
+      else o[r * PX + 4 * ((lp >> 2) ^ T::swz(r)) + (lp & 3)] = rs[i];
+    }
+  };
+
+  const int wk = wave % KS, wt = wave / KS, wci = wt % TCI, wco = wt / TCI;
+  const int ra = wco * 32 + row, rb = TCO * 32 + wci * 32 + row;
+  const int swa = T::swz(ra), swb = T::swz(rb);
   floatx16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  if (VEC) {  // HW % 4 == 0: aligned 16-byte loads, 16 pixels per fragment, two fragments in flight
-    struct Frag { float4 a0, a1, b0, b1; };
-    // Branch-free: rows beyond Cout / Cin read channel 0 (their products land in rows / columns of the
-    // tile that are never stored); pixels beyond the chunk read pixel 0 and get a zero g operand.
-    auto ld = [&](int p, Frag& f) {
-      const int pp = p + 8 * half;
-      const bool v0 = pp < p1, v1 = pp + 4 < p1;
-      const int q0 = v0 ? pp : 0, q1 = v1 ? pp + 4 : 0;
-      f.a0 = *reinterpret_cast<const float4*>(ga + q0);
-      f.b0 = *reinterpret_cast<const float4*>(xb + q0);
-      f.a1 = *reinterpret_cast<const float4*>(ga + q1);
-      f.b1 = *reinterpret_cast<const float4*>(xb + q1);
-      if (!v0) f.a0 = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (!v1) f.a1 = make_float4(0.f, 0.f, 0.f, 0.f);
-    };
-    auto mma = [&](const Frag& f) {
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a0.x, f.b0.x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a0.y, f.b0.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a0.z, f.b0.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a0.w, f.b0.w, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a1.x, f.b1.x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a1.y, f.b1.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a1.z, f.b1.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a1.w, f.b1.w, acc, 0, 0, 0);
-    };
-    Frag f0, f1, f2, f3;
-    for (int p = p0; p < p1; p += 64) {  // four fragments issued before the first MFMA
-      const bool more = p + 32 < p1;     // uniform: a 32-pixel wavefront has two fragments only
-      ld(p, f0);
-      ld(p + 16, f1);
-      if (more) {
-        ld(p + 32, f2);
-        ld(p + 48, f3);
-      }
-      mma(f0);
-      mma(f1);
-      if (more) {
-        mma(f2);
-        mma(f3);
-      }
-    }
-  } else {
-    for (int p = p0; p < p1; p += 32) {  // sixteen pixel pairs requested before the first MFMA
-      float a[16], b[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int pp = p + 2 * u + half;
-        a[u] = (av && pp < p1) ? ga[pp] : 0.f;
-        b[u] = (bv && pp < p1) ? xb[pp] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], acc, 0, 0, 0);
-    }
+  if (s0 < s1) {  // uniform
+    load(s0);
+    store(0);
   }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) sR[wave][r][lane] = acc[r];
   __syncthreads();
-  float* out = part + (size_t)chunk * Cout * Cin;
-  const int ci = ci_base + row;
-  if (ci < Cin) {
+  for (int s = s0; s < s1; ++s) {
+    const int buf = (s - s0) & 1;
+    if (s + 1 < s1) load(s + 1);
+    const float* o = lds + buf * (ROWS * PX);
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int r = 4 * wave + rr;
-      const int co = co_base + 8 * (r >> 2) + 4 * half + (r & 3);
-      if (co < Cout)
-        out[(size_t)co * Cin + ci] = (sR[0][r][lane] + sR[1][r][lane]) + (sR[2][r][lane] + sR[3][r][lane]);
+    for (int k = 0; k < CH / 2 / KS; ++k) {
+      const int j = 2 * (wk * (CH / 2 / KS) + k) + half;
+      const float4 a = *reinterpret_cast<const float4*>(o + ra * PX + 4 * (j ^ swa));
+      const float4 b = *reinterpret_cast<const float4*>(o + rb * PX + 4 * (j ^ swb));
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+    }
+    if (s + 1 < s1) store(buf ^ 1);
+    __syncthreads();
+  }
+  float* out = w.part + (size_t)split * Cout * Cin;
+  const int ci = ci_base + wci * 32 + row;
+  if constexpr (KS == 1) {
+    if (ci < Cin) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int co = co_base + wco * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (co < Cout) out[(size_t)co * Cin + ci] = acc[r];
+      }
+    }
+  } else {  // the KS wavefronts of a tile add their sums in a fixed order; the staging buffers are free by now
+#pragma unroll
+    for (int r = 0; r < 16; ++r) lds[(wave * 16 + r) * 64 + lane] = acc[r];
+    __syncthreads();
+    if (ci < Cin) {
+#pragma unroll
+      for (int rr = 0; rr < 16 / KS; ++rr) {
+        const int r = wk * (16 / KS) + rr;
+        const int co = co_base + wco * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        const float* v = lds + (wt * KS * 16 + r) * 64 + lane;
+        float sum = v[0] + v[16 * 64];
+        if constexpr (KS == 4) sum += v[2 * 16 * 64] + v[3 * 16 * 64];
+        if (co < Cout) out[(size_t)co * Cin + ci] = sum;
+      }
     }
   }
 }
-template <bool VEC>
+
+// The block shapes of the weight gradient: weight tiles (co x ci) per block, wavefronts per tile
+enum { WG_2x2 = 0, WG_2x1 = 1, WG_1x2 = 2, WG_1x1 = 3 };
+template <int SHAPE, bool VEC>
+__device__ __forceinline__ void pw_wgrad_shape(const WgArgs& w, int split, int bci, int bco, float* lds) {
+  if constexpr (SHAPE == WG_2x2) pw_wgrad_body<2, 2, 1, VEC>(w, split, bci, bco, lds);
+  else if constexpr (SHAPE == WG_2x1) pw_wgrad_body<2, 1, 2, VEC>(w, split, bci, bco, lds);
+  else if constexpr (SHAPE == WG_1x2) pw_wgrad_body<1, 2, 2, VEC>(w, split, bci, bco, lds);
+  else pw_wgrad_body<1, 1, 4, VEC>(w, split, bci, bco, lds);
+}
+template <int SHAPE>
+constexpr int wg_lds_floats() {
+  return SHAPE == WG_2x2 ? WgTile<2, 2, 1>::LDS : SHAPE == WG_1x1 ? WgTile<1, 1, 4>::LDS : WgTile<2, 1, 2>::LDS;
+}
+
+template <int SHAPE, bool VEC>
 __global__ __launch_bounds__(256) void pw_wgrad_f32_kernel(WgArgs w) {
-  __shared__ float sR[4][16][64];
+  __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   int bx, t;
   pw_block_xy((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x, gridDim.y * gridDim.z,
               w.tile_order, bx, t);
-  pw_wgrad_body<VEC>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, sR);
+  pw_wgrad_shape<SHAPE, VEC>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, reinterpret_cast<float*>(lds));
 }
 
 // Input gradient and weight-gradient partials of one pointwise conv in ONE launch: the two
@@ -584,11 +633,13 @@ __global__ __launch_bounds__(256) void pw_wgrad_f32_kernel(WgArgs w) {
 // the (x, y, z) grid of the weight-gradient kernel.  VAR selects the product kernel:
 // 0 / 1 = 32-pixel wavefronts with one / two 32-channel chunks per pass, 2 = K split over the
 // block, 3 = 128-pixel wavefronts.
-template <int VAR, bool VEC>
+template <int VAR, int SHAPE, bool VEC>
 __global__ __launch_bounds__(256) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
                                                           unsigned gWx, unsigned gWy) {
-  __shared__ float sR[4][16][64];
+  __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
+  static_assert(wg_lds_floats<SHAPE>() >= 4 * 16 * 64, "the product kernels use 16 KB");
   if (blockIdx.x < nA) {  // uniform per block
+    float(*sR)[16][64] = reinterpret_cast<float(*)[16][64]>(lds);
     int bx, by;
     pw_block_xy(blockIdx.x, gAx, nA / gAx, a.tile_order, bx, by);
     if (VAR == 0) pw_pk_body<1>(a, bx, by, sR, 0);
@@ -598,7 +649,7 @@ __global__ __launch_bounds__(256) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, un
   } else {
     int bx, t;  // the weight-gradient ids start at nA: ids that agree mod 8 still share an XCD
     pw_block_xy(blockIdx.x - nA, gWx, (gridDim.x - nA) / gWx, w.tile_order, bx, t);
-    pw_wgrad_body<VEC>(w, bx, t % (int)gWy, t / (int)gWy, sR);
+    pw_wgrad_shape<SHAPE, VEC>(w, bx, t % (int)gWy, t / (int)gWy, reinterpret_cast<float*>(lds));
   }
 }
 
@@ -625,68 +676,108 @@ __global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __re
   if (q == 0 && i < n) G[i] += (sh[0][o] + sh[1][o]) + (sh[2][o] + sh[3][o]);
 }
 
-// pixels per wavefront: the largest of {256,128,64,32} that still gives >= 768 blocks
-static int wg_pxw(int N, int Cin, int Cout, int HW) {
-  long tiles = (long)cdiv(Cin, 32) * cdiv(Cout, 32);
-  const int cand[4] = {256, 128, 64, 32};
-  for (int c : cand)
-    if ((long)N * cdiv(HW, 4 * c) * tiles >= 768) return c;
-  return 32;
+// Block shape and number of pixel ranges of a weight gradient.  The shape with the fewest padded 32 x 32 tiles
+// (a tie goes to the larger block, which moves fewer bytes per product), about WG_BLOCKS blocks, each with
+// at least 128 pixels.  Where that leaves compute units idle (fewer than two blocks each: the 14x14 and 7x7 planes of
+// a few samples) the time of a launch is its longest chain of steps, so the smallest shape runs, one step of 64 pixels
+// upwards: 96 -> 576 channels at 8 x 14x14 12.3 us with 36 blocks of 2x2 tiles, 7.2 us with 810 of 1x1.
+static constexpr int WG_BLOCKS = 768;
+struct WgPick { int shape; dim3 grid; };
+static WgPick wg_pick(int N, int Cin, int Cout, int HW) {
+  const int a = cdiv(Cout, 32), b = cdiv(Cin, 32);
+  static const int tco[4] = {2, 2, 1, 1}, tci[4] = {2, 1, 2, 1};
+  const long NQ = (long)N * HW;
+  WgPick p;
+  auto splits = [&](int shape, int px) {
+    p.shape = shape;
+    const int gy = cdiv(b, tci[shape]), gz = cdiv(a, tco[shape]);
+    const long s = std::max(1L, std::min((long)cdiv(WG_BLOCKS, (long)gy * gz), NQ / px));
+    p.grid = dim3((unsigned)s, gy, gz);
+    return s * gy * gz;
+  };
+  int shape = 0;
+  long best = -1;
+  for (int i = 0; i < 4; ++i) {
+    const long padded = (long)cdiv(a, tco[i]) * tco[i] * cdiv(b, tci[i]) * tci[i];
+    if (best < 0 || padded < best) { best = padded; shape = i; }
+  }
+  if (splits(shape, 128) < 512) splits(WG_1x1, 64);
+  return p;
 }
+int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW) { return (int)wg_pick(N, Cin, Cout, HW).grid.x; }
 size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW) {
-  int pxw = wg_pxw(N, Cin, Cout, HW);
-  return (size_t)N * cdiv(HW, 4 * pxw) * Cin * Cout;
+  return (size_t)pw_wgrad_f32_parts(N, Cin, Cout, HW) * Cin * Cout;
 }
-static WgArgs wg_args(const float* g, const float* x, float* part, int N, int Cin, int Cout, int HW, dim3& grid) {
+static WgArgs wg_args(const float* g, const float* x, float* part, int N, int Cin, int Cout, int HW, const WgPick& p) {
   WgArgs w;
   w.g = g; w.x = x; w.part = part;
   w.Cin = Cin; w.Cout = Cout; w.HW = HW;
-  w.pxw = wg_pxw(N, Cin, Cout, HW);
-  w.cps = cdiv(HW, 4 * w.pxw);
-  w.tile_order = (pw_tile_order() & 2) && (Cin > 32 || Cout > 32);
-  grid = dim3(N * w.cps, cdiv(Cin, 32), cdiv(Cout, 32));
+  w.NQ = (long)N * HW;
+  w.splits = (int)p.grid.x;
+  w.tile_order = (pw_tile_order() & 2) && p.grid.y * p.grid.z > 1;
   return w;
+}
+template <int SHAPE>
+static void launch_wgrad(hipStream_t st, const WgArgs& w, dim3 grid, bool vec) {
+  if (vec) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true>), grid, dim3(256), 0, st, w);
+  else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false>), grid, dim3(256), 0, st, w);
+}
+static void launch_wgrad(hipStream_t st, const WgArgs& w, const WgPick& p) {
+  const bool vec = w.HW % 4 == 0;
+  switch (p.shape) {
+    case WG_2x2: launch_wgrad<WG_2x2>(st, w, p.grid, vec); break;
+    case WG_2x1: launch_wgrad<WG_2x1>(st, w, p.grid, vec); break;
+    case WG_1x2: launch_wgrad<WG_1x2>(st, w, p.grid, vec); break;
+    default: launch_wgrad<WG_1x1>(st, w, p.grid, vec); break;
+  }
 }
 void pw_wgrad_f32(hipStream_t st, const float* g, const float* x, float* part, float* G, int N,
                   int Cin, int Cout, int HW) {
-  dim3 grid;
-  const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, grid);
-  if (HW % 4 == 0) KLAUNCH(pw_wgrad_f32_kernel<true>, grid, dim3(256), 0, st, w);
-  else KLAUNCH(pw_wgrad_f32_kernel<false>, grid, dim3(256), 0, st, w);
+  const WgPick p = wg_pick(N, Cin, Cout, HW);
+  launch_wgrad(st, wg_args(g, x, part, N, Cin, Cout, HW, p), p);
   size_t n = (size_t)Cin * Cout;
-  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)grid.x);
+  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)p.grid.x);
 }
 
-template <int VAR>
-static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, dim3 gA, dim3 gW, bool vec) {
+template <int VAR, int SHAPE>
+static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, dim3 gA, dim3 gW) {
   const unsigned nA = gA.x * gA.y, nW = gW.x * gW.y * gW.z;
   constexpr const char* name = VAR == 0 ? "pw_bwd_dual_kernel<pk1>" : VAR == 1 ? "pw_bwd_dual_kernel<pk2>"
                              : VAR == 2 ? "pw_bwd_dual_kernel<pkks>" : "pw_bwd_dual_kernel<pk4>";
-  if (vec) KLAUNCH_NAMED(name, (pw_bwd_dual_kernel<VAR, true>), dim3(nA + nW), dim3(256), 0, st, a, w, nA, gA.x, gW.x, gW.y);
-  else KLAUNCH_NAMED(name, (pw_bwd_dual_kernel<VAR, false>), dim3(nA + nW), dim3(256), 0, st, a, w, nA, gA.x, gW.x, gW.y);
+  if (w.HW % 4 == 0)
+    KLAUNCH_NAMED(name, (pw_bwd_dual_kernel<VAR, SHAPE, true>), dim3(nA + nW), dim3(256), 0, st, a, w, nA, gA.x, gW.x, gW.y);
+  else
+    KLAUNCH_NAMED(name, (pw_bwd_dual_kernel<VAR, SHAPE, false>), dim3(nA + nW), dim3(256), 0, st, a, w, nA, gA.x, gW.x, gW.y);
+}
+template <int VAR>
+static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, dim3 gA, const WgPick& p) {
+  switch (p.shape) {
+    case WG_2x2: launch_dual<VAR, WG_2x2>(st, a, w, gA, p.grid); break;
+    case WG_2x1: launch_dual<VAR, WG_2x1>(st, a, w, gA, p.grid); break;
+    case WG_1x2: launch_dual<VAR, WG_1x2>(st, a, w, gA, p.grid); break;
+    default: launch_dual<VAR, WG_1x1>(st, a, w, gA, p.grid); break;
+  }
 }
 
 void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
                      float* part, float* G, int N, int Cin, int Cout, int HW) {
   const PwArgs a = pw_args(Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW);  // dx = W^T g (+ add)
   const PwPick p = pw_pick(a.NQ, HW, Cout, Cin);
-  dim3 gW;
-  const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, gW);
-  const bool vec = HW % 4 == 0;
+  const WgPick wp = wg_pick(N, Cin, Cout, HW);
+  const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
   if (p.var == 2 && p.wv > 4) {
     // long K: the input gradient runs as wider blocks (K split 8 or 16 ways) than the weight-gradient
     // kernel's, so the two go as separate launches
     launch_pkks(st, a, p);
-    if (vec) KLAUNCH(pw_wgrad_f32_kernel<true>, gW, dim3(256), 0, st, w);
-    else KLAUNCH(pw_wgrad_f32_kernel<false>, gW, dim3(256), 0, st, w);
+    launch_wgrad(st, w, wp);
   } else switch (p.var) {
-    case 2: launch_dual<2>(st, a, w, p.grid, gW, vec); break;
-    case 3: launch_dual<3>(st, a, w, p.grid, gW, vec); break;
-    case 1: launch_dual<1>(st, a, w, p.grid, gW, vec); break;
-    default: launch_dual<0>(st, a, w, p.grid, gW, vec); break;
+    case 2: launch_dual<2>(st, a, w, p.grid, wp); break;
+    case 3: launch_dual<3>(st, a, w, p.grid, wp); break;
+    case 1: launch_dual<1>(st, a, w, p.grid, wp); break;
+    default: launch_dual<0>(st, a, w, p.grid, wp); break;
   }
   size_t n = (size_t)Cin * Cout;
-  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)gW.x);
+  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)wp.grid.x);
 }
 
 __global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __restrict__ tasks,
@@ -758,7 +849,6 @@ __global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __rest
 void reduce_tasks_f32(hipStream_t st, const RedTask* tasks_dev, const unsigned short* block_task_dev, int nblocks) {
   KLAUNCH(reduce_tasks_kernel, dim3(nblocks), dim3(256), 0, st, tasks_dev, block_task_dev);
 }
-int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW) { return N * cdiv(HW, 4 * wg_pxw(N, Cin, Cout, HW)); }
 
 void reduce_parts_acc_f32(hipStream_t st, const float* part, float* G, size_t n, int parts) {
   KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, parts);

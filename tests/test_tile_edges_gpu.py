@@ -34,3 +34,18 @@ def test_dense_conv_tiles(A, cin, cout, k, stride, h, w, B):
 ])
 def test_batchnorm_planes_not_a_multiple_of_16_bytes(A, c, h, w, B):
     check(one([bn(c), simple("relu6")], (c, h, w), B=B), rounds=1)
+
+
+@pytest.mark.parametrize("cin,cout,h,w,B", [
+    (96, 128, 16, 16, 64),   # blocks of 2x2 weight tiles, whole
+    (56, 232, 14, 14, 77),   # 2x2, ragged rows of both operands
+    (24, 144, 19, 20, 60),   # one tile of input channels: 1x1 blocks, four wavefronts a tile
+    (160, 40, 13, 14, 90),   # 2x2 and 1x2 pad the same number of tiles
+    (80, 24, 9, 9, 200),     # 1x2, planes no multiple of 16 bytes
+    (24, 80, 9, 9, 200),     # 2x1, the same
+    (256, 192, 7, 7, 43),    # steps of 32 pixels across samples of 49
+    (33, 65, 7, 7, 3),       # few blocks: one step, rows past both edges
+    (8, 8, 1, 1, 5),         # fewer pixels than a step
+])
+def test_pointwise_conv_tiles(A, cin, cout, h, w, B):
+    check(one([conv(cin, cout, 1, 1, 0)], (cin, h, w), B=B), rounds=1)
