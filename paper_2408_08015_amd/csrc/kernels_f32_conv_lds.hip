@@ -12,6 +12,7 @@
 #include <array>
 #include <cmath>
 #include <map>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "kernels.h"
@@ -90,15 +91,22 @@ __device__ __forceinline__ void conv_lds_body(const LdsArgs& a, const LdsClass& 
   for (int pos = tid; pos < NP * 64; pos += T)
     tabv[pos] = virtual_offset(pos, vr0, a.rows, a.rRW, a.rXH1, a.N, a.XH, a.XW, a.XRW, a.XS, (unsigned)a.Kdim * a.XHW);
   const __amdgpu_buffer_rsrc_t rx = rsrc_of(a.X, a.x_bytes);
-  auto stage = [&](int k0, float* dst) __attribute__((always_inline)) {
-    int cc = wave / NP, i = wave - cc * NP;
-    const int dc = waves / NP, di = waves - dc * NP;
-    while (cc < CH) {
-      const unsigned k = (unsigned)min(k0 + cc, a.Kdim - 1);  // rows past Kdim meet zero weights
-      copy_to_lds(rx, dst + cc * PL + i * 64, tabv[i * 64 + lane], k * a.XHW * 4u);
-      cc += dc;
-      i += di;
-      if (i >= NP) { i -= NP; ++cc; }
+  // The copies of a chunk are dealt to the wavefronts round robin; a wavefront takes its share up in pieces: `i` is the
+  // 64-position block and `cc` the channel of its next copy.
+  const int dc = waves / NP, di = waves - dc * NP;
+  const int ncopy = (CH * NP - wave + waves - 1) / waves;  // of this wavefront
+  struct { int cc, i; } cur = {};
+  auto first_copy = [&]() __attribute__((always_inline)) {
+    cur.cc = wave / NP;
+    cur.i = wave - cur.cc * NP;
+  };
+  auto copies = [&](int k0, float* dst, int count) __attribute__((always_inline)) {
+    for (int n = 0; n < count; ++n) {
+      const unsigned k = (unsigned)min(k0 + cur.cc, a.Kdim - 1);  // rows past Kdim meet zero weights
+      copy_to_lds(rx, dst + cur.cc * PL + cur.i * 64, tabv[cur.i * 64 + lane], k * a.XHW * 4u);
+      cur.cc += dc;
+      cur.i += di;
+      if (cur.i >= NP) { cur.i -= NP; ++cur.cc; }
     }
   };
   const unsigned q = q0 + wn * 32 + col;
@@ -134,20 +142,28 @@ __device__ __forceinline__ void conv_lds_body(const LdsArgs& a, const LdsClass& 
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
   __syncthreads();
-  stage(0, buf0);
+  first_copy();
+  copies(0, buf0, ncopy);
   __syncthreads();  // (waits for the copies)
   const int nchunk = (KG + WK - 1) / WK;
-  for (int ch = 0; ch < nchunk; ++ch) {
-    const bool more = ch + 1 < nchunk;
-    if (more) stage((ch + 1) * CH, buf0 + ((ch + 1) & 1) * bufsz);
+  // The copies of the next chunk leave between the products of the first CT taps, so that their issue and their
+  // table reads run beside matrix instructions; the weights of the next chunk follow tap by tap, LATE of them behind the
+  // last copy.  Vector-memory results return in order: vmcnt(LATE) at the end of a chunk waits for the copies and leaves
+  // those weights in flight over the barrier.
+  constexpr int CT = NT == 9 ? 6 : NT == 4 ? 2 : 1, LATE = (NT - CT + 1) * MT;
+  const int piece = (ncopy + CT - 1) / CT;
+  auto chunk = [&](int ch, auto more_c) __attribute__((always_inline)) {
+    constexpr bool more = decltype(more_c)::value;
     const float* lb = buf0 + (ch & 1) * bufsz + (8 * wk + half) * PL + base;
-    const bool live = ch * WK + wk < KG;  // uniform per wavefront
+    float* const next = buf0 + ((ch + 1) & 1) * bufsz;
+    const bool live = more || ch * WK + wk < KG;  // uniform per wavefront; only the last chunk can be short
     float b[2][4];
     auto ldB = [&](int i) __attribute__((always_inline)) {
       const float* p = lb + boff[i];
 #pragma unroll
       for (int e = 0; e < 4; ++e) b[i & 1][e] = p[2 * e * PL];
     };
+    if (more) first_copy();
     ldB(0);
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -161,10 +177,24 @@ __device__ __forceinline__ void conv_lds_body(const LdsArgs& a, const LdsClass& 
             acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b[i & 1][e], acc[m], 0, 0, 0);
           }
       }
-      if (more) ldA(i, ch + 1);
+      if constexpr (more) {
+        if (i < CT) {
+          copies((ch + 1) * CH, next, max(0, min(piece, ncopy - i * piece)));
+          asm volatile("" ::: "memory");  // the copies stay in front of the weights of this tap and the next ones
+        }
+        ldA(i, ch + 1);
+      }
     }
-    __syncthreads();
-  }
+    if constexpr (more) {
+      // lgkmcnt: this wavefront's reads of the buffer that the next chunk overwrites are done
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+  };
+  for (int ch = 0; ch + 1 < nchunk; ++ch) chunk(ch, std::true_type{});
+  chunk(nchunk - 1, std::false_type{});
+  if (WK > 1) __syncthreads();  // the partial tiles overwrite the staged pixels
 
   float* yq = a.Y + (size_t)qn * a.Mdim * a.OH * a.OW + (size_t)(a.SO * qi + c.oy) * a.OW + a.SO * qj + c.ox;
   const size_t OHW = (size_t)a.OH * a.OW;
@@ -456,11 +486,17 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
           acc[i * KK * TJ + t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], bb[t], acc[i * KK * TJ + t], 0, 0, 0);
     };
     ld(0, av[0], b[0]);
-    for (int k = 0; k < ks; k += 2) {  // operands one pair ahead of the products
+    // Operands one pair ahead of the products.  The scheduler, left alone, moves the reads of a pair behind the
+    // products that should cover them; and a conditional last read costs register copies that wait for it.
+    for (int k = 0; k < ks; k += 2) {
       ld(k + 1, av[1], b[1]);
+      __builtin_amdgcn_sched_barrier(0);
       mma(av[0], b[0]);
-      if (k + 2 < ks) ld(k + 2, av[0], b[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      ld(min(k + 2, ks - 1), av[0], b[0]);  // (the last one is not used)
+      __builtin_amdgcn_sched_barrier(0);
       mma(av[1], b[1]);
+      __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
     if (w.nbuf == 1 && s + 1 < s_end) {
