@@ -65,8 +65,7 @@ __device__ __forceinline__ void pw_block_xy(unsigned id, unsigned gx, unsigned g
 // k-group g (8 consecutive k), lane l = (m%32, h) finds the four values A[m][8g + 2e + h],
 // e = 0..3, as one 16-byte word at Wp[(t*KG + g)*64 + l]; out-of-range m and k are zero
 // there.  A wavefront therefore reads its operands with fully coalesced 16-byte loads
-// and needs neither LDS nor a barrier, and all loads of a pass are issued before its first
-// MFMA.  NCH = 32-channel chunks per pass.
+// and needs neither LDS nor a barrier.  NCH = 1: up to 32 input channels, 2: more.
 // Statistics epilogue of the forward product (for a BatchNorm behind the convolution): lane l
 // holds, for each of its 16 accumulator rows, the sum s and sum of squares q of its pixels; the
 // block adds them per channel over its pixels (through LDS, two rounds of 16 KB) and writes one
@@ -98,6 +97,57 @@ __device__ __forceinline__ void pw_stats_epilogue(const float (&s)[16], const fl
   }
 }
 
+// acc += A X over the k-groups [gbeg, gend) of one 32 x 32 tile, in stages of four groups: while a stage is multiplied
+// the next one is in flight, and the one behind it is requested as soon as registers are free.  (With all loads of
+// eight groups in front of their products a wavefront alternated between waiting and multiplying, and the few
+// wavefronts of a SIMD did so in step.)  Branch-free: rows past Kdim read the last row (zero weights in the packed
+// copy), groups past the last read that one again and are not multiplied, pixels past NQ read pixel 0 and are replaced
+// by zero (the statistics epilogue sums every column).  wl: lane's weights of the tile; xq: lane's pixel.
+// Before and after, at 32 x 56x56 pixels with the 128-pixel wavefronts: 64 -> 256 channels 58.9 -> 55.3 us,
+// 256 -> 64 42.8 -> 37.3; backward of 256 -> 64 77.0 -> 73.8, of 64 -> 256 110.1 -> 103.0.
+__device__ __forceinline__ void pw_contract(const float4* __restrict__ wl, const float* __restrict__ xq, int HW, int Kdim,
+                                            int gbeg, int gend, int half, bool qv, floatx16& acc) {
+  if (gbeg >= gend) return;  // uniform
+  float4 a0[4], a1[4];
+  float b0[16], b1[16];
+  auto load = [&](float4 (&a)[4], float (&b)[16], int g0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int gg = min(g0 + g, gend - 1);
+      a[g] = wl[(size_t)gg * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[4 * g + e] = xq[(size_t)min(gg * 8 + 2 * e + half, Kdim - 1) * HW];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma = [&](const float4 (&a)[4], const float (&b)[16], int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (g >= n) break;  // uniform
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(e == 0 ? a[g].x : e == 1 ? a[g].y : e == 2 ? a[g].z : a[g].w,
+                                                   qv ? b[4 * g + e] : 0.f, acc, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load(a0, b0, gbeg);
+  if (gend - gbeg <= 4) {
+    mma(a0, b0, gend - gbeg);
+    return;
+  }
+  load(a1, b1, gbeg + 4);
+  int g = gbeg;
+  for (; g + 8 < gend; g += 8) {
+    mma(a0, b0, 4);
+    load(a0, b0, g + 8);
+    mma(a1, b1, 4);
+    load(a1, b1, g + 12);
+  }
+  mma(a0, b0, 4 < gend - g ? 4 : gend - g);
+  mma(a1, b1, gend - g - 4);
+}
+
 template <int NCH>
 __device__ __forceinline__ void pw_pk_body(const PwArgs& a, int bx, int by, float (*sR)[16][64], int P) {
   const float4* __restrict__ Wp = a.Wp;
@@ -124,31 +174,7 @@ __device__ __forceinline__ void pw_pk_body(const PwArgs& a, int bx, int by, floa
   floatx16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int g0 = 0; g0 < KG; g0 += NCH * 4) {
-    float4 a[NCH * 4];
-    float b[NCH * 16];
-#pragma unroll
-    for (int g = 0; g < NCH * 4; ++g) {
-      const bool ok = g0 + g < KG;
-      a[g] = ok ? wl[(size_t)(g0 + g) * 64] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        // branch-free: rows past Kdim read the last row (zero weights in the packed copy), pixels past
-        // NQ read pixel 0 and are replaced by zero (the statistics epilogue sums every column)
-        const int k = min((g0 + g) * 8 + 2 * e + half, Kdim - 1);
-        const float val = xq[(size_t)k * HW];
-        b[4 * g + e] = qv ? val : 0.f;
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < NCH * 4; ++g) {
-      if (NCH > 1 && g0 + g >= KG) break;  // uniform: skip the empty tail of the last pass
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].x, b[4 * g + 0], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].y, b[4 * g + 1], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].z, b[4 * g + 2], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].w, b[4 * g + 3], acc, 0, 0, 0);
-    }
-  }
+  pw_contract(wl, xq, HW, Kdim, 0, NCH == 1 ? min(KG, 4) : KG, half, qv, acc);
   if (qv) {
     float* yq = Y + (size_t)n * Mdim * HW + p;
     const float* aq = add ? add + (size_t)n * Mdim * HW + p : nullptr;
@@ -174,7 +200,7 @@ __device__ __forceinline__ void pw_pk_body(const PwArgs& a, int bx, int by, floa
   }
 }
 template <int NCH>
-__global__ __launch_bounds__(256) void pw_conv_f32_pk_kernel(PwArgs a) {
+__global__ __launch_bounds__(256, NCH == 1 ? 1 : 4) void pw_conv_f32_pk_kernel(PwArgs a) {
   __shared__ float sR[4][16][64];
   int bx, by;
   pw_block_xy(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, a.tile_order, bx, by);
@@ -195,8 +221,7 @@ __device__ __forceinline__ void pw_pkks_body(const PwArgs& a, int bx, int by, fl
   const long NQ = a.NQ;
   const int HW = a.HW, Kdim = a.Kdim, Mdim = a.Mdim, KG = a.KG;
 
-  constexpr int NCH = 2;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform
   const int col = lane & 31, half = lane >> 5;
   const int m_base = by * 32;
   const unsigned q = (unsigned)bx * 32u + col;  // pixels per micro-batch < 2^31 (checked at create)
@@ -214,29 +239,7 @@ __device__ __forceinline__ void pw_pkks_body(const PwArgs& a, int bx, int by, fl
   floatx16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int g0 = gbeg; g0 < gend; g0 += NCH * 4) {
-    float4 a[NCH * 4];
-    float b[NCH * 16];
-#pragma unroll
-    for (int g = 0; g < NCH * 4; ++g) {
-      const bool ok = g0 + g < gend;
-      a[g] = ok ? wl[(size_t)(g0 + g) * 64] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = min((g0 + g) * 8 + 2 * e + half, Kdim - 1);  // branch-free, as above
-        const float val = xq[(size_t)k * HW];
-        b[4 * g + e] = qv ? val : 0.f;
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < NCH * 4; ++g) {
-      if (g0 + g >= gend) break;  // uniform
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].x, b[4 * g + 0], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].y, b[4 * g + 1], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].z, b[4 * g + 2], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g].w, b[4 * g + 3], acc, 0, 0, 0);
-    }
-  }
+  pw_contract(wl, xq, HW, Kdim, gbeg, gend, half, qv, acc);
 #pragma unroll
   for (int r = 0; r < 16; ++r) sR[wave][r][lane] = acc[r];
   __syncthreads();
@@ -297,33 +300,46 @@ __device__ __forceinline__ void pw_pk4_body(const PwArgs& a, int bx, int by, flo
   for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-  for (int g0 = 0; g0 < KG; g0 += 4) {
-    float4 a[4];
-    float4 b[16];
+  // Stages of two groups, pipelined as in pw_contract.
+  float4 a0[2], a1[2], b0[8], b1[8];
+  auto load = [&](float4 (&a)[2], float4 (&b)[8], int g0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const bool ok = g0 + g < KG;
-      a[g] = ok ? wl[(size_t)(g0 + g) * 64] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int g = 0; g < 2; ++g) {
+      const int gg = min(g0 + g, KG - 1);
+      a[g] = wl[(size_t)gg * 64];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = min((g0 + g) * 8 + 2 * e + half, Kdim - 1);  // branch-free, as above
-        const float4 val = *reinterpret_cast<const float4*>(xq + (size_t)k * HW);
-        b[4 * g + e] = qv ? val : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+      for (int e = 0; e < 4; ++e)
+        b[4 * g + e] = *reinterpret_cast<const float4*>(xq + (size_t)min(gg * 8 + 2 * e + half, Kdim - 1) * HW);
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma = [&](const float4 (&a)[2], const float4 (&b)[8], int n) __attribute__((always_inline)) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (g0 + g >= KG) break;
+    for (int g = 0; g < 2; ++g) {
+      if (g >= n) break;  // uniform
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float av = e == 0 ? a[g].x : e == 1 ? a[g].y : e == 2 ? a[g].z : a[g].w;
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b[4 * g + e].x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b[4 * g + e].y, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b[4 * g + e].z, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b[4 * g + e].w, acc[3], 0, 0, 0);
+        const float4 v = qv ? b[4 * g + e] : make_float4(0.f, 0.f, 0.f, 0.f);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.x, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.y, acc[1], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.z, acc[2], 0, 0, 0);
+        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.w, acc[3], 0, 0, 0);
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load(a0, b0, 0);
+  if (KG > 2) load(a1, b1, 2);
+  int g = 0;
+  for (; g + 4 < KG; g += 4) {
+    mma(a0, b0, 2);
+    load(a0, b0, g + 4);
+    mma(a1, b1, 2);
+    load(a1, b1, g + 6);
   }
+  mma(a0, b0, KG - g);
+  if (KG > 2) mma(a1, b1, KG - g - 2);
   if (qv) {
     float* yq = Y + (size_t)n * Mdim * HW + p;
     const float* aq = add ? add + (size_t)n * Mdim * HW + p : nullptr;
@@ -634,7 +650,7 @@ __global__ __launch_bounds__(256) void pw_wgrad_f32_kernel(WgArgs w) {
 // 0 / 1 = 32-pixel wavefronts with one / two 32-channel chunks per pass, 2 = K split over the
 // block, 3 = 128-pixel wavefronts.
 template <int VAR, int SHAPE, bool VEC>
-__global__ __launch_bounds__(256) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
+__global__ __launch_bounds__(256, VAR == 1 ? 4 : 1) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
                                                           unsigned gWx, unsigned gWy) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   static_assert(wg_lds_floats<SHAPE>() >= 4 * 16 * 64, "the product kernels use 16 KB");
