@@ -566,9 +566,16 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
   const int wk = wave % KS, wt = wave / KS, wci = wt % TCI, wco = wt / TCI;
   const int ra = wco * 32 + row, rb = TCO * 32 + wci * 32 + row;
   const int swa = T::swz(ra), swb = T::swz(rb);
-  floatx16 acc;
+  // The pixels of a chunk go to NA accumulators in turn.  A sum's rounding error grows with its chain of additions, and the
+  // chains of a wavefront that has a tile to itself are the longest.  Relative error of dW against 64 bits with one
+  // accumulator and now: 64 -> 256 channels at 32 x 56x56 3.2e-7, 1.6e-7; 512 -> 2048 at 8 x 7x7 1.5e-7, 0.9e-7; 16 -> 96 at
+  // 16 x 112x112 1.9e-7, 1.4e-7.  Four everywhere cost MobileNetV2's small planes a wavefront per SIMD: 3 % of its round.
+  constexpr int NA = KS == 1 ? 4 : 2;
+  floatx16 acc[NA];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int e = 0; e < NA; ++e)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[e][r] = 0.f;
   if (s0 < s1) {  // uniform
     load(s0);
     store(0);
@@ -583,14 +590,16 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
       const int j = 2 * (wk * (CH / 2 / KS) + k) + half;
       const float4 a = *reinterpret_cast<const float4*>(o + ra * PX + 4 * (j ^ swa));
       const float4 b = *reinterpret_cast<const float4*>(o + rb * PX + 4 * (j ^ swb));
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc[0], 0, 0, 0);
+      acc[1 % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc[1 % NA], 0, 0, 0);
+      acc[2 % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc[2 % NA], 0, 0, 0);
+      acc[3 % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc[3 % NA], 0, 0, 0);
     }
     if (s + 1 < s1) store(buf ^ 1);
     __syncthreads();
   }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][r] = NA == 4 ? (acc[0][r] + acc[1][r]) + (acc[2 % NA][r] + acc[3 % NA][r]) : acc[0][r] + acc[1][r];
   float* out = w.part + (size_t)split * Cout * Cin;
   const int ci = ci_base + wci * 32 + row;
   if constexpr (KS == 1) {
@@ -598,12 +607,12 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int co = co_base + wco * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (co < Cout) out[(size_t)co * Cin + ci] = acc[r];
+        if (co < Cout) out[(size_t)co * Cin + ci] = acc[0][r];
       }
     }
   } else {  // the KS wavefronts of a tile add their sums in a fixed order; the staging buffers are free by now
 #pragma unroll
-    for (int r = 0; r < 16; ++r) lds[(wave * 16 + r) * 64 + lane] = acc[r];
+    for (int r = 0; r < 16; ++r) lds[(wave * 16 + r) * 64 + lane] = acc[0][r];
     __syncthreads();
     if (ci < Cin) {
 #pragma unroll
@@ -633,8 +642,9 @@ constexpr int wg_lds_floats() {
   return SHAPE == WG_2x2 ? WgTile<2, 2, 1>::LDS : SHAPE == WG_1x1 ? WgTile<1, 1, 4>::LDS : WgTile<2, 1, 2>::LDS;
 }
 
+// (four wavefronts per SIMD; with four accumulators and unvectorised staging registers suffice for three)
 template <int SHAPE, bool VEC>
-__global__ __launch_bounds__(256) void pw_wgrad_f32_kernel(WgArgs w) {
+__global__ __launch_bounds__(256, SHAPE == WG_2x2 && !VEC ? 3 : 4) void pw_wgrad_f32_kernel(WgArgs w) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   int bx, t;
   pw_block_xy((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x, gridDim.y * gridDim.z,
@@ -650,7 +660,7 @@ __global__ __launch_bounds__(256) void pw_wgrad_f32_kernel(WgArgs w) {
 // 0 / 1 = 32-pixel wavefronts with one / two 32-channel chunks per pass, 2 = K split over the
 // block, 3 = 128-pixel wavefronts.
 template <int VAR, int SHAPE, bool VEC>
-__global__ __launch_bounds__(256, VAR == 1 ? 4 : 1) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
+__global__ __launch_bounds__(256, VAR >= 2 ? 1 : SHAPE == WG_2x2 && !VEC ? 3 : 4) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
                                                           unsigned gWx, unsigned gWy) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   static_assert(wg_lds_floats<SHAPE>() >= 4 * 16 * 64, "the product kernels use 16 KB");
@@ -796,9 +806,11 @@ void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* d
   if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)wp.grid.x);
 }
 
+// (sums in 64 bits: the kernel waits for memory, and adding partials in 32 bits was a third of the rounding error of a
+// weight gradient)
 __global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __restrict__ tasks,
                                                            const unsigned short* __restrict__ block_task) {
-  __shared__ float sh[4][64];
+  __shared__ double sh[4][64];
   const RedTask t = tasks[block_task[blockIdx.x]];
   if (t.wide) {  // uniform per block
     const size_t i4 = ((size_t)(blockIdx.x - t.block0) * 256 + threadIdx.x) * 4;
@@ -806,23 +818,22 @@ __global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __rest
     const float* p4 = t.part + i4;
     const size_t st4 = t.stride;
     const int parts4 = (int)t.parts;
-    float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    double s4[4] = {0.0, 0.0, 0.0, 0.0};
     int c4 = 0;
     for (; c4 + 4 <= parts4; c4 += 4) {
       const float4 v0 = *reinterpret_cast<const float4*>(p4 + (size_t)c4 * st4);
       const float4 v1 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 1) * st4);
       const float4 v2 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 2) * st4);
       const float4 v3 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 3) * st4);
-      s4.x += (v0.x + v1.x) + (v2.x + v3.x);
-      s4.y += (v0.y + v1.y) + (v2.y + v3.y);
-      s4.z += (v0.z + v1.z) + (v2.z + v3.z);
-      s4.w += (v0.w + v1.w) + (v2.w + v3.w);
+      s4[0] += ((double)v0.x + v1.x) + ((double)v2.x + v3.x);
+      s4[1] += ((double)v0.y + v1.y) + ((double)v2.y + v3.y);
+      s4[2] += ((double)v0.z + v1.z) + ((double)v2.z + v3.z);
+      s4[3] += ((double)v0.w + v1.w) + ((double)v2.w + v3.w);
     }
     for (; c4 < parts4; ++c4) {
       const float4 v = *reinterpret_cast<const float4*>(p4 + (size_t)c4 * st4);
-      s4.x += v.x; s4.y += v.y; s4.z += v.z; s4.w += v.w;
+      s4[0] += v.x; s4[1] += v.y; s4[2] += v.z; s4[3] += v.w;
     }
-    const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       size_t out = i4 + e;
@@ -830,7 +841,7 @@ __global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __rest
         const size_t tp = out / t.mn;
         out = (out - tp * t.mn) * t.taps + tp;
       }
-      t.G[out] += sv[e];
+      t.G[out] = (float)(t.G[out] + s4[e]);
     }
     return;
   }
@@ -839,14 +850,14 @@ __global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __rest
   const size_t i = (size_t)(blockIdx.x - t.block0) * 64 + o;
   const int parts = (int)t.parts;
   const float* p = t.part + i;
-  float s = 0.f;
+  double s = 0.0;
   if (i < n) {
     int c = q;
     for (; c + 28 < parts; c += 32) {  // eight independent loads in flight
-      float v0 = p[(size_t)c * st], v1 = p[(size_t)(c + 4) * st];
-      float v2 = p[(size_t)(c + 8) * st], v3 = p[(size_t)(c + 12) * st];
-      float v4 = p[(size_t)(c + 16) * st], v5 = p[(size_t)(c + 20) * st];
-      float v6 = p[(size_t)(c + 24) * st], v7 = p[(size_t)(c + 28) * st];
+      const double v0 = p[(size_t)c * st], v1 = p[(size_t)(c + 4) * st];
+      const double v2 = p[(size_t)(c + 8) * st], v3 = p[(size_t)(c + 12) * st];
+      const double v4 = p[(size_t)(c + 16) * st], v5 = p[(size_t)(c + 20) * st];
+      const double v6 = p[(size_t)(c + 24) * st], v7 = p[(size_t)(c + 28) * st];
       s += ((v0 + v1) + (v2 + v3)) + ((v4 + v5) + (v6 + v7));
     }
     for (; c < parts; c += 4) s += p[(size_t)c * st];
@@ -859,7 +870,7 @@ __global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __rest
       const size_t tp = i / t.mn;
       out = (i - tp * t.mn) * t.taps + tp;
     }
-    t.G[out] += (sh[0][o] + sh[1][o]) + (sh[2][o] + sh[3][o]);
+    t.G[out] = (float)(t.G[out] + ((sh[0][o] + sh[1][o]) + (sh[2][o] + sh[3][o])));
   }
 }
 void reduce_tasks_f32(hipStream_t st, const RedTask* tasks_dev, const unsigned short* block_task_dev, int nblocks) {

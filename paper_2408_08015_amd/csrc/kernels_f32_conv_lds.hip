@@ -405,6 +405,13 @@ struct LdsWgArgs {
   unsigned npix;
 };
 
+__device__ __forceinline__ double sum8(const float* p) {  // the eight wavefronts' values, rounded once
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) s += p[1024 * w];
+  return s;
+}
+
 // Block of eight wavefronts, one per compute unit: a 32 x 32 tile of (cout, cin), all taps (1x1: 64 x 64), over a run of stages of
 // PT consecutive output pixels, whatever samples they lie in.  A stage copies g [32][PT] and the virtual rows of x
 // under it to LDS with coalesced loads (lanes along the pixels: a load per lane and channel row would touch 64 cache
@@ -518,8 +525,7 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) {
       const int r = 2 * wave + rr, co = ti * 32 + 8 * (r >> 2) + 4 * half + (r & 3), o = r * 64 + lane;
-      so[co * RO + (tj * 32 + row) * KK + tap] = ((sR[o] + sR[o + 1024]) + (sR[o + 2048] + sR[o + 3072])) +
-                                                 ((sR[o + 4096] + sR[o + 5120]) + (sR[o + 6144] + sR[o + 7168]));
+      so[co * RO + (tj * 32 + row) * KK + tap] = (float)sum8(sR + o);
     }
   }
   __syncthreads();
