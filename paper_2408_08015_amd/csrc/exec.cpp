@@ -233,9 +233,9 @@ void bwd_op(Ctx& c, const Op& op) {
       if (gin)  // input gradient and weight-gradient partials share one launch
         pw_conv_bwd_f32(st, s.wpack + op.wp2_off, g, (float*)gin,
                         op.dgrad_add >= 0 ? (cf)grad_ptr(c, op.dgrad_add) : nullptr, (cf)act_ptr(c, op.in), part, Gw,
-                        I.n, op.cin, op.cout, HW);
+                        I.n, op.cin, op.cout, HW, op.wg_cap);
       else
-        pw_wgrad_f32(st, g, (cf)act_ptr(c, op.in), part, Gw, I.n, op.cin, op.cout, HW);
+        pw_wgrad_f32(st, g, (cf)act_ptr(c, op.in), part, Gw, I.n, op.cin, op.cout, HW, op.wg_cap);
       if (op.has_bias) channel_sum_acc_f32(st, g, s.G + op.b_off, I.n, op.cout, HW);
       break;
     }
@@ -287,7 +287,7 @@ void bwd_op(Ctx& c, const Op& op) {
       const Act& O = s.acts[op.out];
       conv_mfma_bwd_f32(st, s.wpack + op.wp2_off, g, (float*)gin, (cf)act_ptr(c, op.in),
                         reinterpret_cast<float*>(scratch(c, op)), s.red_nblocks ? nullptr : s.G + op.w_off, I.n, op.cin,
-                        op.cout, I.h, I.w, op.k, op.stride);
+                        op.cout, I.h, I.w, op.k, op.stride, op.wg_cap);
       if (op.has_bias) channel_sum_acc_f32(st, g, s.G + op.b_off, I.n, op.cout, O.h * O.w);
       break;
     }
@@ -763,7 +763,7 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
     switch (op.kind) {
       case OP_CONV_PW: {
         const size_t n = (size_t)op.cin * op.cout;
-        add(scf, s.G + op.w_off, n, pw_wgrad_f32_parts(I.n, op.cin, op.cout, I.h * I.w), n, 1, n);
+        add(scf, s.G + op.w_off, n, pw_wgrad_f32_parts(I.n, op.cin, op.cout, I.h * I.w, op.wg_cap), n, 1, n);
         break;
       }
       case OP_CONV_GK: {
@@ -773,7 +773,7 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
       }
       case OP_CONV_3X3: {
         const size_t n = (size_t)op.cin * op.cout * op.k * op.k;
-        add(scf, s.G + op.w_off, n, conv_mfma_wgrad_parts(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride), n, 1, n);
+        add(scf, s.G + op.w_off, n, conv_mfma_wgrad_parts(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride, op.wg_cap), n, 1, n);
         break;
       }
       case OP_CONV_DW:

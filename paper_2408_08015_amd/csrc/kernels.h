@@ -38,9 +38,9 @@ void pw_conv_f32(hipStream_t st, const float* Wp, const float* X, float* Y, cons
 //   part[chunk][co][ci] = sum_{p in chunk} g[n][co][p] * x[n][ci][p];  then G += sum_chunk part.
 // `part` must hold pw_wgrad_f32_ws(N,Cin,Cout,HW) floats; with G = NULL only the partials are
 // written (pw_wgrad_f32_parts of them, Cout*Cin floats each).
-size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW);
+size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW, int cap);
 void pw_wgrad_f32(hipStream_t st, const float* g, const float* x, float* part, float* G, int N,
-                  int Cin, int Cout, int HW);
+                  int Cin, int Cout, int HW, int cap);
 
 // Depthwise 3x3 convolution, pad 1, stride 1 or 2, weights [C][3][3].
 // The forward kernel can take over the BatchNorm passes around it:
@@ -82,18 +82,20 @@ bool dw3x3_supported(int H, int W, int stride);  // else the generic grouped-con
 // [Cout][Cin][k*k]); G (may be NULL: the caller reduces the partials) += their sum.
 bool conv_mfma_supported(int Cin, int Cout, int k, int stride, int pad, int groups, int H, int W);
 size_t conv_mfma_pack_floats(int Mdim, int Kdim, int k);
-int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride);
-size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int stride);
+// At most `cap` partials; the small count is what a stage falls back on to fit the static scratch array.
+int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
+int conv_mfma_wgrad_small_parts(int N, int Cin, int Cout, int H, int W, int k, int stride);
+size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
 void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y, const float* bias, int N, int Cin,
                        int Cout, int H, int W, int k, int stride);
 void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* x, float* part,
-                       float* G, int N, int Cin, int Cout, int H, int W, int k, int stride);
+                       float* G, int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
 // The LDS-staged kernels behind the calls above (kernels_f32_conv_lds.hip); false / 0 where no block shape fits.
 bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
                       const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S);
-int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S);
+int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap);
 void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const float* x, float* part, int N, int Cin, int Cout,
-                    int H, int W, int KS, int S);
+                    int H, int W, int KS, int S, int cap);
 // 7x7 dense conv with fewer than 8 input channels (ResNet's stem) on the matrix cores: the contraction index is
 // the flattened (ci, u, v); Wp = pw_pack of W as the [Cout][Cin*49] matrix.  Forward and weight gradient
 // (partials [chunk][Cout][Cin*49] in `part`, G may be NULL: the caller reduces).
@@ -171,11 +173,12 @@ struct RedTask {
   unsigned n, parts, block0, stride, taps, mn, wide, pad;
 };
 void reduce_tasks_f32(hipStream_t st, const RedTask* tasks_dev, const unsigned short* block_task_dev, int nblocks);
-int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW);  // partial count of pw_wgrad_f32
+int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW, int cap);  // partial count of pw_wgrad_f32, at most cap
+int pw_wgrad_f32_small_parts(int N, int Cin, int Cout, int HW);  // the count of a stage that has to fit the static scratch
 // Backward of a pointwise conv in one launch: dx = W^T g (+ add) with Wp_t the packed W^T, and
 // the weight-gradient partials (then G += their sum, unless G is NULL: left to the caller).
 void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
-                     float* part, float* G, int N, int Cin, int Cout, int HW);
+                     float* part, float* G, int N, int Cin, int Cout, int HW, int cap);
 // G[c] += sum_{n,p} g[n][c][p]
 void channel_sum_acc_f32(hipStream_t st, const float* g, float* G, int N, int C, int HW);
 

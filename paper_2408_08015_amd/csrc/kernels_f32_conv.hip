@@ -709,7 +709,7 @@ __global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __re
 // upwards: 96 -> 576 channels at 8 x 14x14 12.3 us with 36 blocks of 2x2 tiles, 7.2 us with 810 of 1x1.
 static constexpr int WG_BLOCKS = 768;
 struct WgPick { int shape; dim3 grid; };
-static WgPick wg_pick(int N, int Cin, int Cout, int HW) {
+static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
   const int a = cdiv(Cout, 32), b = cdiv(Cin, 32);
   static const int tco[4] = {2, 2, 1, 1}, tci[4] = {2, 1, 2, 1};
   const long NQ = (long)N * HW;
@@ -717,7 +717,7 @@ static WgPick wg_pick(int N, int Cin, int Cout, int HW) {
   auto splits = [&](int shape, int px) {
     p.shape = shape;
     const int gy = cdiv(b, tci[shape]), gz = cdiv(a, tco[shape]);
-    const long s = std::max(1L, std::min((long)cdiv(WG_BLOCKS, (long)gy * gz), NQ / px));
+    const long s = std::max(1L, std::min({(long)cdiv(WG_BLOCKS, (long)gy * gz), NQ / px, (long)cap}));
     p.grid = dim3((unsigned)s, gy, gz);
     return s * gy * gz;
   };
@@ -730,9 +730,16 @@ static WgPick wg_pick(int N, int Cin, int Cout, int HW) {
   if (splits(shape, 128) < 512) splits(WG_1x1, 64);
   return p;
 }
-int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW) { return (int)wg_pick(N, Cin, Cout, HW).grid.x; }
-size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW) {
-  return (size_t)pw_wgrad_f32_parts(N, Cin, Cout, HW) * Cin * Cout;
+int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW, int cap) { return (int)wg_pick(N, Cin, Cout, HW, cap).grid.x; }
+// four wavefronts of 256, 128, 64 or 32 pixels of one sample per chunk, the most that leave 768 tiles and chunks
+int pw_wgrad_f32_small_parts(int N, int Cin, int Cout, int HW) {
+  const long tiles = (long)cdiv(Cin, 32) * cdiv(Cout, 32);
+  int px = 256;
+  while (px > 32 && (long)N * cdiv(HW, 4 * px) * tiles < 768) px /= 2;
+  return N * cdiv(HW, 4 * px);
+}
+size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW, int cap) {
+  return (size_t)pw_wgrad_f32_parts(N, Cin, Cout, HW, cap) * Cin * Cout;
 }
 static WgArgs wg_args(const float* g, const float* x, float* part, int N, int Cin, int Cout, int HW, const WgPick& p) {
   WgArgs w;
@@ -758,8 +765,8 @@ static void launch_wgrad(hipStream_t st, const WgArgs& w, const WgPick& p) {
   }
 }
 void pw_wgrad_f32(hipStream_t st, const float* g, const float* x, float* part, float* G, int N,
-                  int Cin, int Cout, int HW) {
-  const WgPick p = wg_pick(N, Cin, Cout, HW);
+                  int Cin, int Cout, int HW, int cap) {
+  const WgPick p = wg_pick(N, Cin, Cout, HW, cap);
   launch_wgrad(st, wg_args(g, x, part, N, Cin, Cout, HW, p), p);
   size_t n = (size_t)Cin * Cout;
   if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)p.grid.x);
@@ -786,10 +793,10 @@ static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, dim3 g
 }
 
 void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
-                     float* part, float* G, int N, int Cin, int Cout, int HW) {
+                     float* part, float* G, int N, int Cin, int Cout, int HW, int cap) {
   const PwArgs a = pw_args(Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW);  // dx = W^T g (+ add)
   const PwPick p = pw_pick(a.NQ, HW, Cout, Cin);
-  const WgPick wp = wg_pick(N, Cin, Cout, HW);
+  const WgPick wp = wg_pick(N, Cin, Cout, HW, cap);
   const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
   if (p.var == 2 && p.wv > 4) {
     // long K: the input gradient runs as wider blocks (K split 8 or 16 ways) than the weight-gradient

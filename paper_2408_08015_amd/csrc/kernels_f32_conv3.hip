@@ -560,14 +560,17 @@ bool conv_mfma_supported(int Cin, int Cout, int k, int stride, int pad, int grou
 
 size_t conv_mfma_pack_floats(int Mdim, int Kdim, int k) { return (size_t)k * k * pw_pack_floats(Mdim, Kdim); }
 
-int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride) {
-  if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride)) return lp;
+int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
+  if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) return lp;
+  return conv_mfma_wgrad_small_parts(N, Cin, Cout, H, W, k, stride);
+}
+int conv_mfma_wgrad_small_parts(int N, int Cin, int Cout, int H, int W, int k, int stride) {
   const int HWo = out_dim(H, k, stride) * out_dim(W, k, stride);
   return N * cdiv(HWo, 4 * c3_pxw(N, Cin, Cout, HWo));
 }
 
-size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int stride) {
-  return (size_t)conv_mfma_wgrad_parts(N, Cin, Cout, H, W, k, stride) * Cin * Cout * k * k;
+size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
+  return (size_t)conv_mfma_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap) * Cin * Cout * k * k;
 }
 
 void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y, const float* bias, int N, int Cin,
@@ -579,16 +582,16 @@ void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y
 }
 
 void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* x, float* part,
-                       float* G, int N, int Cin, int Cout, int H, int W, int k, int stride) {
+                       float* G, int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
   const int Ho = out_dim(H, k, stride), Wo = out_dim(W, k, stride);
   if (dx && !conv_lds_product(st, product_name(k, stride), true, Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, k, stride)) {
     if (k == 3) launch_product<3, true>(st, product_name(k, stride), Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, Ho, Wo, stride);
     else launch_product<1, true>(st, product_name(k, stride), Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, Ho, Wo, stride);
   }
   const size_t n = (size_t)Cin * Cout * k * k;
-  if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride)) {
+  if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) {
     conv_lds_wgrad(st, k == 3 ? "conv3x3_wgrad_mfma_f32_kernel" : "conv1x1s2_wgrad_mfma_f32_kernel", g, x, part, N, Cin, Cout, H, W,
-                   k, stride);
+                   k, stride, cap);
     if (G) KLAUNCH(conv3x3_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, part, G, n, lp);
     return;
   }

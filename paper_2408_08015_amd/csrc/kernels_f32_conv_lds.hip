@@ -574,7 +574,7 @@ LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
   return best;
 }
 
-bool pick_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S, LdsWgPick& p) {
+bool pick_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap, LdsWgPick& p) {
   static thread_local std::map<std::array<int, 7>, LdsWgPick> seen;
   const std::array<int, 7> key = {N, Cin, Cout, H, W, KS, S};
   auto it = seen.find(key);
@@ -583,20 +583,25 @@ bool pick_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S, LdsWgPick
     it = seen.emplace(key, search_wgrad(N, Cin, Cout, H, W, KS, S)).first;
   }
   p = it->second;
+  if (p.PT > 0 && p.chunks > cap) {
+    const int nstage = cdiv((long)N * ((H + 2 * (KS / 2) - KS) / S + 1) * ((W + 2 * (KS / 2) - KS) / S + 1), p.PT);
+    p.per = cdiv(nstage, cap);
+    p.chunks = cdiv(nstage, p.per);
+  }
   return p.PT > 0;
 }
 
 }  // namespace
 
-int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S) {
+int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap) {
   LdsWgPick p;
-  return pick_wgrad(N, Cin, Cout, H, W, KS, S, p) ? p.chunks : 0;
+  return pick_wgrad(N, Cin, Cout, H, W, KS, S, cap, p) ? p.chunks : 0;
 }
 
 void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const float* x, float* part, int N, int Cin, int Cout,
-                    int H, int W, int KS, int S) {
+                    int H, int W, int KS, int S, int cap) {
   LdsWgPick p;
-  if (!pick_wgrad(N, Cin, Cout, H, W, KS, S, p)) return;
+  if (!pick_wgrad(N, Cin, Cout, H, W, KS, S, cap, p)) return;
   LdsWgArgs w;
   w.g = g; w.x = x; w.part = part;
   w.N = N; w.Cin = Cin; w.Cout = Cout; w.H = H; w.W = W; w.S = S;

@@ -490,60 +490,79 @@ ast_status build_plan(Stage& s, std::string& err) {
     if (op.kind == OP_RES_ADD) s.acts[op.in].grad_alias = op.out;
   s.grad_bytes = goff;
 
-  // Scratch: one private region per op (masked upstream gradients, reduction partials), so
-  // that kernels of different ops may overlap on two streams without sharing a buffer.
-  size_t sc = 0;
-  for (Op& op : s.ops) {
-    const Act& I = s.acts[op.in];
-    size_t need = 0;
-    switch (op.kind) {
-      case OP_CONV_PW: need = pw_wgrad_f32_ws(I.n, op.cin, op.cout, I.h * I.w) * sizeof(float); break;
-      case OP_CONV_DW: need = dw3x3_bwd_f32_ws(I.n, I.c, I.h, I.w, op.stride) * sizeof(float); break;
-      case OP_CONV_DWK: need = dwk_bwd_f32_ws(I.n, I.c, op.k) * sizeof(float); break;
-      case OP_CONV_GK:
-        need = std::max(conv_gatherk_wgrad_ws(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride, op.pad),
-                        conv_direct_wgrad_ws(I.n, op.cin, I.h, I.w, op.cout, op.k, op.stride, op.pad, op.groups)) * sizeof(float);
-        break;
-      case OP_CONV_3X3: need = conv_mfma_wgrad_ws(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride) * sizeof(float); break;
-      case OP_CONV_DIRECT:
-        need = conv_direct_wgrad_ws(I.n, op.cin, I.h, I.w, op.cout, op.k, op.stride, op.pad, op.groups) * sizeof(float);
-        break;
-      case OP_BN:
-        need = std::max(bn_ws_doubles(I.c, I.n, I.h * I.w),
-                        (size_t)2 * I.c * std::max(op.given_parts, op.given_bwd_parts)) * sizeof(double);
-        break;
-      case OP_CONV_IGEMM:  // masked upstream gradient + split-K partials
-        need = align_up(s.acts[op.out].bytes, 256) + conv_bf16_ws_bytes(I.n, I.h, I.w, op.cin, op.cout, op.k);
-        break;
-      case OP_LINEAR:
-        if (s.bf16)
-          need = align_up(s.acts[op.out].bytes, 256) + linear_bf16_ws_bytes((size_t)I.n * I.h * I.w, op.cin, op.cout);
-        break;
-      case OP_LAYERNORM: need = layernorm_bf16_ws_bytes((size_t)I.n * I.h, I.c); break;
-      case OP_MHA:  // d_o and dqkv, the row sums, then the split-K partials of each projection
-        need = align_up((size_t)I.n * I.h * 4 * op.cin * 2, 256) +
-               align_up(mha_bf16_ws_bytes(I.n, I.h, op.cin, op.heads), 256) +
-               align_up(linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, op.cin), 256) +
-               linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, 3 * op.cin);
-        break;
-      default: break;
+  auto lay_out_scratch = [&] {
+    // Scratch: one private region per op (masked upstream gradients, reduction partials), so
+    // that kernels of different ops may overlap on two streams without sharing a buffer.
+    size_t sc = 0;
+    for (Op& op : s.ops) {
+      const Act& I = s.acts[op.in];
+      size_t need = 0;
+      switch (op.kind) {
+        case OP_CONV_PW: need = pw_wgrad_f32_ws(I.n, op.cin, op.cout, I.h * I.w, op.wg_cap) * sizeof(float); break;
+        case OP_CONV_DW: need = dw3x3_bwd_f32_ws(I.n, I.c, I.h, I.w, op.stride) * sizeof(float); break;
+        case OP_CONV_DWK: need = dwk_bwd_f32_ws(I.n, I.c, op.k) * sizeof(float); break;
+        case OP_CONV_GK:
+          need = std::max(conv_gatherk_wgrad_ws(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride, op.pad),
+                          conv_direct_wgrad_ws(I.n, op.cin, I.h, I.w, op.cout, op.k, op.stride, op.pad, op.groups)) * sizeof(float);
+          break;
+        case OP_CONV_3X3: need = conv_mfma_wgrad_ws(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride, op.wg_cap) * sizeof(float); break;
+        case OP_CONV_DIRECT:
+          need = conv_direct_wgrad_ws(I.n, op.cin, I.h, I.w, op.cout, op.k, op.stride, op.pad, op.groups) * sizeof(float);
+          break;
+        case OP_BN:
+          need = std::max(bn_ws_doubles(I.c, I.n, I.h * I.w),
+                          (size_t)2 * I.c * std::max(op.given_parts, op.given_bwd_parts)) * sizeof(double);
+          break;
+        case OP_CONV_IGEMM:  // masked upstream gradient + split-K partials
+          need = align_up(s.acts[op.out].bytes, 256) + conv_bf16_ws_bytes(I.n, I.h, I.w, op.cin, op.cout, op.k);
+          break;
+        case OP_LINEAR:
+          if (s.bf16)
+            need = align_up(s.acts[op.out].bytes, 256) + linear_bf16_ws_bytes((size_t)I.n * I.h * I.w, op.cin, op.cout);
+          break;
+        case OP_LAYERNORM: need = layernorm_bf16_ws_bytes((size_t)I.n * I.h, I.c); break;
+        case OP_MHA:  // d_o and dqkv, the row sums, then the split-K partials of each projection
+          need = align_up((size_t)I.n * I.h * 4 * op.cin * 2, 256) +
+                 align_up(mha_bf16_ws_bytes(I.n, I.h, op.cin, op.heads), 256) +
+                 align_up(linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, op.cin), 256) +
+                 linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, 3 * op.cin);
+          break;
+        default: break;
+      }
+      op.sc_off = sc;
+      sc += align_up(need, 256);
     }
-    op.sc_off = sc;
-    sc += align_up(need, 256);
+    // The forward pass has scratch of its own (BatchNorm statistics partials), so that the forward of one
+    // micro-batch may run beside the backward of another.
+    size_t fsc = 0;
+    for (Op& op : s.ops) {
+      if (op.kind != OP_BN) continue;
+      const Act& I = s.acts[op.in];
+      op.fsc_off = fsc;
+      fsc += align_up(std::max(bn_ws_doubles(I.c, I.n, I.h * I.w), (size_t)2 * I.c * op.given_parts) * sizeof(double), 256);
+    }
+    s.scratch_off = align_up(goff, 256);
+    s.scratch_bytes = align_up(sc, 256);
+    s.fscratch_off = s.scratch_off + s.scratch_bytes;
+    s.ws_bytes = s.fscratch_off + align_up(fsc, 256) + 256;
+  };
+  lay_out_scratch();
+  // The kernels choose the number of weight-gradient partials for speed alone.  A stage that this takes past the static
+  // scratch array, and that fits it with fewer, takes fewer.
+  if (s.ws_bytes > (size_t)AST_STATIC_SCRATCH_BYTES) {
+    auto set_caps = [&](bool small) {
+      for (Op& op : s.ops) {
+        const Act& I = s.acts[op.in];
+        op.wg_cap = INT_MAX;
+        if (small && op.kind == OP_CONV_PW) op.wg_cap = pw_wgrad_f32_small_parts(I.n, op.cin, op.cout, I.h * I.w);
+        if (small && op.kind == OP_CONV_3X3)
+          op.wg_cap = conv_mfma_wgrad_small_parts(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride);
+      }
+      lay_out_scratch();
+    };
+    set_caps(true);
+    if (s.ws_bytes > (size_t)AST_STATIC_SCRATCH_BYTES) set_caps(false);
   }
-  // The forward pass has scratch of its own (BatchNorm statistics partials), so that the forward of one
-  // micro-batch may run beside the backward of another.
-  size_t fsc = 0;
-  for (Op& op : s.ops) {
-    if (op.kind != OP_BN) continue;
-    const Act& I = s.acts[op.in];
-    op.fsc_off = fsc;
-    fsc += align_up(std::max(bn_ws_doubles(I.c, I.n, I.h * I.w), (size_t)2 * I.c * op.given_parts) * sizeof(double), 256);
-  }
-  s.scratch_off = align_up(goff, 256);
-  s.scratch_bytes = align_up(sc, 256);
-  s.fscratch_off = s.scratch_off + s.scratch_bytes;
-  s.ws_bytes = s.fscratch_off + align_up(fsc, 256) + 256;
   return AST_OK;
 }
 

@@ -3,6 +3,7 @@
 // a ring of K activation stashes and one gradient/scratch workspace, and enforces the
 // one-forward-one-backward call discipline (Sec. 3.2; memory model Eq. (3)).
 #pragma once
+#include <climits>
 #include <hip/hip_runtime.h>
 
 #include <string>
@@ -51,6 +52,7 @@ struct Act {
 };
 
 struct Op {
+  int wg_cap = INT_MAX;      // most weight-gradient partials of an fp32 convolution
   OpKind kind;
   int layer = -1;         // first layer index covered by this op
   int in = -1, out = -1;  // activation ids

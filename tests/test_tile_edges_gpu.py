@@ -1,8 +1,11 @@
 """GPU parity at the sizes where a tile, a split or a dispatch rule of the kernels can go wrong: remainders, the
 smallest and largest of a range, both sides of a rule.  Oracle and tolerances of test_parity_gpu.py (fp32: 1e-4 for
 activations, 1e-3 for gradients; sums of a few thousand fp32 terms differ by about 1e-6)."""
+import numpy as np
 import pytest
 
+import harness
+from asteroid_workloads import gen
 from asteroid_workloads.configs import bn, conv, simple
 from test_parity_gpu import A, check, one  # noqa: F401  (A: the fixture)
 
@@ -49,3 +52,18 @@ def test_batchnorm_planes_not_a_multiple_of_16_bytes(A, c, h, w, B):
 ])
 def test_pointwise_conv_tiles(A, cin, cout, h, w, B):
     check(one([conv(cin, cout, 1, 1, 0)], (cin, h, w), B=B), rounds=1)
+
+
+@pytest.mark.parametrize("layers,shape,B", [
+    ([conv(128, 128, 1, 1, 0)] * 2, (128, 28, 28), 32),   # pointwise: 192 partials a layer for speed, 48 here
+    ([conv(64, 64, 3, 1, 1)] * 5, (64, 28, 28), 4),       # dense: 49 and 25
+])
+def test_partials_of_a_stage_that_just_fits_the_static_workspace(A, layers, shape, B):
+    cfg = one(layers, shape, B=B, M=1)
+    inp = gen.make_inputs(cfg, randomize_affine=True)
+    ref, _, mem = harness.run_hip(cfg, inp, K=1, rounds=1)
+    assert mem[3] <= 32 << 20
+    got, _, _ = harness.run_hip(cfg, inp, K=1, rounds=1, static_backward=True)
+    for k in ("y", "dx", "G", "W"):
+        assert np.array_equal(ref[0][k], got[0][k]), k
+    check(cfg, rounds=1)
