@@ -10,6 +10,7 @@
 // touches, and a tap is one constant offset from a pixel's position: no border test in the product loop.
 #include <algorithm>
 #include <array>
+#include <climits>
 #include <cmath>
 #include <map>
 #include <type_traits>
@@ -27,6 +28,9 @@ __host__ __device__ constexpr int round_up64(int v) { return (v + 63) & ~63; }
 // floor(n / d) = mulhi(n, reciprocal(d)) while n * d < 2^32
 inline unsigned reciprocal(unsigned d) { return d == 1 ? 0xffffffffu : (unsigned)(((1ull << 32) + d - 1) / d); }
 constexpr size_t kProductLds = 128 * 1024, kWgradLds = 156 * 1024;
+constexpr unsigned kOutside = 0x80000000u;  // buffer offset beyond every extent: a copy writes zeros
+// The copies address a whole tensor in memory with 32-bit byte offsets below kOutside.
+inline bool copies_reach(int N, int C, int H, int W) { return (size_t)N * C * H * W * 4 < kOutside; }
 
 // ------------------------------------------------------------------ product (forward / input gradient)
 // One class of result pixels: all of them, or (input gradient of a stride-2 conv) those of one row / column
@@ -51,7 +55,6 @@ struct LdsArgs {
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
-constexpr unsigned kOutside = 0x80000000u;  // buffer offset beyond every extent: the copy writes zeros
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
@@ -327,29 +330,22 @@ void launch_one(hipStream_t st, const char* name, const LdsArgs& a, const LdsPic
   KLAUNCH_NAMED(name, (conv_lds_f32_kernel<MT, ALL>), grid, dim3(64 * p.WN * p.WK), p.lds, st, a);
 }
 
-}  // namespace
-
-// Y = conv of X (dgrad: gradient of a conv's input from its output gradient X).  H, W: the conv's INPUT size.
-// false: no block shape fits (very wide rows); the caller's direct kernel runs instead.
-bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
-                      const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S) {
+// The sizes of a product and its block shape; false: no shape fits, or the tensors are too large.
+bool plan_product(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, int S, LdsArgs& a, int& ncls, LdsPick& p) {
   const int pad = KS / 2, Ho = (H + 2 * pad - KS) / S + 1, Wo = (W + 2 * pad - KS) / S + 1;
-  LdsArgs a = {};
-  a.Wp = reinterpret_cast<const float4*>(Wp);
-  a.X = X; a.Y = Y; a.bias = bias;
+  a = {};
   a.N = N; a.Kdim = Kdim; a.Mdim = Mdim; a.KG = cdiv(Kdim, 8); a.KS = KS;
   a.tap_stride = (unsigned)(pw_pack_floats(Mdim, Kdim) / 4);
   if (dgrad) { a.XH = Ho; a.XW = Wo; a.OH = H; a.OW = W; a.SI = 1; a.SO = S; }
   else { a.XH = H; a.XW = W; a.OH = Ho; a.OW = Wo; a.SI = S; a.SO = 1; }
   a.XS = 1; a.XRW = a.XW; a.XHW = (unsigned)(a.XH * a.XW);
   if ((size_t)N * (a.XH + 2) * (a.XH + 1) >= ((size_t)1 << 32)) return false;  // reciprocals
-  const size_t x_bytes = (size_t)N * Kdim * a.XHW * 4;
-  if (x_bytes >= kOutside || (size_t)a.tap_stride * KS * KS >= kOutside) return false;  // 32-bit offsets
-  a.x_bytes = (unsigned)x_bytes;
+  if (!copies_reach(N, Kdim, a.XH, a.XW) || (size_t)a.tap_stride * KS * KS >= kOutside) return false;  // 32-bit offsets
+  a.x_bytes = (unsigned)N * Kdim * a.XHW * 4u;
   if (!dgrad && KS == 1 && S > 1) {  // only the pixels a strided 1x1 conv reads: its operand is the subsampled tensor
     a.XH = Ho; a.XW = Wo; a.SI = 1; a.XS = S;
   }
-  int ncls = 0;
+  ncls = 0;
   auto code = [](int u, int d) { return (unsigned)((u << 4) | (d + 1)); };
   // row (or column) taps of a parity class: input row r = S*i + u - pad
   auto taps = [&](int par, unsigned& list) {
@@ -378,10 +374,24 @@ bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float*
       ++ncls;
     }
   a.RW = a.XW + 2;
-  LdsPick p;
   if (!pick_product(a, ncls, p)) return false;
   a.rRW = reciprocal(a.RW); a.rXH1 = reciprocal(a.XH + 1);
   a.WN = p.WN; a.WK = p.WK; a.rows = p.rows; a.NP = p.NP; a.PL = p.PL; a.CH = p.CH;
+  return true;
+}
+
+}  // namespace
+
+// Y = conv of X (dgrad: gradient of a conv's input from its output gradient X).  H, W: the conv's INPUT size.
+// false: the caller's direct kernel runs instead (very wide rows, operands of 2 GiB and more).
+bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
+                      const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S) {
+  LdsArgs a;
+  LdsPick p;
+  int ncls;
+  if (!plan_product(dgrad, N, Kdim, Mdim, H, W, KS, S, a, ncls, p)) return false;
+  a.Wp = reinterpret_cast<const float4*>(Wp);
+  a.X = X; a.Y = Y; a.bias = bias;
   unsigned most = 0;
   for (int i = 0; i < ncls; ++i) most = std::max(most, a.cls[i].npix);
   const dim3 grid((unsigned)cdiv(most, 32 * p.WN), (unsigned)cdiv(Mdim, 32 * p.MT), (unsigned)ncls);
@@ -540,9 +550,9 @@ struct LdsWgPick { int PT = 0, per, chunks, rows, NP, nbuf; size_t lds; };
 LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
   LdsWgPick best;
   const int pad = KS / 2, Ho = (H + 2 * pad - KS) / S + 1, Wo = (W + 2 * pad - KS) / S + 1;
-  if (KS == 1) { H = Ho; W = Wo; S = 1; }
+  if (!copies_reach(N, Cin, H, W) || !copies_reach(N, Cout, Ho, Wo)) return best;
+  if (KS == 1) { H = Ho; W = Wo; S = 1; }  // from here on: the rows and columns that are staged
   const long npix = (long)N * Ho * Wo, tw = KS == 1 ? 64 : 32, tiles = (long)cdiv(Cin, tw) * cdiv(Cout, tw);
-  if ((size_t)N * std::max((size_t)Cin * H * S * (W + 1) * S, (size_t)Cout * Ho * Wo) * 4 >= kOutside) return best;  // 32-bit offsets
   if ((size_t)N * (H + 2) * (H + 1) >= ((size_t)1 << 32) || (size_t)Ho * Wo * Wo >= ((size_t)1 << 32)) return best;  // reciprocals
   double cost = 1e30;
   for (int PT = 32; PT <= 128; PT *= 2) {
@@ -625,3 +635,22 @@ void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const floa
 }
 
 }  // namespace ast
+
+// The choices above, for tests that name one.  what: 0 forward, 1 input gradient, 2 weight gradient of a conv with
+// these sizes (H, W: its input).  0: the direct kernels run.  1: staged; out = {row tiles, pixel groups, shares of the
+// contraction, classes of result pixels}, or for a weight gradient {pixels per stage, stages per block, partials, buffers}.
+extern "C" int ast_conv_lds_choice(int what, int N, int Cin, int Cout, int H, int W, int KS, int S, int out[4]) {
+  using namespace ast;
+  if (what == 2) {
+    LdsWgPick p;
+    if (!pick_wgrad(N, Cin, Cout, H, W, KS, S, INT_MAX, p)) return 0;
+    out[0] = p.PT; out[1] = p.per; out[2] = p.chunks; out[3] = p.nbuf;
+    return 1;
+  }
+  LdsArgs a;
+  LdsPick p;
+  int ncls;
+  if (!plan_product(what == 1, N, what ? Cout : Cin, what ? Cin : Cout, H, W, KS, S, a, ncls, p)) return 0;
+  out[0] = p.MT; out[1] = p.WN; out[2] = p.WK; out[3] = ncls;
+  return 1;
+}

@@ -1,0 +1,38 @@
+"""Which kernel a dense fp32 convolution runs on, at both sides of each limit (host code only)."""
+import ctypes
+
+import pytest
+
+import paper_2408_08015_amd as A
+
+FWD, DGRAD, WGRAD = 0, 1, 2
+
+
+def choice(what, n, cin, cout, h, w, k, s):
+    """None: the direct kernels; else the four words of the staged kernel's block shape."""
+    out = (ctypes.c_int * 4)()
+    lib = ctypes.CDLL(A.lib_path())
+    return tuple(out) if lib.ast_conv_lds_choice(what, n, cin, cout, h, w, k, s, out) else None
+
+
+@pytest.mark.parametrize("what", [FWD, DGRAD, WGRAD])
+@pytest.mark.parametrize("n,cin,cout,h,k,s,reads_x,reads_g", [
+    # the staged kernels address a tensor with 32-bit byte offsets below 2 GiB
+    (668, 64, 64, 112, 1, 2, True, True),       # x of 2 145 124 352 bytes
+    (669, 64, 64, 112, 1, 2, False, True),      # x of 2 148 335 616
+    (1400, 64, 64, 112, 1, 2, False, True),     # x of 4.5 GB, and the subsampled x of 1.1 GB
+    (2674, 64, 64, 112, 1, 2, False, True),
+    (2675, 64, 64, 112, 1, 2, False, False),    # dy of 2 147 532 800
+    (329, 128, 128, 56, 3, 2, True, True),      # x of 528 MB
+    (1337, 128, 128, 56, 3, 2, True, True),     # x of 2 146 729 984
+    (1338, 128, 128, 56, 3, 2, False, True),
+    (2674, 64, 64, 56, 3, 1, True, True),
+    (2675, 64, 64, 56, 3, 1, False, False),     # x and dy of 2 147 532 800
+    (167, 8, 1024, 56, 3, 1, True, True),
+    (168, 8, 1024, 56, 3, 1, True, False),      # dy of 2 157 969 408, x of 16 MB
+])
+def test_size_limit_of_the_staged_convolutions(what, n, cin, cout, h, k, s, reads_x, reads_g):
+    assert (n * cin * h * h * 4 < 2 ** 31) == reads_x
+    assert (n * cout * ((h - 1) // s + 1) ** 2 * 4 < 2 ** 31) == reads_g
+    want = {FWD: reads_x, DGRAD: reads_g, WGRAD: reads_x and reads_g}[what]
+    assert (choice(what, n, cin, cout, h, h, k, s) is not None) == want

@@ -67,3 +67,37 @@ def test_partials_of_a_stage_that_just_fits_the_static_workspace(A, layers, shap
     for k in ("y", "dx", "G", "W"):
         assert np.array_equal(ref[0][k], got[0][k]), k
     check(cfg, rounds=1)
+
+
+@pytest.mark.parametrize("n,cin,cout,hw,k,staged", [
+    (1400, 64, 64, 112, 1, False),   # x of 4.5 GB: beyond 32-bit offsets, direct kernels
+    (1337, 128, 32, 56, 3, True),    # x of 2 146 729 984 bytes, the last that the staged kernels take
+])
+def test_strided_conv_of_a_tensor_around_the_offset_limit(A, n, cin, cout, hw, k, staged):
+    """Three samples spread over the tensor are not zero: the gradients are those of these samples alone."""
+    import torch
+    from test_conv_choices import WGRAD, choice
+    assert (choice(WGRAD, n, cin, cout, hw, hw, k, 2) is not None) == staged
+    dev, at, ho = torch.device("cuda:0"), [0, n // 2, n - 1], hw // 2
+    g = torch.Generator().manual_seed(3)
+    xs, ws = torch.randn(3, cin, hw, hw, generator=g), torch.randn(cout, cin, k, k, generator=g) / (cin * k * k) ** 0.5
+    gs = torch.randn(3, cout, ho, ho, generator=g)
+    x = torch.zeros(n, cin, hw, hw, device=dev)
+    dy = torch.zeros(n, cout, ho, ho, device=dev)
+    for i, s in enumerate(at):
+        x[s].copy_(xs[i])
+        dy[s].copy_(gs[i])
+    y = torch.empty_like(dy)
+    torch.cuda.synchronize()
+    st = A.Stage([conv(cin, cout, k, 2, k // 2)], n, 1, 1, (cin, hw, hw), needs_input_grad=False)
+    st.set_params(ws.numpy().ravel())
+    st.forward(0, x, None, y)
+    st.backward(0, dy)
+    got = torch.from_numpy(st.get_grads()).reshape(ws.shape)
+    st.close()
+    wd = ws.double().requires_grad_()
+    yd = torch.nn.functional.conv2d(xs.double(), wd, stride=2, padding=k // 2)
+    yd.backward(gs.double())
+    for have, want in ((got, wd.grad), (y[at].cpu(), yd.detach())):
+        assert float((have.double() - want).norm() / want.norm()) < 1e-6   # sums of at most 9408 fp32 products
+    assert not y[1:n // 2].any() and not y[n // 2 + 1:n - 1].any()
