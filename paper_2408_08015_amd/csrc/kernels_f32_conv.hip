@@ -566,16 +566,29 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
   const int wk = wave % KS, wt = wave / KS, wci = wt % TCI, wco = wt / TCI;
   const int ra = wco * 32 + row, rb = TCO * 32 + wci * 32 + row;
   const int swa = T::swz(ra), swb = T::swz(rb);
-  // The pixels of a chunk go to NA accumulators in turn.  A sum's rounding error grows with its chain of additions, and the
-  // chains of a wavefront that has a tile to itself are the longest.  Relative error of dW against 64 bits with one
-  // accumulator and now: 64 -> 256 channels at 32 x 56x56 3.2e-7, 1.6e-7; 512 -> 2048 at 8 x 7x7 1.5e-7, 0.9e-7; 16 -> 96 at
-  // 16 x 112x112 1.9e-7, 1.4e-7.  Four everywhere cost MobileNetV2's small planes a wavefront per SIMD: 3 % of its round.
-  constexpr int NA = KS == 1 ? 4 : 2;
-  floatx16 acc[NA];
+  // A sum's rounding error grows with the root of its chain of 32-bit additions, so no chain may grow with the micro-batch:
+  // 32 pixels (16 in the first step where wavefronts share a tile) of `acc` go to `run`, and 16 such sums of a wavefront that
+  // has a tile to itself, whose range may be all pixels, to `sum`.  The other shapes' ranges are at most WG_CHAIN steps.
+  // (Registers and f64 instructions allow no more: 64-bit sums of every 32 pixels cost 24 -> 144 channels at 128 x 56x56 8 %,
+  // this 2 %.)  Relative error of dW against 64 bits, chains of at most 256 pixels with partials added in 32 bits / one chain
+  // per accumulator and range / now: 512 -> 2048 at 128 x 7x7 1.7e-7, 4.1e-7, 1.3e-7; 2048 -> 2048 at 64 x 14x14 2.7e-7,
+  // 1.0e-6, 1.3e-7; 16 -> 96 at 128 x 112x112 3.2e-7, 4.8e-7, 1.5e-7.
+  floatx16 acc;
+  float run[16];
+  double sum[KS == 1 ? 16 : 1];
 #pragma unroll
-  for (int e = 0; e < NA; ++e)
+  for (int r = 0; r < 16; ++r) acc[r] = run[r] = 0.f;
+  if constexpr (KS == 1) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[e][r] = 0.f;
+    for (int r = 0; r < 16; ++r) sum[r] = 0.0;
+  }
+  auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      run[r] += acc[r];
+      acc[r] = 0.f;
+    }
+  };
   if (s0 < s1) {  // uniform
     load(s0);
     store(0);
@@ -584,22 +597,32 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
   for (int s = s0; s < s1; ++s) {
     const int buf = (s - s0) & 1;
     if (s + 1 < s1) load(s + 1);
+    if (KS > 1 && buf == 1) fold();  // here the products of the step before are done: nothing waits for them
     const float* o = lds + buf * (ROWS * PX);
 #pragma unroll
     for (int k = 0; k < CH / 2 / KS; ++k) {
       const int j = 2 * (wk * (CH / 2 / KS) + k) + half;
       const float4 a = *reinterpret_cast<const float4*>(o + ra * PX + 4 * (j ^ swa));
       const float4 b = *reinterpret_cast<const float4*>(o + rb * PX + 4 * (j ^ swb));
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc[0], 0, 0, 0);
-      acc[1 % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc[1 % NA], 0, 0, 0);
-      acc[2 % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc[2 % NA], 0, 0, 0);
-      acc[3 % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc[3 % NA], 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
     }
     if (s + 1 < s1) store(buf ^ 1);
+    if constexpr (KS == 1) {
+      fold();
+      if (((s - s0) & 15) == 15) {  // uniform
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sum[r] += run[r];
+          run[r] = 0.f;
+        }
+      }
+    }
     __syncthreads();
   }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[0][r] = NA == 4 ? (acc[0][r] + acc[1][r]) + (acc[2 % NA][r] + acc[3 % NA][r]) : acc[0][r] + acc[1][r];
+  if constexpr (KS > 1) fold();
   float* out = w.part + (size_t)split * Cout * Cin;
   const int ci = ci_base + wci * 32 + row;
   if constexpr (KS == 1) {
@@ -607,12 +630,12 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int co = co_base + wco * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (co < Cout) out[(size_t)co * Cin + ci] = acc[0][r];
+        if (co < Cout) out[(size_t)co * Cin + ci] = (float)(sum[r] + run[r]);
       }
     }
   } else {  // the KS wavefronts of a tile add their sums in a fixed order; the staging buffers are free by now
 #pragma unroll
-    for (int r = 0; r < 16; ++r) lds[(wave * 16 + r) * 64 + lane] = acc[0][r];
+    for (int r = 0; r < 16; ++r) lds[(wave * 16 + r) * 64 + lane] = run[r];
     __syncthreads();
     if (ci < Cin) {
 #pragma unroll
@@ -620,9 +643,9 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
         const int r = wk * (16 / KS) + rr;
         const int co = co_base + wco * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         const float* v = lds + (wt * KS * 16 + r) * 64 + lane;
-        float sum = v[0] + v[16 * 64];
-        if constexpr (KS == 4) sum += v[2 * 16 * 64] + v[3 * 16 * 64];
-        if (co < Cout) out[(size_t)co * Cin + ci] = sum;
+        double d = (double)v[0] + v[16 * 64];
+        if constexpr (KS == 4) d += (double)v[2 * 16 * 64] + v[3 * 16 * 64];
+        if (co < Cout) out[(size_t)co * Cin + ci] = (float)d;
       }
     }
   }
@@ -642,9 +665,9 @@ constexpr int wg_lds_floats() {
   return SHAPE == WG_2x2 ? WgTile<2, 2, 1>::LDS : SHAPE == WG_1x1 ? WgTile<1, 1, 4>::LDS : WgTile<2, 1, 2>::LDS;
 }
 
-// (four wavefronts per SIMD; with four accumulators and unvectorised staging registers suffice for three)
+// (four wavefronts per SIMD; with single-pixel staging the registers of the 2x2 and 1x1 shapes suffice for three)
 template <int SHAPE, bool VEC>
-__global__ __launch_bounds__(256, SHAPE == WG_2x2 && !VEC ? 3 : 4) void pw_wgrad_f32_kernel(WgArgs w) {
+__global__ __launch_bounds__(256, !VEC && (SHAPE == WG_2x2 || SHAPE == WG_1x1) ? 3 : 4) void pw_wgrad_f32_kernel(WgArgs w) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   int bx, t;
   pw_block_xy((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x, gridDim.y * gridDim.z,
@@ -660,7 +683,7 @@ __global__ __launch_bounds__(256, SHAPE == WG_2x2 && !VEC ? 3 : 4) void pw_wgrad
 // 0 / 1 = 32-pixel wavefronts with one / two 32-channel chunks per pass, 2 = K split over the
 // block, 3 = 128-pixel wavefronts.
 template <int VAR, int SHAPE, bool VEC>
-__global__ __launch_bounds__(256, VAR >= 2 ? 1 : SHAPE == WG_2x2 && !VEC ? 3 : 4) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
+__global__ __launch_bounds__(256, VAR >= 2 ? 1 : !VEC && (SHAPE == WG_2x2 || SHAPE == WG_1x1) ? 3 : 4) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
                                                           unsigned gWx, unsigned gWy) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   static_assert(wg_lds_floats<SHAPE>() >= 4 * 16 * 64, "the product kernels use 16 KB");
@@ -707,7 +730,8 @@ __global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __re
 // at least 128 pixels.  Where that leaves compute units idle (fewer than two blocks each: the 14x14 and 7x7 planes of
 // a few samples) the time of a launch is its longest chain of steps, so the smallest shape runs, one step of 64 pixels
 // upwards: 96 -> 576 channels at 8 x 14x14 12.3 us with 36 blocks of 2x2 tiles, 7.2 us with 810 of 1x1.
-static constexpr int WG_BLOCKS = 768;
+// A range of a shape without 64-bit sums (all but 2x2) is at most WG_CHAIN steps: 32 folds of `acc`, error 1.5e-7.
+static constexpr int WG_BLOCKS = 768, WG_CHAIN = 64;
 struct WgPick { int shape; dim3 grid; };
 static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
   const int a = cdiv(Cout, 32), b = cdiv(Cin, 32);
@@ -717,7 +741,9 @@ static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
   auto splits = [&](int shape, int px) {
     p.shape = shape;
     const int gy = cdiv(b, tci[shape]), gz = cdiv(a, tco[shape]);
-    const long s = std::max(1L, std::min({(long)cdiv(WG_BLOCKS, (long)gy * gz), NQ / px, (long)cap}));
+    const long fill = std::min((long)cdiv(WG_BLOCKS, (long)gy * gz), NQ / px);
+    const long chain = shape == WG_2x2 ? 1 : cdiv(NQ, WG_CHAIN * (shape == WG_1x1 ? 64 : 32));
+    const long s = std::min(std::max(fill, chain), (long)cap);
     p.grid = dim3((unsigned)s, gy, gz);
     return s * gy * gz;
   };

@@ -54,6 +54,40 @@ def test_pointwise_conv_tiles(A, cin, cout, h, w, B):
     check(one([conv(cin, cout, 1, 1, 0)], (cin, h, w), B=B), rounds=1)
 
 
+@pytest.mark.parametrize("cin,cout,k,stride,hw,B", [
+    (512, 2048, 1, 1, 7, 128),      # pointwise, 2x2 weight tiles: three ranges of 65 steps
+    (24, 144, 1, 1, 56, 128),       # 1x1 tiles, ranges of 41 steps
+    (960, 160, 1, 1, 7, 512),       # 2x1 tiles, ranges of 64 steps
+])
+def test_rounding_of_weight_gradients_does_not_grow_with_the_micro_batch(A, cin, cout, k, stride, hw, B):
+    """An fp32 addition rounds by 2^-25.3 of its result (root mean square), a chain of n additions of independent terms by
+    sqrt(n / 2) as much of its sum.  No chain is longer than 128 pixels: 2.0e-7, and 0.3e-7 for the last roundings."""
+    import torch
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(1)
+    ho = (hw - 1) // stride + 1
+    x = torch.randn(B, cin, hw, hw, generator=g, device=dev)
+    dy = torch.randn(B, cout, ho, ho, generator=g, device=dev)
+    y = torch.empty_like(dy)
+    torch.cuda.synchronize()
+    st = A.Stage([conv(cin, cout, k, stride, k // 2)], B, 1, 1, (cin, hw, hw), needs_input_grad=False)
+    st.set_params(np.zeros(st.num_params, np.float32))
+    st.forward(0, x, None, y)
+    st.backward(0, dy)
+    got = torch.from_numpy(st.get_grads()).to(dev).double().reshape(cout, cin, k, k)
+    st.close()
+    want = torch.zeros_like(got)
+    xp = torch.nn.functional.pad(x, (k // 2,) * 4)
+    rows = torch.empty(cout, B * ho * ho, dtype=torch.float64, device=dev)
+    rows.copy_(dy.permute(1, 0, 2, 3).reshape(cout, -1))
+    for u in range(k):
+        for v in range(k):
+            cols = xp[:, :, u:u + stride * (ho - 1) + 1:stride, v:v + stride * (ho - 1) + 1:stride]
+            want[:, :, u, v] = rows @ cols.permute(0, 2, 3, 1).reshape(-1, cin).double()
+    assert float((got - want).norm() / want.norm()) < 2.2e-7
+
+
 @pytest.mark.parametrize("layers,shape,B", [
     ([conv(128, 128, 1, 1, 0)] * 2, (128, 28, 28), 32),   # pointwise: 192 partials a layer for speed, 48 here
     ([conv(64, 64, 3, 1, 1)] * 5, (64, 28, 28), 4),       # dense: 49 and 25
