@@ -569,6 +569,8 @@ int conv_mfma_wgrad_small_parts(int N, int Cin, int Cout, int H, int W, int k, i
   return N * cdiv(HWo, 4 * c3_pxw(N, Cin, Cout, HWo));
 }
 
+int conv_mfma_wgrad_chain(int N, int Cin, int Cout, int HWo) { return std::min(c3_pxw(N, Cin, Cout, HWo), HWo); }
+
 size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
   return (size_t)conv_mfma_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap) * Cin * Cout * k * k;
 }

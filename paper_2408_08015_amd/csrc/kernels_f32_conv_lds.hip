@@ -410,24 +410,20 @@ struct LdsWgArgs {
   float* part;      // [chunk][Cout][Cin][KS*KS]
   int N, Cin, Cout, H, W, Ho, Wo, S, XS, XRW;
   unsigned XHW, x_bytes, g_bytes;
-  int rows, RW, NP, PT, per, nstage, nbuf;
+  int rows, RW, NP, PT, per, nstage, nbuf, flush;
   unsigned rRW, rH1, rWo;
   unsigned npix;
 };
 
-__device__ __forceinline__ double sum8(const float* p) {  // the eight wavefronts' values, rounded once
-  double s = 0.0;
-#pragma unroll
-  for (int w = 0; w < 8; ++w) s += p[1024 * w];
-  return s;
-}
+constexpr int kFlush = 8 * 16 * 64;  // words: one 32 x 32 tile of eight wavefronts
 
 // Block of eight wavefronts, one per compute unit: a 32 x 32 tile of (cout, cin), all taps (1x1: 64 x 64), over a run of stages of
 // PT consecutive output pixels, whatever samples they lie in.  A stage copies g [32][PT] and the virtual rows of x
 // under it to LDS with coalesced loads (lanes along the pixels: a load per lane and channel row would touch 64 cache
 // lines instead of 2 to 4) while the stage before is multiplied; the products read one word of g and one of x per
-// tap for a pair of pixels.  Wavefront w takes the w-th eighth of every stage's pixels; the eight tiles are added
-// through LDS and leave as whole rows of the partial.  Pitches are 2 modulo 64: the 32 channel rows and the two
+// tap for a pair of pixels.  Wavefront w takes the w-th eighth of every stage's pixels; every `flush` stages the eight
+// tiles are added through LDS into totals, two rows of the tile in registers of each wavefront, which leave as whole rows of
+// the partial.  Pitches are 2 modulo 64: the 32 channel rows and the two
 // neighbouring pixels of a pair hit 64 different banks.
 template <int KS>
 __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
@@ -447,6 +443,8 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
   for (int t = 0; t < NA; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+  float tot[NA][2] = {};
+  int left = w.flush;
   const int s_begin = chunk * w.per, s_end = min(s_begin + w.per, w.nstage);
   auto stage = [&](int s, float* buf) __attribute__((always_inline)) {
     const unsigned q0 = (unsigned)s * PT;
@@ -516,6 +514,38 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
       __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
+    // the sums of the stages since the last time, from the accumulators of eight wavefronts to `tot`; taps go through two
+    // scratch areas in turn, [8 wavefronts][8 pairs of rows][64 lanes] each
+    if (--left == 0 || s + 1 == s_end) {  // uniform
+      left = w.flush;
+      float2* const own = reinterpret_cast<float2*>(lds + (buf - lds));  // the stage just multiplied
+      float2* const past = reinterpret_cast<float2*>(lds + w.nbuf * bufsz);
+      float2* const f0 = bufsz >= kFlush ? own : past;
+      float2* const f1 = bufsz >= 2 * kFlush ? own + kFlush / 2 : bufsz >= kFlush ? past : past + kFlush / 2;
+      auto give = [&](int t) __attribute__((always_inline)) {
+        float2* const f = (t & 1 ? f1 : f0) + wave * 512 + lane;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          f[r * 64] = make_float2(acc[t][2 * r], acc[t][2 * r + 1]);
+          acc[t][2 * r] = acc[t][2 * r + 1] = 0.f;
+        }
+      };
+      give(0);
+#pragma unroll
+      for (int t = 0; t < NA; ++t) {
+        __syncthreads();
+        const float2* const f = (t & 1 ? f1 : f0) + wave * 64 + lane;
+        float2 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = f[k * 512];
+        if (t + 1 < NA) give(t + 1);
+        tot[t][0] = (float)(tot[t][0] + ((((double)v[0].x + v[1].x) + ((double)v[2].x + v[3].x)) +
+                                         (((double)v[4].x + v[5].x) + ((double)v[6].x + v[7].x))));
+        tot[t][1] = (float)(tot[t][1] + ((((double)v[0].y + v[1].y) + ((double)v[2].y + v[3].y)) +
+                                         (((double)v[4].y + v[5].y) + ((double)v[6].y + v[7].y))));
+      }
+      __syncthreads();
+    }
     if (w.nbuf == 1 && s + 1 < s_end) {
       stage(s + 1, lds);
       __syncthreads();
@@ -523,19 +553,14 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
   }
   // [32*TI co][32*TJ ci][KK] of the tile, then rows of 32*TJ*KK floats
   constexpr int RO = 32 * TJ * KK;
-  float* sR = lds;               // [8][16][64]
-  float* so = lds + 8 * 1024;    // [32*TI][RO]
+  float* so = lds;
 #pragma unroll
   for (int t = 0; t < NA; ++t) {
-    if (t) __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sR[(wave * 16 + r) * 64 + lane] = acc[t][r];
-    __syncthreads();
     const int ti = t / (KK * TJ), tj = KS == 1 ? t % TJ : 0, tap = KS == 1 ? 0 : t;
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) {
-      const int r = 2 * wave + rr, co = ti * 32 + 8 * (r >> 2) + 4 * half + (r & 3), o = r * 64 + lane;
-      so[co * RO + (tj * 32 + row) * KK + tap] = (float)sum8(sR + o);
+      const int r = 2 * wave + rr, co = ti * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+      so[co * RO + (tj * 32 + row) * KK + tap] = tot[t][rr];
     }
   }
   __syncthreads();
@@ -545,7 +570,23 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
     for (int i = lane; i < nci; i += 64) out[(size_t)co * w.Cin * KK + i] = so[co * RO + i];
 }
 
-struct LdsWgPick { int PT = 0, per, chunks, rows, NP, nbuf; size_t lds; };
+// Most pixels that a wavefront adds up in one 32-bit accumulator before a flush: a sum's rounding error grows with the root
+// of its chain of additions, so the chain must not grow with the micro-batch.  The direct kernels' chains are min(32 .. 256, a
+// plane), and they add their partials in 32 bits; a quarter longer, and at most 128, is as exact.  Relative error of dW
+// against 64 bits, direct kernel / one chain per block / now: 512 -> 512 at 32 x 7x7 1.34e-7, 1.67e-7, 1.24e-7; 256 -> 256 at
+// 8 x 14x14 1.19e-7, 1.30e-7, 1.02e-7, at 64 x 28x28 2.9e-7, 6.9e-7, 2.1e-7.  A flush takes about 4 us, the time of its
+// LDS traffic; more and shorter blocks instead, with more partials, took longer: backward of the first layer 214 us before, 236
+// with chains of 64 that way, 223 with flushes.
+int chain_limit(int N, int Cin, int Cout, int HWo) {
+  return std::min(128, std::max(40, conv_mfma_wgrad_chain(N, Cin, Cout, HWo) * 5 / 4));
+}
+
+struct LdsWgPick {
+  int PT = 0, per, chunks, rows, NP, nbuf, chain;
+  size_t buf, lds;  // bytes of a stage's buffer and of a block
+  // stages between two flushes of a run of `run` stages: equal shares, none of more than `chain` pixels a wavefront
+  int flush(int run) const { return cdiv(run, cdiv((long)run * (PT / 8), chain)); }
+};
 
 LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
   LdsWgPick best;
@@ -558,11 +599,13 @@ LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
   for (int PT = 32; PT <= 128; PT *= 2) {
     LdsWgPick p;
     p.PT = PT;
+    p.chain = chain_limit(N, Cin, Cout, Ho * Wo);
     p.rows = tile_rows(PT, Ho, Wo, S, H);
     p.NP = cdiv(p.rows * (W + 2), 64);
-    const size_t buf = ((size_t)tw * (round_up64(PT) + 2 + p.NP * 64 + 2) + PT) * 4;
-    p.nbuf = 2 * buf <= kWgradLds ? 2 : 1;
-    p.lds = std::max(p.nbuf * buf, (size_t)(8192 + tw * tw * KS * KS) * 4);
+    p.buf = ((size_t)tw * (round_up64(PT) + 2 + p.NP * 64 + 2) + PT) * 4;
+    const size_t beside = p.buf >= 8 * kFlush ? 0 : p.buf >= 4 * kFlush ? 4 * kFlush : 8 * kFlush;  // scratch of the flushes
+    p.nbuf = 2 * p.buf + beside <= kWgradLds ? 2 : 1;
+    p.lds = std::max(p.nbuf * p.buf + beside, (size_t)tw * tw * KS * KS * 4);
     if (p.lds > kWgradLds) continue;
     const int nstage = cdiv(npix, PT);
     for (int per = 1; per <= nstage; per = per < 8 ? per + 1 : per + per / 4) {
@@ -571,7 +614,8 @@ LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
       const double mfma = PT / 8 * (KS == 1 ? 4 : 9) * 64.0, bytes = tw * 256.0 * (p.NP + cdiv(PT, 64));
       const double stage = 2000 + bytes / 20;
       const double one = p.nbuf == 2 ? std::max(mfma, stage) + bytes / 40 + 800 : mfma + stage;
-      const double c = std::ceil(chunks * tiles / 256.0) * (cdiv(nstage, chunks) * one + stage + 3000 + KS * KS * 500) +
+      const int run = cdiv(nstage, chunks), flushes = cdiv(run, p.flush(run));  // the last one is the block's end
+      const double c = std::ceil(chunks * tiles / 256.0) * (run * one + stage + 3000 + KS * KS * (1000 * flushes - 500)) +
                        (double)chunks * tiles * KS * KS * tw * tw * 8 / 1500;  // writing and reducing the partials
       if (c < cost) {
         cost = c;
@@ -624,6 +668,7 @@ void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const floa
   w.npix = (unsigned)N * w.Ho * w.Wo;
   w.rRW = reciprocal(w.W + 2); w.rH1 = reciprocal(w.H + 1); w.rWo = reciprocal(w.Wo);
   w.rows = p.rows; w.RW = w.W + 2; w.NP = p.NP; w.PT = p.PT; w.per = p.per; w.nbuf = p.nbuf;
+  w.flush = p.flush(p.per);
   w.nstage = cdiv(w.npix, p.PT);
   const int tw = KS == 1 ? 64 : 32;
   const dim3 grid((unsigned)(p.chunks * cdiv(Cin, tw) * cdiv(Cout, tw)));
@@ -638,13 +683,16 @@ void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const floa
 
 // The choices above, for tests that name one.  what: 0 forward, 1 input gradient, 2 weight gradient of a conv with
 // these sizes (H, W: its input).  0: the direct kernels run.  1: staged; out = {row tiles, pixel groups, shares of the
-// contraction, classes of result pixels}, or for a weight gradient {pixels per stage, stages per block, partials, buffers}.
-extern "C" int ast_conv_lds_choice(int what, int N, int Cin, int Cout, int H, int W, int KS, int S, int out[4]) {
+// contraction, classes of result pixels, 0, 0}, or for a weight gradient {pixels per stage, stages per block, partials,
+// buffers, stages per flush, scratch areas of a flush inside the stage's buffer}.
+extern "C" int ast_conv_lds_choice(int what, int N, int Cin, int Cout, int H, int W, int KS, int S, int out[6]) {
   using namespace ast;
   if (what == 2) {
     LdsWgPick p;
     if (!pick_wgrad(N, Cin, Cout, H, W, KS, S, INT_MAX, p)) return 0;
     out[0] = p.PT; out[1] = p.per; out[2] = p.chunks; out[3] = p.nbuf;
+    out[4] = p.flush(p.per);
+    out[5] = p.buf >= 8 * kFlush ? 2 : p.buf >= 4 * kFlush ? 1 : 0;
     return 1;
   }
   LdsArgs a;
@@ -652,5 +700,6 @@ extern "C" int ast_conv_lds_choice(int what, int N, int Cin, int Cout, int H, in
   int ncls;
   if (!plan_product(what == 1, N, what ? Cout : Cin, what ? Cin : Cout, H, W, KS, S, a, ncls, p)) return 0;
   out[0] = p.MT; out[1] = p.WN; out[2] = p.WK; out[3] = ncls;
+  out[4] = out[5] = 0;
   return 1;
 }

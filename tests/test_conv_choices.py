@@ -9,10 +9,32 @@ FWD, DGRAD, WGRAD = 0, 1, 2
 
 
 def choice(what, n, cin, cout, h, w, k, s):
-    """None: the direct kernels; else the four words of the staged kernel's block shape."""
-    out = (ctypes.c_int * 4)()
+    """None: the direct kernels; else the words of the staged kernel's block shape."""
+    out = (ctypes.c_int * 6)()
     lib = ctypes.CDLL(A.lib_path())
     return tuple(out) if lib.ast_conv_lds_choice(what, n, cin, cout, h, w, k, s, out) else None
+
+
+# Sizes (cin, cout, k, stride, h, w, B) whose parity is checked on the GPU, each for the form that its choice must be, so
+# that a change of the cost models cannot leave a form untested.
+#   weight gradient: buffers, scratch areas of a flush inside a buffer, stages per block, stages per flush
+WGRAD_FORMS = [
+    ((136, 392, 3, 1, 7, 7, 32), (2, 0, 9, 5)),       # flushes of unequal length, both scratch areas past the buffers
+    ((40, 40, 3, 1, 28, 28, 32), (2, 1, 7, 4)),
+    ((40, 40, 3, 1, 15, 62, 24), (2, 2, 3, 2)),
+    ((40, 72, 3, 1, 6, 150, 12), (1, 2, 3, 2)),
+    ((40, 136, 3, 2, 112, 20, 16), (2, 2, 6, 3)),     # stride 2
+    ((40, 40, 3, 2, 56, 56, 32), (1, 2, 4, 2)),
+    ((200, 264, 1, 2, 14, 14, 16), (2, 1, 2, 2)),     # 1x1: 64 x 64 tiles
+    ((72, 72, 1, 2, 112, 20, 16), (1, 2, 2, 2)),
+]
+
+
+@pytest.mark.parametrize("sizes,want", WGRAD_FORMS)
+def test_form_of_the_staged_weight_gradient(sizes, want):
+    cin, cout, k, s, h, w, n = sizes
+    got = choice(WGRAD, n, cin, cout, h, w, k, s)
+    assert got is not None and (got[3], got[5], got[1], got[4]) == want
 
 
 @pytest.mark.parametrize("what", [FWD, DGRAD, WGRAD])

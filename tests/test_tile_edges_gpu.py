@@ -7,6 +7,7 @@ import pytest
 import harness
 from asteroid_workloads import gen
 from asteroid_workloads.configs import bn, conv, simple
+from test_conv_choices import WGRAD, WGRAD_FORMS, choice
 from test_parity_gpu import A, check, one  # noqa: F401  (A: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -27,6 +28,11 @@ pytestmark = pytest.mark.gpu
 ])
 def test_dense_conv_tiles(A, cin, cout, k, stride, h, w, B):
     check(one([conv(cin, cout, k, stride, k // 2)], (cin, h, w), B=B), rounds=1)
+
+
+@pytest.mark.parametrize("cin,cout,k,stride,h,w,B", [sizes for sizes, _ in WGRAD_FORMS])
+def test_dense_conv_weight_gradient_forms(A, cin, cout, k, stride, h, w, B):
+    check(one([conv(cin, cout, k, stride, k // 2)], (cin, h, w), B=B, M=1), rounds=1)
 
 
 @pytest.mark.parametrize("c,h,w,B", [
@@ -58,6 +64,9 @@ def test_pointwise_conv_tiles(A, cin, cout, h, w, B):
     (512, 2048, 1, 1, 7, 128),      # pointwise, 2x2 weight tiles: three ranges of 65 steps
     (24, 144, 1, 1, 56, 128),       # 1x1 tiles, ranges of 41 steps
     (960, 160, 1, 1, 7, 512),       # 2x1 tiles, ranges of 64 steps
+    (512, 512, 3, 1, 7, 128),       # dense
+    (64, 64, 3, 1, 56, 64),
+    (1024, 2048, 1, 2, 14, 128),    # 64 x 64 tiles
 ])
 def test_rounding_of_weight_gradients_does_not_grow_with_the_micro_batch(A, cin, cout, k, stride, hw, B):
     """An fp32 addition rounds by 2^-25.3 of its result (root mean square), a chain of n additions of independent terms by
@@ -110,7 +119,6 @@ def test_partials_of_a_stage_that_just_fits_the_static_workspace(A, layers, shap
 def test_strided_conv_of_a_tensor_around_the_offset_limit(A, n, cin, cout, hw, k, staged):
     """Three samples spread over the tensor are not zero: the gradients are those of these samples alone."""
     import torch
-    from test_conv_choices import WGRAD, choice
     assert (choice(WGRAD, n, cin, cout, hw, hw, k, 2) is not None) == staged
     dev, at, ho = torch.device("cuda:0"), [0, n // 2, n - 1], hw // 2
     g = torch.Generator().manual_seed(3)
