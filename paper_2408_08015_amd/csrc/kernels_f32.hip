@@ -616,7 +616,7 @@ void maxpool3x3s2_fwd_f32(hipStream_t st, const float* x, float* y, int NC, int 
 }
 void maxpool3x3s2_bwd_f32(hipStream_t st, const float* g, const float* x, float* dx, int NC, int H, int W) {
   const int Ho = (H - 1) / 2 + 1, Wo = (W - 1) / 2 + 1;
-  const size_t total = (size_t)NC * ((H + 1) / 2) * ((W + 1) / 2);
+  const size_t total = (size_t)NC * ((H + 1) / 2) * ((W + 1) / 2);  // below 2^32 (checked at create)
   KLAUNCH(maxpool3x3s2_bwd_kernel, dim3(cdiv(total, 256)), dim3(256), 0, st, g, x, dx, H, W, Ho, Wo, (unsigned)total);
 }
 

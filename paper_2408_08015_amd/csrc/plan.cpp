@@ -214,6 +214,10 @@ ast_status build_plan(Stage& s, std::string& err) {
       }
       case AST_MAXPOOL3X3S2: {
         if (s.bf16 || A.rank != 4) { err = fmt("layer %d: the 3x3 stride-2 max-pool needs an fp32 image tensor", i); return AST_EUNSUPPORTED; }
+        // one thread per result forward, one per 2x2 inputs (the same number) backward; a launch has fewer than 2^32
+        if ((size_t)B * A.c * ((A.h - 1) / 2 + 1) * ((A.w - 1) / 2 + 1) > ((size_t)1 << 32) - 256) {
+          err = fmt("layer %d: the 3x3 stride-2 max-pool needs fewer than 2^32 results per micro-batch", i); return AST_EUNSUPPORTED;
+        }
         op.kind = OP_MAXPOOL; op.k = 3; op.stride = 2; op.pad = 1;
         op.out = cur = new_act(s, B, A.c, (A.h - 1) / 2 + 1, (A.w - 1) / 2 + 1, 4, i, es);
         break;
