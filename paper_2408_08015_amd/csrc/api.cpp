@@ -167,6 +167,9 @@ ast_status asteroid_stage_create(const ast_layer* layers, int32_t n_layers, cons
     return st;
   };
   hipError_t e;
+  bool dense = false;
+  for (const ast::Op& op : s.ops) dense |= op.kind == ast::OP_CONV_3X3;
+  if (dense && (e = ast::conv_lds_allow()) != hipSuccess) return bail(e, "create: dynamic LDS");
   const size_t pbytes = (s.nparams + 4) * sizeof(float);
   if ((e = hipMalloc((void**)&s.W, pbytes)) != hipSuccess) return bail(e, "create: hipMalloc(W)");
   if ((e = hipMalloc((void**)&s.G, pbytes)) != hipSuccess) return bail(e, "create: hipMalloc(G)");

@@ -92,6 +92,8 @@ void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y
 void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* x, float* part,
                        float* G, int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
 // The LDS-staged kernels behind the calls above (kernels_f32_conv_lds.hip); false / 0 where no block shape fits.
+// conv_lds_allow: before the first of their launches on a device.
+hipError_t conv_lds_allow();
 bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
                       const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S);
 int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap);

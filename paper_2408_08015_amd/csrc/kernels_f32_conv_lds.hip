@@ -14,6 +14,7 @@
 #include <cmath>
 #include <map>
 #include <type_traits>
+#include <utility>
 
 #include "device_utils.h"
 #include "kernels.h"
@@ -325,8 +326,6 @@ bool pick_product(const LdsArgs& a, int ncls, LdsPick& p) {
 
 template <int MT, bool ALL>
 void launch_one(hipStream_t st, const char* name, const LdsArgs& a, const LdsPick& p, dim3 grid) {
-  if (p.lds > 64 * 1024)  // more than the default dynamic limit
-    (void)hipFuncSetAttribute((const void*)conv_lds_f32_kernel<MT, ALL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
   KLAUNCH_NAMED(name, (conv_lds_f32_kernel<MT, ALL>), grid, dim3(64 * p.WN * p.WK), p.lds, st, a);
 }
 
@@ -672,11 +671,20 @@ void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const floa
   w.nstage = cdiv(w.npix, p.PT);
   const int tw = KS == 1 ? 64 : 32;
   const dim3 grid((unsigned)(p.chunks * cdiv(Cin, tw) * cdiv(Cout, tw)));
-  if (p.lds > 64 * 1024)
-    (void)hipFuncSetAttribute(KS == 3 ? (const void*)conv_lds_wgrad_f32_kernel<3> : (const void*)conv_lds_wgrad_f32_kernel<1>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
   if (KS == 3) KLAUNCH_NAMED(name, (conv_lds_wgrad_f32_kernel<3>), grid, dim3(512), p.lds, st, w);
   else KLAUNCH_NAMED(name, (conv_lds_wgrad_f32_kernel<1>), grid, dim3(512), p.lds, st, w);
+}
+
+// The kernels of this file may use more than the default 64 KiB of dynamic LDS: allowed once per stage, for its device, always
+// up to the same sizes.  (Set per launch to that launch's size, it was state shared with the launches of other threads.)
+hipError_t conv_lds_allow() {
+  const std::pair<const void*, size_t> kernels[] = {
+      {(const void*)conv_lds_f32_kernel<1, false>, kProductLds}, {(const void*)conv_lds_f32_kernel<1, true>, kProductLds},
+      {(const void*)conv_lds_f32_kernel<2, false>, kProductLds}, {(const void*)conv_lds_f32_kernel<2, true>, kProductLds},
+      {(const void*)conv_lds_wgrad_f32_kernel<1>, kWgradLds},    {(const void*)conv_lds_wgrad_f32_kernel<3>, kWgradLds}};
+  for (const auto& k : kernels)
+    if (hipError_t e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second)) return e;
+  return hipSuccess;
 }
 
 }  // namespace ast

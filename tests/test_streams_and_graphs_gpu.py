@@ -109,12 +109,60 @@ def test_forward_stream_with_one_stash_and_switching_back(A):
     st.close()
 
 
-@pytest.mark.parametrize("name,forward_stream", [("cfg2", False), ("cfg2", True), ("cfg5", False), ("cfg5", True)])
+def test_two_threads_drive_stages_of_different_lds_sizes(A):
+    """Two host threads, a stage and a stream each, dense fp32 convolutions whose blocks take different amounts of LDS:
+    every round has the bits of the same stage run alone."""
+    import threading
+    import torch
+    dev = torch.device("cuda:0")
+    sizes = [(64, 64, 56, 8), (264, 40, 90, 4), (40, 136, 20, 16)]
+
+    def rounds(i, n):
+        cin, cout, hw, B = sizes[i]
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            g = torch.Generator(device=dev)
+            g.manual_seed(i)
+            x = torch.randn(B, cin, hw, hw, generator=g, device=dev)
+            dy = torch.randn(B, cout, hw, hw, generator=g, device=dev)
+            w = torch.randn(cout * cin * 9, generator=g, device=dev).mul_(0.05)
+            y, dx = torch.empty_like(dy), torch.empty_like(x)
+            st = A.Stage([C.conv(cin, cout, 3, 1, 1)], B, 1, 1, (cin, hw, hw), stream=s.cuda_stream)
+            st.set_params(w.cpu().numpy())
+            got = []
+            for _ in range(n):
+                st.forward(0, x, None, y)
+                st.backward(0, dy, dx)
+                got.append((st.get_grads(), y.cpu().numpy(), dx.cpu().numpy()))
+                st.step(0.0, 0.0)
+            st.close()
+        return got
+
+    alone = [rounds(i, 1)[0] for i in range(3)]
+    got = [None] * 3
+
+    def work(i):
+        got[i] = rounds(i, 12)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(3):
+        assert got[i] is not None
+        for r in got[i]:
+            assert all(np.array_equal(a, b) for a, b in zip(alone[i], r)), i
+
+
+@pytest.mark.parametrize("name,forward_stream", [("cfg2", False), ("cfg2", True), ("cfg5", False), ("cfg5", True),
+                                                 ("cfg7", False), ("cfg7", True)])
 def test_round_captured_in_a_graph_replays_bit_identically(A, name, forward_stream):
     """A whole round (K forward passes, 1F1B, the update) is kernel launches and event waits on the
     stage's streams - no allocation, no memset, no host synchronisation - so a caller may capture it
     into a HIP graph.  Every replay is checked against the eager run of the same round, with eager
-    work and synchronisations between the replays."""
+    work and synchronisations between the replays.  (cfg7: dense fp32 convolutions, blocks of more than
+    64 KiB of LDS.)"""
     import torch
     cfg = CASES[name]()
     K = 2
