@@ -26,8 +26,8 @@ namespace {
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 __host__ __device__ constexpr int round_up64(int v) { return (v + 63) & ~63; }
-// floor(n / d) = mulhi(n, reciprocal(d)) while n * d < 2^32
-inline unsigned reciprocal(unsigned d) { return d == 1 ? 0xffffffffu : (unsigned)(((1ull << 32) + d - 1) / d); }
+// floor(n / d) = mulhi(n, reciprocal(d)) for d > 1 while n * d < 2^32; reciprocal(1) is 0
+inline unsigned reciprocal(unsigned d) { return d == 1 ? 0 : (unsigned)(((1ull << 32) + d - 1) / d); }
 constexpr size_t kProductLds = 128 * 1024, kWgradLds = 156 * 1024;
 constexpr unsigned kOutside = 0x80000000u;  // buffer offset beyond every extent: a copy writes zeros
 // The copies address a whole tensor in memory with 32-bit byte offsets below kOutside.
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
         copy_to_lds(rg, buf + c * PG + p0, voff, (unsigned)min(co_base + c, w.Cout - 1) * (unsigned)HWo * 4u);
       }
       if (wave == 0 && p0 + lane < PT) {
-        const int i = w.Wo > 1 ? (int)__umulhi((unsigned)p, w.rWo) : p, j = p - i * w.Wo;
+        const int i = w.rWo ? (int)__umulhi((unsigned)p, w.rWo) : p, j = p - i * w.Wo;
         reinterpret_cast<int*>(buf + TO)[p0 + lane] = ((int)n * H1 + w.S * i - vr0) * RW + w.S * j;
       }
     }
