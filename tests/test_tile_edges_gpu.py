@@ -55,6 +55,9 @@ def test_batchnorm_planes_not_a_multiple_of_16_bytes(A, c, h, w, B):
     (256, 192, 7, 7, 43),    # steps of 32 pixels across samples of 49
     (33, 65, 7, 7, 3),       # few blocks: one step, rows past both edges
     (8, 8, 1, 1, 5),         # fewer pixels than a step
+    (1024, 40, 7, 7, 2),     # product split over 16 wavefronts: 64 channels each, in one pass
+    (1032, 40, 7, 7, 2),     # 72 each, pipelined; the last wavefronts have fewer or none
+    (40, 2056, 5, 5, 2),     # the same in the input gradient, 136 each
 ])
 def test_pointwise_conv_tiles(A, cin, cout, h, w, B):
     check(one([conv(cin, cout, 1, 1, 0)], (cin, h, w), B=B), rounds=1)
