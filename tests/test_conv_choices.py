@@ -29,6 +29,43 @@ WGRAD_FORMS = [
     ((72, 72, 1, 2, 112, 20, 16), (1, 2, 2, 2)),
 ]
 
+#   products, forward and input gradient: 32-row tiles of result channels, groups of 32 pixels, shares of the contraction
+PRODUCT_FORMS = [
+    ((40, 40, 3, 1, 56, 56, 8), (2, 4, 1), (2, 4, 1)),
+    ((264, 40, 3, 1, 5, 90, 12), (1, 2, 2), (2, 4, 1)),     # nine tiles: the last pair has one
+    ((64, 264, 3, 1, 5, 90, 12), (2, 4, 2), (1, 2, 2)),     # ... and the sums of two shares
+    ((64, 72, 3, 2, 15, 62, 12), (2, 1, 4), (1, 3, 4)),     # stride 2: classes of 1, 2 and 4 taps in the input gradient
+    ((200, 64, 3, 2, 5, 90, 5), (1, 2, 2), (2, 2, 4)),
+    ((264, 40, 3, 2, 5, 90, 12), (1, 2, 2), (2, 4, 1)),
+    ((64, 264, 1, 2, 6, 150, 8), (2, 2, 4), (1, 2, 4)),     # 1x1 stride 2
+    ((264, 64, 1, 2, 6, 150, 8), (1, 2, 4), (2, 2, 4)),
+]
+#   rows too long for the staged kernels: which of forward, input gradient and weight gradient are staged all the same
+DIRECT_FORMS = [
+    ((8, 40, 3, 1, 3, 400, 1), (False, False, False)),      # rows a multiple of 16 bytes
+    ((8, 40, 3, 1, 3, 401, 2), (False, False, False)),
+    ((8, 40, 3, 2, 3, 400, 1), (False, True, False)),
+    ((8, 40, 3, 2, 3, 401, 2), (False, True, False)),
+    ((24, 40, 3, 2, 3, 2601, 2), (False, False, False)),
+    ((8, 40, 1, 2, 3, 401, 2), (True, True, False)),
+    ((40, 24, 1, 2, 3, 2601, 2), (False, False, False)),
+    ((40, 8, 1, 2, 4, 802, 1), (False, False, False)),
+]
+
+
+@pytest.mark.parametrize("sizes,forward,backward", PRODUCT_FORMS)
+def test_form_of_the_staged_products(sizes, forward, backward):
+    cin, cout, k, s, h, w, n = sizes
+    for what, want in ((FWD, forward), (DGRAD, backward)):
+        got = choice(what, n, cin, cout, h, w, k, s)
+        assert got is not None and got[:3] == want
+
+
+@pytest.mark.parametrize("sizes,staged", DIRECT_FORMS)
+def test_rows_too_long_for_the_staged_kernels(sizes, staged):
+    cin, cout, k, s, h, w, n = sizes
+    assert tuple(choice(what, n, cin, cout, h, w, k, s) is not None for what in (FWD, DGRAD, WGRAD)) == staged
+
 
 @pytest.mark.parametrize("sizes,want", WGRAD_FORMS)
 def test_form_of_the_staged_weight_gradient(sizes, want):

@@ -323,7 +323,7 @@ def test_dense_conv3x3(A, cin, cout, h, w, B, bias, need_dx):
     (64, 128, 1, 14, 14, 2, False),
     (8, 8, 1, 7, 5, 2, True),
     (8, 8, 1, 1, 1, 2, False),
-    (8, 40, 3, 64, 64, 8, False),   # two result tiles per wavefront in the input gradient (8 channels: one tile) and forward
+    (8, 40, 3, 64, 64, 8, False),   # three and two groups of pixels per block, contraction not split
 ])
 @pytest.mark.parametrize("need_dx", [True, False])
 def test_dense_conv_stride2(A, cin, cout, k, h, w, B, bias, need_dx):

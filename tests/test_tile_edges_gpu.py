@@ -7,7 +7,7 @@ import pytest
 import harness
 from asteroid_workloads import gen
 from asteroid_workloads.configs import bn, conv, simple
-from test_conv_choices import WGRAD, WGRAD_FORMS, choice
+from test_conv_choices import DIRECT_FORMS, PRODUCT_FORMS, WGRAD, WGRAD_FORMS, choice
 from test_parity_gpu import A, check, one  # noqa: F401  (A: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -16,13 +16,13 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("cin,cout,k,stride,h,w,B", [
     (96, 40, 3, 1, 7, 7, 5),        # tiles across samples; 12 groups of channels over 8 shares of the contraction
     (136, 72, 3, 1, 4, 3, 9),       # several samples per tile, 17 groups: the last chunk has empty shares
-    (64, 64, 3, 1, 20, 20, 8),      # two channel tiles per wavefront
+    (64, 64, 3, 1, 20, 20, 8),      # eight shares of the contraction in both products
     (40, 32, 3, 1, 2, 130, 2),      # rows longer than a tile
-    (8, 40, 3, 1, 3, 400, 1),       # rows too long for the staged weight gradient
-    (8, 8, 3, 1, 2, 2600, 1),       # ... and for the staged product: the direct kernels
+    (8, 40, 3, 1, 3, 400, 1),       # rows too long for the staged kernels: the direct ones
+    (8, 8, 3, 1, 2, 2600, 1),
     (128, 128, 3, 2, 14, 14, 3),    # parity classes of 49 pixels each
     (72, 96, 3, 2, 7, 9, 5),        # odd size: classes of different sizes
-    (64, 72, 3, 2, 30, 62, 2),      # stride-2 rows, single-buffered weight gradient
+    (64, 72, 3, 2, 30, 62, 2),      # stride-2 rows
     (192, 136, 1, 2, 9, 7, 4),      # 1x1: three of four classes are zeros; ragged 64 x 64 weight-gradient tiles
     (256, 64, 1, 2, 14, 14, 2),
 ])
@@ -30,8 +30,8 @@ def test_dense_conv_tiles(A, cin, cout, k, stride, h, w, B):
     check(one([conv(cin, cout, k, stride, k // 2)], (cin, h, w), B=B), rounds=1)
 
 
-@pytest.mark.parametrize("cin,cout,k,stride,h,w,B", [sizes for sizes, _ in WGRAD_FORMS])
-def test_dense_conv_weight_gradient_forms(A, cin, cout, k, stride, h, w, B):
+@pytest.mark.parametrize("cin,cout,k,stride,h,w,B", [f[0] for f in PRODUCT_FORMS + WGRAD_FORMS + DIRECT_FORMS])
+def test_dense_conv_forms(A, cin, cout, k, stride, h, w, B):
     check(one([conv(cin, cout, k, stride, k // 2)], (cin, h, w), B=B, M=1), rounds=1)
 
 
