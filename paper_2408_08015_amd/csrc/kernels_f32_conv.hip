@@ -103,8 +103,8 @@ __device__ __forceinline__ void pw_stats_epilogue(const float (&s)[16], const fl
 // wavefronts of a SIMD did so in step.)  Branch-free: rows past Kdim read the last row (zero weights in the packed
 // copy), groups past the last read that one again and are not multiplied, pixels past NQ read pixel 0 and are replaced
 // by zero (the statistics epilogue sums every column).  wl: lane's weights of the tile; xq: lane's pixel.
-// Before and after, at 32 x 56x56 pixels with the 128-pixel wavefronts: 64 -> 256 channels 58.9 -> 55.3 us,
-// 256 -> 64 42.8 -> 37.3; backward of 256 -> 64 77.0 -> 73.8, of 64 -> 256 110.1 -> 103.0.
+// Before and after, at 32 x 56x56 pixels with the 128-pixel wavefronts, forward: 64 -> 256 channels 58.9 -> 55.3 us,
+// 256 -> 64 42.8 -> 37.3.
 __device__ __forceinline__ void pw_contract(const float4* __restrict__ wl, const float* __restrict__ xq, int HW, int Kdim,
                                             int gbeg, int gend, int half, bool qv, floatx16& acc) {
   if (gbeg >= gend) return;  // uniform
@@ -702,11 +702,11 @@ __global__ __launch_bounds__(256, !VEC && (SHAPE == WG_2x2 || SHAPE == WG_1x1) ?
 // are bound by the latency of one load-compute-store chain), so their blocks are dealt from
 // one grid: block ids [0, nA) form the (x, y) grid of the input-gradient product, the rest
 // the (x, y, z) grid of the weight-gradient kernel.  VAR selects the product kernel:
-// 0 / 1 = 32-pixel wavefronts with one / two 32-channel chunks per pass, 2 = K split over the
+// 0 / 1 = 32-pixel wavefronts with up to 32 / more input channels, 2 = K split over the
 // block, 3 = 128-pixel wavefronts.
 template <int VAR, int SHAPE, bool VEC>
-__global__ __launch_bounds__(256, VAR >= 2 ? 1 : !VEC && (SHAPE == WG_2x2 || SHAPE == WG_1x1) ? 3 : 4) void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx,
-                                                          unsigned gWx, unsigned gWy) {
+__global__ __launch_bounds__(256, VAR >= 2 ? 1 : !VEC && (SHAPE == WG_2x2 || SHAPE == WG_1x1) ? 3 : 4)
+void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx, unsigned gWx, unsigned gWy) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   static_assert(wg_lds_floats<SHAPE>() >= 4 * 16 * 64, "the product kernels use 16 KB");
   if (blockIdx.x < nA) {  // uniform per block

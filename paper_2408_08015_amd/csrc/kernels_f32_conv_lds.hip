@@ -1,7 +1,7 @@
 // fp32 dense convolutions on the matrix cores with the pixels staged in LDS: 3x3 pad 1 (stride 1 or 2) and 1x1
 // stride 2, forward, input gradient and weight gradient.
 //
-// v_mfma_f32_32x32x2 takes 64 cycles for 2 + 2 operand words per lane, so the matrix cores are the bound as soon as
+// v_mfma_f32_32x32x2 takes 64 cycles for one word of either operand per lane, so the matrix cores are the bound as soon as
 // operands arrive with few instructions: nine taps are nine shifted reads of one LDS copy of the pixels.
 //
 // LDS copy: "virtual rows".  Row h of sample n of the operand tensor is virtual row n*(XH+1) + h + 1; the rows
@@ -62,10 +62,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, unsigne
 __device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t r, float* dst, unsigned voff, unsigned soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 4, voff, soff, 0, 0);
 }
-// byte offset (without the channel part) of position `pos` of the virtual rows vr0, vr0 + 1, ... (pitch XW + 2), or kOutside for the zeros between samples, beside the rows and past the last row.
+// byte offset (without the channel part) of position `pos` of the virtual rows vr0, vr0 + 1, ... (pitch XW + 2), or
+// kOutside for the zeros between samples, beside the rows and past the last row.
 // rRW, rXH1: reciprocal() of XW + 2 and XH + 1.
-__device__ __forceinline__ unsigned virtual_offset(int pos, int vr0, int rows, unsigned rRW, unsigned rXH1, int N, int XH, int XW,
-                                                   int XRW, int XS, unsigned sample_words) {
+__device__ __forceinline__ unsigned virtual_offset(int pos, int vr0, int rows, unsigned rRW, unsigned rXH1, int N, int XH,
+                                                   int XW, int XRW, int XS, unsigned sample_words) {
   // (an integer division is about 40 vector instructions; 840 of a stage's 9200 cycles this way, 4200 with them)
   const int r = (int)__umulhi((unsigned)pos, rRW), x = pos - r * (XW + 2) - 1;
   const int v = vr0 + r, n = (int)__umulhi((unsigned)v, rXH1), h = v - n * (XH + 1) - 1;
@@ -76,9 +77,9 @@ __device__ __forceinline__ unsigned virtual_offset(int pos, int vr0, int rows, u
 // Block: WN pixel groups of 32 x WK shares of the contraction, one wavefront each, and MT 32-row tiles of result
 // channels.  A chunk of CH = 8*WK operand channels is copied to LDS (buffer_load ... lds: no registers, zeros
 // from the descriptor's bounds check) while the previous chunk is multiplied; wavefront (wn, wk) multiplies the
-// wk-th group of eight channels for every tap.  The weights of a wavefront's taps stay one chunk ahead in registers: their loads are issued behind the copies of the next chunk, and vector-memory results
-// return in order, so a weight load waited for in the same chunk would wait for the copies too.  The WK partial
-// tiles are added through LDS in fixed order.
+// wk-th group of eight channels for every tap.  The weights of a wavefront's taps stay one chunk ahead in registers: their
+// loads are issued behind the copies of the next chunk, and vector-memory results return in order, so a weight load waited
+// for in the same chunk would wait for the copies too.  The WK partial tiles are added through LDS in fixed order.
 template <int MT, int NT>
 __device__ __forceinline__ void conv_lds_body(const LdsArgs& a, const LdsClass& c, float* lds, int tile0, unsigned q0) {
   const int tid = threadIdx.x, lane = tid & 63, T = blockDim.x, waves = T >> 6;
@@ -299,7 +300,8 @@ bool search_product(const LdsArgs& a, int ncls, LdsPick& best) {
         const double chunk_mfma = taps * 4 * MT * 64;
         // bytes through L2 per compute unit: staged pixels (with their halo) and weights
         const double traffic = per_cu * ((double)a.KG * 8 * p.NP * 256 + (double)MT * taps * a.KG * 1024);
-        const double resident = std::min(std::floor(160.0 * 1024 / p.lds), std::max(1.0, std::floor((MT == 2 ? 12.0 : 16.0) / waves)));
+        const double resident = std::min(std::floor(160.0 * 1024 / p.lds),
+                                         std::max(1.0, std::floor((MT == 2 ? 12.0 : 16.0) / waves)));
         const double rounds = std::ceil(per_cu / resident);
         const double stage = 600 + (double)p.CH * p.NP / waves * 30.0;   // not hidden while a block is alone on its CU
         p.cost = simd_waves * nchunk * chunk_mfma + (per_cu > 1 ? 0.3 : 0.6) * rounds * nchunk * stage +
@@ -416,14 +418,14 @@ struct LdsWgArgs {
 
 constexpr int kFlush = 8 * 16 * 64;  // words: one 32 x 32 tile of eight wavefronts
 
-// Block of eight wavefronts, one per compute unit: a 32 x 32 tile of (cout, cin), all taps (1x1: 64 x 64), over a run of stages of
-// PT consecutive output pixels, whatever samples they lie in.  A stage copies g [32][PT] and the virtual rows of x
+// Block of eight wavefronts, one per compute unit: a 32 x 32 tile of (cout, cin), all taps (1x1: 64 x 64), over a run of
+// stages of PT consecutive output pixels, whatever samples they lie in.  A stage copies g [32][PT] and the virtual rows of x
 // under it to LDS with coalesced loads (lanes along the pixels: a load per lane and channel row would touch 64 cache
 // lines instead of 2 to 4) while the stage before is multiplied; the products read one word of g and one of x per
 // tap for a pair of pixels.  Wavefront w takes the w-th eighth of every stage's pixels; every `flush` stages the eight
-// tiles are added through LDS into totals, two rows of the tile in registers of each wavefront, which leave as whole rows of
-// the partial.  Pitches are 2 modulo 64: the 32 channel rows and the two
-// neighbouring pixels of a pair hit 64 different banks.
+// tiles are added through LDS into totals, two rows of the tile in registers of each wavefront, which leave as whole rows
+// of the partial.  Pitches are 2 modulo 64: the 32 channel rows and the two neighbouring pixels of a pair hit 64 different
+// banks.
 template <int KS>
 __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
   constexpr int KK = KS * KS, TI = KS == 1 ? 2 : 1, TJ = TI, NA = KK * TI * TJ;  // 32 x 32 tiles of (cout, cin)
@@ -431,8 +433,10 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
   const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
   const int PT = w.PT, PG = round_up64(PT) + 2, PL = w.NP * 64 + 2, RW = w.RW, H1 = w.H + 1, HWo = w.Ho * w.Wo;
-  const int XO = 32 * TI * PG, TO = XO + 32 * TJ * PL, bufsz = TO + PT;  // g [32*TI][PG], x [32*TJ][PL], [PT] position of an output pixel's tap (0, 0)
-  const unsigned tiles_ci = (unsigned)(w.Cin + 32 * TJ - 1) / (32 * TJ), tiles = tiles_ci * (unsigned)((w.Cout + 32 * TI - 1) / (32 * TI));
+  // a stage: g [32*TI][PG], x [32*TJ][PL], [PT] position of an output pixel's tap (0, 0)
+  const int XO = 32 * TI * PG, TO = XO + 32 * TJ * PL, bufsz = TO + PT;
+  const unsigned tiles_ci = (unsigned)(w.Cin + 32 * TJ - 1) / (32 * TJ);
+  const unsigned tiles = tiles_ci * (unsigned)((w.Cout + 32 * TI - 1) / (32 * TI));
   const unsigned id = xcd_grouped(blockIdx.x, gridDim.x);
   const int chunk = (int)(id / tiles), tile = (int)(id % tiles);
   const int ci_base = (tile % (int)tiles_ci) * 32 * TJ, co_base = (tile / (int)tiles_ci) * 32 * TI;
@@ -464,7 +468,8 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
       }
     }
     for (int i = 0; i < w.NP; ++i) {
-      const unsigned voff = virtual_offset(i * 64 + lane, vr0, w.rows, w.rRW, w.rH1, w.N, w.H, w.W, w.XRW, w.XS, (unsigned)w.Cin * w.XHW);
+      const unsigned voff = virtual_offset(i * 64 + lane, vr0, w.rows, w.rRW, w.rH1, w.N, w.H, w.W, w.XRW, w.XS,
+                                           (unsigned)w.Cin * w.XHW);
 #pragma unroll
       for (int k = 0; k < 4 * TJ; ++k) {
         const int c = wave + 8 * k;
