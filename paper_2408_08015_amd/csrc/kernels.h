@@ -85,7 +85,9 @@ size_t conv_mfma_pack_floats(int Mdim, int Kdim, int k);
 // At most `cap` partials; the small count is what a stage falls back on to fit the static scratch array.
 int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
 int conv_mfma_wgrad_small_parts(int N, int Cin, int Cout, int H, int W, int k, int stride);
-int conv_mfma_wgrad_chain(int N, int Cin, int Cout, int HWo);  // pixels in a row in one accumulator of the direct kernel
+// Pixels of one chain of 32-bit additions with the rounding error of the direct kernel: its own chain, and a quarter per
+// partial for their addition in 32 bits (measured: 0.25 to 0.5).
+int conv_mfma_wgrad_chain(int N, int Cin, int Cout, int HWo);
 size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
 void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y, const float* bias, int N, int Cin,
                        int Cout, int H, int W, int k, int stride);

@@ -13,6 +13,8 @@
 // index), one block per (pixel chunk, 32x32 tile of (cout, cin)) with KS*KS accumulator tiles, one
 // per tap: g is loaded once per pass, x once per tap, shifted, strided and masked.
 // Partials per pixel chunk, layout [chunk][cout][cin][tap] = the layout of the weights.
+#include <algorithm>
+
 #include "device_utils.h"
 #include "kernels.h"
 #include "prof.h"
@@ -569,7 +571,10 @@ int conv_mfma_wgrad_small_parts(int N, int Cin, int Cout, int H, int W, int k, i
   return N * cdiv(HWo, 4 * c3_pxw(N, Cin, Cout, HWo));
 }
 
-int conv_mfma_wgrad_chain(int N, int Cin, int Cout, int HWo) { return std::min(c3_pxw(N, Cin, Cout, HWo), HWo); }
+int conv_mfma_wgrad_chain(int N, int Cin, int Cout, int HWo) {
+  const int px = c3_pxw(N, Cin, Cout, HWo);
+  return std::min(px, HWo) + N * cdiv(HWo, 4 * px) / 4;
+}
 
 size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
   return (size_t)conv_mfma_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap) * Cin * Cout * k * k;

@@ -575,21 +575,19 @@ __global__ __launch_bounds__(512) void conv_lds_wgrad_f32_kernel(LdsWgArgs w) {
 }
 
 // Most pixels that a wavefront adds up in one 32-bit accumulator before a flush: a sum's rounding error grows with the root
-// of its chain of additions, so the chain must not grow with the micro-batch.  The direct kernels' chains are min(32 .. 256, a
-// plane), and they add their partials in 32 bits; a quarter longer, and at most 128, is as exact.  Relative error of dW
-// against 64 bits, direct kernel / one chain per block / now: 512 -> 512 at 32 x 7x7 1.34e-7, 1.67e-7, 1.24e-7; 256 -> 256 at
-// 8 x 14x14 1.19e-7, 1.30e-7, 1.02e-7, at 64 x 28x28 2.9e-7, 6.9e-7, 2.1e-7.  A flush takes about 4 us, the time of its
-// LDS traffic; more and shorter blocks instead, with more partials, took longer: backward of the first layer 214 us before, 236
-// with chains of 64 that way, 223 with flushes.
-int chain_limit(int N, int Cin, int Cout, int HWo) {
-  return std::min(128, std::max(40, conv_mfma_wgrad_chain(N, Cin, Cout, HWo) * 5 / 4));
-}
+// of its chain of additions, so the chain must not grow with the micro-batch.  As long as the direct kernel's, and at most
+// 128.  Relative error of dW against 64 bits, direct kernel / one chain per block / now: 512 -> 512 at 32 x 7x7 1.34e-7,
+// 1.67e-7, 1.24e-7; 256 -> 256 at 8 x 14x14 1.19e-7, 1.30e-7, 1.02e-7, at 64 x 28x28 2.9e-7, 6.9e-7, 2.1e-7.  A flush takes
+// about 4 us, the time of its LDS traffic; more and shorter blocks instead, with more partials, took longer: backward of the
+// first layer 214 us before, 236 with chains of 64 that way, 223 with flushes.
+int chain_limit(int N, int Cin, int Cout, int HWo) { return std::min(128, conv_mfma_wgrad_chain(N, Cin, Cout, HWo)); }
 
 struct LdsWgPick {
   int PT = 0, per, chunks, rows, NP, nbuf, chain;
+  long npix;
   size_t buf, lds;  // bytes of a stage's buffer and of a block
   // stages between two flushes of a run of `run` stages: equal shares, none of more than `chain` pixels a wavefront
-  int flush(int run) const { return cdiv(run, cdiv((long)run * (PT / 8), chain)); }
+  int flush(int run) const { return cdiv(run, cdiv(std::min((long)run * PT, npix), 8 * chain)); }
 };
 
 LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
@@ -604,6 +602,7 @@ LdsWgPick search_wgrad(int N, int Cin, int Cout, int H, int W, int KS, int S) {
     LdsWgPick p;
     p.PT = PT;
     p.chain = chain_limit(N, Cin, Cout, Ho * Wo);
+    p.npix = npix;
     p.rows = tile_rows(PT, Ho, Wo, S, H);
     p.NP = cdiv(p.rows * (W + 2), 64);
     p.buf = ((size_t)tw * (round_up64(PT) + 2 + p.NP * 64 + 2) + PT) * 4;

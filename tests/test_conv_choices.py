@@ -20,13 +20,15 @@ def choice(what, n, cin, cout, h, w, k, s):
 #   weight gradient: buffers, scratch areas of a flush inside a buffer, stages per block, stages per flush
 WGRAD_FORMS = [
     ((136, 392, 3, 1, 7, 7, 32), (2, 0, 9, 5)),       # flushes of unequal length, both scratch areas past the buffers
-    ((40, 40, 3, 1, 28, 28, 32), (2, 1, 7, 4)),
-    ((40, 40, 3, 1, 15, 62, 24), (2, 2, 3, 2)),
-    ((40, 72, 3, 1, 6, 150, 12), (1, 2, 3, 2)),
-    ((40, 136, 3, 2, 112, 20, 16), (2, 2, 6, 3)),     # stride 2
-    ((40, 40, 3, 2, 56, 56, 32), (1, 2, 4, 2)),
-    ((200, 264, 1, 2, 14, 14, 16), (2, 1, 2, 2)),     # 1x1: 64 x 64 tiles
-    ((72, 72, 1, 2, 112, 20, 16), (1, 2, 2, 2)),
+    ((40, 392, 3, 1, 14, 14, 12), (2, 1, 5, 3)),
+    ((40, 264, 3, 1, 30, 62, 2), (2, 2, 3, 2)),
+    ((40, 72, 3, 1, 5, 90, 12), (2, 2, 3, 3)),        # no flush before the end
+    ((40, 392, 3, 1, 6, 150, 3), (1, 2, 3, 2)),
+    ((392, 392, 3, 2, 7, 7, 12), (2, 1, 3, 2)),       # stride 2
+    ((40, 392, 3, 2, 28, 28, 12), (2, 2, 5, 3)),
+    ((392, 392, 3, 2, 5, 90, 2), (1, 2, 3, 2)),
+    ((72, 392, 1, 2, 14, 14, 24), (2, 1, 2, 2)),      # 1x1: 64 x 64 tiles
+    ((72, 136, 1, 2, 6, 150, 12), (1, 2, 2, 2)),
 ]
 
 #   products, forward and input gradient: 32-row tiles of result channels, groups of 32 pixels, shares of the contraction
