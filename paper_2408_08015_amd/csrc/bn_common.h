@@ -10,10 +10,18 @@ namespace ast {
 // of the calling wavefront
 __device__ __forceinline__ void bn_add_partials(const double* __restrict__ ws, int c, int P, double& s1, double& s2) {
   const int lane = threadIdx.x & 63;
+  const double2* const w = reinterpret_cast<const double2*>(ws) + (size_t)c * P;
   double a = 0.0, b = 0.0;
-  for (int k = lane; k < P; k += 64) {
-    a += ws[((size_t)c * P + k) * 2 + 0];
-    b += ws[((size_t)c * P + k) * 2 + 1];
+  int k = lane;
+  for (; k + 192 < P; k += 256) {  // four loads in flight
+    const double2 v0 = w[k], v1 = w[k + 64], v2 = w[k + 128], v3 = w[k + 192];
+    a += (v0.x + v1.x) + (v2.x + v3.x);
+    b += (v0.y + v1.y) + (v2.y + v3.y);
+  }
+  for (; k < P; k += 64) {
+    const double2 v = w[k];
+    a += v.x;
+    b += v.y;
   }
   s1 = wave_sum_d(a);
   s2 = wave_sum_d(b);

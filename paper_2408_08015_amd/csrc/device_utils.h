@@ -18,6 +18,7 @@ constexpr int kWave = 64;
 // dpp_move<CTRL>(v) = v of the lane that control CTRL pairs this lane with, 0 where there is none.
 constexpr int DPP_QUAD_SWAP1 = 0xB1;    // quad_perm [1,0,3,2]: lane ^ 1
 constexpr int DPP_QUAD_SWAP2 = 0x4E;    // quad_perm [2,3,0,1]: lane ^ 2
+constexpr int DPP_QUAD_MIRROR = 0x1B;   // quad_perm [3,2,1,0]: lane ^ 3
 constexpr int DPP_HALF_MIRROR = 0x141;  // lane i of a group of 8 <- lane 7 - i (the other quad)
 constexpr int DPP_ROW_MIRROR = 0x140;   // lane i of a row of 16 <- lane 15 - i (the other half row)
 constexpr int DPP_WAVE_SHR1 = 0x138;    // lane i <- lane i - 1 over the whole wavefront

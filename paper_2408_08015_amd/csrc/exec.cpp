@@ -529,34 +529,35 @@ ast_status run_backward(Stage& s, int slot, const void* dy, void* dx, char* stat
 static ast_status build_pack_tasks(Stage& s, std::string& err) {
   std::vector<PackTask> tasks;
   std::vector<unsigned short> block_task;
-  auto add = [&](const float* W, int lda_m, int lda_k, size_t off, int Mdim, int Kdim) {
+  auto add = [&](const float* W, int lda_m, int lda_k, size_t off, int Mdim, int Kdim, bool split) {
     PackTask t = {};
-    t.W = W; t.lda_m = lda_m; t.lda_k = lda_k; t.Mdim = Mdim; t.Kdim = Kdim; t.KG = (Kdim + 7) / 8;
+    t.W = W; t.lda_m = lda_m; t.lda_k = lda_k; t.Mdim = Mdim; t.Kdim = Kdim; t.split = split;
+    t.KG = split ? (Kdim + 15) / 16 : (Kdim + 7) / 8;
     t.block0 = (unsigned)block_task.size();
     if (off != (size_t)t.block0 * 256) return false;  // the arena is laid out in op order: cannot happen
-    for (size_t b = 0; b < pw_pack_floats(Mdim, Kdim) / 256; ++b) block_task.push_back((unsigned short)tasks.size());
+    for (size_t b = 0; b < (split ? x3_pack_floats(Mdim, Kdim) : pw_pack_floats(Mdim, Kdim)) / 256; ++b) block_task.push_back((unsigned short)tasks.size());
     tasks.push_back(t);
     return true;
   };
   for (const Op& op : s.ops)
     if (op.kind == OP_CONV_PW) {
       if (tasks.size() + 2 >= 65535) return AST_OK;  // per-conv launches instead
-      if (!add(s.W + op.w_off, op.cin, 1, op.wp_off, op.cout, op.cin) ||
-          !add(s.W + op.w_off, 1, op.cin, op.wp2_off, op.cin, op.cout))
+      if (!add(s.W + op.w_off, op.cin, 1, op.wp_off, op.cout, op.cin, true) ||
+          !add(s.W + op.w_off, 1, op.cin, op.wp2_off, op.cin, op.cout, true))
         return AST_OK;
     } else if (op.kind == OP_CONV_GK) {
       if (tasks.size() + 1 >= 65535) return AST_OK;
       const int kd = op.cin * op.k * op.k;
-      if (!add(s.W + op.w_off, kd, 1, op.wp_off, op.cout, kd)) return AST_OK;
+      if (!add(s.W + op.w_off, kd, 1, op.wp_off, op.cout, kd, false)) return AST_OK;
     } else if (op.kind == OP_CONV_3X3) {
       // W[co][ci][tap]: forward copy t is A[co][ci] = W[..][t]; input-gradient copy t is A[ci][co] = W[..][t]
       const int kk = op.k * op.k;
       if (tasks.size() + 2 * kk >= 65535) return AST_OK;
       const float* W = s.W + op.w_off;
       for (int t = 0; t < kk; ++t)
-        if (!add(W + t, op.cin * kk, kk, op.wp_off + t * pw_pack_floats(op.cout, op.cin), op.cout, op.cin)) return AST_OK;
+        if (!add(W + t, op.cin * kk, kk, op.wp_off + t * pw_pack_floats(op.cout, op.cin), op.cout, op.cin, false)) return AST_OK;
       for (int t = 0; t < kk; ++t)
-        if (!add(W + t, kk, op.cin * kk, op.wp2_off + t * pw_pack_floats(op.cin, op.cout), op.cin, op.cout)) return AST_OK;
+        if (!add(W + t, kk, op.cin * kk, op.wp2_off + t * pw_pack_floats(op.cin, op.cout), op.cin, op.cout, false)) return AST_OK;
     }
   if (tasks.empty()) return AST_OK;
   hipError_t e;
@@ -838,21 +839,21 @@ ast_status refresh_shadow(Stage& s, std::string& err) {
   for (const Op& op : s.ops) {
     if (op.kind == OP_CONV_PW) {
       if (s.pack_nblocks) continue;
-      pw_pack_f32(s.stream, s.W + op.w_off, op.cin, 1, s.wpack + op.wp_off, op.cout, op.cin);
-      pw_pack_f32(s.stream, s.W + op.w_off, 1, op.cin, s.wpack + op.wp2_off, op.cin, op.cout);
+      pw_pack_f32(s.stream, s.W + op.w_off, op.cin, 1, s.wpack + op.wp_off, op.cout, op.cin, true);
+      pw_pack_f32(s.stream, s.W + op.w_off, 1, op.cin, s.wpack + op.wp2_off, op.cin, op.cout, true);
     } else if (op.kind == OP_CONV_GK) {
       if (s.pack_nblocks) continue;
       const int kd = op.cin * op.k * op.k;
-      pw_pack_f32(s.stream, s.W + op.w_off, kd, 1, s.wpack + op.wp_off, op.cout, kd);
+      pw_pack_f32(s.stream, s.W + op.w_off, kd, 1, s.wpack + op.wp_off, op.cout, kd, false);
     } else if (op.kind == OP_CONV_3X3) {
       if (s.pack_nblocks) continue;
       const float* W = s.W + op.w_off;
       const int kk = op.k * op.k;
       for (int t = 0; t < kk; ++t) {
         pw_pack_f32(s.stream, W + t, op.cin * kk, kk, s.wpack + op.wp_off + t * pw_pack_floats(op.cout, op.cin), op.cout,
-                    op.cin);
+                    op.cin, false);
         pw_pack_f32(s.stream, W + t, kk, op.cin * kk, s.wpack + op.wp2_off + t * pw_pack_floats(op.cin, op.cout), op.cin,
-                    op.cout);
+                    op.cout, false);
       }
     } else if (!s.bf16) {
       continue;  // the remaining copies are bf16 layouts

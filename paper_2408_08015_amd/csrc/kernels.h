@@ -11,23 +11,27 @@ namespace ast {
 typedef unsigned short bf16_t;
 
 // ------------------------------------------------------------------ fp32, NCHW
-// Pointwise (1x1) convolution as a per-pixel matrix product on the fp32 matrix cores:
+// Pointwise (1x1) convolution as a per-pixel matrix product:
 //   Y[n][m][p] = sum_k A[m][k] * X[n][k][p] (+ bias[m]) (+ add[n][m][p])
-// A is given as a packed copy Wp (pw_pack_floats(Mdim, Kdim) floats, written by
-// pw_pack_f32 from A[m][k] = W[m*lda_m + k*lda_k]), so the same kernel serves the forward
-// pass (A = W[Cout][Cin]) and the input gradient (A = W^T).
+// A is given as a packed copy Wp in the order of the matrix cores' operands: split into bf16 pieces
+// (x3_pack_floats(Mdim, Kdim) words), so the same kernel serves the forward pass (A = W[Cout][Cin]) and the input
+// gradient (A = W^T).  The other convolutions on the matrix cores read fp32 copies (pw_pack_floats words).
+size_t x3_pack_floats(int Mdim, int Kdim);
 size_t pw_pack_floats(int Mdim, int Kdim);
-void pw_pack_f32(hipStream_t st, const float* W, int lda_m, int lda_k, float* Wp, int Mdim, int Kdim);
+// one copy, of A[m][k] = W[m*lda_m + k*lda_k]
+void pw_pack_f32(hipStream_t st, const float* W, int lda_m, int lda_k, float* Wp, int Mdim, int Kdim, bool split);
 // All packed copies of a stage in one launch.  The copies lie back to back in `arena` in task
-// order (each pw_pack_floats() long = a whole number of 256-float blocks); block b of the
-// launch writes arena[256*b, +256) for task block_task[b], whose first block is block0.
+// order (each a whole number of 256-word blocks); block b of the launch writes arena[256*b, +256) for task
+// block_task[b], whose first block is block0.
 struct PackTask {
   const float* W;
-  int lda_m, lda_k, Mdim, Kdim, KG;
+  int lda_m, lda_k, Mdim, Kdim, KG;  // KG: groups of 16 (split) or 8 columns
   unsigned block0;
+  int split;
 };
 void pw_pack_all_f32(hipStream_t st, const PackTask* tasks_dev, const unsigned short* block_task_dev, float* arena,
                      int nblocks);
+bool pw_conv_supported(int Cin, int Cout, int HW);  // else (planes of hundreds of MiB) the generic kernels apply
 // stats (may be NULL; needs bias == add == NULL and pw_conv_stats_parts() > 0): the kernel also
 // leaves (sum, sum of squares) of Y per channel and pixel block, stats[Mdim][pw_conv_stats_parts()][2],
 // for a BatchNorm behind the convolution.

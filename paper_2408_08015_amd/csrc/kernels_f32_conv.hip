@@ -1,16 +1,8 @@
-// fp32 NCHW convolution kernels of the MobileNetV2-style stages.
+// fp32 NCHW depthwise 3x3 convolution.
 //
-// Pointwise (1x1) convolution = per-pixel matrix product on the fp32 matrix cores
-// (v_mfma_f32_32x32x2f32).  In NCHW a channel plane is contiguous, so pixels go on the MFMA
-// N dimension: lane l supplies B[k = l/32][pixel = l%32] with one coalesced global load,
-// the small weight matrix is A[m = l%32][k = l/32], read from a copy packed in exactly that
-// lane order, and accumulator register r of lane l is D[8*(r/4) + 4*(l/32) + r%4][l%32].
-// At these shapes the kernels are HBM / latency bound, so the launch shapes are chosen for
-// wavefront count first.
-//
-// Depthwise 3x3: a block stages whole (n, c) planes (they are contiguous) with a zero halo
-// in LDS; the backward kernel produces the input gradient and the nine weight-gradient
-// sums of each plane from one read of g and x.
+// The first kernels stage whole (n, c) planes (they are contiguous) with a zero halo in LDS; the
+// backward kernel produces the input gradient and the nine weight-gradient sums of each plane from
+// one read of g and x.  The ones behind them keep a window of rows in registers and take most shapes.
 #include <algorithm>
 #include "bn_common.h"
 #include "device_utils.h"
@@ -21,920 +13,6 @@ namespace ast {
 
 static inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 static inline int conv_out(int H, int k, int stride, int pad) { return (H + 2 * pad - k) / stride + 1; }
-
-// ============================================================== pointwise conv (fwd / dgrad)
-// Block = 4 wavefronts; wavefront w owns pixels [128*bx + 32*w, +32) of the flattened
-// (n, p) index and one 32-row tile of output channels.  MFMA 32x32x2: lane l supplies
-// A[m = l%32][k = l/32] and B[k = l/32][q = l%32]; accumulator register r of lane l is
-// D[8*(r/4) + 4*(l/32) + r%4][l%32].
-struct PwArgs {  // one pointwise-conv product Y = A X (+ bias) (+ add)
-  const float4* Wp;
-  const float* X;
-  float* Y;
-  const float* bias;
-  const float* add;
-  double* stats;  // or NULL: per block (sum, sum of squares) of the output per channel, stats[m][gridDim.x][2]
-  long NQ;
-  int HW, Kdim, Mdim, KG;
-  int tile_order;  // 1: the channel tiles of one pixel block run side by side on one XCD (they share X)
-};
-struct WgArgs {  // one pointwise-conv weight-gradient launch (partials only)
-  const float* g;
-  const float* x;
-  float* part;
-  long NQ;
-  int Cin, Cout, HW, splits;
-  int tile_order;  // 1: the (ci, co) tiles of one pixel range run side by side on one XCD
-};
-
-// Block coordinates of a product grid of gx pixel blocks x gy channel tiles from the flat block id:
-// pixel blocks fastest, or (tile_order) channel tiles fastest within XCD-grouped ids, so that the
-// gy blocks that read the same pixels of X hit one L2.
-__device__ __forceinline__ void pw_block_xy(unsigned id, unsigned gx, unsigned gy, int tile_order, int& bx, int& by) {
-  if (tile_order) {
-    id = xcd_grouped(id, gx * gy);
-    by = (int)(id % gy);
-    bx = (int)(id / gy);
-  } else {
-    bx = (int)(id % gx);
-    by = (int)(id / gx);
-  }
-}
-
-// The A operand comes from a packed copy of the weights (pw_pack_f32): for m-tile t and
-// k-group g (8 consecutive k), lane l = (m%32, h) finds the four values A[m][8g + 2e + h],
-// e = 0..3, as one 16-byte word at Wp[(t*KG + g)*64 + l]; out-of-range m and k are zero
-// there.  A wavefront therefore reads its operands with fully coalesced 16-byte loads
-// and needs neither LDS nor a barrier.  NCH = 1: up to 32 input channels, 2: more.
-// Statistics epilogue of the forward product (for a BatchNorm behind the convolution): lane l
-// holds, for each of its 16 accumulator rows, the sum s and sum of squares q of its pixels; the
-// block adds them per channel over its pixels (through LDS, two rounds of 16 KB) and writes one
-// (sum, sum of squares) pair per channel and block.  All 256 threads take part.
-__device__ __forceinline__ void pw_stats_epilogue(const float (&s)[16], const float (&q)[16], float (*sR)[16][64],
-                                                  double* __restrict__ stats, int m_base, int Mdim, int bx, int P) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ci = threadIdx.x >> 3, part = threadIdx.x & 7;  // channel of the 32-row tile, slice of its 128 values
-  const int r = 4 * (ci >> 3) + (ci & 3), half = (ci >> 2) & 1;
-  const int w = part >> 1, c0 = half * 32 + (part & 1) * 16;
-  const int rot = (ci & 3) * 4 + w;  // start of the 16-value walk: the 64 lanes of a wavefront hit 64 banks
-  float tot[2];
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    if (pass) __syncthreads();  // the first round has been read
-#pragma unroll
-    for (int k = 0; k < 16; ++k) sR[wave][k][lane] = pass ? q[k] : s[k];
-    __syncthreads();
-    float v = 0.f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v += sR[w][r][c0 + ((k + rot) & 15)];
-    v = group8_sum(v);
-    tot[pass] = v;
-  }
-  if (part == 0 && m_base + ci < Mdim) {
-    double* o = stats + ((size_t)(m_base + ci) * P + bx) * 2;
-    o[0] = (double)tot[0];
-    o[1] = (double)tot[1];
-  }
-}
-
-// acc += A X over the k-groups [gbeg, gend) of one 32 x 32 tile, in stages of four groups: while a stage is multiplied
-// the next one is in flight, and the one behind it is requested as soon as registers are free.  (With all loads of
-// eight groups in front of their products a wavefront alternated between waiting and multiplying, and the few
-// wavefronts of a SIMD did so in step.)  Branch-free: rows past Kdim read the last row (zero weights in the packed
-// copy), groups past the last read that one again and are not multiplied, pixels past NQ read pixel 0 and are replaced
-// by zero (the statistics epilogue sums every column).  wl: lane's weights of the tile; xq: lane's pixel.
-// Before and after, at 32 x 56x56 pixels with the 128-pixel wavefronts, forward: 64 -> 256 channels 58.9 -> 55.3 us,
-// 256 -> 64 42.8 -> 37.3.
-__device__ __forceinline__ void pw_contract(const float4* __restrict__ wl, const float* __restrict__ xq, int HW, int Kdim,
-                                            int gbeg, int gend, int half, bool qv, floatx16& acc) {
-  if (gbeg >= gend) return;  // uniform
-  float4 a0[4], a1[4];
-  float b0[16], b1[16];
-  auto load = [&](float4 (&a)[4], float (&b)[16], int g0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int gg = min(g0 + g, gend - 1);
-      a[g] = wl[(size_t)gg * 64];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) b[4 * g + e] = xq[(size_t)min(gg * 8 + 2 * e + half, Kdim - 1) * HW];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  auto mma = [&](const float4 (&a)[4], const float (&b)[16], int n) __attribute__((always_inline)) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (g >= n) break;  // uniform
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(e == 0 ? a[g].x : e == 1 ? a[g].y : e == 2 ? a[g].z : a[g].w,
-                                                   qv ? b[4 * g + e] : 0.f, acc, 0, 0, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  load(a0, b0, gbeg);
-  if (gend - gbeg <= 4) {
-    mma(a0, b0, gend - gbeg);
-    return;
-  }
-  load(a1, b1, gbeg + 4);
-  int g = gbeg;
-  for (; g + 8 < gend; g += 8) {
-    mma(a0, b0, 4);
-    load(a0, b0, g + 8);
-    mma(a1, b1, 4);
-    load(a1, b1, g + 12);
-  }
-  mma(a0, b0, 4 < gend - g ? 4 : gend - g);
-  mma(a1, b1, gend - g - 4);
-}
-
-template <int NCH>
-__device__ __forceinline__ void pw_pk_body(const PwArgs& a, int bx, int by, float (*sR)[16][64], int P) {
-  const float4* __restrict__ Wp = a.Wp;
-  const float* __restrict__ X = a.X;
-  float* __restrict__ Y = a.Y;
-  const float* __restrict__ bias = a.bias;
-  const float* __restrict__ add = a.add;
-  const long NQ = a.NQ;
-  const int HW = a.HW, Kdim = a.Kdim, Mdim = a.Mdim, KG = a.KG;
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = lane & 31, half = lane >> 5;
-  const int m_base = by * 32;
-  const unsigned q = (unsigned)bx * 128u + wave * 32 + col;  // pixels per micro-batch < 2^31 (checked at create)
-  const bool qv = q < NQ;
-  unsigned n = 0;
-  int p = 0;
-  if (qv) {
-    n = q / (unsigned)HW;  // 32-bit: a 64-bit division is ~150 instructions
-    p = (int)(q - n * (unsigned)HW);
-  }
-  const float* xq = X + (size_t)n * Kdim * HW + p;
-  const float4* wl = Wp + (size_t)by * KG * 64 + lane;
-  floatx16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  pw_contract(wl, xq, HW, Kdim, 0, NCH == 1 ? min(KG, 4) : KG, half, qv, acc);
-  if (qv) {
-    float* yq = Y + (size_t)n * Mdim * HW + p;
-    const float* aq = add ? add + (size_t)n * Mdim * HW + p : nullptr;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = m_base + 8 * (r >> 2) + 4 * half + (r & 3);
-      if (m < Mdim) {
-        float v = acc[r];
-        if (bias) v += bias[m];
-        if (aq) v += aq[(size_t)m * HW];
-        yq[(size_t)m * HW] = v;
-      }
-    }
-  }
-  if (a.stats) {  // uniform; only without bias / add (the accumulators are the outputs; invalid pixels hold zeros)
-    float s[16], q2[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      s[r] = acc[r];
-      q2[r] = acc[r] * acc[r];
-    }
-    pw_stats_epilogue(s, q2, sR, a.stats, m_base, Mdim, bx, P);
-  }
-}
-template <int NCH>
-__global__ __launch_bounds__(256, NCH == 1 ? 1 : 4) void pw_conv_f32_pk_kernel(PwArgs a) {
-  __shared__ float sR[4][16][64];
-  int bx, by;
-  pw_block_xy(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, a.tile_order, bx, by);
-  pw_pk_body<NCH>(a, bx, by, sR, gridDim.x);
-}
-
-// Few pixels, long K (the 14x14 / 7x7 layers of a whole network): the four wavefronts of a
-// block share one 32-pixel x 32-channel output tile and split K between them, so there are
-// four times as many wavefronts and a quarter of the dependent passes; the four partial
-// tiles are added through LDS in a fixed order.
-template <int WV>  // wavefronts per block = ways K is split (4, 8 or 16)
-__device__ __forceinline__ void pw_pkks_body(const PwArgs& a, int bx, int by, float (*sR)[16][64]) {
-  const float4* __restrict__ Wp = a.Wp;
-  const float* __restrict__ X = a.X;
-  float* __restrict__ Y = a.Y;
-  const float* __restrict__ bias = a.bias;
-  const float* __restrict__ add = a.add;
-  const long NQ = a.NQ;
-  const int HW = a.HW, Kdim = a.Kdim, Mdim = a.Mdim, KG = a.KG;
-
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform
-  const int col = lane & 31, half = lane >> 5;
-  const int m_base = by * 32;
-  const unsigned q = (unsigned)bx * 32u + col;  // pixels per micro-batch < 2^31 (checked at create)
-  const bool qv = q < NQ;
-  unsigned n = 0;
-  int p = 0;
-  if (qv) {
-    n = q / (unsigned)HW;  // 32-bit: a 64-bit division is ~150 instructions
-    p = (int)(q - n * (unsigned)HW);
-  }
-  const float* xq = X + (size_t)n * Kdim * HW + p;
-  const float4* wl = Wp + (size_t)by * KG * 64 + lane;
-  const int gper = (KG + WV - 1) / WV;  // k-groups per wavefront
-  const int gbeg = wave * gper, gend = min(gbeg + gper, KG);
-  floatx16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  // Up to 64 channels of a wavefront in one pass: with all loads requested first there is no second wait, and the short
-  // code matters to a kernel of 7 us (whole MobileNetV2 at 8 samples 14.13 -> 13.99 ms per round).  More are pipelined
-  // (whole ResNet50 45.53 -> 45.42 ms).
-  if (gend - gbeg > 8) {  // uniform
-    pw_contract(wl, xq, HW, Kdim, gbeg, gend, half, qv, acc);
-  } else {
-    float4 a[8];
-    float b[32];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      a[g] = gbeg + g < gend ? wl[(size_t)(gbeg + g) * 64] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) b[4 * g + e] = xq[(size_t)min((gbeg + g) * 8 + 2 * e + half, Kdim - 1) * HW];
-    }
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      if (gbeg + g >= gend) break;  // uniform
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(e == 0 ? a[g].x : e == 1 ? a[g].y : e == 2 ? a[g].z : a[g].w,
-                                                   qv ? b[4 * g + e] : 0.f, acc, 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) sR[wave][r][lane] = acc[r];
-  __syncthreads();
-  if (!qv) return;
-  float* yq = Y + (size_t)n * Mdim * HW + p;
-  const float* aq = add ? add + (size_t)n * Mdim * HW + p : nullptr;
-  constexpr int RW = 16 / WV;  // rows of the register layout each wavefront finishes
-#pragma unroll
-  for (int rr = 0; rr < RW; ++rr) {
-    const int r = RW * wave + rr;
-    const int m = m_base + 8 * (r >> 2) + 4 * half + (r & 3);
-    if (m < Mdim) {
-      float v = 0.f;
-#pragma unroll
-      for (int k = 0; k < WV; k += 4)  // fixed order
-        v += (sR[k][r][lane] + sR[k + 1][r][lane]) + (sR[k + 2][r][lane] + sR[k + 3][r][lane]);
-      if (bias) v += bias[m];
-      if (aq) v += aq[(size_t)m * HW];
-      yq[(size_t)m * HW] = v;
-    }
-  }
-}
-template <int WV>
-__global__ __launch_bounds__(64 * WV) void pw_conv_f32_pkks_kernel(PwArgs a) {
-  __shared__ float sR[WV][16][64];
-  pw_pkks_body<WV>(a, blockIdx.x, blockIdx.y, sR);
-}
-
-// Large images: a wavefront owns 128 pixels; every lane loads four consecutive pixels
-// (16 bytes) per input channel and feeds four MFMA column tiles (column j of tile t is
-// pixel 4j + t), so each output row is stored as 16 bytes per lane.  Four times the bytes
-// per memory instruction and a quarter of the weight traffic of the kernel above; needs
-// HW % 4 == 0.
-__device__ __forceinline__ void pw_pk4_body(const PwArgs& a, int bx, int by, float (*sR)[16][64], int P) {
-  const float4* __restrict__ Wp = a.Wp;
-  const float* __restrict__ X = a.X;
-  float* __restrict__ Y = a.Y;
-  const float* __restrict__ bias = a.bias;
-  const float* __restrict__ add = a.add;
-  const long NQ = a.NQ;
-  const int HW = a.HW, Kdim = a.Kdim, Mdim = a.Mdim, KG = a.KG;
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = lane & 31, half = lane >> 5;
-  const int m_base = by * 32;
-  const unsigned q = (unsigned)bx * 512u + wave * 128 + col * 4;  // pixels per micro-batch < 2^31 (checked at create)
-  const bool qv = q < NQ;  // NQ % 4 == 0: the four pixels are valid together
-  unsigned n = 0;
-  int p = 0;
-  if (qv) {
-    n = q / (unsigned)HW;  // 32-bit: a 64-bit division is ~150 instructions
-    p = (int)(q - n * (unsigned)HW);
-  }
-  const float* xq = X + (size_t)n * Kdim * HW + p;
-  const float4* wl = Wp + (size_t)by * KG * 64 + lane;
-  floatx16 acc[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-  // Stages of two groups, pipelined as in pw_contract.
-  float4 a0[2], a1[2], b0[8], b1[8];
-  auto load = [&](float4 (&a)[2], float4 (&b)[8], int g0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const int gg = min(g0 + g, KG - 1);
-      a[g] = wl[(size_t)gg * 64];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        b[4 * g + e] = *reinterpret_cast<const float4*>(xq + (size_t)min(gg * 8 + 2 * e + half, Kdim - 1) * HW);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  auto mma = [&](const float4 (&a)[2], const float4 (&b)[8], int n) __attribute__((always_inline)) {
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      if (g >= n) break;  // uniform
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float av = e == 0 ? a[g].x : e == 1 ? a[g].y : e == 2 ? a[g].z : a[g].w;
-        const float4 v = qv ? b[4 * g + e] : make_float4(0.f, 0.f, 0.f, 0.f);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.y, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.z, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, v.w, acc[3], 0, 0, 0);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  load(a0, b0, 0);
-  if (KG > 2) load(a1, b1, 2);
-  int g = 0;
-  for (; g + 4 < KG; g += 4) {
-    mma(a0, b0, 2);
-    load(a0, b0, g + 4);
-    mma(a1, b1, 2);
-    load(a1, b1, g + 6);
-  }
-  mma(a0, b0, KG - g);
-  if (KG > 2) mma(a1, b1, KG - g - 2);
-  if (qv) {
-    float* yq = Y + (size_t)n * Mdim * HW + p;
-    const float* aq = add ? add + (size_t)n * Mdim * HW + p : nullptr;
-    // bias and addend of eight rows at a time are requested before the first is used (rows past Mdim
-    // read the last row)
-#pragma unroll
-    for (int r0 = 0; r0 < 16; r0 += 8) {
-      float bv[8];
-      float4 kv[8];
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int r = r0 + rr;
-        const int mc = min(m_base + 8 * (r >> 2) + 4 * half + (r & 3), Mdim - 1);
-        bv[rr] = 0.f;
-        kv[rr] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (bias) bv[rr] = bias[mc];
-        if (aq) kv[rr] = *reinterpret_cast<const float4*>(aq + (size_t)mc * HW);
-      }
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int r = r0 + rr;
-        const int m = m_base + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (m < Mdim)
-          *reinterpret_cast<float4*>(yq + (size_t)m * HW) =
-              make_float4(acc[0][r] + bv[rr] + kv[rr].x, acc[1][r] + bv[rr] + kv[rr].y, acc[2][r] + bv[rr] + kv[rr].z,
-                          acc[3][r] + bv[rr] + kv[rr].w);
-      }
-    }
-  }
-  if (a.stats) {  // uniform; only without bias / add (invalid pixels hold zeros)
-    float s[16], q2[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      s[r] = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
-      q2[r] = (acc[0][r] * acc[0][r] + acc[1][r] * acc[1][r]) + (acc[2][r] * acc[2][r] + acc[3][r] * acc[3][r]);
-    }
-    pw_stats_epilogue(s, q2, sR, a.stats, m_base, Mdim, bx, P);
-  }
-}
-__global__ __launch_bounds__(256) void pw_conv_f32_pk4_kernel(PwArgs a) {
-  __shared__ float sR[4][16][64];
-  int bx, by;
-  pw_block_xy(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, a.tile_order, bx, by);
-  pw_pk4_body(a, bx, by, sR, gridDim.x);
-}
-
-// Packed operand copy: Wp[((t*KG + g)*64 + l)*4 + e] = A[32t + l%32][8g + 2e + l/32], zero
-// outside Mdim x Kdim, with A[m][k] = W[m*lda_m + k*lda_k].
-__global__ void pw_pack_kernel(const float* __restrict__ W, int lda_m, int lda_k, float* __restrict__ Wp,
-                               int Mdim, int Kdim, int KG, size_t total) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int e = (int)(i & 3), l = (int)((i >> 2) & 63);
-  const size_t tg = i >> 8;
-  const int g = (int)(tg % KG), t = (int)(tg / KG);
-  const int m = 32 * t + (l & 31), k = 8 * g + 2 * e + (l >> 5);
-  Wp[i] = (m < Mdim && k < Kdim) ? W[(size_t)m * lda_m + (size_t)k * lda_k] : 0.f;
-}
-
-size_t pw_pack_floats(int Mdim, int Kdim) { return (size_t)cdiv(Mdim, 32) * cdiv(Kdim, 8) * 256; }
-
-// Every packed copy of a stage in one launch: the copies sit back to back in one arena, each a
-// multiple of 256 floats, so block b (256 floats of the arena) belongs to one task.
-__global__ __launch_bounds__(256) void pw_pack_all_kernel(const PackTask* __restrict__ tasks,
-                                                          const unsigned short* __restrict__ block_task,
-                                                          float* __restrict__ arena) {
-  const PackTask t = tasks[block_task[blockIdx.x]];
-  const size_t i = (size_t)(blockIdx.x - t.block0) * 256 + threadIdx.x;  // index inside the copy
-  const int e = (int)(i & 3), l = (int)((i >> 2) & 63);
-  const size_t tg = i >> 8;
-  const int g = (int)(tg % t.KG), tt = (int)(tg / t.KG);
-  const int m = 32 * tt + (l & 31), k = 8 * g + 2 * e + (l >> 5);
-  arena[(size_t)blockIdx.x * 256 + threadIdx.x] =
-      (m < t.Mdim && k < t.Kdim) ? t.W[(size_t)m * t.lda_m + (size_t)k * t.lda_k] : 0.f;
-}
-void pw_pack_all_f32(hipStream_t st, const PackTask* tasks_dev, const unsigned short* block_task_dev, float* arena,
-                     int nblocks) {
-  KLAUNCH(pw_pack_all_kernel, dim3(nblocks), dim3(256), 0, st, tasks_dev, block_task_dev, arena);
-}
-
-void pw_pack_f32(hipStream_t st, const float* W, int lda_m, int lda_k, float* Wp, int Mdim, int Kdim) {
-  const size_t total = pw_pack_floats(Mdim, Kdim);
-  KLAUNCH(pw_pack_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, st, W, lda_m, lda_k, Wp, Mdim, Kdim,
-          cdiv(Kdim, 8), total);
-}
-
-// which product kernel serves a shape, and its grid
-struct PwPick { int var; dim3 grid; int wv; };  // wv: wavefronts per block of the K-split kernel
-static PwPick pw_pick(long NQ, int HW, int Kdim, int Mdim) {
-  const int mt = cdiv(Mdim, 32), KG = cdiv(Kdim, 8);
-  PwPick p;
-  // Measured on 32-sample micro-batches: 128-pixel wavefronts win from 56x56 images up,
-  // 32-pixel ones below (more wavefronts in flight matter more than bytes per instruction);
-  // under one block per CU and K >= 128 the block splits K instead.
-  p.wv = 4;
-  if ((long)cdiv(NQ, 128) * mt < 256 && KG >= 16) {
-    p.var = 2;
-    p.grid = dim3((unsigned)cdiv(NQ, 32), mt);
-    // one pass of 64 channels per wavefront where K allows: a longer K is a chain of dependent
-    // load-then-multiply passes, the whole cost of these small products
-    p.wv = KG <= 32 ? 4 : (KG <= 64 ? 8 : 16);
-  }
-  else if (HW % 4 == 0 && NQ >= 65536) { p.var = 3; p.grid = dim3((unsigned)cdiv(NQ, 512), mt); }
-  else if (Kdim > 32) { p.var = 1; p.grid = dim3((unsigned)cdiv(NQ, 128), mt); }
-  else { p.var = 0; p.grid = dim3((unsigned)cdiv(NQ, 128), mt); }
-  return p;
-}
-static int pw_tile_order() {
-  static const int v = [] { const char* e = getenv("ASTEROID_PW_TILE_ORDER"); return e ? atoi(e) : 3; }();
-  return v;
-}
-static PwArgs pw_args(const float* Wp, const float* X, float* Y, const float* bias, const float* add, int N, int Kdim,
-                      int Mdim, int HW) {
-  PwArgs a;
-  a.Wp = reinterpret_cast<const float4*>(Wp);
-  a.X = X; a.Y = Y; a.bias = bias; a.add = add;
-  a.stats = nullptr;
-  a.NQ = (long)N * HW;
-  a.HW = HW; a.Kdim = Kdim; a.Mdim = Mdim; a.KG = cdiv(Kdim, 8);
-  a.tile_order = (pw_tile_order() & 1) && Mdim > 32;
-  return a;
-}
-
-static void launch_pkks(hipStream_t st, const PwArgs& a, const PwPick& p) {
-  if (p.wv == 16) KLAUNCH_NAMED("pw_conv_f32_pkks_kernel<16>", (pw_conv_f32_pkks_kernel<16>), p.grid, dim3(1024), 0, st, a);
-  else if (p.wv == 8) KLAUNCH_NAMED("pw_conv_f32_pkks_kernel<8>", (pw_conv_f32_pkks_kernel<8>), p.grid, dim3(512), 0, st, a);
-  else KLAUNCH_NAMED("pw_conv_f32_pkks_kernel", (pw_conv_f32_pkks_kernel<4>), p.grid, dim3(256), 0, st, a);
-}
-
-// Partial pairs per channel that the forward product can leave for a BatchNorm behind it: the
-// number of pixel blocks of the 32- and 128-pixel-wavefront kernels while that is at most 256
-// (more would cost the consumer more than a statistics pass of its own); 0 = not offered.
-int pw_conv_stats_parts(int N, int Kdim, int Mdim, int HW) {
-  const PwPick p = pw_pick((long)N * HW, HW, Kdim, Mdim);
-  if (p.var == 2 || p.grid.x > 256) return 0;
-  return (int)p.grid.x;
-}
-
-void pw_conv_f32(hipStream_t st, const float* Wp, const float* X, float* Y, const float* bias, const float* add,
-                 int N, int Kdim, int Mdim, int HW, double* stats) {
-  PwArgs a = pw_args(Wp, X, Y, bias, add, N, Kdim, Mdim, HW);
-  const PwPick p = pw_pick(a.NQ, HW, Kdim, Mdim);
-  if (stats && !bias && !add && p.var != 2) a.stats = stats;
-  switch (p.var) {
-    case 2: launch_pkks(st, a, p); break;
-    case 3: KLAUNCH(pw_conv_f32_pk4_kernel, p.grid, dim3(256), 0, st, a); break;
-    case 1: KLAUNCH(pw_conv_f32_pk_kernel<2>, p.grid, dim3(256), 0, st, a); break;
-    default: KLAUNCH(pw_conv_f32_pk_kernel<1>, p.grid, dim3(256), 0, st, a); break;
-  }
-}
-
-// ============================================================== pointwise conv wgrad
-// dW[co][ci] = sum over the pixels q of all samples of g[co][q] x[ci][q].  A block owns TCO x TCI tiles of
-// 32 x 32 weights (KS wavefronts per tile share its pixels) and the pixels of one of `splits` equal ranges of the
-// flattened (sample, pixel) index, in steps of PX.  Each step copies PX pixels of the block's rows of g and x to LDS
-// once, in whole 128 / 256-byte runs and one step ahead through registers, and the wavefronts read their operands
-// there: lane (m = l%32, h = l/32) takes the four pixels of 16-byte chunk 2k + h of row m from either matrix and
-// feeds four MFMAs.  Chunk j of a row sits at position j ^ f(row), so the sixteen lanes of one LDS access hit
-// all 64 banks.  The partials of the splits are added to G in a fixed order by a later launch.
-//
-// The kernel before this one loaded the operands of a 32 x 32 tile from global memory, sixteen bytes per lane from 32
-// different rows: every instruction touched 64 cache lines, and a chunk of pixels ended with its sample (49 pixels of
-// a 7x7 plane occupied two of four wavefronts).
-template <int TCO, int TCI, int KS>
-struct WgTile {
-  static constexpr int PX = KS == 4 ? 64 : 32, CH = PX / 4, ROWS = (TCO + TCI) * 32;
-  static constexpr int LDS = 2 * ROWS * PX;  // floats, two steps
-  static __device__ __forceinline__ int swz(int row) { return PX == 64 ? (row & 15) : ((row >> 1) & 7); }
-};
-
-template <int TCO, int TCI, int KS, bool VEC>
-__device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bci, int bco, float* __restrict__ lds) {
-  using T = WgTile<TCO, TCI, KS>;
-  constexpr int PX = T::PX, CH = T::CH, ROWS = T::ROWS;
-  static_assert(TCO * TCI * KS == 4, "four wavefronts");
-  const int Cin = w.Cin, Cout = w.Cout, HW = w.HW;
-  const unsigned Q = (unsigned)w.NQ;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int row = lane & 31, half = lane >> 5;
-  const int co_base = bco * (TCO * 32), ci_base = bci * (TCI * 32);
-  const int steps = (int)((Q + PX - 1) / PX);
-  const int s0 = (int)((long)steps * split / w.splits), s1 = (int)((long)steps * (split + 1) / w.splits);
-
-  // Staging: LPR threads per row and pass, RP rows per pass.  16-byte words (VEC: HW % 4 == 0, so a word never
-  // leaves its sample) or single pixels.  Rows past Cout / Cin read the last row: their products are never stored.
-  constexpr int LPR = VEC ? CH : PX, RP = 256 / LPR, NL = ROWS / RP;
-  const int lp = t % LPR, lr = t / LPR;
-  const int px = VEC ? 4 * (lp ^ T::swz(lr)) : lp;  // VEC: RP keeps swz(row) the same for all rows of a thread
-  float4 rv[VEC ? NL : 1];
-  float rs[VEC ? 1 : NL];
-  auto load = [&](int s) {
-    unsigned q = (unsigned)s * PX + px;
-    const bool ok = q < Q;
-    if (!ok) q = 0;
-    const unsigned n = q / (unsigned)HW;
-    const unsigned p = q - n * (unsigned)HW;
-    const float* gp = w.g + (size_t)n * Cout * HW + p;
-    const float* xp = w.x + (size_t)n * Cin * HW + p;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const bool isg = RP * i < TCO * 32;  // RP divides 32
-      const int r = lr + RP * i;
-      const float* src = isg ? gp + (size_t)min(co_base + r, Cout - 1) * HW
-                             : xp + (size_t)min(ci_base + r - TCO * 32, Cin - 1) * HW;
-      if constexpr (VEC) {
-        const float4 v = *reinterpret_cast<const float4*>(src);
-        rv[i] = ok ? v : make_float4(0.f, 0.f, 0.f, 0.f);
-      } else {
-        const float v = *src;
-        rs[i] = ok ? v : 0.f;
-      }
-    }
-  };
-  auto store = [&](int buf) {
-    float* o = lds + buf * (ROWS * PX);
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int r = lr + RP * i;
-      if constexpr (VEC) *reinterpret_cast<float4*>(o + r * PX + 4 * lp) = rv[i];
-      else o[r * PX + 4 * ((lp >> 2) ^ T::swz(r)) + (lp & 3)] = rs[i];
-    }
-  };
-
-  const int wk = wave % KS, wt = wave / KS, wci = wt % TCI, wco = wt / TCI;
-  const int ra = wco * 32 + row, rb = TCO * 32 + wci * 32 + row;
-  const int swa = T::swz(ra), swb = T::swz(rb);
-  // A sum's rounding error grows with the root of its chain of 32-bit additions, so no chain may grow with the micro-batch:
-  // 32 pixels (16 in the first step where wavefronts share a tile) of `acc` go to `run`, and 16 such sums of a wavefront that
-  // has a tile to itself, whose range may be all pixels, to `sum`.  The other shapes' ranges are at most WG_CHAIN steps.
-  // (Registers and f64 instructions allow no more: 64-bit sums of every 32 pixels cost 24 -> 144 channels at 128 x 56x56 8 %,
-  // this 2 %.)  Relative error of dW against 64 bits, chains of at most 256 pixels with partials added in 32 bits / one chain
-  // per accumulator and range / now: 512 -> 2048 at 128 x 7x7 1.7e-7, 4.1e-7, 1.3e-7; 2048 -> 2048 at 64 x 14x14 2.7e-7,
-  // 1.0e-6, 1.3e-7; 16 -> 96 at 128 x 112x112 3.2e-7, 4.8e-7, 1.5e-7.
-  floatx16 acc;
-  float run[16];
-  double sum[KS == 1 ? 16 : 1];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = run[r] = 0.f;
-  if constexpr (KS == 1) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sum[r] = 0.0;
-  }
-  auto fold = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      run[r] += acc[r];
-      acc[r] = 0.f;
-    }
-  };
-  if (s0 < s1) {  // uniform
-    load(s0);
-    store(0);
-  }
-  __syncthreads();
-  for (int s = s0; s < s1; ++s) {
-    const int buf = (s - s0) & 1;
-    if (s + 1 < s1) load(s + 1);
-    if (KS > 1 && buf == 1) fold();  // here the products of the step before are done: nothing waits for them
-    const float* o = lds + buf * (ROWS * PX);
-#pragma unroll
-    for (int k = 0; k < CH / 2 / KS; ++k) {
-      const int j = 2 * (wk * (CH / 2 / KS) + k) + half;
-      const float4 a = *reinterpret_cast<const float4*>(o + ra * PX + 4 * (j ^ swa));
-      const float4 b = *reinterpret_cast<const float4*>(o + rb * PX + 4 * (j ^ swb));
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
-    }
-    if (s + 1 < s1) store(buf ^ 1);
-    if constexpr (KS == 1) {
-      fold();
-      if (((s - s0) & 15) == 15) {  // uniform
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sum[r] += run[r];
-          run[r] = 0.f;
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if constexpr (KS > 1) fold();
-  float* out = w.part + (size_t)split * Cout * Cin;
-  const int ci = ci_base + wci * 32 + row;
-  if constexpr (KS == 1) {
-    if (ci < Cin) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int co = co_base + wco * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (co < Cout) out[(size_t)co * Cin + ci] = (float)(sum[r] + run[r]);
-      }
-    }
-  } else {  // the KS wavefronts of a tile add their sums in a fixed order; the staging buffers are free by now
-#pragma unroll
-    for (int r = 0; r < 16; ++r) lds[(wave * 16 + r) * 64 + lane] = run[r];
-    __syncthreads();
-    if (ci < Cin) {
-#pragma unroll
-      for (int rr = 0; rr < 16 / KS; ++rr) {
-        const int r = wk * (16 / KS) + rr;
-        const int co = co_base + wco * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        const float* v = lds + (wt * KS * 16 + r) * 64 + lane;
-        double d = (double)v[0] + v[16 * 64];
-        if constexpr (KS == 4) d += (double)v[2 * 16 * 64] + v[3 * 16 * 64];
-        if (co < Cout) out[(size_t)co * Cin + ci] = (float)d;
-      }
-    }
-  }
-}
-
-// The block shapes of the weight gradient: weight tiles (co x ci) per block, wavefronts per tile
-enum { WG_2x2 = 0, WG_2x1 = 1, WG_1x2 = 2, WG_1x1 = 3 };
-template <int SHAPE, bool VEC>
-__device__ __forceinline__ void pw_wgrad_shape(const WgArgs& w, int split, int bci, int bco, float* lds) {
-  if constexpr (SHAPE == WG_2x2) pw_wgrad_body<2, 2, 1, VEC>(w, split, bci, bco, lds);
-  else if constexpr (SHAPE == WG_2x1) pw_wgrad_body<2, 1, 2, VEC>(w, split, bci, bco, lds);
-  else if constexpr (SHAPE == WG_1x2) pw_wgrad_body<1, 2, 2, VEC>(w, split, bci, bco, lds);
-  else pw_wgrad_body<1, 1, 4, VEC>(w, split, bci, bco, lds);
-}
-template <int SHAPE>
-constexpr int wg_lds_floats() {
-  return SHAPE == WG_2x2 ? WgTile<2, 2, 1>::LDS : SHAPE == WG_1x1 ? WgTile<1, 1, 4>::LDS : WgTile<2, 1, 2>::LDS;
-}
-
-// (four wavefronts per SIMD; with single-pixel staging the registers of the 2x2 and 1x1 shapes suffice for three)
-template <int SHAPE, bool VEC>
-__global__ __launch_bounds__(256, !VEC && (SHAPE == WG_2x2 || SHAPE == WG_1x1) ? 3 : 4) void pw_wgrad_f32_kernel(WgArgs w) {
-  __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
-  int bx, t;
-  pw_block_xy((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x, gridDim.y * gridDim.z,
-              w.tile_order, bx, t);
-  pw_wgrad_shape<SHAPE, VEC>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, reinterpret_cast<float*>(lds));
-}
-
-// Input gradient and weight-gradient partials of one pointwise conv in ONE launch: the two
-// products only share their input g, and each alone is too short to fill the chip (they
-// are bound by the latency of one load-compute-store chain), so their blocks are dealt from
-// one grid: block ids [0, nA) form the (x, y) grid of the input-gradient product, the rest
-// the (x, y, z) grid of the weight-gradient kernel.  VAR selects the product kernel:
-// 0 / 1 = 32-pixel wavefronts with up to 32 / more input channels, 2 = K split over the
-// block, 3 = 128-pixel wavefronts.
-template <int VAR, int SHAPE, bool VEC>
-__global__ __launch_bounds__(256, VAR >= 2 ? 1 : !VEC && (SHAPE == WG_2x2 || SHAPE == WG_1x1) ? 3 : 4)
-void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gAx, unsigned gWx, unsigned gWy) {
-  __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
-  static_assert(wg_lds_floats<SHAPE>() >= 4 * 16 * 64, "the product kernels use 16 KB");
-  if (blockIdx.x < nA) {  // uniform per block
-    float(*sR)[16][64] = reinterpret_cast<float(*)[16][64]>(lds);
-    int bx, by;
-    pw_block_xy(blockIdx.x, gAx, nA / gAx, a.tile_order, bx, by);
-    if (VAR == 0) pw_pk_body<1>(a, bx, by, sR, 0);
-    else if (VAR == 1) pw_pk_body<2>(a, bx, by, sR, 0);
-    else if (VAR == 2) pw_pkks_body<4>(a, bx, by, sR);
-    else pw_pk4_body(a, bx, by, sR, 0);
-  } else {
-    int bx, t;  // the weight-gradient ids start at nA: ids that agree mod 8 still share an XCD
-    pw_block_xy(blockIdx.x - nA, gWx, (gridDim.x - nA) / gWx, w.tile_order, bx, t);
-    pw_wgrad_shape<SHAPE, VEC>(w, bx, t % (int)gWy, t / (int)gWy, reinterpret_cast<float*>(lds));
-  }
-}
-
-// G[i] += sum_c part[c][i]: 64 outputs per block, four interleaved part lanes, fixed order
-__global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __restrict__ part,
-                                                               float* __restrict__ G, size_t n, int parts) {
-  __shared__ float sh[4][64];
-  const int o = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const size_t i = (size_t)blockIdx.x * 64 + o;
-  float s = 0.f;
-  if (i < n) {
-    int c = q;
-    for (; c + 28 < parts; c += 32) {  // eight independent loads in flight
-      float v0 = part[(size_t)c * n + i], v1 = part[(size_t)(c + 4) * n + i];
-      float v2 = part[(size_t)(c + 8) * n + i], v3 = part[(size_t)(c + 12) * n + i];
-      float v4 = part[(size_t)(c + 16) * n + i], v5 = part[(size_t)(c + 20) * n + i];
-      float v6 = part[(size_t)(c + 24) * n + i], v7 = part[(size_t)(c + 28) * n + i];
-      s += ((v0 + v1) + (v2 + v3)) + ((v4 + v5) + (v6 + v7));
-    }
-    for (; c < parts; c += 4) s += part[(size_t)c * n + i];
-  }
-  sh[q][o] = s;
-  __syncthreads();
-  if (q == 0 && i < n) G[i] += (sh[0][o] + sh[1][o]) + (sh[2][o] + sh[3][o]);
-}
-
-// Block shape and number of pixel ranges of a weight gradient.  The shape with the fewest padded 32 x 32 tiles
-// (a tie goes to the larger block, which moves fewer bytes per product), about WG_BLOCKS blocks, each with
-// at least 128 pixels.  Where that leaves compute units idle (fewer than two blocks each: the 14x14 and 7x7 planes of
-// a few samples) the time of a launch is its longest chain of steps, so the smallest shape runs, one step of 64 pixels
-// upwards: 96 -> 576 channels at 8 x 14x14 12.3 us with 36 blocks of 2x2 tiles, 7.2 us with 810 of 1x1.
-// A range of a shape without 64-bit sums (all but 2x2) is at most WG_CHAIN steps: 32 folds of `acc`, error 1.5e-7.
-static constexpr int WG_BLOCKS = 768, WG_CHAIN = 64;
-struct WgPick { int shape; dim3 grid; };
-static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
-  const int a = cdiv(Cout, 32), b = cdiv(Cin, 32);
-  static const int tco[4] = {2, 2, 1, 1}, tci[4] = {2, 1, 2, 1};
-  const long NQ = (long)N * HW;
-  WgPick p;
-  auto splits = [&](int shape, int px) {
-    p.shape = shape;
-    const int gy = cdiv(b, tci[shape]), gz = cdiv(a, tco[shape]);
-    const long fill = std::min((long)cdiv(WG_BLOCKS, (long)gy * gz), NQ / px);
-    const long chain = shape == WG_2x2 ? 1 : cdiv(NQ, WG_CHAIN * (shape == WG_1x1 ? 64 : 32));
-    const long s = std::min(std::max(fill, chain), (long)cap);
-    p.grid = dim3((unsigned)s, gy, gz);
-    return s * gy * gz;
-  };
-  int shape = 0;
-  long best = -1;
-  for (int i = 0; i < 4; ++i) {
-    const long padded = (long)cdiv(a, tco[i]) * tco[i] * cdiv(b, tci[i]) * tci[i];
-    if (best < 0 || padded < best) { best = padded; shape = i; }
-  }
-  if (splits(shape, 128) < 512) splits(WG_1x1, 64);
-  return p;
-}
-int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW, int cap) { return (int)wg_pick(N, Cin, Cout, HW, cap).grid.x; }
-// four wavefronts of 256, 128, 64 or 32 pixels of one sample per chunk, the most that leave 768 tiles and chunks
-int pw_wgrad_f32_small_parts(int N, int Cin, int Cout, int HW) {
-  const long tiles = (long)cdiv(Cin, 32) * cdiv(Cout, 32);
-  int px = 256;
-  while (px > 32 && (long)N * cdiv(HW, 4 * px) * tiles < 768) px /= 2;
-  return N * cdiv(HW, 4 * px);
-}
-size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW, int cap) {
-  return (size_t)pw_wgrad_f32_parts(N, Cin, Cout, HW, cap) * Cin * Cout;
-}
-static WgArgs wg_args(const float* g, const float* x, float* part, int N, int Cin, int Cout, int HW, const WgPick& p) {
-  WgArgs w;
-  w.g = g; w.x = x; w.part = part;
-  w.Cin = Cin; w.Cout = Cout; w.HW = HW;
-  w.NQ = (long)N * HW;
-  w.splits = (int)p.grid.x;
-  w.tile_order = (pw_tile_order() & 2) && p.grid.y * p.grid.z > 1;
-  return w;
-}
-template <int SHAPE>
-static void launch_wgrad(hipStream_t st, const WgArgs& w, dim3 grid, bool vec) {
-  if (vec) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true>), grid, dim3(256), 0, st, w);
-  else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false>), grid, dim3(256), 0, st, w);
-}
-static void launch_wgrad(hipStream_t st, const WgArgs& w, const WgPick& p) {
-  const bool vec = w.HW % 4 == 0;
-  switch (p.shape) {
-    case WG_2x2: launch_wgrad<WG_2x2>(st, w, p.grid, vec); break;
-    case WG_2x1: launch_wgrad<WG_2x1>(st, w, p.grid, vec); break;
-    case WG_1x2: launch_wgrad<WG_1x2>(st, w, p.grid, vec); break;
-    default: launch_wgrad<WG_1x1>(st, w, p.grid, vec); break;
-  }
-}
-void pw_wgrad_f32(hipStream_t st, const float* g, const float* x, float* part, float* G, int N,
-                  int Cin, int Cout, int HW, int cap) {
-  const WgPick p = wg_pick(N, Cin, Cout, HW, cap);
-  launch_wgrad(st, wg_args(g, x, part, N, Cin, Cout, HW, p), p);
-  size_t n = (size_t)Cin * Cout;
-  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)p.grid.x);
-}
-
-template <int VAR, int SHAPE>
-static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, dim3 gA, dim3 gW) {
-  const unsigned nA = gA.x * gA.y, nW = gW.x * gW.y * gW.z;
-  constexpr const char* name = VAR == 0 ? "pw_bwd_dual_kernel<pk1>" : VAR == 1 ? "pw_bwd_dual_kernel<pk2>"
-                             : VAR == 2 ? "pw_bwd_dual_kernel<pkks>" : "pw_bwd_dual_kernel<pk4>";
-  if (w.HW % 4 == 0)
-    KLAUNCH_NAMED(name, (pw_bwd_dual_kernel<VAR, SHAPE, true>), dim3(nA + nW), dim3(256), 0, st, a, w, nA, gA.x, gW.x, gW.y);
-  else
-    KLAUNCH_NAMED(name, (pw_bwd_dual_kernel<VAR, SHAPE, false>), dim3(nA + nW), dim3(256), 0, st, a, w, nA, gA.x, gW.x, gW.y);
-}
-template <int VAR>
-static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, dim3 gA, const WgPick& p) {
-  switch (p.shape) {
-    case WG_2x2: launch_dual<VAR, WG_2x2>(st, a, w, gA, p.grid); break;
-    case WG_2x1: launch_dual<VAR, WG_2x1>(st, a, w, gA, p.grid); break;
-    case WG_1x2: launch_dual<VAR, WG_1x2>(st, a, w, gA, p.grid); break;
-    default: launch_dual<VAR, WG_1x1>(st, a, w, gA, p.grid); break;
-  }
-}
-
-void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
-                     float* part, float* G, int N, int Cin, int Cout, int HW, int cap) {
-  const PwArgs a = pw_args(Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW);  // dx = W^T g (+ add)
-  const PwPick p = pw_pick(a.NQ, HW, Cout, Cin);
-  const WgPick wp = wg_pick(N, Cin, Cout, HW, cap);
-  const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
-  if (p.var == 2 && p.wv > 4) {
-    // long K: the input gradient runs as wider blocks (K split 8 or 16 ways) than the weight-gradient
-    // kernel's, so the two go as separate launches
-    launch_pkks(st, a, p);
-    launch_wgrad(st, w, wp);
-  } else switch (p.var) {
-    case 2: launch_dual<2>(st, a, w, p.grid, wp); break;
-    case 3: launch_dual<3>(st, a, w, p.grid, wp); break;
-    case 1: launch_dual<1>(st, a, w, p.grid, wp); break;
-    default: launch_dual<0>(st, a, w, p.grid, wp); break;
-  }
-  size_t n = (size_t)Cin * Cout;
-  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)wp.grid.x);
-}
-
-// (sums in 64 bits: the kernel waits for memory, and adding partials in 32 bits was a third of the rounding error of a
-// weight gradient)
-__global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __restrict__ tasks,
-                                                           const unsigned short* __restrict__ block_task) {
-  __shared__ double sh[4][64];
-  const RedTask t = tasks[block_task[blockIdx.x]];
-  if (t.wide) {  // uniform per block
-    const size_t i4 = ((size_t)(blockIdx.x - t.block0) * 256 + threadIdx.x) * 4;
-    if (i4 >= t.n) return;
-    const float* p4 = t.part + i4;
-    const size_t st4 = t.stride;
-    const int parts4 = (int)t.parts;
-    double s4[4] = {0.0, 0.0, 0.0, 0.0};
-    int c4 = 0;
-    for (; c4 + 4 <= parts4; c4 += 4) {
-      const float4 v0 = *reinterpret_cast<const float4*>(p4 + (size_t)c4 * st4);
-      const float4 v1 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 1) * st4);
-      const float4 v2 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 2) * st4);
-      const float4 v3 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 3) * st4);
-      s4[0] += ((double)v0.x + v1.x) + ((double)v2.x + v3.x);
-      s4[1] += ((double)v0.y + v1.y) + ((double)v2.y + v3.y);
-      s4[2] += ((double)v0.z + v1.z) + ((double)v2.z + v3.z);
-      s4[3] += ((double)v0.w + v1.w) + ((double)v2.w + v3.w);
-    }
-    for (; c4 < parts4; ++c4) {
-      const float4 v = *reinterpret_cast<const float4*>(p4 + (size_t)c4 * st4);
-      s4[0] += v.x; s4[1] += v.y; s4[2] += v.z; s4[3] += v.w;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      size_t out = i4 + e;
-      if (t.taps > 1) {
-        const size_t tp = out / t.mn;
-        out = (out - tp * t.mn) * t.taps + tp;
-      }
-      t.G[out] = (float)(t.G[out] + s4[e]);
-    }
-    return;
-  }
-  const int o = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const size_t n = t.n, st = t.stride;
-  const size_t i = (size_t)(blockIdx.x - t.block0) * 64 + o;
-  const int parts = (int)t.parts;
-  const float* p = t.part + i;
-  double s = 0.0;
-  if (i < n) {
-    int c = q;
-    for (; c + 28 < parts; c += 32) {  // eight independent loads in flight
-      const double v0 = p[(size_t)c * st], v1 = p[(size_t)(c + 4) * st];
-      const double v2 = p[(size_t)(c + 8) * st], v3 = p[(size_t)(c + 12) * st];
-      const double v4 = p[(size_t)(c + 16) * st], v5 = p[(size_t)(c + 20) * st];
-      const double v6 = p[(size_t)(c + 24) * st], v7 = p[(size_t)(c + 28) * st];
-      s += ((v0 + v1) + (v2 + v3)) + ((v4 + v5) + (v6 + v7));
-    }
-    for (; c < parts; c += 4) s += p[(size_t)c * st];
-  }
-  sh[q][o] = s;
-  __syncthreads();
-  if (q == 0 && i < n) {
-    size_t out = i;
-    if (t.taps > 1) {
-      const size_t tp = i / t.mn;
-      out = (i - tp * t.mn) * t.taps + tp;
-    }
-    t.G[out] = (float)(t.G[out] + ((sh[0][o] + sh[1][o]) + (sh[2][o] + sh[3][o])));
-  }
-}
-void reduce_tasks_f32(hipStream_t st, const RedTask* tasks_dev, const unsigned short* block_task_dev, int nblocks) {
-  KLAUNCH(reduce_tasks_kernel, dim3(nblocks), dim3(256), 0, st, tasks_dev, block_task_dev);
-}
-
-void reduce_parts_acc_f32(hipStream_t st, const float* part, float* G, size_t n, int parts) {
-  KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, parts);
-}
 
 // ============================================================== depthwise 3x3 (pad 1, stride 1 or 2)
 struct DwGeom {

@@ -1,0 +1,1083 @@
+// fp32 pointwise (1x1) convolution: forward product, input gradient, weight gradient, and the packed weight copies.
+//
+// The products run on the bf16 matrix cores with their operands split in three (kernels_f32_x3.h).  In NCHW a channel plane is
+// contiguous, so pixels go on the MFMA N dimension: lane l supplies eight channels B[k = 8*(l/32) + 0..7] of pixel l%32 with
+// coalesced loads and splits them in registers, the weights are A[m = l%32][k], read from a copy that is split and packed in
+// exactly that lane order, and accumulator register r of lane l is D[8*(r/4) + 4*(l/32) + r%4][l%32].  No LDS and no barrier
+// in front of the products: a wavefront waits for its own loads alone, and the others of its SIMD fill the gaps.  (A version
+// that staged the split pixels of a block in LDS needed half the loads and took as long as the fp32 kernels: 64 -> 256
+// channels at 32 x 56x56 52 us against 45, 24 -> 144 31 us against 17; two wavefronts per SIMD ran in step.)
+#include <algorithm>
+
+#include "device_utils.h"
+#include "kernels.h"
+#include "kernels_f32_x3.h"
+#include "prof.h"
+
+namespace ast {
+
+static inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
+
+// Sample (counted from the first one) of position r of consecutive planes of HW pixels, r < HW + 512: floor(r / HW) without
+// the forty instructions of a division.  rHW: ceil(2^20 / HW) where planes are small enough for r to pass several.
+__host__ __device__ constexpr unsigned plane_reciprocal(int HW) { return HW >= 512 ? 0u : ((1u << 20) + HW - 1) / HW; }
+__device__ __forceinline__ unsigned plane_of(unsigned r, unsigned HW, unsigned rHW) {
+  return rHW ? r * rHW >> 20 : r >= HW;  // (rHW is uniform; the error of r * rHW is below 1024 * 512)
+}
+
+struct WgArgs {  // one pointwise-conv weight-gradient launch (partials only)
+  const float* g;
+  const float* x;
+  float* part;
+  long NQ;
+  int Cin, Cout, HW, splits;
+  unsigned rHW;  // plane_reciprocal(HW)
+  int tile_order;  // 1: the (ci, co) tiles of one pixel range run side by side on one XCD
+};
+
+// Block coordinates of a product grid of gx pixel blocks x gy channel tiles from the flat block id:
+// pixel blocks fastest, or (tile_order) channel tiles fastest within XCD-grouped ids, so that the
+// gy blocks that read the same pixels of X hit one L2.
+__device__ __forceinline__ void pw_block_xy(unsigned id, unsigned gx, unsigned gy, int tile_order, int& bx, int& by) {
+  if (tile_order) {
+    id = xcd_grouped(id, gx * gy);
+    by = (int)(id % gy);
+    bx = (int)(id / gy);
+  } else {
+    bx = (int)(id % gx);
+    by = (int)(id / gx);
+  }
+}
+
+// ============================================================== product (forward / input gradient)
+// Y[n][m][p] = sum_k A[m][k] X[n][k][p] (+ bias[m]) (+ add[n][m][p]); A from its split copy (x3_pack layout).
+struct PwArgs {
+  const uint4* Wp;
+  const float* X;
+  float* Y;
+  const float* bias;
+  const float* add;
+  double* stats;  // or NULL: per block (sum, sum of squares) of the output per channel, stats[m][pixel blocks][2]
+  size_t x_words, y_words;
+  unsigned NQ;    // pixels of all samples
+  unsigned rHW;   // plane_reciprocal(HW)
+  int HW, Kdim, Mdim, KG, gy;
+  int mper;       // the wide kernel: row tiles of a wavefront
+  int order;      // 1: the channel tiles of one pixel block run side by side on one XCD (they share X), 0: the pixel blocks
+                  // of one channel tile (they share the weights)
+};
+
+// Block coordinates of a product grid from the flat block id.  (Both from one division, in scalar registers: everything
+// that follows from them is uniform.)
+__device__ __forceinline__ void pw_product_xy(unsigned id, unsigned n, const PwArgs& a, int& bx, int& by) {
+  id = xcd_grouped(id, n);
+  const unsigned d = a.order ? (unsigned)a.gy : n / (unsigned)a.gy, hi = id / d, lo = id - hi * d;
+  bx = __builtin_amdgcn_readfirstlane(a.order ? hi : lo);
+  by = __builtin_amdgcn_readfirstlane(a.order ? lo : hi);
+}
+
+// one element of the product by its definition, from the weights' pieces (their sum is the weight)
+__device__ __forceinline__ float pw_element(const uint4* Wp, const float* xp, int m, int Kdim, int KG, int HW) {
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(Wp + ((size_t)(m >> 5) * KG * 3) * 64 + (m & 31));
+  float s = 0.f;
+  for (int k = 0; k < Kdim; ++k) {
+    const size_t o = ((size_t)(k >> 4) * 3 * 64 + 32 * ((k >> 3) & 1)) * 4 + ((k & 7) >> 1);
+    float p[3];
+    for (int i = 0; i < 3; ++i) {
+      const uint32_t u = w[o + (size_t)i * 256];
+      p[i] = __uint_as_float((k & 1) ? u & 0xffff0000u : u << 16);
+    }
+    s = fmaf(p[0] + (p[1] + p[2]), xp[(size_t)k * HW], s);
+  }
+  return s;
+}
+
+template <int PXL> struct PxVec { float v[PXL]; };  // PXL neighbouring pixels
+template <int PXL>
+__device__ __forceinline__ PxVec<PXL> px_load(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so) {
+  PxVec<PXL> o;
+  if constexpr (PXL == 1) {
+    o.v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+  } else {
+    const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0);
+    o.v[0] = __uint_as_float(u[0]);
+    o.v[1] = __uint_as_float(u[1]);
+  }
+  return o;
+}
+template <int PXL>
+__device__ __forceinline__ void px_store(__amdgpu_buffer_rsrc_t r, unsigned vo, const PxVec<PXL>& p) {
+  if constexpr (PXL == 1) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(p.v[0]), r, vo, 0, 0);
+  } else {
+    typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(uint2_t{__float_as_uint(p.v[0]), __float_as_uint(p.v[1])}, r, vo, 0, 0);
+  }
+}
+
+// Where the 32 * PXL pixels from q0 on of a wavefront lie: descriptors of operand and result from the first pixel's sample
+// on, and the lane's byte offsets in them (kOutside for pixels past the last).
+template <int PXL>
+struct PwLane {
+  unsigned n0, k, p;  // first sample; the lane's sample from there and its pixel
+  bool valid;
+  unsigned vx, vy;    // channel 8 * (l/32) of X, row m0 + 4 * (l/32) of Y
+  size_t xo, yo;
+  __amdgpu_buffer_rsrc_t rx, ry;
+  __device__ __forceinline__ PwLane(const PwArgs& a, unsigned q0, int m0) {
+    const unsigned HW = (unsigned)a.HW, lane = threadIdx.x & 63, half = lane >> 5;
+    n0 = __builtin_amdgcn_readfirstlane(min(q0, a.NQ - 1) / HW);
+    const unsigned q = q0 + (lane & 31) * PXL, r = q - n0 * HW;
+    k = plane_of(r, HW, a.rHW);
+    p = r - k * HW;
+    valid = q < a.NQ;  // (HW % PXL == 0: the pixels of a lane are valid together)
+    xo = (size_t)n0 * a.Kdim * HW;
+    yo = ((size_t)n0 * a.Mdim + m0) * HW;
+    rx = rsrc_words(a.X + xo, a.x_words - xo);
+    ry = rsrc_words(a.Y + yo, a.y_words - yo);
+    vx = valid ? (k * (unsigned)a.Kdim * HW + p + 8u * half * HW) * 4u : kOutside;
+    vy = valid ? (k * (unsigned)a.Mdim * HW + p + 4u * half * HW) * 4u : kOutside;
+  }
+};
+// row of accumulator register i, without the lane's 4 * (l/32)
+__device__ __forceinline__ constexpr int acc_row(int i) { return 8 * (i >> 2) + (i & 3); }
+
+// acc + acs += A X over the groups [gbeg, gend) of 16 channels; PXL column tiles (column j of tile t is pixel PXL*j + t of
+// the wavefront), MT row tiles.  The next group is in flight while one is multiplied; the loads past the last group are
+// outside every extent, and channels past Kdim meet zero weights.
+template <int PXL, int MT>
+__device__ __forceinline__ void pw_contract(const uint4* wl, size_t wt, __amdgpu_buffer_rsrc_t rx, unsigned vx, unsigned row_bytes,
+                                            int gbeg, int gend, floatx16 (&acc)[MT][PXL], floatx16 (&acs)[MT][PXL]) {
+  if (gbeg >= gend) return;  // uniform
+  uint4 a0[MT][3], a1[MT][3];
+  PxVec<PXL> b0[8], b1[8];
+  auto load = [&](uint4 (&a)[MT][3], PxVec<PXL> (&b)[8], int g) __attribute__((always_inline)) {
+    const unsigned v = g < gend ? vx : kOutside;
+    const int gg = min(g, gend - 1);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = px_load<PXL>(rx, v, (unsigned)(gg * 16 + j) * row_bytes);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) a[m][p] = wl[m * wt + (size_t)(gg * 3 + p) * 64];
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma = [&](const uint4 (&a)[MT][3], const PxVec<PXL> (&b)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < PXL; ++t) {
+      float v[8];
+      uint4 x[3];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = b[j].v[t];
+      split3(v, x);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acs[m][t] = mfma_bf16(a[m][2], x[0], acs[m][t]);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[m][t] = mfma_bf16(a[m][0], x[0], acc[m][t]);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acs[m][t] = mfma_bf16(a[m][1], x[0], acs[m][t]);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acs[m][t] = mfma_bf16(a[m][1], x[1], acs[m][t]);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acs[m][t] = mfma_bf16(a[m][0], x[1], acs[m][t]);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acs[m][t] = mfma_bf16(a[m][0], x[2], acs[m][t]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load(a0, b0, gbeg);
+  for (int g = gbeg; g < gend; g += 2) {
+    load(a1, b1, g + 1);
+    mma(a0, b0);
+    if (g + 1 < gend) {
+      load(a0, b0, g + 2);
+      mma(a1, b1);
+    }
+  }
+}
+
+// Sum over the 32 lanes of a half of each of 16 values: lane l ends with that of value 8*l4 + 4*l3 + 2*l2 + l1 (bits of l).
+// Every step halves the number of values, so it takes 39 instructions instead of 80.
+__device__ __forceinline__ float half_sums(const float (&v)[16]) {
+  const int lane = threadIdx.x & 63;
+  float a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {  // even rows of 16 lanes keep value i, odd ones value i + 8
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    a[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+  const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = (b3 ? a[i + 4] : a[i]) + dpp_move<DPP_ROW_MIRROR>(b3 ? a[i] : a[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = (b2 ? b[i + 2] : b[i]) + dpp_move<DPP_HALF_MIRROR>(b2 ? b[i] : b[i + 2]);
+  float d = (b1 ? c[1] : c[0]) + dpp_move<DPP_QUAD_MIRROR>(b1 ? c[0] : c[1]);
+  d += dpp_move<DPP_QUAD_SWAP1>(d);
+  return d;
+}
+// The statistics of one row tile, one wavefront's pixels: sums to sd[32] in row order
+__device__ __forceinline__ void tile_stats(const float (&s)[16], const float (&q)[16], float2* sd) {
+  const int lane = threadIdx.x & 63, i = 8 * (lane >> 4 & 1) + 4 * (lane >> 3 & 1) + 2 * (lane >> 2 & 1) + (lane >> 1 & 1);
+  const float a = half_sums(s), b = half_sums(q);
+  if (!(lane & 1)) sd[8 * (i >> 2) + (i & 3) + 4 * (lane >> 5)] = make_float2(a, b);
+}
+// ... and the sums of all wavefronts of a block to stats[m][P][2]; sd[waves][rows] in LDS, m0: the block's first channel
+__device__ __forceinline__ void block_stats(const float2* sd, int waves, int rows, double* stats, int m0, int Mdim, int bx, int P) {
+  __syncthreads();
+  for (int c = threadIdx.x; c < rows && m0 + c < Mdim; c += blockDim.x) {
+    double s = 0.0, q = 0.0;
+    for (int w = 0; w < waves; ++w) {
+      s += sd[w * rows + c].x;
+      q += sd[w * rows + c].y;
+    }
+    double* o = stats + ((size_t)(m0 + c) * P + bx) * 2;
+    o[0] = s;
+    o[1] = q;
+  }
+}
+
+// Results that are not finite again by their definition, over what was stored: rows [m0, m1) of the wavefront's pixels,
+// and the statistics of those rows if sd != NULL.
+template <int PXL>
+__device__ __forceinline__ void pw_again(const PwArgs& a, const PwLane<PXL>& L, int m0, int m1, float2* sd) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores in front
+  const int lane = threadIdx.x & 63;
+  for (int m = m0; m < m1; ++m) {
+    float s = 0.f, q = 0.f;
+    if (L.valid && lane < 32 && m < a.Mdim)
+      for (int t = 0; t < PXL; ++t) {
+        float v = pw_element(a.Wp, a.X + L.xo + (size_t)L.k * a.Kdim * a.HW + L.p + t, m, a.Kdim, a.KG, a.HW);
+        s += v;
+        q = fmaf(v, v, q);
+        const size_t o = ((size_t)(L.n0 + L.k) * a.Mdim + m) * a.HW + L.p + t;
+        if (a.bias) v += a.bias[m];
+        if (a.add) v += a.add[o];
+        a.Y[o] = v;
+      }
+    if (sd) {  // uniform
+      s = wave_sum(s);
+      q = wave_sum(q);
+      if (lane == 0) sd[m - m0] = make_float2(s, q);
+    }
+  }
+}
+// Sum of 0 * v: 0 as long as every v is finite, else NaN
+template <int N>
+__device__ __forceinline__ float finite_test(const float (&v)[N], float c) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) c = fmaf(v[i], 0.f, c);
+  return c;
+}
+
+// A wavefront: 32 * PXL pixels x MT 32-row tiles, blocks of any number of wavefronts side by side over the pixels.  More
+// pixels and tiles per wavefront read and split the operands less often, and leave fewer wavefronts: 94 registers at 1 x 1
+// (five wavefronts per SIMD), 142 at 2 x 1, 153 at 1 x 2, 233 at 2 x 2.
+// us, forward, fp32 matrix instructions / now: 256 -> 64 channels at 32 x 56x56 50 / 36 (2 x 2), 256 -> 128 at 8 x 56x56 30 /
+// 16, 144 -> 24 at 32 x 56x56 20 / 14 (2 x 1), 240 -> 40 at 32 x 30x30 16 / 10, 64 -> 64 at 32 x 56x56 18 / 13 (1 x 1).
+template <int PXL, int MT>
+__device__ __forceinline__ void pw_body(const PwArgs& a, int bx, int by, float2* sd, int P) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, Mdim = a.Mdim, KG = a.KG, m0 = by * 32 * MT;
+  const unsigned row_bytes = (unsigned)a.HW * 4u;
+  const PwLane<PXL> L(a, ((unsigned)bx * (blockDim.x >> 6) + wave) * (32u * PXL), m0);
+  const uint4* wl = a.Wp + (size_t)by * MT * KG * 192 + lane;
+  const size_t wt = MT > 1 && m0 + 32 < Mdim ? (size_t)KG * 192 : 0;  // the second tile, where it exists
+  floatx16 acc[MT][PXL], acs[MT][PXL];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int t = 0; t < PXL; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[m][t][i] = acs[m][t][i] = 0.f;
+  pw_contract<PXL, MT>(wl, wt, L.rx, L.vx, row_bytes, 0, KG, acc, acs);
+  float bad = 0.f;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int t = 0; t < PXL; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        acc[m][t][i] += acs[m][t][i];
+        bad = fmaf(acc[m][t][i], 0.f, bad);
+      }
+  if (a.stats) {  // uniform; only without bias and addend; pixels past the last hold zeros
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      float s[16], q[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        s[i] = acc[m][0][i];
+        q[i] = s[i] * s[i];
+        if constexpr (PXL == 2) {
+          s[i] += acc[m][1][i];
+          q[i] = fmaf(acc[m][1][i], acc[m][1][i], q[i]);
+        }
+      }
+      tile_stats(s, q, sd + (wave * MT + m) * 32);
+    }
+  }
+  if (a.bias || a.add) {  // uniform
+    const __amdgpu_buffer_rsrc_t ra = rsrc_words(a.add ? a.add + L.yo : a.Y, a.add ? a.y_words - L.yo : 0);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int i0 = 0; i0 < 16; i0 += 8) {  // eight rows at a time are requested before the first is used
+        PxVec<PXL> kv[8];
+        float bv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int r = 32 * m + acc_row(i0 + i);
+          bv[i] = a.bias ? a.bias[min(m0 + r + 4 * half, Mdim - 1)] : 0.f;
+          kv[i] = px_load<PXL>(ra, L.vy, (unsigned)r * row_bytes);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int t = 0; t < PXL; ++t) acc[m][t][i0 + i] += bv[i] + kv[i].v[t];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  }
+  const int rows = Mdim - m0 - 4 * half;   // of the lane, in acc_row's numbering
+  const bool full = m0 + 32 * MT <= Mdim;  // uniform
+  unsigned vo = L.vy;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      PxVec<PXL> v;
+#pragma unroll
+      for (int t = 0; t < PXL; ++t) v.v[t] = acc[m][t][i];
+      px_store<PXL>(L.ry, full || 32 * m + acc_row(i) < rows ? vo : kOutside, v);
+      vo += (i & 3) == 3 ? 5 * row_bytes : row_bytes;
+    }
+  if (__any(bad != 0.f)) pw_again<PXL>(a, L, m0, m0 + 32 * MT, a.stats ? sd + wave * MT * 32 : nullptr);  // (NaN != 0)
+  if (a.stats) block_stats(sd, blockDim.x >> 6, 32 * MT, a.stats, m0, Mdim, bx, P);
+}
+template <int PXL, int MT>
+__global__ __launch_bounds__(512, PXL * MT == 1 ? 4 : 2) void pw_conv_f32_kernel(PwArgs a) {
+  __shared__ float2 sd[8 * 32 * MT];
+  int bx, by;
+  pw_product_xy(blockIdx.x, gridDim.x, a, bx, by);
+  pw_body<PXL, MT>(a, bx, by, sd, gridDim.x / a.gy);
+}
+
+// Few pixels, long K (the 14x14 / 7x7 layers of a whole network): the WK wavefronts of a block share one tile of 32 pixels
+// x MT * 32 channels and split K between them, so there are WK times as many wavefronts and a WK-th of the dependent
+// passes; their tiles are added through LDS in a fixed order.
+// us, fp32 matrix instructions / now: 1024 -> 256 channels at 8 x 14x14 18.5 / 11.3 (WK 4, MT 2), 512 -> 2048 at 8 x 7x7
+// 18.1 / 11.6, 960 -> 160 at 8 x 7x7 9.5 / 7.4 (WK 8, MT 1), 576 -> 96 at 8 x 14x14 7.5 / 5.6.
+template <int MT, int WK>
+__device__ __forceinline__ void pw_ks_body(const PwArgs& a, int bx, int by, float (*sR)[16][64]) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, Mdim = a.Mdim, KG = a.KG, m0 = by * 32 * MT;
+  const unsigned row_bytes = (unsigned)a.HW * 4u;
+  const PwLane<1> L(a, (unsigned)bx * 32u, m0);
+  const uint4* wl = a.Wp + (size_t)by * MT * KG * 192 + lane;
+  const size_t wt = MT > 1 && m0 + 32 < Mdim ? (size_t)KG * 192 : 0;  // the second tile, where it exists
+  floatx16 acc[MT][1], acs[MT][1];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[m][0][i] = acs[m][0][i] = 0.f;
+  const int gper = (KG + WK - 1) / WK, gbeg = wave * gper;
+  pw_contract<1, MT>(wl, wt, L.rx, L.vx, row_bytes, gbeg, min(gbeg + gper, KG), acc, acs);
+  constexpr int RW = 16 / WK;  // rows of the register layout that each wavefront finishes
+  const __amdgpu_buffer_rsrc_t ra = rsrc_words(a.add ? a.add + L.yo : a.Y, a.add ? a.y_words - L.yo : 0);
+  bool bad = false;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    if (m) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sR[wave][i][lane] = acc[m][0][i] + acs[m][0][i];
+    __syncthreads();
+#pragma unroll
+    for (int rr = 0; rr < RW; ++rr) {
+      const int i = RW * wave + rr, r = 32 * m + acc_row(i), mm = m0 + r + 4 * half;
+      float v = 0.f;
+#pragma unroll
+      for (int s = 0; s < WK; s += 4)  // fixed order
+        v += (sR[s][i][lane] + sR[s + 1][i][lane]) + (sR[s + 2][i][lane] + sR[s + 3][i][lane]);
+      const unsigned vo = L.valid && mm < Mdim ? L.vy + (unsigned)r * row_bytes : kOutside;
+      if (!finite_f(v) && vo != kOutside) {
+        bad = true;
+        v = pw_element(a.Wp, a.X + L.xo + (size_t)L.k * a.Kdim * a.HW + L.p, mm, a.Kdim, KG, a.HW);
+      }
+      if (a.bias) v += a.bias[min(mm, Mdim - 1)];
+      if (a.add) v += px_load<1>(ra, vo, 0).v[0];
+      px_store<1>(L.ry, vo, {v});
+    }
+  }
+}
+template <int MT, int WK>
+__global__ __launch_bounds__(64 * WK) void pw_conv_f32_ks_kernel(PwArgs a) {
+  __shared__ float sR[WK][16][64];
+  int bx, by;
+  pw_product_xy(blockIdx.x, gridDim.x, a, bx, by);
+  pw_ks_body<MT, WK>(a, bx, by, sR);
+}
+
+// Short contractions into many channels (at most 16 * G of them in): a wavefront reads and splits its 32 pixels once and
+// walks the row tiles [by * mper, (by + 1) * mper), the weights one tile ahead.  These products write several times what they
+// read, so what counts is that stores never wait for anything.
+// us, fp32 matrix instructions / now: 24 -> 144 channels at 32 x 56x56 21.8 / 17.5 (copy of its bytes 13.8), at 32 x 60x60
+// 29.3 / 19.6, 40 -> 240 at 32 x 30x30 15.7 / 12.4, 16 -> 96 at 8 x 112x112 15.3 / 10.6, 64 -> 256 at 32 x 56x56 59 / 45.6.
+template <int G, bool ADD>
+__device__ __forceinline__ void pw_wide_body(const PwArgs& a, int bx, int by, float2* sd) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, Mdim = a.Mdim, KG = a.KG;
+  const unsigned row_bytes = (unsigned)a.HW * 4u;
+  const int t0 = by * a.mper, t1 = min(t0 + a.mper, (Mdim + 31) / 32);
+  const PwLane<1> L(a, ((unsigned)bx * (blockDim.x >> 6) + wave) * 32u, t0 * 32);
+  const uint4* wl = a.Wp + lane;
+  uint4 a0[G][3], a1[G][3], x[G][3];
+  auto loadA = [&](uint4 (&w)[G][3], int t) __attribute__((always_inline)) {
+    const uint4* s = wl + (size_t)min(t, t1 - 1) * KG * 192;
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) w[g][i] = s[(min(g, KG - 1) * 3 + i) * 64];
+  };
+  float v[G][8];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[g][j] = px_load<1>(L.rx, g < KG ? L.vx : kOutside, (unsigned)(g * 16 + j) * row_bytes).v[0];
+  loadA(a0, t0);
+#pragma unroll
+  for (int g = 0; g < G; ++g) split3(v[g], x[g]);
+  float bad = 0.f;
+  const __amdgpu_buffer_rsrc_t ra = rsrc_words(a.add ? a.add + L.yo : a.Y, a.add ? a.y_words - L.yo : 0);
+  auto tile = [&](const uint4 (&w)[G][3], int t) __attribute__((always_inline)) {
+    floatx16 acc, acs;
+    const unsigned vt = L.vy + (unsigned)(t - t0) * 32u * row_bytes;
+    float kv[16];  // requested in front of the products
+    if constexpr (ADD) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) kv[i] = px_load<1>(ra, L.valid ? vt : kOutside, (unsigned)acc_row(i) * row_bytes).v[0];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = acs[i] = 0.f;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      acs = mfma_bf16(w[g][2], x[g][0], acs);
+      acc = mfma_bf16(w[g][0], x[g][0], acc);
+      acs = mfma_bf16(w[g][1], x[g][0], acs);
+      acs = mfma_bf16(w[g][1], x[g][1], acs);
+      acs = mfma_bf16(w[g][0], x[g][1], acs);
+      acs = mfma_bf16(w[g][0], x[g][2], acs);
+    }
+    const int rows = L.valid ? Mdim - t * 32 - 4 * half : 0;
+    unsigned vo = vt;
+    float o[16], q[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      o[i] = acc[i] + acs[i];
+      bad = fmaf(o[i], 0.f, bad);
+      px_store<1>(L.ry, acc_row(i) < rows ? vo : kOutside, {ADD ? o[i] + kv[i] : o[i]});
+      vo += (i & 3) == 3 ? 5 * row_bytes : row_bytes;
+    }
+    if (a.stats) {  // uniform; pixels past the last hold zeros
+#pragma unroll
+      for (int i = 0; i < 16; ++i) q[i] = o[i] * o[i];
+      tile_stats(o, q, sd + (wave * a.mper + t - t0) * 32);
+    }
+  };
+  for (int t = t0; t < t1; t += 2) {
+    loadA(a1, t + 1);
+    tile(a0, t);
+    if (t + 1 < t1) {
+      loadA(a0, t + 2);
+      tile(a1, t + 1);
+    }
+  }
+  if (__any(bad != 0.f))  // (NaN != 0)
+    pw_again<1>(a, L, t0 * 32, t1 * 32, a.stats ? sd + wave * a.mper * 32 : nullptr);
+}
+constexpr int kWideTiles = 8;  // most row tiles of a wavefront
+template <int G>
+__global__ __launch_bounds__(512, G <= 2 ? 4 : 2) void pw_conv_f32_wide_kernel(PwArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  int bx, by;
+  pw_product_xy(blockIdx.x, gridDim.x, a, bx, by);
+  const int waves = blockDim.x >> 6, rows = a.mper * 32;
+  float2* const sd = reinterpret_cast<float2*>(lds);  // [waves][rows]
+  pw_wide_body<G, false>(a, bx, by, sd);
+  if (a.stats) block_stats(sd, waves, rows, a.stats, by * rows, a.Mdim, bx, gridDim.x / a.gy);
+}
+
+// Split copy of A[m][k] = W[m*lda_m + k*lda_k]: for tile t of 32 rows, group g of 16 columns and piece i, lane l finds
+// A[32t + l%32][16g + 8*(l/32) + 0..7] as one 16-byte word at Wp[((t*KG + g)*3 + i)*64 + l]; zero outside.
+size_t x3_pack_floats(int Mdim, int Kdim) { return (size_t)cdiv(Mdim, 32) * cdiv(Kdim, 16) * 768; }
+// fp32 copy (the other convolutions): Wp[((t*KG + g)*64 + l)*4 + e] = A[32t + l%32][8g + 2e + l/32], zero outside.
+size_t pw_pack_floats(int Mdim, int Kdim) { return (size_t)cdiv(Mdim, 32) * cdiv(Kdim, 8) * 256; }
+
+// 256 words of a copy, the b-th of it
+__device__ __forceinline__ float pack_word(const PackTask& t, unsigned b) {
+  const int e = threadIdx.x & 3, l = threadIdx.x >> 2;
+  auto at = [&](int m, int k) { return m < t.Mdim && k < t.Kdim ? t.W[(size_t)m * t.lda_m + (size_t)k * t.lda_k] : 0.f; };
+  if (t.split) {  // uniform
+    const unsigned piece = b % 3u, tg = b / 3u, tile = tg / (unsigned)t.KG, g = tg - tile * t.KG;
+    const int m = (int)(32 * tile) + (l & 31), k = (int)(16 * g) + 8 * (l >> 5) + 2 * e;
+    // (every finite weight is the sum of its pieces, also one whose first piece would round to infinity)
+    auto piece_of = [&](float w) -> uint32_t {
+      if (!finite_f(w)) return piece == 0 ? f2bf(w) : 0;
+      uint32_t h = f2bf(w);
+      if (!finite_f(bf2f((bf16_t)h))) h = __float_as_uint(w) >> 16;
+      for (unsigned i = 0; i < piece; ++i) {
+        w -= bf2f((bf16_t)h);
+        h = f2bf(w);
+      }
+      return h;
+    };
+    return __uint_as_float(piece_of(at(m, k)) | piece_of(at(m, k + 1)) << 16);
+  }
+  const unsigned tile = b / (unsigned)t.KG, g = b - tile * t.KG;
+  return at((int)(32 * tile) + (l & 31), (int)(8 * g) + 2 * e + (l >> 5));
+}
+// Every packed copy of a stage in one launch: the copies sit back to back in one arena, each a multiple of 256 words, so
+// block b (256 words of the arena) belongs to one task.
+__global__ __launch_bounds__(256) void pw_pack_all_kernel(const PackTask* __restrict__ tasks,
+                                                          const unsigned short* __restrict__ block_task,
+                                                          float* __restrict__ arena) {
+  const PackTask t = tasks[block_task[blockIdx.x]];
+  arena[(size_t)blockIdx.x * 256 + threadIdx.x] = pack_word(t, blockIdx.x - t.block0);
+}
+void pw_pack_all_f32(hipStream_t st, const PackTask* tasks_dev, const unsigned short* block_task_dev, float* arena,
+                     int nblocks) {
+  KLAUNCH(pw_pack_all_kernel, dim3(nblocks), dim3(256), 0, st, tasks_dev, block_task_dev, arena);
+}
+__global__ __launch_bounds__(256) void pw_pack_kernel(PackTask t, float* __restrict__ Wp) {
+  Wp[(size_t)blockIdx.x * 256 + threadIdx.x] = pack_word(t, blockIdx.x);
+}
+void pw_pack_f32(hipStream_t st, const float* W, int lda_m, int lda_k, float* Wp, int Mdim, int Kdim, bool split) {
+  PackTask t = {};
+  t.W = W; t.lda_m = lda_m; t.lda_k = lda_k; t.Mdim = Mdim; t.Kdim = Kdim; t.split = split;
+  t.KG = cdiv(Kdim, split ? 16 : 8);
+  const size_t total = split ? x3_pack_floats(Mdim, Kdim) : pw_pack_floats(Mdim, Kdim);
+  KLAUNCH(pw_pack_kernel, dim3((unsigned)(total / 256)), dim3(256), 0, st, t, Wp);
+}
+
+// ---- which product kernel serves a shape, and its grid
+enum PwVar { PW_1x1, PW_1x2, PW_2x1, PW_2x2, PW_KS4, PW_KS4x2, PW_KS8, PW_WIDE };
+struct PwPick { PwVar var; int waves, gx, gy, mper; };
+// Measured over the layers of MobileNetV2, EfficientNet-B1 and ResNet50 at 1 to 32 samples; `tiles` counts 32 x 32 tiles.
+static PwPick pw_pick(long NQ, int HW, int Kdim, int Mdim, bool wide) {
+  const int mt = cdiv(Mdim, 32), KG = cdiv(Kdim, 16);
+  const long tiles = (long)cdiv(NQ, 32) * mt;
+  PwPick p = {PW_1x1, 4, 0, mt, 0};
+  if (tiles < 1024 && KG >= 6) {
+    // under one wavefront per SIMD: K is split.  Two row tiles per wavefront where that leaves K long (512 -> 2048 at
+    // 8 x 7x7 11.6 us, one tile 13.2), eight shares where there are few tiles (960 -> 160 at 8 x 7x7 7.4 us, four 7.7).
+    // Below six groups a share is too short (64 -> 384 at 8 x 14x14: split 4.5 us, not 4.3).
+    if (KG >= 32 && mt >= 2 && tiles >= 384) { p.var = PW_KS4x2; p.gy = cdiv(mt, 2); }
+    else if (KG >= 16 && tiles < 256) { p.var = PW_KS8; p.waves = 8; }
+    else p.var = PW_KS4;
+    p.gx = cdiv(NQ, 32);
+    return p;
+  }
+  if (KG <= 4 && mt >= 3 && tiles >= 7000 && wide) {
+    // enough wavefronts even with all row tiles in one: below, more and shorter ones win (24 -> 144 at 8 x 56x56 7.7 us, 7.3)
+    p.var = PW_WIDE;
+    p.mper = std::min(mt, kWideTiles);
+    p.gy = cdiv(mt, p.mper);
+    p.gx = cdiv(NQ, 128);
+    return p;
+  }
+  // Longer contractions are bound by reading and splitting the pixels once per row tile.
+  if (KG > 4 && HW % 2 == 0) {
+    if (mt >= 2 && mt != 3 && tiles >= 3000) { p.var = PW_2x2; p.gy = cdiv(mt, 2); p.gx = cdiv(NQ, 256); }
+    else { p.var = PW_2x1; p.gx = cdiv(NQ, 256); }
+    return p;
+  }
+  if (KG > 4 && mt >= 2) { p.var = PW_1x2; p.gy = cdiv(mt, 2); }
+  p.gx = cdiv(NQ, 128);
+  return p;
+}
+
+// A wavefront's offsets from its first sample are 32-bit; operands that they do not reach go to the generic kernels.
+bool pw_conv_supported(int Cin, int Cout, int HW) { return ((size_t)HW + 64) * (std::max(Cin, Cout) + 64) * 4 < ((size_t)1 << 30); }
+
+static PwArgs pw_args(const float* Wp, const float* X, float* Y, const float* bias, const float* add, int N, int Kdim,
+                      int Mdim, int HW, const PwPick& p) {
+  PwArgs a;
+  a.Wp = reinterpret_cast<const uint4*>(Wp);
+  a.X = X; a.Y = Y; a.bias = bias; a.add = add;
+  a.stats = nullptr;
+  a.NQ = (unsigned)((size_t)N * HW);
+  a.x_words = (size_t)a.NQ * Kdim; a.y_words = (size_t)a.NQ * Mdim;
+  a.HW = HW; a.rHW = plane_reciprocal(HW); a.Kdim = Kdim; a.Mdim = Mdim; a.KG = cdiv(Kdim, 16);
+  a.gy = p.gy; a.mper = p.mper;
+  // What the blocks of an XCD share is the larger operand: 2048 -> 512 channels at 8 x 7x7 (6 bytes a weight) 14.1 us with
+  // the weights shared, 15.5 with the pixels; 256 -> 64 at 8 x 56x56 11.3 and 10.6.
+  a.order = (size_t)Mdim * 3 < (size_t)a.NQ * 2;
+  return a;
+}
+
+// Partial pairs per channel that the forward product can leave for a BatchNorm behind it: its pixel blocks, of eight
+// wavefronts where four would leave more than 256, while they are at most 512; 0 = not offered.  (24 -> 144 channels at
+// 32 x 56x56 as 392 blocks of eight wavefronts 19.5 us, as 196 of sixteen 25.9 us: one block on a compute unit, and its loads
+// and stores take turns.)
+static bool pw_stats_blocks(PwPick& p, long NQ) {
+  if (p.var == PW_KS4 || p.var == PW_KS4x2 || p.var == PW_KS8) return false;
+  if (p.gx > 256) {
+    p.waves = 8;
+    p.gx = cdiv(NQ, 256L * (p.var == PW_2x1 || p.var == PW_2x2 ? 2 : 1));
+  }
+  return p.gx <= 512;
+}
+int pw_conv_stats_parts(int N, int Kdim, int Mdim, int HW) {
+  PwPick p = pw_pick((long)N * HW, HW, Kdim, Mdim, true);
+  return pw_stats_blocks(p, (long)N * HW) ? p.gx : 0;
+}
+
+template <int G>
+static void launch_wide(hipStream_t st, const PwArgs& a, const PwPick& p) {
+  const size_t lds = a.stats ? (size_t)p.waves * p.mper * 32 * sizeof(float2) : 0;
+  KLAUNCH_NAMED("pw_conv_f32_wide_kernel", (pw_conv_f32_wide_kernel<G>), dim3(p.gx * p.gy), dim3(64 * p.waves), lds, st, a);
+}
+static void launch_product(hipStream_t st, const PwArgs& a, const PwPick& p) {
+  const dim3 grid(p.gx * p.gy), block(64 * p.waves);
+  switch (p.var) {
+    case PW_1x1: KLAUNCH_NAMED("pw_conv_f32_kernel", (pw_conv_f32_kernel<1, 1>), grid, block, 0, st, a); break;
+    case PW_1x2: KLAUNCH_NAMED("pw_conv_f32_kernel", (pw_conv_f32_kernel<1, 2>), grid, block, 0, st, a); break;
+    case PW_2x1: KLAUNCH_NAMED("pw_conv_f32_kernel", (pw_conv_f32_kernel<2, 1>), grid, block, 0, st, a); break;
+    case PW_2x2: KLAUNCH_NAMED("pw_conv_f32_kernel", (pw_conv_f32_kernel<2, 2>), grid, block, 0, st, a); break;
+    case PW_KS4: KLAUNCH_NAMED("pw_conv_f32_ks_kernel", (pw_conv_f32_ks_kernel<1, 4>), grid, block, 0, st, a); break;
+    case PW_KS4x2: KLAUNCH_NAMED("pw_conv_f32_ks_kernel", (pw_conv_f32_ks_kernel<2, 4>), grid, block, 0, st, a); break;
+    case PW_KS8: KLAUNCH_NAMED("pw_conv_f32_ks_kernel", (pw_conv_f32_ks_kernel<1, 8>), grid, block, 0, st, a); break;
+    case PW_WIDE:
+      if (a.KG == 1) launch_wide<1>(st, a, p);
+      else if (a.KG == 2) launch_wide<2>(st, a, p);
+      else launch_wide<4>(st, a, p);
+      break;
+  }
+}
+
+void pw_conv_f32(hipStream_t st, const float* Wp, const float* X, float* Y, const float* bias, const float* add,
+                 int N, int Kdim, int Mdim, int HW, double* stats) {
+  const bool plain = !bias && !add;
+  PwPick p = pw_pick((long)N * HW, HW, Kdim, Mdim, plain), q = p;
+  const bool given = stats && plain && pw_stats_blocks(q, (long)N * HW);
+  if (given) p = q;
+  PwArgs a = pw_args(Wp, X, Y, bias, add, N, Kdim, Mdim, HW, p);
+  if (given) a.stats = stats;
+  launch_product(st, a, p);
+}
+
+// ============================================================== weight gradient
+// dW[co][ci] = sum over the pixels q of all samples of g[co][q] x[ci][q], with the split operands of the products above.  A
+// block owns TCO x TCI tiles of 32 x 32 weights and the pixels of one of `splits` equal ranges of the flattened (sample,
+// pixel) index, in steps of 64 of which each of its four wavefronts multiplies 16 for every tile.  A step's rows of g and x
+// are loaded in whole 128-byte runs one step ahead, split in registers and copied to LDS as three planes of 128-byte rows; a
+// lane reads eight pixels of row l%32 as one 16-byte word.  Which pixels of a step are neighbours in LDS does not matter
+// as long as g and x agree: word c of a row holds pixels 4c..4c+3 and 32+4c..32+4c+3, so that eight lanes load whole runs.
+// Word c lies at position c ^ (row/2 & 7): the sixteen lanes of one LDS access hit all 64 banks.
+//
+// Chains of additions: a rounding per 16 pixels (the small products have accumulators of their own), and a range is at most
+// WG_CHAIN steps, so no chain grows with the micro-batch; wavefronts and partials are added in 64 bits.
+template <int TCO, int TCI>
+struct WgTile {
+  static constexpr int ROWS = (TCO + TCI) * 32, PLANE = ROWS * 128, LDS = 3 * PLANE / 4;  // bytes, floats
+};
+// dW of one element over the pixels [q0, q1), by its definition
+__device__ __forceinline__ float wg_element(const WgArgs& w, int co, int ci, unsigned q0, unsigned q1) {
+  float s = 0.f;
+  const unsigned HW = (unsigned)w.HW;
+  unsigned n = q0 / HW, p = q0 - n * HW;
+  for (unsigned q = q0; q < q1; ++q) {
+    s = fmaf(w.g[((size_t)n * w.Cout + co) * HW + p], w.x[((size_t)n * w.Cin + ci) * HW + p], s);
+    if (++p == HW) { p = 0; ++n; }
+  }
+  return s;
+}
+
+template <int TCO, int TCI, bool VEC>
+__device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bci, int bco, char* __restrict__ lds) {
+  using T = WgTile<TCO, TCI>;
+  constexpr int NI = TCO + TCI;  // a thread stages eight pixels of one row of each 32-row tile
+  const int Cin = w.Cin, Cout = w.Cout;
+  const unsigned HW = (unsigned)w.HW, Q = (unsigned)w.NQ;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int co_base = bco * (TCO * 32), ci_base = bci * (TCI * 32);
+  const int steps = (int)((Q + 63) / 64);
+  const int s0 = (int)((long)steps * split / w.splits), s1 = (int)((long)steps * (split + 1) / w.splits);
+
+  const int sr = t >> 3, sc = t & 7;
+  const unsigned row_bytes = HW * 4u;
+  float rv[NI][8];
+  unsigned q0 = (unsigned)s0 * 64u, n0 = __builtin_amdgcn_readfirstlane(q0 / HW), p0 = q0 - n0 * HW;  // of the step to load
+  auto load = [&]() __attribute__((always_inline)) {
+    const size_t go = ((size_t)n0 * Cout + co_base) * HW, xo = ((size_t)n0 * Cin + ci_base) * HW;
+    const __amdgpu_buffer_rsrc_t rg = rsrc_words(w.g + go, (size_t)Q * Cout - go), rx = rsrc_words(w.x + xo, (size_t)Q * Cin - xo);
+    constexpr int NV = VEC ? 2 : 8;  // words of four pixels (HW % 4 == 0: they never leave their sample) or single ones
+    unsigned og[NV], ox[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const unsigned d = VEC ? 32 * j + 4 * sc : 32 * (j >> 2) + 4 * sc + (j & 3);
+      const unsigned k = plane_of(p0 + d, HW, w.rHW), p = p0 + d - k * HW;
+      const bool ok = q0 + d < Q;
+      og[j] = ok ? (k * (unsigned)Cout * HW + p + (unsigned)sr * HW) * 4u : kOutside;
+      ox[j] = ok ? (k * (unsigned)Cin * HW + p + (unsigned)sr * HW) * 4u : kOutside;
+    }
+    q0 += 64;
+    for (p0 += 64; p0 >= HW; p0 -= HW) ++n0;  // uniform
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const bool isg = i < TCO;
+      const int tile = isg ? i : i - TCO;
+      const bool in = isg ? co_base + tile * 32 + sr < Cout : ci_base + tile * 32 + sr < Cin;
+      const unsigned so = (unsigned)tile * 32u * row_bytes;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        const unsigned vo = in ? (isg ? og[j] : ox[j]) : kOutside;
+        if constexpr (VEC) {
+          const auto v = __builtin_amdgcn_raw_buffer_load_b128(isg ? rg : rx, vo, so, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) rv[i][4 * j + e] = __uint_as_float(v[e]);
+        } else {
+          rv[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(isg ? rg : rx, vo, so, 0));
+        }
+      }
+    }
+  };
+  char* const st = lds + sr * 128 + ((sc ^ (sr >> 1 & 7)) * 16);
+  auto put = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      uint4 p[3];
+      split3(rv[i], p);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<uint4*>(st + k * T::PLANE + i * 4096) = p[k];
+    }
+  };
+  auto barrier = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the loads of the next step stay in flight)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  const int row = lane & 31, half = lane >> 5;
+  const char* const ld = lds + row * 128 + (((2 * wave + half) ^ (row >> 1 & 7)) * 16);
+  floatx16 acc[TCO][TCI], acs[TCO][TCI];
+#pragma unroll
+  for (int i = 0; i < TCO; ++i)
+#pragma unroll
+    for (int j = 0; j < TCI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = acs[i][j][r] = 0.f;
+  if (s0 < s1) load();  // uniform
+  for (int s = s0; s < s1; ++s) {
+    put();
+    barrier();
+    if (s + 1 < s1) load();  // uniform
+    uint4 f[NI][3];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) f[i][k] = *reinterpret_cast<const uint4*>(ld + k * T::PLANE + i * 4096);
+    auto mma = [&](floatx16(&c)[TCO][TCI], int a, int b) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TCO; ++i)
+#pragma unroll
+        for (int j = 0; j < TCI; ++j) c[i][j] = mfma_bf16(f[i][a], f[TCO + j][b], c[i][j]);
+    };
+    mma(acs, 2, 0);
+    mma(acc, 0, 0);
+    mma(acs, 0, 2);
+    mma(acs, 1, 1);
+    mma(acs, 1, 0);
+    mma(acs, 0, 1);
+    if (s + 1 < s1) barrier();  // the buffer has been read
+  }
+  // the four wavefronts' sums of a tile are added in a fixed order; the staging buffer is free by now
+  float* out = w.part + (size_t)split * Cout * Cin;
+  float* const red = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int i = 0; i < TCO; ++i)
+#pragma unroll
+    for (int j = 0; j < TCI; ++j) {
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = acc[i][j][r] + acs[i][j][r];
+      __syncthreads();
+      const int ci = ci_base + j * 32 + row;
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int r = wave * 4 + rr, co = co_base + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        const float* v = red + r * 64 + lane;
+        float d = (float)(((double)v[0] + v[16 * 64]) + ((double)v[2 * 16 * 64] + v[3 * 16 * 64]));
+        if (ci < Cin && co < Cout) {
+          if (!finite_f(d)) d = wg_element(w, co, ci, (unsigned)s0 * 64u, min((unsigned)s1 * 64u, Q));
+          out[(size_t)co * Cin + ci] = d;
+        }
+      }
+    }
+}
+
+// The block shapes of the weight gradient: weight tiles (co x ci) per block, wavefronts per tile
+enum { WG_2x2 = 0, WG_2x1 = 1, WG_1x2 = 2, WG_1x1 = 3 };
+template <int SHAPE, bool VEC>
+__device__ __forceinline__ void pw_wgrad_shape(const WgArgs& w, int split, int bci, int bco, float* lds) {
+  constexpr int TCO = SHAPE == WG_2x2 || SHAPE == WG_2x1 ? 2 : 1, TCI = SHAPE == WG_2x2 || SHAPE == WG_1x2 ? 2 : 1;
+  pw_wgrad_body<TCO, TCI, VEC>(w, split, bci, bco, reinterpret_cast<char*>(lds));
+}
+template <int SHAPE>
+constexpr int wg_lds_floats() {
+  return SHAPE == WG_2x2 ? WgTile<2, 2>::LDS : SHAPE == WG_1x1 ? WgTile<1, 1>::LDS : WgTile<2, 1>::LDS;
+}
+
+template <int SHAPE, bool VEC>
+__global__ __launch_bounds__(256, SHAPE == WG_2x2 ? 2 : 3) void pw_wgrad_f32_kernel(WgArgs w) {
+  __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
+  int bx, t;
+  pw_block_xy((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x, gridDim.y * gridDim.z,
+              w.tile_order, bx, t);
+  pw_wgrad_shape<SHAPE, VEC>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, reinterpret_cast<float*>(lds));
+}
+
+// the wide product's forms in the launch below: more than 32 channels in, an addend
+constexpr int PW_WIDE4 = PW_WIDE + 1, PW_WIDE_ADD = PW_WIDE + 2, PW_WIDE4_ADD = PW_WIDE + 3;
+
+// Input gradient and weight-gradient partials of one pointwise conv in ONE launch: the two products only share their input
+// g, and each alone is too short to fill the chip, so their blocks are dealt from one grid: block ids [0, nA) are those of
+// the input-gradient product, the rest the (x, y, z) grid of the weight-gradient kernel.
+template <int VAR, int SHAPE, bool VEC>
+__global__ __launch_bounds__(256, 2)
+void pw_bwd_dual_kernel(PwArgs a, WgArgs w, unsigned nA, unsigned gWx, unsigned gWy) {
+  __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
+  static_assert(wg_lds_floats<SHAPE>() >= 4 * 16 * 64, "the product kernels use 16 KB");
+  if (blockIdx.x < nA) {  // uniform per block
+    int bx, by;
+    pw_product_xy(blockIdx.x, nA, a, bx, by);
+    if constexpr (VAR == PW_1x1) pw_body<1, 1>(a, bx, by, nullptr, 0);
+    else if constexpr (VAR == PW_1x2) pw_body<1, 2>(a, bx, by, nullptr, 0);
+    else if constexpr (VAR == PW_2x1) pw_body<2, 1>(a, bx, by, nullptr, 0);
+    else if constexpr (VAR == PW_2x2) pw_body<2, 2>(a, bx, by, nullptr, 0);
+    else if constexpr (VAR == PW_KS4) pw_ks_body<1, 4>(a, bx, by, reinterpret_cast<float(*)[16][64]>(lds));
+    else if constexpr (VAR == PW_KS4x2) pw_ks_body<2, 4>(a, bx, by, reinterpret_cast<float(*)[16][64]>(lds));
+    else if constexpr (VAR == PW_WIDE) pw_wide_body<2, false>(a, bx, by, nullptr);
+    else if constexpr (VAR == PW_WIDE4) pw_wide_body<4, false>(a, bx, by, nullptr);
+    else if constexpr (VAR == PW_WIDE_ADD) pw_wide_body<2, true>(a, bx, by, nullptr);
+    else pw_wide_body<4, true>(a, bx, by, nullptr);
+  } else {
+    int bx, t;  // the weight-gradient ids start at nA: ids that agree mod 8 still share an XCD
+    pw_block_xy(blockIdx.x - nA, gWx, (gridDim.x - nA) / gWx, w.tile_order, bx, t);
+    pw_wgrad_shape<SHAPE, VEC>(w, bx, t % (int)gWy, t / (int)gWy, reinterpret_cast<float*>(lds));
+  }
+}
+// G[i] += sum_c part[c][i]: 64 outputs per block, four interleaved part lanes, fixed order
+__global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __restrict__ part,
+                                                               float* __restrict__ G, size_t n, int parts) {
+  __shared__ float sh[4][64];
+  const int o = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const size_t i = (size_t)blockIdx.x * 64 + o;
+  float s = 0.f;
+  if (i < n) {
+    int c = q;
+    for (; c + 28 < parts; c += 32) {  // eight independent loads in flight
+      float v0 = part[(size_t)c * n + i], v1 = part[(size_t)(c + 4) * n + i];
+      float v2 = part[(size_t)(c + 8) * n + i], v3 = part[(size_t)(c + 12) * n + i];
+      float v4 = part[(size_t)(c + 16) * n + i], v5 = part[(size_t)(c + 20) * n + i];
+      float v6 = part[(size_t)(c + 24) * n + i], v7 = part[(size_t)(c + 28) * n + i];
+      s += ((v0 + v1) + (v2 + v3)) + ((v4 + v5) + (v6 + v7));
+    }
+    for (; c < parts; c += 4) s += part[(size_t)c * n + i];
+  }
+  sh[q][o] = s;
+  __syncthreads();
+  if (q == 0 && i < n) G[i] += (sh[0][o] + sh[1][o]) + (sh[2][o] + sh[3][o]);
+}
+
+// Block shape and number of pixel ranges of a weight gradient.  A larger block reads and splits less per product, and leaves
+// fewer blocks: 204 registers at 2x2 (two blocks per compute unit), 130 at 2x1, 82 at 1x1 (four and more).  Measured, us:
+//   one channel tile on a side: 24 -> 144 at 32 x 56x56 1x1 17.3, 2x1 18.1; 192 -> 32 at 32 x 28x28 9.3, 9.5
+//   much work: 64 -> 256 at 32 x 56x56 2x2 33.3, 2x1 35.2; 512 -> 256 at 8 x 28x28 19.9, 20.7; many tiles over few pixels:
+//     512 -> 2048 at 8 x 7x7 20.5, 24.0; 256 -> 1024 at 8 x 14x14 13.8, 14.8
+//   between: 40 -> 240 at 32 x 30x30 2x1 14.5, 2x2 15.6; 64 -> 64 at 32 x 56x56 14.8, 15.8
+//   little (less than two blocks per compute unit): the smallest blocks with one step upwards
+// A range is at most WG_CHAIN steps: chains of 32 roundings.  Relative error of dW against 64 bits 5e-8 to 9e-8 over these
+// sizes (the fp32 matrix instructions with their sums in two levels: 8e-8 to 1.3e-7).
+static constexpr int WG_CHAIN = 32;
+struct WgPick { int shape; dim3 grid; };
+static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
+  const int a = cdiv(Cout, 32), b = cdiv(Cin, 32);
+  static const int tco[4] = {2, 2, 1, 1}, tci[4] = {2, 1, 2, 1}, blocks[4] = {512, 768, 768, 1024};
+  const long NQ = (long)N * HW;
+  WgPick p;
+  auto splits = [&](int shape, int px) {
+    p.shape = shape;
+    const int gy = cdiv(b, tci[shape]), gz = cdiv(a, tco[shape]);
+    const long fill = std::min((long)cdiv(blocks[shape], (long)gy * gz), NQ / px);
+    const long s = std::min(std::max(fill, (long)cdiv(NQ, WG_CHAIN * 64)), (long)cap);
+    p.grid = dim3((unsigned)s, gy, gz);
+    return s * gy * gz;
+  };
+  if (a == 1 || b == 1) splits(WG_1x1, 64);
+  else if (NQ * a * b >= 600000 || (NQ < 2048 && a * b >= 256)) splits(WG_2x2, 128);
+  else if (splits(a % 2 && b % 2 == 0 ? WG_1x2 : WG_2x1, 128) < 512) splits(WG_1x1, 64);
+  return p;
+}
+int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW, int cap) { return (int)wg_pick(N, Cin, Cout, HW, cap).grid.x; }
+// four wavefronts of 256, 128, 64 or 32 pixels of one sample per chunk, the most that leave 768 tiles and chunks
+int pw_wgrad_f32_small_parts(int N, int Cin, int Cout, int HW) {
+  const long tiles = (long)cdiv(Cin, 32) * cdiv(Cout, 32);
+  int px = 256;
+  while (px > 32 && (long)N * cdiv(HW, 4 * px) * tiles < 768) px /= 2;
+  return N * cdiv(HW, 4 * px);
+}
+size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW, int cap) {
+  return (size_t)pw_wgrad_f32_parts(N, Cin, Cout, HW, cap) * Cin * Cout;
+}
+static WgArgs wg_args(const float* g, const float* x, float* part, int N, int Cin, int Cout, int HW, const WgPick& p) {
+  WgArgs w;
+  w.g = g; w.x = x; w.part = part;
+  w.Cin = Cin; w.Cout = Cout; w.HW = HW; w.rHW = plane_reciprocal(HW);
+  w.NQ = (long)N * HW;
+  w.splits = (int)p.grid.x;
+  w.tile_order = p.grid.y * p.grid.z > 1;
+  return w;
+}
+template <int SHAPE>
+static void launch_wgrad(hipStream_t st, const WgArgs& w, dim3 grid, bool vec) {
+  if (vec) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true>), grid, dim3(256), 0, st, w);
+  else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false>), grid, dim3(256), 0, st, w);
+}
+static void launch_wgrad(hipStream_t st, const WgArgs& w, const WgPick& p) {
+  const bool vec = w.HW % 4 == 0;
+  switch (p.shape) {
+    case WG_2x2: launch_wgrad<WG_2x2>(st, w, p.grid, vec); break;
+    case WG_2x1: launch_wgrad<WG_2x1>(st, w, p.grid, vec); break;
+    case WG_1x2: launch_wgrad<WG_1x2>(st, w, p.grid, vec); break;
+    default: launch_wgrad<WG_1x1>(st, w, p.grid, vec); break;
+  }
+}
+void pw_wgrad_f32(hipStream_t st, const float* g, const float* x, float* part, float* G, int N,
+                  int Cin, int Cout, int HW, int cap) {
+  const WgPick p = wg_pick(N, Cin, Cout, HW, cap);
+  launch_wgrad(st, wg_args(g, x, part, N, Cin, Cout, HW, p), p);
+  size_t n = (size_t)Cin * Cout;
+  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)p.grid.x);
+}
+
+template <int VAR, int SHAPE>
+static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, unsigned nA, dim3 gW) {
+  const dim3 grid(nA + gW.x * gW.y * gW.z);
+  if (w.HW % 4 == 0)
+    KLAUNCH_NAMED("pw_bwd_dual_kernel", (pw_bwd_dual_kernel<VAR, SHAPE, true>), grid, dim3(256), 0, st, a, w, nA, gW.x, gW.y);
+  else
+    KLAUNCH_NAMED("pw_bwd_dual_kernel", (pw_bwd_dual_kernel<VAR, SHAPE, false>), grid, dim3(256), 0, st, a, w, nA, gW.x, gW.y);
+}
+template <int VAR>
+static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, unsigned nA, const WgPick& p) {
+  switch (p.shape) {
+    case WG_2x2: launch_dual<VAR, WG_2x2>(st, a, w, nA, p.grid); break;
+    case WG_2x1: launch_dual<VAR, WG_2x1>(st, a, w, nA, p.grid); break;
+    case WG_1x2: launch_dual<VAR, WG_1x2>(st, a, w, nA, p.grid); break;
+    default: launch_dual<VAR, WG_1x1>(st, a, w, nA, p.grid); break;
+  }
+}
+
+void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
+                     float* part, float* G, int N, int Cin, int Cout, int HW, int cap) {
+  const PwPick p = pw_pick((long)N * HW, HW, Cout, Cin, true);  // dx = W^T g (+ add)
+  const PwArgs a = pw_args(Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW, p);
+  const WgPick wp = wg_pick(N, Cin, Cout, HW, cap);
+  const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
+  const unsigned nA = p.gx * p.gy;
+  switch (p.var) {
+    case PW_1x1: launch_dual<PW_1x1>(st, a, w, nA, wp); break;
+    case PW_1x2: launch_dual<PW_1x2>(st, a, w, nA, wp); break;
+    case PW_2x1: launch_dual<PW_2x1>(st, a, w, nA, wp); break;
+    case PW_2x2: launch_dual<PW_2x2>(st, a, w, nA, wp); break;
+    case PW_KS4: launch_dual<PW_KS4>(st, a, w, nA, wp); break;
+    case PW_KS4x2: launch_dual<PW_KS4x2>(st, a, w, nA, wp); break;
+    case PW_WIDE:
+      if (a.KG <= 2 && !add) launch_dual<PW_WIDE>(st, a, w, nA, wp);
+      else if (!add) launch_dual<PW_WIDE4>(st, a, w, nA, wp);
+      else if (a.KG <= 2) launch_dual<PW_WIDE_ADD>(st, a, w, nA, wp);
+      else launch_dual<PW_WIDE4_ADD>(st, a, w, nA, wp);
+      break;
+    case PW_KS8:  // blocks of eight wavefronts: the two go as separate launches
+      launch_product(st, a, p);
+      launch_wgrad(st, w, wp);
+      break;
+  }
+  size_t n = (size_t)Cin * Cout;
+  if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)wp.grid.x);
+}
+
+// (sums in 64 bits: the kernel waits for memory, and adding partials in 32 bits was a third of the rounding error of a
+// weight gradient)
+__global__ __launch_bounds__(256) void reduce_tasks_kernel(const RedTask* __restrict__ tasks,
+                                                           const unsigned short* __restrict__ block_task) {
+  __shared__ double sh[4][64];
+  const RedTask t = tasks[block_task[blockIdx.x]];
+  if (t.wide) {  // uniform per block
+    const size_t i4 = ((size_t)(blockIdx.x - t.block0) * 256 + threadIdx.x) * 4;
+    if (i4 >= t.n) return;
+    const float* p4 = t.part + i4;
+    const size_t st4 = t.stride;
+    const int parts4 = (int)t.parts;
+    double s4[4] = {0.0, 0.0, 0.0, 0.0};
+    int c4 = 0;
+    for (; c4 + 4 <= parts4; c4 += 4) {
+      const float4 v0 = *reinterpret_cast<const float4*>(p4 + (size_t)c4 * st4);
+      const float4 v1 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 1) * st4);
+      const float4 v2 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 2) * st4);
+      const float4 v3 = *reinterpret_cast<const float4*>(p4 + (size_t)(c4 + 3) * st4);
+      s4[0] += ((double)v0.x + v1.x) + ((double)v2.x + v3.x);
+      s4[1] += ((double)v0.y + v1.y) + ((double)v2.y + v3.y);
+      s4[2] += ((double)v0.z + v1.z) + ((double)v2.z + v3.z);
+      s4[3] += ((double)v0.w + v1.w) + ((double)v2.w + v3.w);
+    }
+    for (; c4 < parts4; ++c4) {
+      const float4 v = *reinterpret_cast<const float4*>(p4 + (size_t)c4 * st4);
+      s4[0] += v.x; s4[1] += v.y; s4[2] += v.z; s4[3] += v.w;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      size_t out = i4 + e;
+      if (t.taps > 1) {
+        const size_t tp = out / t.mn;
+        out = (out - tp * t.mn) * t.taps + tp;
+      }
+      t.G[out] = (float)(t.G[out] + s4[e]);
+    }
+    return;
+  }
+  const int o = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const size_t n = t.n, st = t.stride;
+  const size_t i = (size_t)(blockIdx.x - t.block0) * 64 + o;
+  const int parts = (int)t.parts;
+  const float* p = t.part + i;
+  double s = 0.0;
+  if (i < n) {
+    int c = q;
+    for (; c + 28 < parts; c += 32) {  // eight independent loads in flight
+      const double v0 = p[(size_t)c * st], v1 = p[(size_t)(c + 4) * st];
+      const double v2 = p[(size_t)(c + 8) * st], v3 = p[(size_t)(c + 12) * st];
+      const double v4 = p[(size_t)(c + 16) * st], v5 = p[(size_t)(c + 20) * st];
+      const double v6 = p[(size_t)(c + 24) * st], v7 = p[(size_t)(c + 28) * st];
+      s += ((v0 + v1) + (v2 + v3)) + ((v4 + v5) + (v6 + v7));
+    }
+    for (; c < parts; c += 4) s += p[(size_t)c * st];
+  }
+  sh[q][o] = s;
+  __syncthreads();
+  if (q == 0 && i < n) {
+    size_t out = i;
+    if (t.taps > 1) {
+      const size_t tp = i / t.mn;
+      out = (i - tp * t.mn) * t.taps + tp;
+    }
+    t.G[out] = (float)(t.G[out] + ((sh[0][o] + sh[1][o]) + (sh[2][o] + sh[3][o])));
+  }
+}
+void reduce_tasks_f32(hipStream_t st, const RedTask* tasks_dev, const unsigned short* block_task_dev, int nblocks) {
+  KLAUNCH(reduce_tasks_kernel, dim3(nblocks), dim3(256), 0, st, tasks_dev, block_task_dev);
+}
+
+void reduce_parts_acc_f32(hipStream_t st, const float* part, float* G, size_t n, int parts) {
+  KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, parts);
+}
+
+}  // namespace ast

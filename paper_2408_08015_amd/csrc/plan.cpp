@@ -89,7 +89,7 @@ ast_status build_plan(Stage& s, std::string& err) {
           op.sh_off = shadow; shadow += (size_t)Cout * k * k * Cin;   // [Cout][tap][Cin]
           op.sh2_off = shadow; shadow += (size_t)Cout * k * k * Cin;  // [Cin][tap flipped][Cout]
           if (i + 1 < nl && s.layers[i + 1].kind == AST_RELU) { op.act = 1; ++i; }
-        } else if (k == 1 && st == 1 && pad == 0 && g == 1) {
+        } else if (k == 1 && st == 1 && pad == 0 && g == 1 && pw_conv_supported(Cin, Cout, A.h * A.w)) {
           op.kind = OP_CONV_PW;
         } else if (k == 3 && pad == 1 && g == Cin && Cin == Cout && (st == 1 || st == 2) && !hb &&
                    dw3x3_supported(A.h, A.w, st)) {
@@ -327,8 +327,8 @@ ast_status build_plan(Stage& s, std::string& err) {
   size_t wpk = 0;
   for (Op& op : s.ops)
     if (op.kind == OP_CONV_PW) {
-      op.wp_off = wpk; wpk += pw_pack_floats(op.cout, op.cin);
-      op.wp2_off = wpk; wpk += pw_pack_floats(op.cin, op.cout);
+      op.wp_off = wpk; wpk += x3_pack_floats(op.cout, op.cin);
+      op.wp2_off = wpk; wpk += x3_pack_floats(op.cin, op.cout);
     } else if (op.kind == OP_CONV_GK) {   // the weights as one [cout][cin*k*k] matrix
       op.wp_off = wpk; wpk += conv_gatherk_pack_floats(op.cin, op.cout, op.k);
     } else if (op.kind == OP_CONV_3X3) {  // k*k copies (one per tap) for each direction
