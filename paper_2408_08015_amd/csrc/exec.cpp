@@ -555,9 +555,11 @@ static ast_status build_pack_tasks(Stage& s, std::string& err) {
       if (tasks.size() + 2 * kk >= 65535) return AST_OK;
       const float* W = s.W + op.w_off;
       for (int t = 0; t < kk; ++t)
-        if (!add(W + t, op.cin * kk, kk, op.wp_off + t * pw_pack_floats(op.cout, op.cin), op.cout, op.cin, false)) return AST_OK;
+        if (!add(W + t, op.cin * kk, kk, op.wp_off + t * conv_mfma_pack_floats(op.cout, op.cin, op.wp_split),
+                 op.cout, op.cin, op.wp_split)) return AST_OK;
       for (int t = 0; t < kk; ++t)
-        if (!add(W + t, kk, op.cin * kk, op.wp2_off + t * pw_pack_floats(op.cin, op.cout), op.cin, op.cout, false)) return AST_OK;
+        if (!add(W + t, kk, op.cin * kk, op.wp2_off + t * conv_mfma_pack_floats(op.cin, op.cout, op.wp2_split),
+                 op.cin, op.cout, op.wp2_split)) return AST_OK;
     }
   if (tasks.empty()) return AST_OK;
   hipError_t e;
@@ -850,10 +852,10 @@ ast_status refresh_shadow(Stage& s, std::string& err) {
       const float* W = s.W + op.w_off;
       const int kk = op.k * op.k;
       for (int t = 0; t < kk; ++t) {
-        pw_pack_f32(s.stream, W + t, op.cin * kk, kk, s.wpack + op.wp_off + t * pw_pack_floats(op.cout, op.cin), op.cout,
-                    op.cin, false);
-        pw_pack_f32(s.stream, W + t, kk, op.cin * kk, s.wpack + op.wp2_off + t * pw_pack_floats(op.cin, op.cout), op.cin,
-                    op.cout, false);
+        pw_pack_f32(s.stream, W + t, op.cin * kk, kk, s.wpack + op.wp_off + t * conv_mfma_pack_floats(op.cout, op.cin, op.wp_split),
+                    op.cout, op.cin, op.wp_split);
+        pw_pack_f32(s.stream, W + t, kk, op.cin * kk, s.wpack + op.wp2_off + t * conv_mfma_pack_floats(op.cin, op.cout, op.wp2_split),
+                    op.cin, op.cout, op.wp2_split);
       }
     } else if (!s.bf16) {
       continue;  // the remaining copies are bf16 layouts

@@ -85,7 +85,8 @@ bool dw3x3_supported(int H, int W, int stride);  // else the generic grouped-con
 // and the weight-gradient partials in `part` (conv_mfma_wgrad_ws floats, conv_mfma_wgrad_parts chunks of
 // [Cout][Cin][k*k]); G (may be NULL: the caller reduces the partials) += their sum.
 bool conv_mfma_supported(int Cin, int Cout, int k, int stride, int pad, int groups, int H, int W);
-size_t conv_mfma_pack_floats(int Mdim, int Kdim, int k);
+// (copies for the product on the bf16 matrix cores, where conv_x3_takes it, are split ones)
+size_t conv_mfma_pack_floats(int Mdim, int Kdim, bool split);  // words of one copy
 // At most `cap` partials; the small count is what a stage falls back on to fit the static scratch array.
 int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
 int conv_mfma_wgrad_small_parts(int N, int Cin, int Cout, int H, int W, int k, int stride);
@@ -102,6 +103,11 @@ void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float*
 hipError_t conv_lds_allow();
 bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
                       const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S);
+// Products on the bf16 matrix cores, for channel counts that fill their tiles; Wp: split copies.  Which of the two packed
+// layouts a direction's copies have is decided by conv_x3_takes alone (H, W: the conv's input).
+bool conv_x3_takes(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, int S);
+bool conv_x3_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
+                     const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S);
 int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap);
 void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const float* x, float* part, int N, int Cin, int Cout,
                     int H, int W, int KS, int S, int cap);

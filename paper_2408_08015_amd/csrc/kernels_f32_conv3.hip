@@ -560,7 +560,9 @@ bool conv_mfma_supported(int Cin, int Cout, int k, int stride, int pad, int grou
   return shape && groups == 1 && Cin >= 8 && Cout >= 8 && H >= 1 && W >= 1 && (long)H * W < (1L << 30);
 }
 
-size_t conv_mfma_pack_floats(int Mdim, int Kdim, int k) { return (size_t)k * k * pw_pack_floats(Mdim, Kdim); }
+size_t conv_mfma_pack_floats(int Mdim, int Kdim, bool split) {
+  return split ? x3_pack_floats(Mdim, Kdim) : pw_pack_floats(Mdim, Kdim);
+}
 
 int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
   if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) return lp;
@@ -582,6 +584,7 @@ size_t conv_mfma_wgrad_ws(int N, int Cin, int Cout, int H, int W, int k, int str
 
 void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y, const float* bias, int N, int Cin,
                        int Cout, int H, int W, int k, int stride) {
+  if (conv_x3_product(st, product_name(k, stride), false, Wp, x, y, bias, N, Cin, Cout, H, W, k, stride)) return;
   if (conv_lds_product(st, product_name(k, stride), false, Wp, x, y, bias, N, Cin, Cout, H, W, k, stride)) return;
   const int Ho = out_dim(H, k, stride), Wo = out_dim(W, k, stride);
   if (k == 3) launch_product<3, false>(st, product_name(k, stride), Wp, x, y, bias, N, Cin, Cout, Ho, Wo, H, W, stride);
@@ -591,7 +594,8 @@ void conv_mfma_fwd_f32(hipStream_t st, const float* Wp, const float* x, float* y
 void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* x, float* part,
                        float* G, int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
   const int Ho = out_dim(H, k, stride), Wo = out_dim(W, k, stride);
-  if (dx && !conv_lds_product(st, product_name(k, stride), true, Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, k, stride)) {
+  if (dx && !conv_x3_product(st, product_name(k, stride), true, Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, k, stride) &&
+      !conv_lds_product(st, product_name(k, stride), true, Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, k, stride)) {
     if (k == 3) launch_product<3, true>(st, product_name(k, stride), Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, Ho, Wo, stride);
     else launch_product<1, true>(st, product_name(k, stride), Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, Ho, Wo, stride);
   }

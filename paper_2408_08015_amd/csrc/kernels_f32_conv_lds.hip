@@ -18,6 +18,7 @@
 
 #include "device_utils.h"
 #include "kernels.h"
+#include "kernels_f32_x3.h"
 #include "prof.h"
 
 namespace ast {
@@ -29,7 +30,6 @@ __host__ __device__ constexpr int round_up64(int v) { return (v + 63) & ~63; }
 // floor(n / d) = mulhi(n, reciprocal(d)) for d > 1 while n * d < 2^32; reciprocal(1) is 0
 inline unsigned reciprocal(unsigned d) { return d == 1 ? 0 : (unsigned)(((1ull << 32) + d - 1) / d); }
 constexpr size_t kProductLds = 128 * 1024, kWgradLds = 156 * 1024;
-constexpr unsigned kOutside = 0x80000000u;  // buffer offset beyond every extent: a copy writes zeros
 // The copies address a whole tensor in memory with 32-bit byte offsets below kOutside.
 inline bool copies_reach(int N, int C, int H, int W) { return (size_t)N * C * H * W * 4 < kOutside; }
 
@@ -331,8 +331,8 @@ void launch_one(hipStream_t st, const char* name, const LdsArgs& a, const LdsPic
   KLAUNCH_NAMED(name, (conv_lds_f32_kernel<MT, ALL>), grid, dim3(64 * p.WN * p.WK), p.lds, st, a);
 }
 
-// The sizes of a product and its block shape; false: no shape fits, or the tensors are too large.
-bool plan_product(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, int S, LdsArgs& a, int& ncls, LdsPick& p) {
+// The sizes of a product and its classes of result pixels; false: the tensors are too large.
+bool product_sizes(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, int S, LdsArgs& a, int& ncls) {
   const int pad = KS / 2, Ho = (H + 2 * pad - KS) / S + 1, Wo = (W + 2 * pad - KS) / S + 1;
   a = {};
   a.N = N; a.Kdim = Kdim; a.Mdim = Mdim; a.KG = cdiv(Kdim, 8); a.KS = KS;
@@ -375,8 +375,12 @@ bool plan_product(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, i
       ++ncls;
     }
   a.RW = a.XW + 2;
-  if (!pick_product(a, ncls, p)) return false;
   a.rRW = reciprocal(a.RW); a.rXH1 = reciprocal(a.XH + 1);
+  return true;
+}
+// ... and the block shape; false: no shape fits.
+bool plan_product(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, int S, LdsArgs& a, int& ncls, LdsPick& p) {
+  if (!product_sizes(dgrad, N, Kdim, Mdim, H, W, KS, S, a, ncls) || !pick_product(a, ncls, p)) return false;
   a.WN = p.WN; a.WK = p.WK; a.rows = p.rows; a.NP = p.NP; a.PL = p.PL; a.CH = p.CH;
   return true;
 }
@@ -399,6 +403,390 @@ bool conv_lds_product(hipStream_t st, const char* name, bool dgrad, const float*
   const bool all = ncls == 1 && a.cls[0].nr * a.cls[0].nc == 9;
   if (p.MT == 2) all ? launch_one<2, true>(st, name, a, p, grid) : launch_one<2, false>(st, name, a, p, grid);
   else all ? launch_one<1, true>(st, name, a, p, grid) : launch_one<1, false>(st, name, a, p, grid);
+  return true;
+}
+
+// ------------------------------------------------------------------ product on the bf16 matrix cores
+namespace {
+
+// The same product with its operands split in three (kernels_f32_x3.h).  Pixels are split once per block on their way to
+// LDS, where eight channels of a staged position lie together, three planes of 16-byte words [piece][group of 8][position]:
+// a tap of 32 pixels and 16 channels is three aligned 16-byte reads per lane, conflict-free (positions of neighbouring pixels
+// are neighbours).  They travel through registers, loaded between the taps of the chunk before and split at its end.
+//
+// Block: WM row tiles x WN groups of 32 * NT pixels x WK shares of the contraction, one wavefront each.  A wavefront's weights
+// (3 KB per tap and group) come from L2 and are its largest stream: 64 bytes per clock and compute unit with NT = 1 at the full
+// matrix rate, 32 with 2.  They are requested up to two taps ahead, in front of that tap's share of the pixel loads: vector
+// memory returns in order, so weights requested behind the pixels of a chunk would wait for them.
+struct X3Shape { int NT, NI, WM, WN, WK, rows, NP; size_t lds; double cost; };
+struct X3Args {
+  LdsArgs p;
+  int WM;
+  size_t x_words, y_words;
+};
+
+// one result by its definition
+__device__ __forceinline__ float x3_element(const LdsArgs& a, const LdsClass& c, unsigned n, int i, int j, int m) {
+  float s = 0.f;
+  for (int t = 0; t < c.nr * c.nc; ++t) {
+    const unsigned rc = c.rows >> (8 * (t / c.nc)), cc = c.cols >> (8 * (t % c.nc));
+    const int h = a.SI * i + (int)(rc & 15) - 1, x = a.SI * j + (int)(cc & 15) - 1;
+    if (h < 0 || h >= a.XH || x < 0 || x >= a.XW) continue;
+    const float* xp = a.X + (size_t)n * a.Kdim * a.XHW + (size_t)(h * a.XRW + x) * a.XS;
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint4*>(a.Wp) +
+        (size_t)((rc >> 4 & 15) * a.KS + (cc >> 4 & 15)) * a.tap_stride + (size_t)(m >> 5) * a.KG * 192 + (m & 31));
+    for (int k = 0; k < a.Kdim; ++k) {
+      const size_t o = ((size_t)(k >> 4) * 192 + 32 * ((k >> 3) & 1)) * 4 + ((k & 7) >> 1);
+      float p[3];
+      for (int e = 0; e < 3; ++e) {
+        const uint32_t u = w[o + (size_t)e * 256];
+        p[e] = __uint_as_float((k & 1) ? u & 0xffff0000u : u << 16);
+      }
+      s = fmaf(p[0] + (p[1] + p[2]), xp[(size_t)k * a.XHW], s);
+    }
+  }
+  return s;
+}
+
+template <int NT, int TAPS, int NI>
+__device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c, char* lds, int tile0, unsigned q0) {
+  const LdsArgs& a = xa.p;
+  const int tid = threadIdx.x, lane = tid & 63, T = blockDim.x, waves = T >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
+  const int col = lane & 31, half = lane >> 5;
+  const int WM = xa.WM, WN = a.WN, WK = a.WK, wm = wave % WM, wr = wave / WM, wn = wr % WN, wk = wr / WN;
+  const int XH1 = a.XH + 1, RW = a.RW, KG = a.KG, NP = a.NP;
+  const unsigned PHW = (unsigned)(c.PH * c.PW);
+  const unsigned n0 = q0 / PHW;
+  const int vr0 = (int)n0 * XH1 + a.SI * (int)((q0 - n0 * PHW) / (unsigned)c.PW);
+  const int G8 = 2 * WK, PL = NP * 16, PS = G8 * PL, BS = 3 * PS;  // bytes of a group, a piece and a chunk
+  const int tile = tile0 + wm;
+  const bool live = tile * 32 < a.Mdim;  // uniform per wavefront
+
+  // staging: item i of a thread is a group of eight channels of one position
+  const __amdgpu_buffer_rsrc_t rx = rsrc_of(a.X, a.x_bytes);
+  unsigned voff[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int u = tid + i * T, g8 = u / NP, pos = u - g8 * NP;
+    const unsigned v = virtual_offset(pos, vr0, a.rows, a.rRW, a.rXH1, a.N, a.XH, a.XW, a.XRW, a.XS, (unsigned)a.Kdim * a.XHW);
+    voff[i] = g8 < G8 && v != kOutside ? v + (unsigned)(g8 * 8) * a.XHW * 4u : kOutside;
+  }
+  float xr[NI][8];
+  auto fetch = [&](int i, int ch) __attribute__((always_inline)) {
+    const unsigned k0 = (unsigned)(ch * 16 * WK);
+    unsigned vo = voff[i];
+    if ((ch + 1) * WK > KG) vo = k0 + (unsigned)((tid + i * T) / NP * 8) < (unsigned)a.Kdim ? vo : kOutside;  // uniform: a short chunk
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      xr[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, vo, (k0 + j) * a.XHW * 4u, 0));
+  };
+  auto put = [&](int i, int buf) __attribute__((always_inline)) {
+    uint4 p[3];
+    split3(xr[i], p);
+    const int u = tid + i * T;
+    if (u < G8 * NP) {
+      char* const d = lds + buf * BS + u * 16;
+      *reinterpret_cast<uint4*>(d) = p[0];
+      *reinterpret_cast<uint4*>(d + PS) = p[1];
+      *reinterpret_cast<uint4*>(d + 2 * PS) = p[2];
+    }
+  };
+
+  // the pixels of the wavefront: position of tap (0, 0) in LDS
+  unsigned qn[NT];
+  int qi[NT], qj[NT];
+  bool qv[NT];
+  const char* bl[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const unsigned q = q0 + (wn * NT + n) * 32 + col;
+    qv[n] = q < c.npix;
+    const unsigned qc = qv[n] ? q : c.npix - 1;
+    qn[n] = qc / PHW;
+    const int qp = (int)(qc - qn[n] * PHW);
+    qi[n] = qp / c.PW;
+    qj[n] = qp - qi[n] * c.PW;
+    bl[n] = lds + (2 * wk + half) * PL + (((int)qn[n] * XH1 + a.SI * qi[n] - vr0) * RW + a.SI * qj[n]) * 16;
+  }
+  unsigned woff[TAPS];  // tap t: offset of its weight copy, and of its shift in LDS (uniform)
+  int boff[TAPS];
+#pragma unroll
+  for (int t = 0; t < TAPS; ++t) {
+    const int ri = t / c.nc, ci = t - ri * c.nc;
+    const unsigned rc = c.rows >> (8 * ri), cc = c.cols >> (8 * ci);
+    woff[t] = ((rc >> 4 & 15) * (unsigned)a.KS + (cc >> 4 & 15)) * a.tap_stride;
+    boff[t] = ((int)(rc & 15) * RW + (int)(cc & 15)) * 16;
+  }
+  constexpr int RING = TAPS == 9 ? 3 : TAPS;  // taps whose weights are in registers (9 of 9: 3 % slower)
+  const uint4* const wl = reinterpret_cast<const uint4*>(a.Wp) + (size_t)min(tile, (a.Mdim - 1) / 32) * KG * 192 + lane;
+  uint4 A[RING][3];
+  auto ldA = [&](int t, int ch) __attribute__((always_inline)) {
+    const uint4* w = wl + (woff[t] + (unsigned)min(ch * WK + wk, KG - 1) * 192u);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) A[t % RING][p] = w[p * 64];
+  };
+  floatx16 acc[NT], acs[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[n][r] = acs[n][r] = 0.f;
+  auto tap = [&](int t, int buf) __attribute__((always_inline)) {
+    constexpr int NB = NT == 1 ? 1 : 2;
+    const uint4(&w)[3] = A[t % RING];
+#pragma unroll
+    for (int n0 = 0; n0 < NT; n0 += NB) {
+      uint4 x[NB][3];
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) x[n][p] = *reinterpret_cast<const uint4*>(bl[n0 + n] + boff[t] + buf * BS + p * PS);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[2], x[n][0], acs[n0 + n]);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acc[n0 + n] = mfma_bf16(w[0], x[n][0], acc[n0 + n]);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[1], x[n][0], acs[n0 + n]);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[1], x[n][1], acs[n0 + n]);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[0], x[n][1], acs[n0 + n]);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[0], x[n][2], acs[n0 + n]);
+    }
+  };
+  auto barrier = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (loads to registers stay in flight)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i) fetch(i, 0);
+#pragma unroll
+  for (int t = 0; t < (RING < TAPS ? RING : TAPS); ++t) ldA(t, 0);
+#pragma unroll
+  for (int i = 0; i < NI; ++i) put(i, 0);
+  barrier();
+  const int nchunk = (KG + WK - 1) / WK;
+  constexpr int PER = (NI + TAPS - 1) / TAPS;  // items requested per tap
+  auto chunk = [&](int ch, auto more_c) __attribute__((always_inline)) {
+    constexpr bool more = decltype(more_c)::value;
+    const int buf = ch & 1;
+    const bool on = more || ch * WK + wk < KG;  // uniform per wavefront; only the last chunk can be short
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) {
+      if (on) tap(t, buf);
+      if (t + RING < TAPS) ldA(t + RING, ch);
+      else if constexpr (more) ldA(t + RING - TAPS, ch + 1);
+      if constexpr (more) {
+#pragma unroll
+        for (int i = t * PER; i < (t + 1) * PER; ++i)
+          if (i < NI) fetch(i, ch + 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (more) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) put(i, buf ^ 1);
+      barrier();
+    }
+  };
+  for (int ch = 0; ch + 1 < nchunk; ++ch) chunk(ch, std::true_type{});
+  chunk(nchunk - 1, std::false_type{});
+
+  const size_t OHW = (size_t)a.OH * a.OW;
+  auto row = [&](int r) { return tile * 32 + 8 * (r >> 2) + 4 * half + (r & 3); };
+  auto at = [&](int n) {
+    return a.Y + (size_t)qn[n] * a.Mdim * OHW + (size_t)(a.SO * qi[n] + c.oy) * a.OW + a.SO * qj[n] + c.ox;
+  };
+  if (WK == 1) {
+    if (!live) return;
+    float bad = 0.f;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      float* const yq = at(n);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float v = acc[n][r] + acs[n][r];
+        bad = fmaf(v, 0.f, bad);
+        if (qv[n]) yq[(size_t)row(r) * OHW] = v + (a.bias ? a.bias[row(r)] : 0.f);  // (Mdim % 32 == 0)
+      }
+    }
+    if (__any(bad != 0.f)) {  // (NaN != 0) what is not finite again by its definition, over what was stored
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      for (int n = 0; n < NT; ++n) {
+        const unsigned q = q0 + (wn * NT + n) * 32 + col;
+        if (q >= c.npix) continue;
+        const unsigned sn = q / PHW, sp = q - sn * PHW;
+        const int si = (int)(sp / (unsigned)c.PW), sj = (int)sp - si * c.PW;
+        float* const yq = a.Y + (size_t)sn * a.Mdim * OHW + (size_t)(a.SO * si + c.oy) * a.OW + a.SO * sj + c.ox;
+        for (int r = 0; r < 16; ++r)
+          yq[(size_t)row(r) * OHW] = x3_element(a, c, sn, si, sj, row(r)) + (a.bias ? a.bias[row(r)] : 0.f);
+      }
+    }
+    return;
+  }
+  float* const red = reinterpret_cast<float*>(lds);
+  const int rpw = 16 / WK;  // accumulator rows that each of the WK wavefronts finishes
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    __syncthreads();  // the partial tiles overwrite the staged pixels, and then each other
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = acc[n][r] + acs[n][r];
+    __syncthreads();
+    for (int rr = 0; rr < rpw; ++rr) {
+      const int r = wk * rpw + rr;
+      float v = 0.f;
+      for (int k = 0; k < WK; k += 2)  // fixed order
+        v += red[(((k * WN + wn) * WM + wm) * 16 + r) * 64 + lane] + red[((((k + 1) * WN + wn) * WM + wm) * 16 + r) * 64 + lane];
+      if (!qv[n] || !live) continue;
+      if (!finite_f(v)) v = x3_element(a, c, qn[n], qi[n], qj[n], row(r));
+      at(n)[(size_t)row(r) * OHW] = v + (a.bias ? a.bias[row(r)] : 0.f);
+    }
+  }
+}
+
+// ALL: one class reached by all nine taps; else the class decides (1, 2 or 4 taps, or none: zeros)
+template <int NT, bool ALL, int NI>
+__global__ __launch_bounds__(512, 2) void conv_x3_f32_kernel(X3Args xa) {
+  extern __shared__ __attribute__((aligned(16))) char xlds[];
+  const LdsArgs& a = xa.p;
+  const LdsClass& c = a.cls[blockIdx.z];
+  const unsigned id = xcd_grouped(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  // the row tiles of one pixel block share an L2, or the pixel blocks of one row tile (the larger operand)
+  const unsigned d = a.CH ? gridDim.y : gridDim.x, hi = id / d, lo = id - hi * d;
+  const int tile0 = __builtin_amdgcn_readfirstlane((int)(a.CH ? lo : hi)) * xa.WM;
+  const unsigned q0 = __builtin_amdgcn_readfirstlane(a.CH ? hi : lo) * (unsigned)(32 * NT * a.WN);
+  if (q0 >= c.npix) return;  // uniform: a smaller parity class
+  if constexpr (ALL) {
+    conv_x3_body<NT, 9, NI>(xa, c, xlds, tile0, q0);
+  } else {
+    const int nt = c.nr * c.nc;
+    if (nt == 4) conv_x3_body<NT, 4, NI>(xa, c, xlds, tile0, q0);
+    else if (nt == 2) conv_x3_body<NT, 2, NI>(xa, c, xlds, tile0, q0);
+    else if (nt == 1) conv_x3_body<NT, 1, NI>(xa, c, xlds, tile0, q0);
+    else {
+      const unsigned PHW = (unsigned)(c.PH * c.PW), P = 32 * NT * a.WN;
+      for (unsigned i = threadIdx.x; i < P * 32u * xa.WM; i += blockDim.x) {
+        const unsigned q = q0 + i % P, m = tile0 * 32 + i / P;
+        if (q >= c.npix || m >= (unsigned)a.Mdim) continue;
+        const unsigned n = q / PHW, p = q - n * PHW, r = p / (unsigned)c.PW;
+        a.Y[((size_t)n * a.Mdim + m) * a.OH * a.OW + (size_t)(a.SO * r + c.oy) * a.OW + a.SO * (p - r * c.PW) + c.ox] = 0.f;
+      }
+    }
+  }
+}
+constexpr size_t kX3Lds = 156 * 1024;
+
+bool x3_shape(const LdsArgs& a, int ncls, int NT, int WM, int WN, int WK, X3Shape& p) {
+  const int waves = WM * WN * WK, P = 32 * NT * WN;
+  if (waves > 8 || waves < 2 || (WK > 1 && WK > a.KG) || WM > a.Mdim / 32) return false;
+  p.NT = NT; p.WM = WM; p.WN = WN; p.WK = WK;
+  p.rows = 0;
+  for (int i = 0; i < ncls; ++i) p.rows = std::max(p.rows, tile_rows(P, a.cls[i].PH, a.cls[i].PW, a.SI, a.XH));
+  p.NP = (p.rows * a.RW + 15) & ~15;
+  p.NI = cdiv(2 * WK * p.NP, 64 * waves);
+  p.lds = std::max((size_t)2 * 96 * WK * p.NP, WK > 1 ? (size_t)waves * 4096 : (size_t)0);
+  return p.NI <= 4 && p.lds <= kX3Lds;
+}
+
+template <int NT, int NI>
+void launch_x3(hipStream_t st, const char* name, const X3Args& a, const X3Shape& p, dim3 grid, bool all) {
+  const dim3 block(64 * p.WM * p.WN * p.WK);
+  if (all) KLAUNCH_NAMED(name, (conv_x3_f32_kernel<NT, true, NI>), grid, block, p.lds, st, a);
+  else KLAUNCH_NAMED(name, (conv_x3_f32_kernel<NT, false, NI>), grid, block, p.lds, st, a);
+}
+template <int NT>
+void launch_x3(hipStream_t st, const char* name, const X3Args& a, const X3Shape& p, dim3 grid, bool all) {
+  switch (p.NI) {
+    case 1: launch_x3<NT, 1>(st, name, a, p, grid, all); break;
+    case 2: launch_x3<NT, 2>(st, name, a, p, grid, all); break;
+    case 3: launch_x3<NT, 3>(st, name, a, p, grid, all); break;
+    default: launch_x3<NT, 4>(st, name, a, p, grid, all); break;
+  }
+}
+void run_x3(hipStream_t st, const char* name, const LdsArgs& sizes, int ncls, const X3Shape& p, const float* Wp, const float* X,
+            float* Y, const float* bias) {
+  X3Args a;
+  a.p = sizes;
+  a.p.Wp = reinterpret_cast<const float4*>(Wp);
+  a.p.X = X; a.p.Y = Y; a.p.bias = bias;
+  a.p.KG = cdiv(sizes.Kdim, 16);
+  a.p.tap_stride = (unsigned)(x3_pack_floats(sizes.Mdim, sizes.Kdim) / 4);
+  a.p.WN = p.WN; a.p.WK = p.WK; a.p.rows = p.rows; a.p.NP = p.NP;
+  a.WM = p.WM;
+  unsigned most = 0;
+  for (int i = 0; i < ncls; ++i) most = std::max(most, a.p.cls[i].npix);
+  // (6 bytes a weight)
+  a.p.CH = (size_t)sizes.Mdim * sizes.KS * sizes.KS * 3 < (size_t)sizes.N * sizes.XH * sizes.XW * 2;
+  const dim3 grid((unsigned)cdiv(most, 32 * p.NT * p.WN), (unsigned)cdiv(sizes.Mdim / 32, p.WM), (unsigned)ncls);
+  const bool all = ncls == 1 && a.p.cls[0].nr * a.p.cls[0].nc == 9;
+  if (p.NT == 1) launch_x3<1>(st, name, a, p, grid, all);
+  else if (p.NT == 2) launch_x3<2>(st, name, a, p, grid, all);
+  else launch_x3<4>(st, name, a, p, grid, all);
+}
+
+// The block shape: enough shares of the contraction for two wavefronts per SIMD, up to four row tiles per block (more pixels
+// instead only where there are fewer), and more pixels per wavefront where there is plenty of work; of the shapes that fit, the
+// nearest.
+// Measured at ResNet50's layers (us, fp32 matrix instructions / best shape / this one's neighbours): 64 -> 64 at 32 x 56x56 104 /
+// 54 (4 pixel groups) / 59 (2) / 75 (1); 128 -> 128 at 8 x 28x28 32.5 / 20.2 (2 shares, 4 row tiles) / 20.6 (2 row tiles); 256 ->
+// 256 at 8 x 14x14 33.2 / 20.9 (4 shares) / 22.7 (2); 512 -> 512 at 8 x 7x7 36.8 / 24.0 (8 shares) / 26.3 (4).
+bool search_x3(const LdsArgs& sizes, int ncls, X3Shape& best) {
+  LdsArgs a = sizes;
+  a.KG = cdiv(sizes.Kdim, 16);
+  const int mt = sizes.Mdim / 32;
+  long tiles = 0;
+  for (int i = 0; i < ncls; ++i) tiles += sizes.cls[i].nr * sizes.cls[i].nc ? (long)cdiv(sizes.cls[i].npix, 32) * mt : 0;
+  const bool all = ncls == 1 && sizes.cls[0].nr * sizes.cls[0].nc == 9;
+  int wk = 1;
+  while (wk < 8 && wk * tiles < (all && a.KG >= 16 * wk ? 2000 : 1200) && wk * 2 <= std::max(1, a.KG / 2)) wk *= 2;
+  const int wm = std::min(mt, std::max(1, std::min(4, 8 / wk))), wn = wk == 1 && (wm < 4 || (!all && sizes.KS == 3)) ? 8 / wm : 1;
+  const int nt = all && tiles >= 6000 ? 4 : tiles >= 3000 && sizes.KS == 1 && ncls == 1 ? 2 : 1;
+  best.cost = 1e30;
+  for (int NT = 1; NT <= 4; NT *= 2)
+    for (int WM = 1; WM <= 8; ++WM)
+      for (int WN = 1; WN <= 8; WN *= 2)
+        for (int WK = 1; WK <= 8; WK *= 2) {
+          X3Shape p;
+          if (!x3_shape(a, ncls, NT, WM, WN, WK, p)) continue;
+          p.cost = 3 * std::fabs(std::log2((double)WK / wk)) + 2 * std::fabs(std::log2((double)NT / nt)) +
+                   std::fabs(std::log2((double)WM / wm)) + 1.1 * std::fabs(std::log2((double)WN / wn));
+          if (p.cost < best.cost) best = p;
+        }
+  return best.cost < 1e30;
+}
+// The sizes that this product takes; other channel counts leave its tiles partly empty and stay with the kernels above.
+bool plan_x3(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, int S, LdsArgs& a, int& ncls, X3Shape& p) {
+  if (Kdim % 16 || Mdim % 32 || !product_sizes(dgrad, N, Kdim, Mdim, H, W, KS, S, a, ncls)) return false;
+  if ((x3_pack_floats(Mdim, Kdim) / 4) * KS * KS >= kOutside) return false;
+  static thread_local std::map<std::array<int, 9>, X3Shape> seen;  // (the choice depends on the sizes alone)
+  const std::array<int, 9> key = {dgrad, N, Kdim, Mdim, H, W, KS, S, 0};
+  auto it = seen.find(key);
+  if (it == seen.end()) {
+    X3Shape q;
+    search_x3(a, ncls, q);
+    if (seen.size() >= 1024) seen.clear();
+    it = seen.emplace(key, q).first;
+  }
+  p = it->second;
+  return p.cost < 1e30;
+}
+}  // namespace
+
+bool conv_x3_takes(bool dgrad, int N, int Kdim, int Mdim, int H, int W, int KS, int S) {
+  LdsArgs a;
+  X3Shape p;
+  int ncls;
+  return plan_x3(dgrad, N, Kdim, Mdim, H, W, KS, S, a, ncls, p);
+}
+bool conv_x3_product(hipStream_t st, const char* name, bool dgrad, const float* Wp, const float* X, float* Y,
+                     const float* bias, int N, int Kdim, int Mdim, int H, int W, int KS, int S) {
+  LdsArgs a;
+  X3Shape p;
+  int ncls;
+  if (!plan_x3(dgrad, N, Kdim, Mdim, H, W, KS, S, a, ncls, p)) return false;
+  run_x3(st, name, a, ncls, p, Wp, X, Y, bias);
   return true;
 }
 
@@ -681,6 +1069,18 @@ void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const floa
 
 // The kernels of this file may use more than the default 64 KiB of dynamic LDS: allowed once per stage, for its device, always
 // up to the same sizes.  (Set per launch to that launch's size, it was state shared with the launches of other threads.)
+template <int NT, int NI>
+static hipError_t x3_allow() {
+  if (hipError_t e = hipFuncSetAttribute((const void*)conv_x3_f32_kernel<NT, true, NI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kX3Lds)) return e;
+  return hipFuncSetAttribute((const void*)conv_x3_f32_kernel<NT, false, NI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kX3Lds);
+}
+template <int NT>
+static hipError_t x3_allow() {
+  if (hipError_t e = x3_allow<NT, 1>()) return e;
+  if (hipError_t e = x3_allow<NT, 2>()) return e;
+  if (hipError_t e = x3_allow<NT, 3>()) return e;
+  return x3_allow<NT, 4>();
+}
 hipError_t conv_lds_allow() {
   const std::pair<const void*, size_t> kernels[] = {
       {(const void*)conv_lds_f32_kernel<1, false>, kProductLds}, {(const void*)conv_lds_f32_kernel<1, true>, kProductLds},
@@ -688,7 +1088,9 @@ hipError_t conv_lds_allow() {
       {(const void*)conv_lds_wgrad_f32_kernel<1>, kWgradLds},    {(const void*)conv_lds_wgrad_f32_kernel<3>, kWgradLds}};
   for (const auto& k : kernels)
     if (hipError_t e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second)) return e;
-  return hipSuccess;
+  if (hipError_t e = x3_allow<1>()) return e;
+  if (hipError_t e = x3_allow<2>()) return e;
+  return x3_allow<4>();
 }
 
 }  // namespace ast
@@ -713,5 +1115,17 @@ extern "C" int ast_conv_lds_choice(int what, int N, int Cin, int Cout, int H, in
   if (!plan_product(what == 1, N, what ? Cout : Cin, what ? Cin : Cout, H, W, KS, S, a, ncls, p)) return 0;
   out[0] = p.MT; out[1] = p.WN; out[2] = p.WK; out[3] = ncls;
   out[4] = out[5] = 0;
+  return 1;
+}
+
+// The same for the products on the bf16 matrix cores; out = {pixel groups per wavefront, row tiles, pixel groups, shares of
+// the contraction, items per thread, classes}.
+extern "C" int ast_conv_x3_choice(int dgrad, int N, int Cin, int Cout, int H, int W, int KS, int S, int out[6]) {
+  using namespace ast;
+  LdsArgs a;
+  X3Shape p;
+  int ncls;
+  if (!plan_x3(dgrad != 0, N, dgrad ? Cout : Cin, dgrad ? Cin : Cout, H, W, KS, S, a, ncls, p)) return 0;
+  out[0] = p.NT; out[1] = p.WM; out[2] = p.WN; out[3] = p.WK; out[4] = p.NI; out[5] = ncls;
   return 1;
 }

@@ -332,8 +332,12 @@ ast_status build_plan(Stage& s, std::string& err) {
     } else if (op.kind == OP_CONV_GK) {   // the weights as one [cout][cin*k*k] matrix
       op.wp_off = wpk; wpk += conv_gatherk_pack_floats(op.cin, op.cout, op.k);
     } else if (op.kind == OP_CONV_3X3) {  // k*k copies (one per tap) for each direction
-      op.wp_off = wpk; wpk += conv_mfma_pack_floats(op.cout, op.cin, op.k);
-      op.wp2_off = wpk; wpk += conv_mfma_pack_floats(op.cin, op.cout, op.k);
+      const Act& I = s.acts[op.in];
+      const size_t kk = (size_t)op.k * op.k;
+      op.wp_split = conv_x3_takes(false, I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride);
+      op.wp2_split = conv_x3_takes(true, I.n, op.cout, op.cin, I.h, I.w, op.k, op.stride);
+      op.wp_off = wpk; wpk += kk * conv_mfma_pack_floats(op.cout, op.cin, op.wp_split);
+      op.wp2_off = wpk; wpk += kk * conv_mfma_pack_floats(op.cin, op.cout, op.wp2_split);
     }
   s.wpack_floats = wpk;
 

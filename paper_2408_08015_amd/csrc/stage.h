@@ -79,7 +79,8 @@ struct Op {
   bool grad_accum = false;            // global average pool that opens a squeeze-and-excitation branch: its input
                                       // gradient is added to the one OP_SE_SCALE has already written
   size_t sh_off = 0, sh2_off = 0;     // bf16 weight copies (elements) in the shadow arena
-  size_t wp_off = 0, wp2_off = 0;     // fp32 pointwise conv: packed forward / dgrad operands (floats)
+  size_t wp_off = 0, wp2_off = 0;     // fp32 conv on the matrix cores: packed forward / dgrad operands (words)
+  bool wp_split = false, wp2_split = false;  // ... of a dense conv: split copies (conv_x3_takes)
   size_t sc_off = 0;                  // this op's private scratch region (bytes past scratch_off)
   size_t fsc_off = 0;                 // BatchNorm: its forward-pass scratch (bytes past fscratch_off)
   // fp32 BatchNorm passes taken over by the depthwise conv next to them:

@@ -97,3 +97,89 @@ def test_pointwise_operands_that_are_not_finite(A, cin, cout, h, B):
         np.testing.assert_array_equal(got[~fin], want[~fin])
         assert np.isfinite(got[fin]).all()
         np.testing.assert_allclose(got[fin], want[fin], rtol=1e-5, atol=2e-3)
+
+
+def x3_choice(dgrad, n, cin, cout, h, w, k, s):
+    import ctypes
+    out = (ctypes.c_int * 6)()
+    import paper_2408_08015_amd as A_
+    lib = ctypes.CDLL(A_.lib_path())
+    return tuple(out) if lib.ast_conv_x3_choice(dgrad, n, cin, cout, h, w, k, s, out) else None
+
+
+# dense convolutions (cin, cout, k, stride, h, w, B), and the forms of forward and input gradient: groups of 32 pixels per
+# wavefront, row tiles, pixel groups, shares of the contraction
+DENSE = [
+    ((64, 64, 3, 1, 56, 56, 32), (4, 2, 4, 1), (4, 2, 4, 1)),
+    ((64, 96, 3, 1, 9, 30, 20), (1, 3, 1, 2), None),          # three row tiles; 270 pixels a plane
+    ((32, 32, 3, 1, 5, 3, 3), (1, 1, 8, 1), (1, 1, 8, 1)),    # one tile, most of it past the last pixel
+    ((128, 64, 3, 1, 7, 7, 2), None, None),                   # tiles across samples
+    ((192, 32, 3, 1, 2, 63, 3), None, None),                  # twelve groups in eight shares' chunks
+    ((64, 64, 3, 2, 15, 14, 3), None, None),                  # classes of different sizes
+    ((160, 96, 3, 2, 8, 9, 2), None, None),
+    ((64, 128, 1, 2, 14, 14, 3), None, None),                 # 1x1: three of four classes are zeros
+    ((512, 512, 3, 1, 7, 7, 3), (1, 1, 1, 8), (1, 1, 1, 8)),
+    ((48, 64, 3, 1, 11, 11, 2), None, None),                  # forward alone: 48 is no multiple of 32
+]
+
+
+@pytest.mark.parametrize("sizes,fwd,dgrad", DENSE)
+def test_dense_forms(A, sizes, fwd, dgrad):
+    cin, cout, k, s, h, w, B = sizes
+    for d, want in ((0, fwd), (1, dgrad)):
+        got = x3_choice(d, B, cin, cout, h, w, k, s)
+        assert (got is not None) == (((cout, cin)[d] % 32, (cin, cout)[d] % 16) == (0, 0))
+        assert want is None or got[:4] == want
+    cfg = one([conv(cin, cout, k, s, k // 2)], (cin, h, w), B=min(B, 8), M=1)
+    if B == 32:     # (at 32 samples for the form alone: the oracle takes a minute)
+        return
+    inp = gen.make_inputs(cfg)
+    ora, _ = harness.run_oracle(cfg, inp, rounds=1)
+    hip, _, _ = harness.run_hip(cfg, inp, rounds=1)
+    sc = harness.score(cfg, hip, ora)
+    assert sc["r0.y"] <= bound(cin * k * k)
+    assert sc["r0.dx"] <= (bound(cout * k * k) if x3_choice(1, B, cin, cout, h, w, k, s) else 1e-6)
+
+
+@pytest.mark.parametrize("cin,cout,k,s,h,B", [(64, 64, 3, 1, 12, 4), (64, 32, 3, 2, 9, 2), (256, 64, 3, 1, 5, 2)])
+def test_dense_operands_that_are_not_finite(A, cin, cout, k, s, h, B):
+    import torch
+    rng = np.random.default_rng(4)
+    ho = (h - 1) // s + 1
+    x = rng.standard_normal((B, cin, h, h)).astype(np.float32)
+    dy = rng.standard_normal((B, cout, ho, ho)).astype(np.float32)
+    wt = (rng.standard_normal((cout, cin, k, k)) * 0.1).astype(np.float32)
+    x[0, 1, 2, 2] = np.inf
+    x[1, 5, 0, 3] = np.nan
+    x[1, 7, h - 1, 0] = 3.4e38   # rounds to infinity in bf16
+    wt[:, 7] *= 1e-6
+    dy[0, 3, 1, 1] = -np.inf
+    st = A.Stage([conv(cin, cout, k, s, k // 2)], B, 1, 1, (cin, h, h), "f32", "nchw", True,
+                 stream=torch.cuda.current_stream().cuda_stream)
+    st.set_params(wt.ravel())
+    dev = torch.device("cuda:0")
+    tx, tg = torch.from_numpy(x).to(dev), torch.from_numpy(dy).to(dev)
+    y, dx = torch.empty_like(tg), torch.empty_like(tx)
+    st.forward(0, tx, None, y, None)
+    st.backward(0, tg, dx)
+    torch.cuda.synchronize()
+    st.close()
+    with np.errstate(all="ignore"):
+        ry, rdx = np.zeros(dy.shape), np.zeros((B, cin, h + 2, h + 2))
+        xp = np.zeros((B, cin, h + 2, h + 2))
+        xp[:, :, 1:-1, 1:-1] = x
+        for u in range(k):
+            for v in range(k):
+                # (only the taps inside the image: an infinity times the zero border is no term)
+                sl = (slice(None), slice(None), slice(u, u + s * (ho - 1) + 1, s), slice(v, v + s * (ho - 1) + 1, s))
+                ry += np.einsum("oc,ncij->noij", wt[:, :, u, v].astype(np.float64), xp[sl])
+                rdx[sl] += np.einsum("oc,noij->ncij", wt[:, :, u, v].astype(np.float64), dy.astype(np.float64))
+        rdx = rdx[:, :, 1:-1, 1:-1]
+    for got, want in ((y.cpu().numpy(), ry.astype(np.float32)), (dx.cpu().numpy(), rdx.astype(np.float32))):
+        fin = np.isfinite(want)
+        assert not fin.all()
+        np.testing.assert_array_equal(got[~fin], want[~fin])
+        assert np.isfinite(got[fin]).all()
+        big = np.abs(want) > 1e6
+        np.testing.assert_allclose(got[fin & ~big], want[fin & ~big], rtol=1e-5, atol=1e-4)
+        np.testing.assert_allclose(got[fin & big], want[fin & big], rtol=1e-5)
