@@ -18,13 +18,6 @@ namespace ast {
 
 static inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
-// Sample (counted from the first one) of position r of consecutive planes of HW pixels, r < HW + 512: floor(r / HW) without
-// the forty instructions of a division.  rHW: ceil(2^20 / HW) where planes are small enough for r to pass several.
-__host__ __device__ constexpr unsigned plane_reciprocal(int HW) { return HW >= 512 ? 0u : ((1u << 20) + HW - 1) / HW; }
-__device__ __forceinline__ unsigned plane_of(unsigned r, unsigned HW, unsigned rHW) {
-  return rHW ? r * rHW >> 20 : r >= HW;  // (rHW is uniform; the error of r * rHW is below 1024 * 512)
-}
-
 struct WgArgs {  // one pointwise-conv weight-gradient launch (partials only)
   const float* g;
   const float* x;
@@ -978,7 +971,11 @@ static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, unsign
 
 void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
                      float* part, float* G, int N, int Cin, int Cout, int HW, int cap) {
-  const PwPick p = pw_pick((long)N * HW, HW, Cout, Cin, true);  // dx = W^T g (+ add)
+  PwPick p = pw_pick((long)N * HW, HW, Cout, Cin, true);  // dx = W^T g (+ add)
+  if (p.var == PW_KS8) {  // a launch has blocks of one size: four shares of the contraction cost less than a second launch
+    p.var = PW_KS4;
+    p.waves = 4;
+  }
   const PwArgs a = pw_args(Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW, p);
   const WgPick wp = wg_pick(N, Cin, Cout, HW, cap);
   const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
@@ -996,10 +993,7 @@ void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* d
       else if (a.KG <= 2) launch_dual<PW_WIDE_ADD>(st, a, w, nA, wp);
       else launch_dual<PW_WIDE4_ADD>(st, a, w, nA, wp);
       break;
-    case PW_KS8:  // blocks of eight wavefronts: the two go as separate launches
-      launch_product(st, a, p);
-      launch_wgrad(st, w, wp);
-      break;
+    default: break;
   }
   size_t n = (size_t)Cin * Cout;
   if (G) KLAUNCH(reduce_parts_acc_kernel, dim3(cdiv(n, 64)), dim3(256), 0, st, part, G, n, (int)wp.grid.x);

@@ -42,4 +42,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_words(const float* p, siz
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, __builtin_amdgcn_readfirstlane(n), 0x00020000);
 }
 
+// Sample (counted from the first one) of position r of consecutive planes of HW pixels, r < HW + 512: floor(r / HW) without
+// the forty instructions of a division.  rHW: ceil(2^20 / HW) where planes are small enough for r to pass several.
+__host__ __device__ constexpr unsigned plane_reciprocal(int HW) { return HW >= 512 ? 0u : ((1u << 20) + HW - 1) / HW; }
+__device__ __forceinline__ unsigned plane_of(unsigned r, unsigned HW, unsigned rHW) {
+  return rHW ? r * rHW >> 20 : r >= HW;  // (rHW is uniform; the error of r * rHW is below 1024 * 512)
+}
+
 }  // namespace ast
