@@ -111,6 +111,12 @@ bool conv_x3_product(hipStream_t st, const char* name, bool dgrad, const float* 
 int conv_lds_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap);
 void conv_lds_wgrad(hipStream_t st, const char* name, const float* g, const float* x, float* part, int N, int Cin, int Cout,
                     int H, int W, int KS, int S, int cap);
+// Weight gradients of 3x3 convolutions of stride 1 on the bf16 matrix cores (kernels_f32_conv_wg.hip), called by the two
+// above where it takes the sizes.
+hipError_t conv_x3_wgrad_allow();
+int conv_x3_wgrad_parts(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap);
+bool conv_x3_wgrad(hipStream_t st, const char* name, const float* g, const float* x, float* part, int N, int Cin, int Cout,
+                   int H, int W, int KS, int S, int cap);
 // 7x7 dense conv with fewer than 8 input channels (ResNet's stem) on the matrix cores: the contraction index is
 // the flattened (ci, u, v); Wp = pw_pack of W as the [Cout][Cin*49] matrix.  Forward and weight gradient
 // (partials [chunk][Cout][Cin*49] in `part`, G may be NULL: the caller reduces).

@@ -565,6 +565,7 @@ size_t conv_mfma_pack_floats(int Mdim, int Kdim, bool split) {
 }
 
 int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
+  if (const int xp = conv_x3_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) return xp;
   if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) return lp;
   return conv_mfma_wgrad_small_parts(N, Cin, Cout, H, W, k, stride);
 }
@@ -600,6 +601,11 @@ void conv_mfma_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float*
     else launch_product<1, true>(st, product_name(k, stride), Wp_t, g, dx, nullptr, N, Cout, Cin, H, W, Ho, Wo, stride);
   }
   const size_t n = (size_t)Cin * Cout * k * k;
+  if (conv_x3_wgrad(st, "conv3x3_wgrad_mfma_f32_kernel", g, x, part, N, Cin, Cout, H, W, k, stride, cap)) {
+    if (G) KLAUNCH(conv3x3_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, part, G, n,
+                   conv_x3_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap));
+    return;
+  }
   if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) {
     conv_lds_wgrad(st, k == 3 ? "conv3x3_wgrad_mfma_f32_kernel" : "conv1x1s2_wgrad_mfma_f32_kernel", g, x, part, N, Cin, Cout, H, W,
                    k, stride, cap);

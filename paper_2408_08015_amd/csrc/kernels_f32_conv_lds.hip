@@ -1088,6 +1088,7 @@ hipError_t conv_lds_allow() {
       {(const void*)conv_lds_wgrad_f32_kernel<1>, kWgradLds},    {(const void*)conv_lds_wgrad_f32_kernel<3>, kWgradLds}};
   for (const auto& k : kernels)
     if (hipError_t e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second)) return e;
+  if (hipError_t e = conv_x3_wgrad_allow()) return e;
   if (hipError_t e = x3_allow<1>()) return e;
   if (hipError_t e = x3_allow<2>()) return e;
   return x3_allow<4>();

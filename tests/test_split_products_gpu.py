@@ -183,3 +183,91 @@ def test_dense_operands_that_are_not_finite(A, cin, cout, k, s, h, B):
         big = np.abs(want) > 1e6
         np.testing.assert_allclose(got[fin & ~big], want[fin & ~big], rtol=1e-5, atol=1e-4)
         np.testing.assert_allclose(got[fin & big], want[fin & big], rtol=1e-5)
+
+
+def wgrad_choice(n, cin, cout, h, w, k, s):
+    import ctypes
+    out = (ctypes.c_int * 4)()
+    import paper_2408_08015_amd as A_
+    lib = ctypes.CDLL(A_.lib_path())
+    return tuple(out) if lib.ast_conv_wgrad_x3_choice(n, cin, cout, h, w, k, s, out) else None
+
+
+def weight_gradient(A, x, dy):
+    """Of the HIP path, and in 64 bits (terms inside the image alone)."""
+    import torch
+    (B, cin, h, w), cout = x.shape, dy.shape[1]
+    st = A.Stage([conv(cin, cout, 3, 1, 1)], B, 1, 1, (cin, h, w), "f32", "nchw", True,
+                 stream=torch.cuda.current_stream().cuda_stream)
+    st.set_params(np.zeros(cout * cin * 9, np.float32))
+    tx, tg = torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda()
+    y, dx = torch.empty_like(tg), torch.empty_like(tx)
+    st.forward(0, tx, None, y, None)
+    st.backward(0, tg, dx)
+    torch.cuda.synchronize()
+    G = st.get_grads().reshape(cout, cin, 3, 3)
+    st.close()
+    ref = np.zeros((cout, cin, 3, 3))
+    x, dy = x.astype(np.float64), dy.astype(np.float64)
+    with np.errstate(all="ignore"):
+        for u in range(3):
+            for v in range(3):
+                gs = dy[:, :, max(0, 1 - u):h - max(0, u - 1), max(0, 1 - v):w - max(0, v - 1)]
+                xs = x[:, :, max(0, u - 1):h - max(0, 1 - u), max(0, v - 1):w - max(0, 1 - v)]
+                if gs.size:
+                    ref[:, :, u, v] = (gs.transpose(1, 0, 2, 3).reshape(cout, -1) @ xs.transpose(1, 0, 2, 3).reshape(cin, -1).T)
+    return G, ref
+
+
+# (cin, cout, h, w, B), rows per stage, chunks of eight columns per row; loads of four, two and one words
+WEIGHT_GRADIENTS = [
+    ((8, 8, 1, 1, 1), 2, 1),           # one pixel
+    ((33, 65, 3, 2, 1), 4, 1),         # tiles with one channel
+    ((64, 96, 7, 7, 40), 8, 1),        # a sample per stage
+    ((40, 72, 17, 23, 5), 2, 3),       # an odd number of chunks per row
+    ((32, 32, 5, 48, 3), 1, 7),        # ... and per stage; rows of whole vectors
+    ((64, 64, 30, 54, 9), 1, 7),
+    ((64, 32, 40, 56, 8), 1, 8),       # runs of several stages: the ring goes round
+    ((264, 264, 14, 13, 4), 4, 2),
+    ((8, 40, 3, 63, 2), 1, 8),
+    ((8, 40, 20, 64, 12), 1, 9),       # the long-row form
+    ((16, 24, 9, 71, 7), 1, 9),
+    ((8, 24, 12, 127, 5), 1, 16),
+]
+
+
+@pytest.mark.parametrize("sizes,rows,chunks", WEIGHT_GRADIENTS)
+def test_dense_weight_gradient_forms(A, sizes, rows, chunks):
+    cin, cout, h, w, B = sizes
+    got = wgrad_choice(B, cin, cout, h, w, 3, 1)
+    assert got is not None and got[:2] == (rows, chunks)
+    assert wgrad_choice(B, cin, cout, h, w, 3, 2) is None and wgrad_choice(B, cin, cout, h, 128, 3, 1) is None
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((B, cin, h, w)).astype(np.float32)
+    G, ref = weight_gradient(A, x, rng.standard_normal((B, cout, h, w)).astype(np.float32))
+    # at most 32 roundings of a sum in a wavefront, whose errors add up as their root; one more of the sum of the
+    # wavefronts and of the partials each, and of the pieces
+    assert np.linalg.norm(G - ref) <= 2.0 ** -24 * (32 ** 0.5 + 3) * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("cin,cout,h,w,B", [(40, 64, 6, 10, 3), (8, 40, 4, 70, 2)])
+def test_dense_weight_gradient_of_operands_that_are_not_finite(A, cin, cout, h, w, B):
+    rng = np.random.default_rng(6)
+    x = rng.standard_normal((B, cin, h, w)).astype(np.float32)
+    dy = rng.standard_normal((B, cout, h, w)).astype(np.float32)
+    x[0, 1, 2, w - 1] = np.inf       # (at the row's end: the next column is padding)
+    x[1, 5, 0, 3] = np.nan
+    x[1, 7, h - 1, 0] = 3.4e38       # rounds to infinity in bf16
+    dy[0, 3, 1, 1] = -np.inf
+    dy[:, :, h - 1, :2] *= 1e-6
+    dy[1, :, h - 2, :2] *= 1e-6
+    G, ref = weight_gradient(A, x, dy)
+    with np.errstate(all="ignore"):
+        want = ref.astype(np.float32)
+    fin = np.isfinite(want)
+    assert not fin.all() and fin.any()
+    np.testing.assert_array_equal(G[~fin], want[~fin])
+    assert np.isfinite(G[fin]).all()
+    big = np.abs(want) > 1e6
+    np.testing.assert_allclose(G[fin & ~big], want[fin & ~big], rtol=1e-5, atol=1e-4)
+    np.testing.assert_allclose(G[fin & big], want[fin & big], rtol=1e-5)
