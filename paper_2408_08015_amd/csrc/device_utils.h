@@ -160,6 +160,9 @@ __device__ __forceinline__ float apply_act(float v, int act) {
   if (act == ACT_RELU6) return relu6f(v);
   return v;
 }
+__device__ __forceinline__ float4 apply_act4(float4 v, int act) {
+  return make_float4(apply_act(v.x, act), apply_act(v.y, act), apply_act(v.z, act), apply_act(v.w, act));
+}
 // derivative mask of the activation evaluated at pre-activation v (0 at the kinks); the activated
 // value gives the same answer
 __device__ __forceinline__ float act_mask(float v, int act) {

@@ -128,10 +128,13 @@ void fwd_op(Ctx& c, const Op& op, const int32_t* labels, float* loss) {
       float* aux = reinterpret_cast<float*>(c.slot + op.aux_off);
       double* ws = reinterpret_cast<double*>(fscratch(c, op));
       cf x = (cf)act_ptr(c, op.in);
+      const Op* a = op.act_behind >= 0 ? &s.ops[op.act_behind] : nullptr;
+      float* const y2 = a ? (float*)act_ptr(c, a->out) : nullptr;
+      const int act2 = a ? a->act : 0;
       if (!op.bn_stats_given && !op.bn_lazy && op.act != 4 && bn_onepass_fits(I.n, HW)) {  // small tensor: one launch
         bn_fwd_onepass_f32(st, x, s.W + op.w_off, s.W + op.b_off, op.skip >= 0 ? (cf)act_ptr(c, op.skip) : nullptr,
                            (float*)act_ptr(c, op.out), aux, aux + 2 * I.c, s.running + op.run_off, I.n, I.c, HW, op.eps,
-                           op.act);
+                           op.act, y2, act2);
         break;
       }
       // statistics: from the depthwise conv in front (one partial pair per plane) or a pass of its own
@@ -139,10 +142,11 @@ void fwd_op(Ctx& c, const Op& op, const int32_t* labels, float* loss) {
       if (!op.bn_lazy)  // else the depthwise conv behind normalises on load
         bn_apply_f32(st, x, s.W + op.w_off, s.W + op.b_off, op.skip >= 0 ? (cf)act_ptr(c, op.skip) : nullptr,
                      (float*)act_ptr(c, op.out), aux, aux + 2 * I.c, s.running + op.run_off, ws,
-                     op.bn_stats_given ? op.given_parts : bn_parts(I.n, HW), I.n, I.c, HW, op.eps, op.act);
+                     op.bn_stats_given ? op.given_parts : bn_parts(I.n, HW), I.n, I.c, HW, op.eps, op.act, y2, act2);
       break;
     }
     case OP_ACT:
+      if (op.act_fwd_done) break;
       if (s.bf16) act_fwd_bf16(st, (cb)act_ptr(c, op.in), (bf16_t*)act_ptr(c, op.out), I.elems, op.act);
       else act_fwd_f32(st, (cf)act_ptr(c, op.in), (float*)act_ptr(c, op.out), I.elems, op.act);
       break;
@@ -157,6 +161,9 @@ void fwd_op(Ctx& c, const Op& op, const int32_t* labels, float* loss) {
     }
     case OP_RES_ADD:
       if (s.bf16) add_bf16(st, (cb)act_ptr(c, op.in), (cb)act_ptr(c, op.skip), (bf16_t*)act_ptr(c, op.out), I.elems);
+      else if (op.act_behind >= 0)
+        add_act_f32(st, (cf)act_ptr(c, op.in), (cf)act_ptr(c, op.skip), (float*)act_ptr(c, op.out),
+                    (float*)act_ptr(c, s.ops[op.act_behind].out), I.elems, s.ops[op.act_behind].act);
       else add_f32(st, (cf)act_ptr(c, op.in), (cf)act_ptr(c, op.skip), (float*)act_ptr(c, op.out), I.elems);
       break;
     case OP_GAP:
@@ -333,19 +340,23 @@ void bwd_op(Ctx& c, const Op& op) {
       // partial sums: left per plane by the backward of the depthwise conv behind (it ran just before), or
       // a pass of its own; input gradient: formed by the depthwise conv in front on load, or a pass of its own
       const bool given = op.bn_bwd_sums_given;
+      const Op* a = op.act_bwd_behind >= 0 ? &s.ops[op.act_bwd_behind] : nullptr;
+      cf pre = a ? (cf)act_ptr(c, a->in) : nullptr, gy = a ? (cf)grad_ptr(c, a->out) : g;
+      float* const gp = a ? (float*)grad_ptr(c, a->in) : nullptr;  // (where g is)
+      const int act2 = a ? a->act : 0;
       if (!given && !op.bn_bwd_apply_fused && op.act != 4 && bn_onepass_fits(I.n, HW)) {  // small tensor: one launch
-        bn_bwd_onepass_f32(st, g, x, aux, aux + 2 * I.c, s.W + op.w_off, (float*)gin, s.G + op.w_off, s.G + op.b_off, I.n,
-                           I.c, HW, op.act);
+        bn_bwd_onepass_f32(st, gy, x, aux, aux + 2 * I.c, s.W + op.w_off, (float*)gin, s.G + op.w_off, s.G + op.b_off, I.n,
+                           I.c, HW, op.act, pre, gp, act2);
         break;
       }
-      if (!given) bn_bwd_partial_f32(st, g, x, aux, aux + 2 * I.c, ws, I.n, I.c, HW, op.act);
+      if (!given) bn_bwd_partial_f32(st, gy, x, aux, aux + 2 * I.c, ws, I.n, I.c, HW, op.act, pre, gp, act2);
       if (!op.bn_bwd_apply_fused)
         bn_bwd_apply_f32(st, g, x, aux, aux + 2 * I.c, s.W + op.w_off, ws, given ? op.given_bwd_parts : bn_parts(I.n, HW), (float*)gin,
                          s.G + op.w_off, s.G + op.b_off, I.n, I.c, HW, op.act);
       break;
     }
     case OP_ACT:
-      if (!gin) break;
+      if (!gin || op.act_bwd_done) break;
       if (s.bf16)
         act_bwd_bf16(st, (cb)grad_ptr(c, op.out), op.act == 3 ? (cb)act_ptr(c, op.in) : (cb)act_ptr(c, op.out),
                      (bf16_t*)gin, I.elems, op.act);

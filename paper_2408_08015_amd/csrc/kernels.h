@@ -220,28 +220,34 @@ int bn_parts(int N, int HW);
 void bn_stats_f32(hipStream_t st, const float* x, double* ws, int N, int C, int HW);
 void bn_apply_f32(hipStream_t st, const float* x, const float* gamma, const float* beta, const float* skip, float* y,
                   float* stat, float* scale_shift, float* running, const double* ws, int P, int N, int C, int HW,
-                  float eps, int act);
+                  float eps, int act, float* y2 = nullptr, int act2 = 0);
 void bn_bwd_f32(hipStream_t st, const float* g, const float* x, const float* stat, const float* scale_shift,
                 const float* gamma, float* dx, float* Ggamma, float* Gbeta, double* ws, int N, int C, int HW,
                 int act);
+// y2, pre, gp, act2: a ReLU or ReLU6 (act2) that stands alone behind a residual block's end.  Forward: y2 = act2(y) is
+// written beside y.  Backward: g is the gradient behind it; gp = g * act2'(pre) is written, and is the gradient of y from
+// there on (bn_bwd_apply_f32 is given gp).  Not with swish as the BatchNorm's own activation.
 // Small tensors (bn_onepass_fits: at most 8192 elements per channel): forward and backward as ONE
 // launch each, one block per channel, no workspace.
 bool bn_onepass_fits(int N, int HW);
 void bn_fwd_onepass_f32(hipStream_t st, const float* x, const float* gamma, const float* beta, const float* skip,
                         float* y, float* stat, float* scale_shift, float* running, int N, int C, int HW, float eps,
-                        int act);
+                        int act, float* y2 = nullptr, int act2 = 0);
 void bn_bwd_onepass_f32(hipStream_t st, const float* g, const float* x, const float* stat, const float* scale_shift,
-                        const float* gamma, float* dx, float* Ggamma, float* Gbeta, int N, int C, int HW, int act);
+                        const float* gamma, float* dx, float* Ggamma, float* Gbeta, int N, int C, int HW, int act,
+                        const float* pre = nullptr, float* gp = nullptr, int act2 = 0);
 // Its two halves: the partial sums ws[C][bn_parts(N, HW)][2] = (sum g', sum g'*xhat), and the input
 // gradient (+ dgamma, dbeta) from P partial pairs per channel, whoever wrote them.
 void bn_bwd_partial_f32(hipStream_t st, const float* g, const float* x, const float* stat, const float* scale_shift,
-                        double* ws, int N, int C, int HW, int act);
+                        double* ws, int N, int C, int HW, int act, const float* pre = nullptr, float* gp = nullptr,
+                        int act2 = 0);
 void bn_bwd_apply_f32(hipStream_t st, const float* g, const float* x, const float* stat, const float* scale_shift,
                       const float* gamma, const double* ws, int P, float* dx, float* Ggamma, float* Gbeta, int N,
                       int C, int HW, int act);
 
 // Elementwise
 void act_fwd_f32(hipStream_t st, const float* x, float* y, size_t n, int act);
+void add_act_f32(hipStream_t st, const float* a, const float* b, float* y, float* y2, size_t n, int act);  // y = a + b, y2 = act(y); 16-byte aligned, n % 4 == 0
 void act_bwd_f32(hipStream_t st, const float* g, const float* x, float* dx, size_t n, int act);
 void add_f32(hipStream_t st, const float* a, const float* b, float* y, size_t n);
 void copy_bytes(hipStream_t st, const void* src, void* dst, size_t bytes);

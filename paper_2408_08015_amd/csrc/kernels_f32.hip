@@ -344,6 +344,15 @@ __global__ void act_bwd4_kernel(const float4* __restrict__ g, const float4* __re
   d.x *= act_slope(v.x, act); d.y *= act_slope(v.y, act); d.z *= act_slope(v.z, act); d.w *= act_slope(v.w, act);
   dx[i] = d;
 }
+// y = a + b and the ReLU / ReLU6 behind it (bound by memory; as two launches y is read again)
+__global__ void add_act4_kernel(const float4* __restrict__ a, const float4* __restrict__ b, float4* __restrict__ y,
+                                float4* __restrict__ y2, size_t n4, int act) {
+  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  const float4 u = a[i], v = b[i], r = make_float4(u.x + v.x, u.y + v.y, u.z + v.z, u.w + v.w);
+  y[i] = r;
+  y2[i] = apply_act4(r, act);
+}
 // y may alias a (in-place accumulation of a skip gradient): no __restrict__ here
 __global__ void add_kernel(const float* a, const float* b, float* y, size_t n) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -371,6 +380,10 @@ void act_fwd_f32(hipStream_t st, const float* x, float* y, size_t n, int act) {
     KLAUNCH(act_fwd4_kernel, dim3(cdiv(n / 4, 256)), dim3(256), 0, st, (const float4*)x, (float4*)y, n / 4, act);
   else
     KLAUNCH(act_fwd_kernel, dim3(cdiv(n, 256)), dim3(256), 0, st, x, y, n, act);
+}
+void add_act_f32(hipStream_t st, const float* a, const float* b, float* y, float* y2, size_t n, int act) {
+  KLAUNCH(add_act4_kernel, dim3(cdiv(n / 4, 256)), dim3(256), 0, st, (const float4*)a, (const float4*)b, (float4*)y,
+          (float4*)y2, n / 4, act);
 }
 void act_bwd_f32(hipStream_t st, const float* g, const float* x, float* dx, size_t n, int act) {
   if (n % 4 == 0 && n >= 4096 && aligned16(g) && aligned16(x) && aligned16(dx))

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void bn_stats_partial_kernel(const float* __re
   }
 }
 
-// y = act(x*scale + shift) (+ skip); grid (planes, chunks)
+// y = act(x*scale + shift) (+ skip); y2, if there: act2(y), the activation behind a residual block's end; grid (planes, chunks)
 template <bool VEC, bool SW = false>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const float* __restrict__ x,
                                                        const double* __restrict__ ws,
@@ -124,7 +124,8 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const float* __restrict__
                                                        const float* __restrict__ skip, float* __restrict__ y,
                                                        float* __restrict__ stat, float* __restrict__ ss,
                                                        float* __restrict__ running, int C, int HW, int S,
-                                                       double count, float eps, int act, int chunk) {
+                                                       double count, float eps, int act, int chunk,
+                                                       float* __restrict__ y2, int act2) {
   __shared__ float coef[2];
   const int plane = blockIdx.x, c = plane % C;
   const int e0 = blockIdx.y * chunk, e1 = min(e0 + chunk, HW);
@@ -165,6 +166,7 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const float* __restrict__
           v.x += kv[u].x; v.y += kv[u].y; v.z += kv[u].z; v.w += kv[u].w;
         }
         *reinterpret_cast<float4*>(y + base + e) = v;
+        if (y2) *reinterpret_cast<float4*>(y2 + base + e) = apply_act4(v, act2);
       }
     }
     for (int e = e0 + 4 * threadIdx.x + 4096; e < e1; e += 1024) {  // longer chunks (not produced by the launcher)
@@ -178,12 +180,14 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const float* __restrict__
         v.x += k.x; v.y += k.y; v.z += k.z; v.w += k.w;
       }
       *reinterpret_cast<float4*>(y + base + e) = v;
+      if (y2) *reinterpret_cast<float4*>(y2 + base + e) = apply_act4(v, act2);
     }
   } else {
     for (int e = e0 + threadIdx.x; e < e1; e += 256) {
       float v = apply_act_sw<SW>(x[base + e] * sc + sf, act);
       if (skip) v += skip[base + e];
       y[base + e] = v;
+      if (y2) y2[base + e] = apply_act(v, act2);
     }
   }
 }
@@ -204,14 +208,14 @@ void bn_stats_f32(hipStream_t st, const float* x, double* ws, int N, int C, int 
 
 void bn_apply_f32(hipStream_t st, const float* x, const float* gamma, const float* beta, const float* skip, float* y,
                   float* stat, float* scale_shift, float* running, const double* ws, int P, int N, int C, int HW,
-                  float eps, int act) {
+                  float eps, int act, float* y2, int act2) {
   size_t per = (size_t)N * HW;
   int nchunks, chunk;
   bn_chunking(HW, nchunks, chunk);
   dim3 grid((unsigned)(N * C), nchunks);
 #define BN_APPLY(name, kern)                                                                                          \
   KLAUNCH_NAMED(name, kern, grid, dim3(256), 0, st, x, ws, gamma, beta, skip, y, stat, scale_shift, running, C, HW, P, \
-                (double)per, eps, act, chunk)
+                (double)per, eps, act, chunk, y2, act2)
   const bool sw = act == ACT_SWISH;  // the swish instantiations share the profile names of the others
   if (HW % 4 == 0) {
     if (sw) BN_APPLY("bn_apply_kernel<true>", (bn_apply_kernel<true, true>));
@@ -230,13 +234,17 @@ void bn_fwd_f32(hipStream_t st, const float* x, const float* gamma, const float*
   bn_apply_f32(st, x, gamma, beta, skip, y, stat, scale_shift, running, ws, bn_parts(N, HW), N, C, HW, eps, act);
 }
 
-template <bool VEC, bool SW = false>
+// PRE: g comes from behind an activation that stands alone at a residual block's end; the pass writes the gradient in front
+// of it, g * act2'(pre), to gp and goes on with that.
+template <bool VEC, bool SW = false, bool PRE = false>
 __global__ __launch_bounds__(256) void bn_bwd_partial_kernel(const float* __restrict__ g,
                                                              const float* __restrict__ x,
                                                              const float* __restrict__ stat,
                                                              const float* __restrict__ ss,
                                                              double* __restrict__ ws, int N, int C,
-                                                             int HW, BnSplit b, int act) {
+                                                             int HW, BnSplit b, int act,
+                                                             const float* __restrict__ pre, float* __restrict__ gp,
+                                                             int act2) {
   __shared__ double sh[8];
   const int c = blockIdx.x, grp = blockIdx.y / b.nchunks, ch = blockIdx.y - grp * b.nchunks;
   const int n0 = grp * b.spb, n1 = min(n0 + b.spb, N);
@@ -247,7 +255,7 @@ __global__ __launch_bounds__(256) void bn_bwd_partial_kernel(const float* __rest
     // a block's share is at most 4096 elements: all of a thread's words are requested at once
     const int q = len >> 2, total = (n1 - n0) * q;
     for (int i0 = threadIdx.x; i0 < total; i0 += 1024) {
-      float4 xq[4], gq[4];
+      float4 xq[4], gq[4], pq[PRE ? 4 : 1];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int idx = i0 + 256 * u;
@@ -257,6 +265,19 @@ __global__ __launch_bounds__(256) void bn_bwd_partial_kernel(const float* __rest
           const size_t off = ((size_t)(n0 + nl) * C + c) * HW + e;
           xq[u] = *reinterpret_cast<const float4*>(x + off);
           gq[u] = *reinterpret_cast<const float4*>(g + off);
+          if (PRE) pq[u] = *reinterpret_cast<const float4*>(pre + off);
+        }
+      }
+      if (PRE) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int idx = i0 + 256 * u;
+          if (idx < total) {
+            const int nl = idx / q, e = e0 + 4 * (idx - nl * q);
+            gq[u].x *= act_mask(pq[u].x, act2); gq[u].y *= act_mask(pq[u].y, act2);
+            gq[u].z *= act_mask(pq[u].z, act2); gq[u].w *= act_mask(pq[u].w, act2);
+            *reinterpret_cast<float4*>(gp + ((size_t)(n0 + nl) * C + c) * HW + e) = gq[u];
+          }
         }
       }
 #pragma unroll
@@ -280,6 +301,10 @@ __global__ __launch_bounds__(256) void bn_bwd_partial_kernel(const float* __rest
         const size_t off = ((size_t)(n0 + nl) * C + c) * HW + e;
         xq[u] = x[off];
         gq[u] = g[off];
+        if (PRE) {
+          gq[u] *= act_mask(pre[off], act2);
+          if (i0 + 256 * u < total) gp[off] = gq[u];
+        }
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -404,7 +429,7 @@ __global__ __launch_bounds__(T) void bn_fwd_onepass_kernel(const float* __restri
                                                            const float* __restrict__ skip, float* __restrict__ y,
                                                            float* __restrict__ stat, float* __restrict__ ss,
                                                            float* __restrict__ running, int N, int C, int HW,
-                                                           float eps, int act) {
+                                                           float eps, int act, float* __restrict__ y2, int act2) {
   __shared__ double sh[2 * (T / 64)];
   const int c = blockIdx.x, E = N * HW;
   float v[8], kv[8];
@@ -434,7 +459,11 @@ __global__ __launch_bounds__(T) void bn_fwd_onepass_kernel(const float* __restri
   bn_coefficients(d1, d2, (double)E, gamma[c], beta[c], eps, c, C, threadIdx.x == 0, stat, ss, running, sc, sf);
 #pragma unroll
   for (int k = 0; k < 8; ++k)
-    if (threadIdx.x + k * T < E) y[off[k]] = apply_act(v[k] * sc + sf, act) + kv[k];
+    if (threadIdx.x + k * T < E) {
+      const float r = apply_act(v[k] * sc + sf, act) + kv[k];
+      y[off[k]] = r;
+      if (y2) y2[off[k]] = apply_act(r, act2);
+    }
 }
 
 template <int T>
@@ -444,7 +473,9 @@ __global__ __launch_bounds__(T) void bn_bwd_onepass_kernel(const float* __restri
                                                            const float* __restrict__ ss,
                                                            const float* __restrict__ gamma, float* __restrict__ dx,
                                                            float* __restrict__ Ggamma, float* __restrict__ Gbeta,
-                                                           int N, int C, int HW, int act) {
+                                                           int N, int C, int HW, int act,
+                                                           const float* __restrict__ pre, float* __restrict__ gp,
+                                                           int act2) {
   __shared__ double sh[2 * (T / 64)];
   const int c = blockIdx.x, E = N * HW;
   const float mean = stat[c], istd = stat[C + c], sc = ss[c], sf = ss[C + c];
@@ -461,7 +492,9 @@ __global__ __launch_bounds__(T) void bn_bwd_onepass_kernel(const float* __restri
       const int n = idx / HW, e = idx - n * HW;
       off[k] = ((size_t)n * C + c) * HW + e;
       const float xv = x[off[k]];
-      gm[k] = g[off[k]] * act_mask(xv * sc + sf, act);
+      float gv = g[off[k]];
+      if (pre) gp[off[k]] = gv = gv * act_mask(pre[off[k]], act2);
+      gm[k] = gv * act_mask(xv * sc + sf, act);
       xh[k] = (xv - mean) * istd;
     }
   }
@@ -487,35 +520,38 @@ bool bn_onepass_fits(int N, int HW) { return (long)N * HW <= 8192; }
 
 void bn_fwd_onepass_f32(hipStream_t st, const float* x, const float* gamma, const float* beta, const float* skip,
                         float* y, float* stat, float* scale_shift, float* running, int N, int C, int HW, float eps,
-                        int act) {
+                        int act, float* y2, int act2) {
   if ((long)N * HW <= 2048)
     KLAUNCH_NAMED("bn_fwd_onepass_kernel", (bn_fwd_onepass_kernel<256>), dim3(C), dim3(256), 0, st, x, gamma, beta,
-                  skip, y, stat, scale_shift, running, N, C, HW, eps, act);
+                  skip, y, stat, scale_shift, running, N, C, HW, eps, act, y2, act2);
   else
     KLAUNCH_NAMED("bn_fwd_onepass_kernel", (bn_fwd_onepass_kernel<1024>), dim3(C), dim3(1024), 0, st, x, gamma, beta,
-                  skip, y, stat, scale_shift, running, N, C, HW, eps, act);
+                  skip, y, stat, scale_shift, running, N, C, HW, eps, act, y2, act2);
 }
 
 void bn_bwd_onepass_f32(hipStream_t st, const float* g, const float* x, const float* stat, const float* ss,
-                        const float* gamma, float* dx, float* Ggamma, float* Gbeta, int N, int C, int HW, int act) {
+                        const float* gamma, float* dx, float* Ggamma, float* Gbeta, int N, int C, int HW, int act,
+                        const float* pre, float* gp, int act2) {
   if ((long)N * HW <= 2048)
     KLAUNCH_NAMED("bn_bwd_onepass_kernel", (bn_bwd_onepass_kernel<256>), dim3(C), dim3(256), 0, st, g, x, stat, ss,
-                  gamma, dx, Ggamma, Gbeta, N, C, HW, act);
+                  gamma, dx, Ggamma, Gbeta, N, C, HW, act, pre, gp, act2);
   else
     KLAUNCH_NAMED("bn_bwd_onepass_kernel", (bn_bwd_onepass_kernel<1024>), dim3(C), dim3(1024), 0, st, g, x, stat, ss,
-                  gamma, dx, Ggamma, Gbeta, N, C, HW, act);
+                  gamma, dx, Ggamma, Gbeta, N, C, HW, act, pre, gp, act2);
 }
 
 void bn_bwd_partial_f32(hipStream_t st, const float* g, const float* x, const float* stat, const float* ss,
-                        double* ws, int N, int C, int HW, int act) {
+                        double* ws, int N, int C, int HW, int act, const float* pre, float* gp, int act2) {
   const BnSplit b = bn_split(N, HW);
-#define BN_BWDP(name, kern) KLAUNCH_NAMED(name, kern, dim3(C, b.P), dim3(256), 0, st, g, x, stat, ss, ws, N, C, HW, b, act)
+#define BN_BWDP(name, kern) KLAUNCH_NAMED(name, kern, dim3(C, b.P), dim3(256), 0, st, g, x, stat, ss, ws, N, C, HW, b, act, pre, gp, act2)
   const bool sw = act == ACT_SWISH;
   if (HW % 4 == 0) {
     if (sw) BN_BWDP("bn_bwd_partial_kernel<true>", (bn_bwd_partial_kernel<true, true>));
+    else if (pre) BN_BWDP("bn_bwd_partial_kernel<true>", (bn_bwd_partial_kernel<true, false, true>));
     else BN_BWDP("bn_bwd_partial_kernel<true>", (bn_bwd_partial_kernel<true, false>));
   } else {
     if (sw) BN_BWDP("bn_bwd_partial_kernel<false>", (bn_bwd_partial_kernel<false, true>));
+    else if (pre) BN_BWDP("bn_bwd_partial_kernel<false>", (bn_bwd_partial_kernel<false, false, true>));
     else BN_BWDP("bn_bwd_partial_kernel<false>", (bn_bwd_partial_kernel<false, false>));
   }
 #undef BN_BWDP

@@ -463,6 +463,26 @@ ast_status build_plan(Stage& s, std::string& err) {
     }
   }
 
+  // A standalone ReLU / ReLU6 behind a BatchNorm that adds a skip, or behind a RES_ADD: its value is written by the pass in
+  // front, and its gradient is formed by the statistics pass of the BatchNorm's backward.  (A pass of its own reads what has
+  // just been written: 256 channels of 32 x 56x56, 32 us forward and 46 us backward; without it a round of the bottleneck
+  // stage at 4 x 32 x 56x56 takes 9.11 ms, with it 9.42; ResNet-50 at 8 x 8 x 224x224 38.2, 39.1.)
+  for (size_t j = 1; !s.bf16 && j < s.ops.size(); ++j) {
+    Op& a = s.ops[j];
+    Op& f = s.ops[j - 1];
+    if (a.kind != OP_ACT || (a.act != 1 && a.act != 2) || a.in != f.out || (f.kind != OP_BN && f.kind != OP_RES_ADD)) continue;
+    Op& b = f.kind == OP_BN ? f : s.ops[j >= 2 ? j - 2 : 0];
+    const bool bn = b.kind == OP_BN && !b.bn_lazy && b.act != 4 && (&b == &f || f.in == b.out);
+    if (f.kind == OP_RES_ADD ? s.acts[f.out].elems % 4 == 0 : bn) {
+      f.act_behind = (int)j;
+      a.act_fwd_done = true;
+    }
+    if (bn && !b.bn_bwd_sums_given) {
+      b.act_bwd_behind = (int)j;
+      a.act_bwd_done = true;
+    }
+  }
+
   // Stash slot: every activation (the stage input is copied in; the final output goes to
   // the caller's buffer) followed by the per-op extras.
   size_t off = 0;

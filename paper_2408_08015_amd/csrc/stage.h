@@ -96,6 +96,10 @@ struct Op {
   int bn_out_op = -1;                 // depthwise conv: index of the BatchNorm op it writes statistics for
   int bn_bwd_out_op = -1;             // depthwise conv: index of the BatchNorm op whose backward apply it does
   int stats_op = -1;                  // pointwise conv: index of the BatchNorm op it writes statistics for
+  // A ReLU / ReLU6 that stands alone at a residual block's end (fp32), done by its neighbours' passes:
+  int act_behind = -1;                // BatchNorm or RES_ADD: index of the OP_ACT whose forward it does
+  int act_bwd_behind = -1;            // BatchNorm: ... whose backward it does
+  bool act_fwd_done = false, act_bwd_done = false;  // OP_ACT: by them
   bool wg_grouped = false;            // bf16 linear / attention projections: the weight (and bias) gradient is part of
                                       // the stage's one grouped weight-gradient launch at the end of the backward pass
 };

@@ -1,0 +1,34 @@
+"""A ReLU or ReLU6 that stands alone at a residual block's end: its passes ride along with the BatchNorm or the addition in
+front."""
+import pytest
+
+import harness
+from asteroid_workloads import gen
+from asteroid_workloads.configs import bn, conv, simple
+from test_parity_gpu import A, one  # noqa: F401  (A: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def layers_of(two, act, c, mid):
+    main = [conv(c, mid, 1), bn(mid), simple("relu"), conv(mid, c, 1), bn(c)]
+    if two:
+        return [simple("res_begin")] + main + [simple("res_swap"), conv(c, c, 1), bn(c), simple("res_add"), simple(act)]
+    return [simple("res_begin")] + main + [simple("res_add"), simple(act)]
+
+
+# planes of whole vectors and odd ones, in one launch per BatchNorm (at most 8192 elements per channel) and in two
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("act,c,mid,hw,B", [("relu", 16, 24, 8, 3), ("relu6", 24, 16, 7, 3), ("relu", 16, 16, 56, 4),
+                                            ("relu6", 16, 24, 45, 6)])
+def test_activation_behind_a_residual_block(A, two, act, c, mid, hw, B):
+    # one block in front of another: the first one's activation lies in the stash, the second one's is the stage's output
+    layers = layers_of(two, act, c, mid) + layers_of(False, act, c, mid)
+    cfg = one(layers, (c, hw, hw), B=B, M=1)
+    inp = gen.make_inputs(cfg)
+    ora, _ = harness.run_oracle(cfg, inp, rounds=1)
+    hip, _, _ = harness.run_hip(cfg, inp, rounds=1)
+    sc = harness.score(cfg, hip, ora)
+    assert sc["r0.y"] <= 2e-6
+    # (an element within the rounding of an activation's edge takes another slope: its whole gradient differs)
+    assert sc["r0.dx"] <= 1e-3
