@@ -1,10 +1,10 @@
-"""A ReLU or ReLU6 that stands alone at a residual block's end: its passes ride along with the BatchNorm or the addition in
-front."""
+"""Short passes that ride with their neighbours: a ReLU or ReLU6 that stands alone at a residual block's end with the
+BatchNorm or the addition in front, and the sum of a few rows' losses with their softmax."""
 import pytest
 
 import harness
 from asteroid_workloads import gen
-from asteroid_workloads.configs import bn, conv, simple
+from asteroid_workloads.configs import bn, conv, linear, simple
 from test_parity_gpu import A, one  # noqa: F401  (A: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -32,3 +32,15 @@ def test_activation_behind_a_residual_block(A, two, act, c, mid, hw, B):
     assert sc["r0.y"] <= 2e-6
     # (an element within the rounding of an activation's edge takes another slope: its whole gradient differs)
     assert sc["r0.dx"] <= 1e-3
+
+
+# on either side of sixteen rows and 64 classes, the largest heads that one block takes
+@pytest.mark.parametrize("B,classes", [(1, 2), (4, 10), (16, 64), (17, 64), (16, 65)])
+def test_loss_of_few_rows(A, B, classes):
+    cfg = one([simple("global_avgpool"), linear(24, classes), simple("softmax_ce")], (24, 5, 5), B=B, M=2)
+    inp = gen.make_inputs(cfg)
+    ora, _ = harness.run_oracle(cfg, inp, rounds=1)
+    hip, _, _ = harness.run_hip(cfg, inp, rounds=1)
+    sc = harness.score(cfg, hip, ora)
+    # (a few roundings each: the exponential, the sum of at most 65 of them, the logarithm)
+    assert max(sc["r0.y"], sc["r0.dx"], sc["r0.loss"]) <= 2e-6
