@@ -70,18 +70,24 @@ def kernel_model(cfg):
                 lazy_bn.add(i - 2)
             if i + 1 < len(kinds) and kinds[i + 1] == "batchnorm2d":
                 given_bn.add(i + 1)
-    # statistics partials that a pointwise conv (no bias) leaves for the BatchNorm behind it: offered by the
-    # 32- and 128-pixel-wavefront kernels while there are at most 256 pixel blocks
+    def pw_kernel(nq, kd, m, plain):
+        """The pointwise product's kernel family: contraction kd, m result channels, nq pixels."""
+        mt, kg = _cdiv(m, 32), _cdiv(kd, 16)
+        tiles = _cdiv(nq, 32) * mt
+        if tiles < 1024 and kg >= 6:
+            return "pw_conv_f32_ks_kernel"           # the contraction split over wavefronts
+        return "pw_conv_f32_wide_kernel" if kg <= 4 and mt >= 3 and tiles >= 7000 and plain else "pw_conv_f32_kernel"
+    # statistics partials that a pointwise conv (no bias) leaves for the BatchNorm behind it: offered where the contraction
+    # is not split and there are at most 512 partials (of 256 pixels, or 512 where a lane has two)
     stat_bn = set()
     shp = tuple(cfg.in_shape)
     outs = gen.layer_shapes(cfg.layers, cfg.in_shape)
     for i, L in enumerate(cfg.layers):
         if L["kind"] == "conv2d" and cfg.dtype == "f32" and L["k"] == 1 and L["groups"] == 1 and not L.get("bias", False) \
                 and i + 1 < len(kinds) and kinds[i + 1] == "batchnorm2d" and (i + 1) not in given_bn:
-            hw_, nq_ = shp[1] * shp[2], B * shp[1] * shp[2]
-            ks = not (_cdiv(nq_, 128) * _cdiv(L["cout"], 32) < 256 and _cdiv(L["cin"], 8) >= 16)
-            parts = _cdiv(nq_, 512) if (hw_ % 4 == 0 and nq_ >= 65536) else _cdiv(nq_, 128)
-            if ks and parts <= 256:
+            nq_ = B * shp[1] * shp[2]
+            if pw_kernel(nq_, L["cin"], L["cout"], True) != "pw_conv_f32_ks_kernel" and \
+                    nq_ <= 512 * (512 if _cdiv(L["cin"], 16) > 4 and shp[1] * shp[2] % 2 == 0 else 256):
                 stat_bn.add(i + 1)
         shp = outs[i]
     for i, L in enumerate(cfg.layers):
@@ -91,32 +97,15 @@ def kernel_model(cfg):
             res_open = True
         if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 1 and L["groups"] == 1:
             cin, cout = L["cin"], L["cout"]
-            hw = shape[1] * shape[2]
-            nq = B * hw
-
-            def cls(m, kd):
-                kg = _cdiv(kd, 8)
-                if _cdiv(nq, 128) * _cdiv(m, 32) < 256 and kg >= 16:    # K split over 4 / 8 / 16 wavefronts
-                    return "pkks" if kg <= 32 else ("pkks8" if kg <= 64 else "pkks16")
-                if hw % 4 == 0 and nq >= 65536:
-                    return "pk4"
-                return "pk2" if kd > 32 else "pk1"
-            fwd_names = {"pkks": "pw_conv_f32_pkks_kernel", "pkks8": "pw_conv_f32_pkks_kernel<8>",
-                         "pkks16": "pw_conv_f32_pkks_kernel<16>", "pk4": "pw_conv_f32_pk4_kernel",
-                         "pk2": "pw_conv_f32_pk_kernel<2>", "pk1": "pw_conv_f32_pk_kernel<1>"}
-            wg_name = "pw_wgrad_f32_kernel<true>" if hw % 4 == 0 else "pw_wgrad_f32_kernel<false>"
-            out.setdefault(fwd_names[cls(cout, cin)], []).append(4 * (cin + cout) * nq)      # forward
+            nq = B * shape[1] * shape[2]
+            plain = not L.get("bias", False)
+            out.setdefault(pw_kernel(nq, cin, cout, plain), []).append(4 * (cin + cout) * nq)      # forward
             if not first or cfg.needs_input_grad:
                 extra = 4 * cin * nq if (res_open and cfg.layers[i - 1]["kind"] == "res_begin") else 0
-                bc = cls(cin, cout)
-                if bc in ("pkks8", "pkks16"):   # long K: input gradient and weight gradient as two launches
-                    out.setdefault(fwd_names[bc], []).append(4 * (cin + cout) * nq + extra)
-                    out.setdefault(wg_name, []).append(4 * (cin + cout) * nq)
-                else:
-                    # input gradient and weight-gradient partials in one launch: g and x in, dx out
-                    out.setdefault("pw_bwd_dual_kernel<%s>" % bc, []).append(4 * (2 * cin + cout) * nq + extra)
+                # input gradient and weight-gradient partials in one launch: g and x in, dx out
+                out.setdefault("pw_bwd_dual_kernel", []).append(4 * (2 * cin + cout) * nq + extra)
             else:
-                out.setdefault(wg_name, []).append(4 * (cin + cout) * nq)                   # g and x in
+                out.setdefault("pw_wgrad_f32_kernel", []).append(4 * (cin + cout) * nq)            # g and x in
         if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 3 and L["groups"] == 1 and L["stride"] == 1 \
                 and L["pad"] == 1 and L["cin"] >= 8 and L["cout"] >= 8:
             # dense 3x3 on the matrix cores: flops of one product (forward; the input gradient is the same
@@ -126,8 +115,7 @@ def kernel_model(cfg):
             out.setdefault("conv3x3_mfma_f32_kernel", []).append(flops)
             if not first or cfg.needs_input_grad:
                 out.setdefault("conv3x3_mfma_f32_kernel", []).append(flops)
-            wg = "conv3x3_wgrad_vec_mfma_f32_kernel" if w % 4 == 0 else "conv3x3_wgrad_mfma_f32_kernel"
-            out.setdefault(wg, []).append(flops)
+            out.setdefault("conv3x3_wgrad_mfma_f32_kernel", []).append(flops)
         if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 5 and L["groups"] == L["cin"] == L["cout"]:
             c, h, w = shape
             oc, oh, ow = oshape

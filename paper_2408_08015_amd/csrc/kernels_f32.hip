@@ -821,7 +821,7 @@ __global__ void loss_sum_kernel(const float* __restrict__ row_loss, float* __res
   if (threadIdx.x == 0) out[0] = s * inv_denom;
 }
 // Up to 16 rows of up to 64 classes in one block, a wavefront per row: the rows' losses are added in the same launch (10
-// classes, 4 rows: one launch of 3 us in place of two of 2.8 and 1.8 and the gap between them).  More rows would wait for
+// classes, 4 rows: one launch of 2.2 us in place of two of 2.8 and 1.8 and the gap between them).  More rows would wait for
 // each other in one block, more classes for each other in one wavefront.  Same sums in the same order as above.
 __global__ __launch_bounds__(1024) void softmax_ce_few_kernel(const float* __restrict__ z,
                                                               const int32_t* __restrict__ labels,
