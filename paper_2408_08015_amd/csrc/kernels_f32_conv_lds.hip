@@ -806,6 +806,7 @@ struct LdsWgArgs {
 
 constexpr int kFlush = 8 * 16 * 64;  // words: one 32 x 32 tile of eight wavefronts
 
+// Strided convolutions, and rows of 128 columns and more (the others: kernels_f32_conv_wg.hip).
 // Block of eight wavefronts, one per compute unit: a 32 x 32 tile of (cout, cin), all taps (1x1: 64 x 64), over a run of
 // stages of PT consecutive output pixels, whatever samples they lie in.  A stage copies g [32][PT] and the virtual rows of x
 // under it to LDS with coalesced loads (lanes along the pixels: a load per lane and channel row would touch 64 cache
