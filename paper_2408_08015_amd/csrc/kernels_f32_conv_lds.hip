@@ -416,8 +416,8 @@ namespace {
 //
 // Block: WM row tiles x WN groups of 32 * NT pixels x WK shares of the contraction, one wavefront each.  A wavefront's weights
 // (3 KB per tap and group) come from L2 and are its largest stream: 64 bytes per clock and compute unit with NT = 1 at the full
-// matrix rate, 32 with 2.  They are requested up to two taps ahead, in front of that tap's share of the pixel loads: vector
-// memory returns in order, so weights requested behind the pixels of a chunk would wait for them.
+// matrix rate, 32 with 2.  They are requested up to two taps ahead (one with NT = 4), in front of that tap's share of the pixel
+// loads: vector memory returns in order, so weights requested behind the pixels of a chunk would wait for them.
 struct X3Shape { int NT, NI, WM, WN, WK, rows, NP; size_t lds; double cost; };
 struct X3Args {
   LdsArgs p;
@@ -425,27 +425,30 @@ struct X3Args {
   size_t x_words, y_words;
 };
 
-// one result by its definition
-__device__ __forceinline__ float x3_element(const LdsArgs& a, const LdsClass& c, unsigned n, int i, int j, int m) {
-  float s = 0.f;
+// acc += a wavefront's share (groups g0, g0 + gstep, ...) for one row tile and pixel (n, i, j) of each lane, on the fp32
+// matrix instructions (kernels_f32_x3.h: where the pieces gave no finite sum).  As above, what lies outside the image is 0.
+__device__ __forceinline__ void x3_contract_f32(const LdsArgs& a, const LdsClass& c, unsigned n, int i, int j, bool valid,
+                                                const uint4* wl, int g0, int gstep, floatx16& acc) {
+  const int half = threadIdx.x >> 5 & 1;
+#pragma unroll 1
   for (int t = 0; t < c.nr * c.nc; ++t) {
     const unsigned rc = c.rows >> (8 * (t / c.nc)), cc = c.cols >> (8 * (t % c.nc));
     const int h = a.SI * i + (int)(rc & 15) - 1, x = a.SI * j + (int)(cc & 15) - 1;
-    if (h < 0 || h >= a.XH || x < 0 || x >= a.XW) continue;
-    const float* xp = a.X + (size_t)n * a.Kdim * a.XHW + (size_t)(h * a.XRW + x) * a.XS;
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint4*>(a.Wp) +
-        (size_t)((rc >> 4 & 15) * a.KS + (cc >> 4 & 15)) * a.tap_stride + (size_t)(m >> 5) * a.KG * 192 + (m & 31));
-    for (int k = 0; k < a.Kdim; ++k) {
-      const size_t o = ((size_t)(k >> 4) * 192 + 32 * ((k >> 3) & 1)) * 4 + ((k & 7) >> 1);
-      float p[3];
-      for (int e = 0; e < 3; ++e) {
-        const uint32_t u = w[o + (size_t)e * 256];
-        p[e] = __uint_as_float((k & 1) ? u & 0xffff0000u : u << 16);
-      }
-      s = fmaf(p[0] + (p[1] + p[2]), xp[(size_t)k * a.XHW], s);
+    const bool in = valid && h >= 0 && h < a.XH && x >= 0 && x < a.XW;
+    const float* const xp = in ? a.X + ((size_t)n * a.Kdim + 8 * half) * a.XHW + (size_t)(h * a.XRW + x) * a.XS : a.X;
+    const uint4* const w = wl + (size_t)((rc >> 4 & 15) * a.KS + (cc >> 4 & 15)) * a.tap_stride;
+#pragma unroll 1
+    for (int g = g0; g < a.KG; g += gstep) {
+      uint4 p[3];
+      float wv[8], xv[8];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) p[e] = w[(size_t)g * 192 + e * 64];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xv[e] = in ? xp[(size_t)(g * 16 + e) * a.XHW] : 0.f;  // (Kdim % 16 == 0)
+      join3(p, wv);
+      acc = mfma_f32(wv, xv, acc);
     }
   }
-  return s;
 }
 
 template <int NT, int TAPS, int NI>
@@ -518,7 +521,8 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
     woff[t] = ((rc >> 4 & 15) * (unsigned)a.KS + (cc >> 4 & 15)) * a.tap_stride;
     boff[t] = ((int)(rc & 15) * RW + (int)(cc & 15)) * 16;
   }
-  constexpr int RING = TAPS == 9 ? 3 : TAPS;  // taps whose weights are in registers (9 of 9: 3 % slower)
+  constexpr int RING = TAPS == 9 ? 3 : TAPS;  // taps whose weights are in registers (9 of 9: 3 % slower), a divisor of TAPS
+  constexpr int AHEAD = RING == 3 && NT == 4 ? 2 : RING;  // (NT = 4 takes all registers: 64 -> 64 at 32 x 56x56 49 us, 3 ahead 54 to 57)
   const uint4* const wl = reinterpret_cast<const uint4*>(a.Wp) + (size_t)min(tile, (a.Mdim - 1) / 32) * KG * 192 + lane;
   uint4 A[RING][3];
   auto ldA = [&](int t, int ch) __attribute__((always_inline)) {
@@ -563,7 +567,7 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
 #pragma unroll
   for (int i = 0; i < NI; ++i) fetch(i, 0);
 #pragma unroll
-  for (int t = 0; t < (RING < TAPS ? RING : TAPS); ++t) ldA(t, 0);
+  for (int t = 0; t < AHEAD; ++t) ldA(t, 0);
 #pragma unroll
   for (int i = 0; i < NI; ++i) put(i, 0);
   barrier();
@@ -576,8 +580,8 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
 #pragma unroll
     for (int t = 0; t < TAPS; ++t) {
       if (on) tap(t, buf);
-      if (t + RING < TAPS) ldA(t + RING, ch);
-      else if constexpr (more) ldA(t + RING - TAPS, ch + 1);
+      if (t + AHEAD < TAPS) ldA(t + AHEAD, ch);
+      else if constexpr (more) ldA(t + AHEAD - TAPS, ch + 1);
       if constexpr (more) {
 #pragma unroll
         for (int i = t * PER; i < (t + 1) * PER; ++i)
@@ -599,7 +603,18 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
   auto at = [&](int n) {
     return a.Y + (size_t)qn[n] * a.Mdim * OHW + (size_t)(a.SO * qi[n] + c.oy) * a.OW + a.SO * qj[n] + c.ox;
   };
-  if (WK == 1) {
+  // the sums of pixel group n that are not finite, over the wavefront's share of the contraction
+  auto again = [&](int n, unsigned& sn, int& si, int& sj, bool& in) __attribute__((always_inline)) {
+    const unsigned q = q0 + (wn * NT + n) * 32 + col, qc = min(q, c.npix - 1);
+    sn = qc / PHW;
+    si = (int)((qc - sn * PHW) / (unsigned)c.PW);
+    sj = (int)(qc - sn * PHW) - si * c.PW;
+    in = q < c.npix;
+    floatx16 v = zero16();
+    x3_contract_f32(a, c, sn, si, sj, in, wl, wk, WK, v);
+    return v;
+  };
+  if (NT == 4 || WK == 1) {  // (NT = 4 never splits the contraction: x3_shape)
     if (!live) return;
     float bad = 0.f;
 #pragma unroll
@@ -612,19 +627,36 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
         if (qv[n]) yq[(size_t)row(r) * OHW] = v + (a.bias ? a.bias[row(r)] : 0.f);  // (Mdim % 32 == 0)
       }
     }
-    if (__any(bad != 0.f)) {  // (NaN != 0) what is not finite again by its definition, over what was stored
+    if (any_not_finite(bad)) {  // over what was stored
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll 1
       for (int n = 0; n < NT; ++n) {
-        const unsigned q = q0 + (wn * NT + n) * 32 + col;
-        if (q >= c.npix) continue;
-        const unsigned sn = q / PHW, sp = q - sn * PHW;
-        const int si = (int)(sp / (unsigned)c.PW), sj = (int)sp - si * c.PW;
+        unsigned sn;
+        int si, sj;
+        bool in;
+        const floatx16 v = again(n, sn, si, sj, in);
         float* const yq = a.Y + (size_t)sn * a.Mdim * OHW + (size_t)(a.SO * si + c.oy) * a.OW + a.SO * sj + c.ox;
+#pragma unroll
         for (int r = 0; r < 16; ++r)
-          yq[(size_t)row(r) * OHW] = x3_element(a, c, sn, si, sj, row(r)) + (a.bias ? a.bias[row(r)] : 0.f);
+          if (in && !finite_f(yq[(size_t)row(r) * OHW])) yq[(size_t)row(r) * OHW] = v[r] + (a.bias ? a.bias[row(r)] : 0.f);
       }
     }
     return;
+  }
+  float bad = 0.f;
+#pragma unroll
+  for (int n = 0; n < NT; ++n) bad = add_small(acc[n], acs[n], bad);
+  if (any_not_finite(bad)) {
+#pragma unroll 1
+    for (int n = 0; n < NT; ++n) {
+      unsigned sn;
+      int si, sj;
+      bool in;
+      const floatx16 v = again(n, sn, si, sj, in);
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        if (n == j) take_not_finite(acc[j], v);
+    }
   }
   float* const red = reinterpret_cast<float*>(lds);
   const int rpw = 16 / WK;  // accumulator rows that each of the WK wavefronts finishes
@@ -632,7 +664,7 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
   for (int n = 0; n < NT; ++n) {
     __syncthreads();  // the partial tiles overwrite the staged pixels, and then each other
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = acc[n][r] + acs[n][r];
+    for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = acc[n][r];
     __syncthreads();
     for (int rr = 0; rr < rpw; ++rr) {
       const int r = wk * rpw + rr;
@@ -640,7 +672,6 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
       for (int k = 0; k < WK; k += 2)  // fixed order
         v += red[(((k * WN + wn) * WM + wm) * 16 + r) * 64 + lane] + red[((((k + 1) * WN + wn) * WM + wm) * 16 + r) * 64 + lane];
       if (!qv[n] || !live) continue;
-      if (!finite_f(v)) v = x3_element(a, c, qn[n], qi[n], qj[n], row(r));
       at(n)[(size_t)row(r) * OHW] = v + (a.bias ? a.bias[row(r)] : 0.f);
     }
   }
@@ -680,7 +711,7 @@ constexpr size_t kX3Lds = 156 * 1024;
 
 bool x3_shape(const LdsArgs& a, int ncls, int NT, int WM, int WN, int WK, X3Shape& p) {
   const int waves = WM * WN * WK, P = 32 * NT * WN;
-  if (waves > 8 || waves < 2 || (WK > 1 && WK > a.KG) || WM > a.Mdim / 32) return false;
+  if (waves > 8 || waves < 2 || (WK > 1 && (WK > a.KG || NT == 4)) || WM > a.Mdim / 32) return false;
   p.NT = NT; p.WM = WM; p.WN = WN; p.WK = WK;
   p.rows = 0;
   for (int i = 0; i < ncls; ++i) p.rows = std::max(p.rows, tile_rows(P, a.cls[i].PH, a.cls[i].PW, a.SI, a.XH));

@@ -29,20 +29,34 @@ constexpr size_t kWgX3Lds = 156 * 1024;
 constexpr int kWaves = 12, kThreads = kWaves * 64, kShares = kWaves / 3;
 constexpr size_t kSumsLds = (size_t)kWaves * 3 * 1024 * 4;
 
-// One partial's element by its definition, where the product gave none: rows v0 to v1 of the virtual rows.
-__device__ float wgx3_element(const WgX3Args& w, int co, int ci, int tap, int v0, int v1) {
-  float v = 0.f;
-  for (int vr = v0; vr < v1; ++vr) {
-    const int n = vr / (w.H + 1), i = vr - n * (w.H + 1), h = i + tap / 3 - 1;
-    if (i == w.H || h < 0 || h >= w.H) continue;
-    const float* gr = w.g + ((size_t)n * w.Cout + co) * w.HW + (size_t)i * w.W;
-    const float* xr = w.x + ((size_t)n * w.Cin + ci) * w.HW + (size_t)h * w.W;
-    for (int j = 0; j < w.W; ++j) {
-      const int c = j + tap % 3 - 1;
-      if (c >= 0 && c < w.W) v = fmaf(gr[j], xr[c], v);
+// acc += tap (dy, dx) of one 32 x 32 tile over share sh of the stages [s0, s1), in steps of 16 columns, on the fp32 matrix
+// instructions (kernels_f32_x3.h: where the pieces gave no finite sum).  x outside the image is 0.
+template <int kSteps>
+__device__ __forceinline__ void wgx3_contract_f32(const WgX3Args& w, int co, int ci, int dy, int dx, int sh, int s0, int s1,
+                                                  floatx16& acc) {
+  const int half = threadIdx.x >> 5 & 1, RC = w.R * w.C8;
+  co += threadIdx.x & 31;
+  ci += threadIdx.x & 31;
+#pragma unroll 1
+  for (int s = s0; s < s1; ++s)
+#pragma unroll 1
+    for (int j = 0; j < kSteps; ++j) {
+      const int k0 = 2 * (sh + j * kShares), k = k0 + half;
+      if (k0 >= RC) break;  // uniform
+      const int lr = k / w.C8, c = (k - lr * w.C8) * 8, vr = s * w.R + lr, n = vr / (w.H + 1), i = vr - n * (w.H + 1);
+      const int h = i + dy - 1;
+      const bool row = k < RC && vr < w.rows && i < w.H, xrow = row && h >= 0 && h < w.H && ci < w.Cin;
+      const float* const gp = w.g + ((size_t)n * w.Cout + co) * w.HW + (size_t)i * w.W;
+      const float* const xp = w.x + ((size_t)n * w.Cin + ci) * w.HW + (size_t)(xrow ? h : 0) * w.W;
+      float g[8], x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int cx = c + e + dx - 1;
+        g[e] = row && co < w.Cout && c + e < w.W ? gp[c + e] : 0.f;
+        x[e] = xrow && c + e < w.W && cx >= 0 && cx < w.W ? xp[cx] : 0.f;  // (no term past the row's end)
+      }
+      acc = mfma_f32(g, x, acc);
     }
-  }
-  return v;
 }
 
 // eight values of a row from column `col` on, zeros past its end; VL: words that divide W
@@ -225,12 +239,25 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_x3_f32_kernel(WgX3Args w)
     base -= base >= NS ? NS : 0;
   }
 
+  float bad = 0.f;
+#pragma unroll
+  for (int t = 0; t < 3; ++t) bad = add_small(acc[t], acs[t], bad);
+  if (any_not_finite(bad)) {
+#pragma unroll 1
+    for (int t = 0; t < 3; ++t) {
+      floatx16 again = zero16();
+      wgx3_contract_f32<kSteps>(w, co_base, ci_base, dy, t, sh, s_begin, s_end, again);
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (t == j) take_not_finite(acc[j], again);
+    }
+  }
   // the sums of the four wavefronts of a tap, added in 64 bits; then [32 co][32 ci][9], whole rows of which leave
   __syncthreads();
 #pragma unroll
   for (int t = 0; t < 3; ++t)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) lds[((sh * 9 + dy * 3 + t) * 16 + r) * 64 + lane] = acc[t][r] + acs[t][r];
+    for (int r = 0; r < 16; ++r) lds[((sh * 9 + dy * 3 + t) * 16 + r) * 64 + lane] = acc[t][r];
   __syncthreads();
   float tot[9 * 1024 / kThreads];
 #pragma unroll
@@ -251,11 +278,7 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_x3_f32_kernel(WgX3Args w)
   const int nci = min(32, w.Cin - ci_base) * 9, nco = min(32, w.Cout - co_base);
   float* out = w.part + (((size_t)chunk * w.Cout + co_base) * w.Cin + ci_base) * 9;
   for (int co = wave; co < nco; co += kWaves)
-    for (int i = lane; i < nci; i += 64) {
-      float d = lds[co * 288 + i];
-      if (!finite_f(d)) d = wgx3_element(w, co_base + co, ci_base + i / 9, i % 9, r0, min(s_end * R, w.rows));
-      out[(size_t)co * w.Cin * 9 + i] = d;
-    }
+    for (int i = lane; i < nci; i += 64) out[(size_t)co * w.Cin * 9 + i] = lds[co * 288 + i];
 }
 
 struct WgX3Pick {

@@ -69,22 +69,6 @@ __device__ __forceinline__ void pw_product_xy(unsigned id, unsigned n, const PwA
   by = __builtin_amdgcn_readfirstlane(a.order ? lo : hi);
 }
 
-// one element of the product by its definition, from the weights' pieces (their sum is the weight)
-__device__ __forceinline__ float pw_element(const uint4* Wp, const float* xp, int m, int Kdim, int KG, int HW) {
-  const uint32_t* w = reinterpret_cast<const uint32_t*>(Wp + ((size_t)(m >> 5) * KG * 3) * 64 + (m & 31));
-  float s = 0.f;
-  for (int k = 0; k < Kdim; ++k) {
-    const size_t o = ((size_t)(k >> 4) * 3 * 64 + 32 * ((k >> 3) & 1)) * 4 + ((k & 7) >> 1);
-    float p[3];
-    for (int i = 0; i < 3; ++i) {
-      const uint32_t u = w[o + (size_t)i * 256];
-      p[i] = __uint_as_float((k & 1) ? u & 0xffff0000u : u << 16);
-    }
-    s = fmaf(p[0] + (p[1] + p[2]), xp[(size_t)k * HW], s);
-  }
-  return s;
-}
-
 template <int PXL> struct PxVec { float v[PXL]; };  // PXL neighbouring pixels
 template <int PXL>
 __device__ __forceinline__ PxVec<PXL> px_load(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so) {
@@ -115,6 +99,9 @@ struct PwLane {
   unsigned n0, k, p;  // first sample; the lane's sample from there and its pixel
   bool valid;
   unsigned vx, vy;    // channel 8 * (l/32) of X, row m0 + 4 * (l/32) of Y
+  __device__ __forceinline__ const float* pixel(const PwArgs& a) const {  // channel 0 of X
+    return valid ? a.X + xo + (size_t)k * a.Kdim * a.HW + p : a.X;
+  }
   size_t xo, yo;
   __amdgpu_buffer_rsrc_t rx, ry;
   __device__ __forceinline__ PwLane(const PwArgs& a, unsigned q0, int m0) {
@@ -135,13 +122,12 @@ struct PwLane {
 // row of accumulator register i, without the lane's 4 * (l/32)
 __device__ __forceinline__ constexpr int acc_row(int i) { return 8 * (i >> 2) + (i & 3); }
 
-// acc + acs += A X over the groups [gbeg, gend) of 16 channels; PXL column tiles (column j of tile t is pixel PXL*j + t of
+// acc + acs += A X over the groups [gbeg, gend) of 16 channels, at least one; PXL column tiles (column j of tile t is pixel PXL*j + t of
 // the wavefront), MT row tiles.  The next group is in flight while one is multiplied; the loads past the last group are
 // outside every extent, and channels past Kdim meet zero weights.
 template <int PXL, int MT>
 __device__ __forceinline__ void pw_contract(const uint4* wl, size_t wt, __amdgpu_buffer_rsrc_t rx, unsigned vx, unsigned row_bytes,
                                             int gbeg, int gend, floatx16 (&acc)[MT][PXL], floatx16 (&acs)[MT][PXL]) {
-  if (gbeg >= gend) return;  // uniform
   uint4 a0[MT][3], a1[MT][3];
   PxVec<PXL> b0[8], b1[8];
   auto load = [&](uint4 (&a)[MT][3], PxVec<PXL> (&b)[8], int g) __attribute__((always_inline)) {
@@ -179,13 +165,34 @@ __device__ __forceinline__ void pw_contract(const uint4* wl, size_t wt, __amdgpu
     __builtin_amdgcn_sched_barrier(0);
   };
   load(a0, b0, gbeg);
-  for (int g = gbeg; g < gend; g += 2) {
+  int g = gbeg;
+  do {
     load(a1, b1, g + 1);
     mma(a0, b0);
     if (g + 1 < gend) {
       load(a0, b0, g + 2);
       mma(a1, b1);
     }
+    g += 2;
+  } while (g < gend);
+}
+
+// acc += A X over the groups [gbeg, gend) for one row tile and the pixel at xq of each lane, on the fp32 matrix instructions
+// (kernels_f32_x3.h: where the pieces gave no finite sum)
+__device__ __forceinline__ void pw_contract_f32(const uint4* wl, const float* xq, bool valid, size_t HW, int Kdim, int gbeg,
+                                                int gend, floatx16& acc) {
+  const int half = threadIdx.x >> 5 & 1;
+#pragma unroll 1
+  for (int g = gbeg; g < gend; ++g) {
+    uint4 p[3];
+    float w[8], x[8];
+    const int k = g * 16 + 8 * half;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) p[i] = wl[(size_t)(g * 3 + i) * 64];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = valid && k + j < Kdim ? xq[(size_t)(k + j) * HW] : 0.f;
+    join3(p, w);
+    acc = mfma_f32(w, x, acc);
   }
 }
 
@@ -229,37 +236,39 @@ __device__ __forceinline__ void block_stats(const float2* sd, int waves, int row
   }
 }
 
-// Results that are not finite again by their definition, over what was stored: rows [m0, m1) of the wavefront's pixels,
-// and the statistics of those rows if sd != NULL.
+// The results of rows [m0, m1) of the wavefront's pixels that are not finite once more, over what was stored, and the
+// statistics of those rows.  (Behind everything else: a branch in front of the stores costs the wide form its registers.)
 template <int PXL>
-__device__ __forceinline__ void pw_again(const PwArgs& a, const PwLane<PXL>& L, int m0, int m1, float2* sd) {
+__device__ __forceinline__ void pw_again(const PwArgs& a, const PwLane<PXL>& L, const uint4* wl, int m0, int m1, float2* sd) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores in front
-  const int lane = threadIdx.x & 63;
-  for (int m = m0; m < m1; ++m) {
-    float s = 0.f, q = 0.f;
-    if (L.valid && lane < 32 && m < a.Mdim)
-      for (int t = 0; t < PXL; ++t) {
-        float v = pw_element(a.Wp, a.X + L.xo + (size_t)L.k * a.Kdim * a.HW + L.p + t, m, a.Kdim, a.KG, a.HW);
-        s += v;
-        q = fmaf(v, v, q);
-        const size_t o = ((size_t)(L.n0 + L.k) * a.Mdim + m) * a.HW + L.p + t;
-        if (a.bias) v += a.bias[m];
-        if (a.add) v += a.add[o];
-        a.Y[o] = v;
-      }
-    if (sd) {  // uniform
-      s = wave_sum(s);
-      q = wave_sum(q);
-      if (lane == 0) sd[m - m0] = make_float2(s, q);
-    }
-  }
-}
-// Sum of 0 * v: 0 as long as every v is finite, else NaN
-template <int N>
-__device__ __forceinline__ float finite_test(const float (&v)[N], float c) {
+  const int half = threadIdx.x >> 5 & 1;
+  const unsigned row_bytes = (unsigned)a.HW * 4u;
+  const __amdgpu_buffer_rsrc_t ra = rsrc_words(a.add ? a.add + L.yo : a.Y, a.add ? a.y_words - L.yo : 0);
+#pragma unroll 1
+  for (int m = m0; m < m1; m += 32) {
+    float s[16], q[16];
 #pragma unroll
-  for (int i = 0; i < N; ++i) c = fmaf(v[i], 0.f, c);
-  return c;
+    for (int i = 0; i < 16; ++i) s[i] = q[i] = 0.f;
+#pragma unroll 1
+    for (int t = 0; t < PXL; ++t) {
+      floatx16 v = zero16();
+      pw_contract_f32(wl + (size_t)(m - m0) / 32 * a.KG * 192, L.pixel(a) + t, L.valid, a.HW, a.Kdim, 0, a.KG, v);
+      const int rows = L.valid ? m1 - m - 4 * half : 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const unsigned at = acc_row(i) < rows ? L.vy + (unsigned)(m - m0 + acc_row(i)) * row_bytes + 4u * t : kOutside;
+        const float y = px_load<1>(L.ry, at, 0).v[0];
+        float o = v[i];
+        if (a.bias) o += a.bias[min(m + acc_row(i) + 4 * half, m1 - 1)];
+        if (a.add) o += px_load<1>(ra, at, 0).v[0];
+        o = finite_f(y) ? y : o;
+        px_store<1>(L.ry, at, {o});
+        s[i] += o;
+        q[i] = fmaf(o, o, q[i]);
+      }
+    }
+    if (a.stats) tile_stats(s, q, sd + (m - m0));  // uniform
+  }
 }
 
 // A wavefront: 32 * PXL pixels x MT 32-row tiles, blocks of any number of wavefronts side by side over the pixels.  More
@@ -287,12 +296,7 @@ __device__ __forceinline__ void pw_body(const PwArgs& a, int bx, int by, float2*
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int t = 0; t < PXL; ++t)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        acc[m][t][i] += acs[m][t][i];
-        bad = fmaf(acc[m][t][i], 0.f, bad);
-      }
+    for (int t = 0; t < PXL; ++t) bad = add_small(acc[m][t], acs[m][t], bad);
   if (a.stats) {  // uniform; only without bias and addend; pixels past the last hold zeros
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
@@ -343,7 +347,7 @@ __device__ __forceinline__ void pw_body(const PwArgs& a, int bx, int by, float2*
       px_store<PXL>(L.ry, full || 32 * m + acc_row(i) < rows ? vo : kOutside, v);
       vo += (i & 3) == 3 ? 5 * row_bytes : row_bytes;
     }
-  if (__any(bad != 0.f)) pw_again<PXL>(a, L, m0, m0 + 32 * MT, a.stats ? sd + wave * MT * 32 : nullptr);  // (NaN != 0)
+  if (any_not_finite(bad)) pw_again<PXL>(a, L, wl, m0, min(m0 + 32 * MT, Mdim), sd + wave * MT * 32);
   if (a.stats) block_stats(sd, blockDim.x >> 6, 32 * MT, a.stats, m0, Mdim, bx, P);
 }
 template <int PXL, int MT>
@@ -372,16 +376,28 @@ __device__ __forceinline__ void pw_ks_body(const PwArgs& a, int bx, int by, floa
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[m][0][i] = acs[m][0][i] = 0.f;
-  const int gper = (KG + WK - 1) / WK, gbeg = wave * gper;
-  pw_contract<1, MT>(wl, wt, L.rx, L.vx, row_bytes, gbeg, min(gbeg + gper, KG), acc, acs);
+  const int gper = (KG + WK - 1) / WK, gbeg = wave * gper, gend = min(gbeg + gper, KG);
+  if (gbeg < gend) pw_contract<1, MT>(wl, wt, L.rx, L.vx, row_bytes, gbeg, gend, acc, acs);  // uniform
+  float bad = 0.f;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) bad = add_small(acc[m][0], acs[m][0], bad);
+  if (any_not_finite(bad)) {  // the wavefront's share again
+#pragma unroll 1
+    for (int m = 0; m < MT; ++m) {
+      floatx16 again = zero16();
+      pw_contract_f32(wl + m * wt, L.pixel(a), L.valid, a.HW, a.Kdim, gbeg, gend, again);
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+        if (m == j) take_not_finite(acc[j][0], again);
+    }
+  }
   constexpr int RW = 16 / WK;  // rows of the register layout that each wavefront finishes
   const __amdgpu_buffer_rsrc_t ra = rsrc_words(a.add ? a.add + L.yo : a.Y, a.add ? a.y_words - L.yo : 0);
-  bool bad = false;
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     if (m) __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sR[wave][i][lane] = acc[m][0][i] + acs[m][0][i];
+    for (int i = 0; i < 16; ++i) sR[wave][i][lane] = acc[m][0][i];
     __syncthreads();
 #pragma unroll
     for (int rr = 0; rr < RW; ++rr) {
@@ -391,10 +407,6 @@ __device__ __forceinline__ void pw_ks_body(const PwArgs& a, int bx, int by, floa
       for (int s = 0; s < WK; s += 4)  // fixed order
         v += (sR[s][i][lane] + sR[s + 1][i][lane]) + (sR[s + 2][i][lane] + sR[s + 3][i][lane]);
       const unsigned vo = L.valid && mm < Mdim ? L.vy + (unsigned)r * row_bytes : kOutside;
-      if (!finite_f(v) && vo != kOutside) {
-        bad = true;
-        v = pw_element(a.Wp, a.X + L.xo + (size_t)L.k * a.Kdim * a.HW + L.p, mm, a.Kdim, KG, a.HW);
-      }
       if (a.bias) v += a.bias[min(mm, Mdim - 1)];
       if (a.add) v += px_load<1>(ra, vo, 0).v[0];
       px_store<1>(L.ry, vo, {v});
@@ -483,8 +495,7 @@ __device__ __forceinline__ void pw_wide_body(const PwArgs& a, int bx, int by, fl
       tile(a1, t + 1);
     }
   }
-  if (__any(bad != 0.f))  // (NaN != 0)
-    pw_again<1>(a, L, t0 * 32, t1 * 32, a.stats ? sd + wave * a.mper * 32 : nullptr);
+  if (any_not_finite(bad)) pw_again<1>(a, L, wl + (size_t)t0 * KG * 192, t0 * 32, min(t1 * 32, Mdim), sd + wave * a.mper * 32);
 }
 constexpr int kWideTiles = 8;  // most row tiles of a wavefront
 template <int G>
@@ -672,16 +683,25 @@ template <int TCO, int TCI>
 struct WgTile {
   static constexpr int ROWS = (TCO + TCI) * 32, PLANE = ROWS * 128, LDS = 3 * PLANE / 4;  // bytes, floats
 };
-// dW of one element over the pixels [q0, q1), by its definition
-__device__ __forceinline__ float wg_element(const WgArgs& w, int co, int ci, unsigned q0, unsigned q1) {
-  float s = 0.f;
-  const unsigned HW = (unsigned)w.HW;
-  unsigned n = q0 / HW, p = q0 - n * HW;
-  for (unsigned q = q0; q < q1; ++q) {
-    s = fmaf(w.g[((size_t)n * w.Cout + co) * HW + p], w.x[((size_t)n * w.Cin + ci) * HW + p], s);
-    if (++p == HW) { p = 0; ++n; }
+// acc += one 32 x 32 tile of dW over a wavefront's pixels of the steps [s0, s1), on the fp32 matrix instructions
+// (kernels_f32_x3.h: where the pieces gave no finite sum)
+__device__ __forceinline__ void wg_contract_f32(const WgArgs& w, int co, int ci, int wave, int s0, int s1, floatx16& acc) {
+  const unsigned HW = (unsigned)w.HW, Q = (unsigned)w.NQ;
+  const int half = threadIdx.x >> 5 & 1;
+  co += threadIdx.x & 31;
+  ci += threadIdx.x & 31;
+#pragma unroll 1
+  for (int s = s0; s < s1; ++s) {
+    const unsigned q0 = (unsigned)s * 64u + 4u * (2 * wave + half), n0 = q0 / HW;  // (word 2 * wave + half of every row)
+    float g[8], x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const unsigned q = q0 + 32 * (e >> 2) + (e & 3), r = q - n0 * HW, k = plane_of(r, HW, w.rHW), n = n0 + k, p = r - k * HW;
+      g[e] = q < Q && co < w.Cout ? w.g[((size_t)n * w.Cout + co) * HW + p] : 0.f;
+      x[e] = q < Q && ci < w.Cin ? w.x[((size_t)n * w.Cin + ci) * HW + p] : 0.f;
+    }
+    acc = mfma_f32(g, x, acc);
   }
-  return s;
 }
 
 template <int TCO, int TCI, bool VEC>
@@ -789,19 +809,28 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
 #pragma unroll
     for (int j = 0; j < TCI; ++j) {
       __syncthreads();
+      float bad = 0.f, *const own = red + wave * 1024 + lane;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = acc[i][j][r] + acs[i][j][r];
+      for (int r = 0; r < 16; ++r) {
+        const float v = acc[i][j][r] + acs[i][j][r];
+        bad = fmaf(v, 0.f, bad);
+        own[r * 64] = v;
+      }
+      if (any_not_finite(bad)) {
+        floatx16 again = zero16();
+        wg_contract_f32(w, co_base + i * 32, ci_base + j * 32, wave, s0, s1, again);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (!finite_f(own[r * 64])) own[r * 64] = again[r];
+      }
       __syncthreads();
       const int ci = ci_base + j * 32 + row;
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
         const int r = wave * 4 + rr, co = co_base + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         const float* v = red + r * 64 + lane;
-        float d = (float)(((double)v[0] + v[16 * 64]) + ((double)v[2 * 16 * 64] + v[3 * 16 * 64]));
-        if (ci < Cin && co < Cout) {
-          if (!finite_f(d)) d = wg_element(w, co, ci, (unsigned)s0 * 64u, min((unsigned)s1 * 64u, Q));
-          out[(size_t)co * Cin + ci] = d;
-        }
+        const float d = (float)(((double)v[0] + v[16 * 64]) + ((double)v[2 * 16 * 64] + v[3 * 16 * 64]));
+        if (ci < Cin && co < Cout) out[(size_t)co * Cin + ci] = d;
       }
     }
 }
@@ -969,13 +998,17 @@ static void launch_dual(hipStream_t st, const PwArgs& a, const WgArgs& w, unsign
   }
 }
 
-void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
-                     float* part, float* G, int N, int Cin, int Cout, int HW, int cap) {
-  PwPick p = pw_pick((long)N * HW, HW, Cout, Cin, true);  // dx = W^T g (+ add)
+static PwPick bwd_pick(int N, int Cin, int Cout, int HW) {
+  PwPick p = pw_pick((long)N * HW, HW, Cout, Cin, true);
   if (p.var == PW_KS8) {  // a launch has blocks of one size: four shares of the contraction cost less than a second launch
     p.var = PW_KS4;
     p.waves = 4;
   }
+  return p;
+}
+void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,
+                     float* part, float* G, int N, int Cin, int Cout, int HW, int cap) {
+  const PwPick p = bwd_pick(N, Cin, Cout, HW);  // dx = W^T g (+ add)
   const PwArgs a = pw_args(Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW, p);
   const WgPick wp = wg_pick(N, Cin, Cout, HW, cap);
   const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
@@ -1075,3 +1108,16 @@ void reduce_parts_acc_f32(hipStream_t st, const float* part, float* G, size_t n,
 }
 
 }  // namespace ast
+
+// The choices above, for tests: out = {product's form (PwVar), pixel blocks, row tiles of a block's wavefront walk, wavefronts}
+// of a forward product without bias or of an input gradient, and {block shape, ranges} of a weight gradient.
+extern "C" void ast_pw_choice(int dgrad, int N, int Cin, int Cout, int HW, int out[4]) {
+  using namespace ast;
+  const PwPick p = dgrad ? bwd_pick(N, Cin, Cout, HW) : pw_pick((long)N * HW, HW, Cin, Cout, true);
+  out[0] = p.var; out[1] = p.gx; out[2] = p.mper; out[3] = p.waves;
+}
+extern "C" void ast_pw_wgrad_choice(int N, int Cin, int Cout, int HW, int cap, int out[2]) {
+  using namespace ast;
+  const WgPick p = wg_pick(N, Cin, Cout, HW, cap);
+  out[0] = p.shape; out[1] = (int)p.grid.x;
+}

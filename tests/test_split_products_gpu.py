@@ -5,7 +5,7 @@ import pytest
 
 import harness
 from asteroid_workloads import gen
-from asteroid_workloads.configs import conv, simple
+from asteroid_workloads.configs import bn, conv, simple
 from test_parity_gpu import A, one  # noqa: F401  (A: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -57,11 +57,27 @@ def test_pointwise_skip_gradient(A):
         assert max(sc["r0.y"], sc["r0.dx"]) <= 4e-7
 
 
-@pytest.mark.parametrize("cin,cout,h,B", [(24, 40, 6, 3), (160, 40, 7, 2), (72, 72, 24, 90), (24, 104, 56, 20)])
-def test_pointwise_operands_that_are_not_finite(A, cin, cout, h, B):
+KS4, KS4X2, KS8, WIDE = 4, 5, 6, 7
+PX1, PX1X2, PX2, PX2X2 = 0, 1, 2, 3
+
+
+def pw_choice(dgrad, n, cin, cout, hw):
+    """Form of a pointwise product: pixels per lane x row tiles, shares of the contraction, or all row tiles in one wavefront."""
+    import ctypes
+    out = (ctypes.c_int * 4)()
+    import paper_2408_08015_amd as A_
+    ctypes.CDLL(A_.lib_path()).ast_pw_choice(dgrad, n, cin, cout, hw, out)
+    return out[0]
+
+
+@pytest.mark.parametrize("cin,cout,h,B,fwd,dgrad", [
+    (24, 40, 6, 3, PX1, PX1), (272, 40, 7, 2, KS8, PX1), (40, 272, 7, 2, PX1, KS4), (528, 520, 7, 16, KS4X2, KS4X2),
+    (72, 72, 24, 90, PX2, PX2), (80, 72, 25, 20, PX1X2, PX1X2), (104, 136, 24, 35, PX2X2, PX2), (24, 104, 56, 20, WIDE, PX2)])
+def test_pointwise_operands_that_are_not_finite(A, cin, cout, h, B, fwd, dgrad):
     """An infinity or NaN reaches the outputs that its definition gives and no others, with the right sign, and the largest
     finite values are still values."""
     import torch
+    assert (pw_choice(0, B, cin, cout, h * h), pw_choice(1, B, cin, cout, h * h)) == (fwd, dgrad)
     rng = np.random.default_rng(3)
     x = rng.standard_normal((B, cin, h, h)).astype(np.float32)
     dy = rng.standard_normal((B, cout, h, h)).astype(np.float32)
@@ -97,6 +113,63 @@ def test_pointwise_operands_that_are_not_finite(A, cin, cout, h, B):
         np.testing.assert_array_equal(got[~fin], want[~fin])
         assert np.isfinite(got[fin]).all()
         np.testing.assert_allclose(got[fin], want[fin], rtol=1e-5, atol=2e-3)
+
+
+@pytest.mark.parametrize("cin,cout,h,B,form", [(24, 104, 56, 20, WIDE), (104, 136, 24, 35, PX2X2), (16, 40, 14, 9, PX1)])
+def test_statistics_of_operands_that_round_to_infinity(A, cin, cout, h, B, form):
+    """The sums that a product leaves for the BatchNorm behind it are those of the values it stored."""
+    import torch
+    assert pw_choice(0, B, cin, cout, h * h) == form
+    rng = np.random.default_rng(8)
+    x = rng.standard_normal((B, cin, h, h)).astype(np.float32)
+    wt = rng.standard_normal((cout, cin)).astype(np.float32)
+    x[B - 1, 3, 1, 2] = 3.4e38
+    wt[:, 3] *= 1e-37 ** 0.9
+    wt[1, 3] = 0                 # (a channel of ordinary values)
+    st = A.Stage([conv(cin, cout, 1), bn(cout)], B, 1, 1, (cin, h, h), "f32", "nchw", True,
+                 stream=torch.cuda.current_stream().cuda_stream)
+    st.set_params(np.concatenate([wt.ravel(), np.ones(cout, np.float32), np.zeros(cout, np.float32)]))
+    y = torch.empty(B, cout, h, h, device="cuda")
+    st.forward(0, torch.from_numpy(x).cuda(), None, y, None)
+    torch.cuda.synchronize()
+    st.close()
+    z = np.matmul(wt.astype(np.float64), x.reshape(B, cin, -1).astype(np.float64))
+    want = (z - z.mean((0, 2), keepdims=True)) / np.sqrt(z.var((0, 2), keepdims=True) + 1e-5)
+    # (the values other than the large one are differences from the mean that it dominates)
+    np.testing.assert_allclose(y.cpu().numpy().reshape(z.shape), want, rtol=1e-5, atol=2e-5)
+
+
+@pytest.mark.parametrize("cin,cout,k,h,B", [(24, 144, 1, 56, 8), (256, 64, 1, 56, 4), (528, 520, 1, 7, 16), (512, 40, 1, 7, 4),
+                                            (64, 64, 3, 56, 4), (256, 256, 3, 14, 2), (64, 64, 3, 56, 16)])
+def test_time_of_operands_that_are_not_finite(A, cin, cout, k, h, B):
+    """A mini-batch that has diverged takes a few times as long as another one, not a hundred times."""
+    import torch
+    st = A.Stage([conv(cin, cout, k, 1, k // 2)], B, 1, 1, (cin, h, h), "f32", "nchw", True,
+                 stream=torch.cuda.current_stream().cuda_stream)
+    x, g = torch.randn(B, cin, h, h, device="cuda"), torch.randn(B, cout, h, h, device="cuda")
+    y, dx = torch.empty_like(g), torch.empty_like(x)
+    best = []
+    for bad in (False, True):
+        if bad:
+            x.fill_(float("nan"))
+            g.fill_(float("nan"))
+        ts = []
+        for _ in range(10):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            torch.cuda.synchronize()
+            ev[0].record()
+            st.forward(0, x, None, y, None)
+            st.backward(0, g, dx)
+            ev[1].record()
+            torch.cuda.synchronize()
+            st.step(0.0, 0.0)
+            ts.append(ev[0].elapsed_time(ev[1]))
+        best.append(min(ts))
+    print("%d -> %d k%d %dx%d B %d: finite %.0f us, NaN %.0f us" % (cin, cout, k, h, h, B, 1e3 * best[0], 1e3 * best[1]))
+    st.close()
+    # (2.7 times the matrix instructions, on top of the first attempt, and loads that nothing hides)
+    assert best[1] <= 8 * best[0]
+    assert torch.isnan(y).all() and torch.isnan(dx).all()
 
 
 def x3_choice(dgrad, n, cin, cout, h, w, k, s):
@@ -141,7 +214,8 @@ def test_dense_forms(A, sizes, fwd, dgrad):
     assert sc["r0.dx"] <= (bound(cout * k * k) if x3_choice(1, B, cin, cout, h, w, k, s) else 1e-6)
 
 
-@pytest.mark.parametrize("cin,cout,k,s,h,B", [(64, 64, 3, 1, 12, 4), (64, 32, 3, 2, 9, 2), (256, 64, 3, 1, 5, 2)])
+@pytest.mark.parametrize("cin,cout,k,s,h,B", [(64, 64, 3, 1, 12, 4), (64, 32, 3, 2, 9, 2), (256, 64, 3, 1, 5, 2),
+                                              (32, 512, 3, 1, 41, 8)])   # (the last: four pixel groups per wavefront)
 def test_dense_operands_that_are_not_finite(A, cin, cout, k, s, h, B):
     import torch
     rng = np.random.default_rng(4)
