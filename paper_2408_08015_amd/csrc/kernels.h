@@ -89,6 +89,7 @@ bool conv_mfma_supported(int Cin, int Cout, int k, int stride, int pad, int grou
 size_t conv_mfma_pack_floats(int Mdim, int Kdim, bool split);  // words of one copy
 // At most `cap` partials; the small count is what a stage falls back on to fit the static scratch array.
 int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap);
+int conv_mfma_wgrad_compact_parts(int N, int Cin, int Cout, int H, int W, int k, int stride);
 int conv_mfma_wgrad_small_parts(int N, int Cin, int Cout, int H, int W, int k, int stride);
 // Pixels of one chain of 32-bit additions with the rounding error of the direct kernel: its own chain, and a quarter per
 // partial for their addition in 32 bits (measured: 0.25 to 0.5).
@@ -195,7 +196,7 @@ struct RedTask {
 };
 void reduce_tasks_f32(hipStream_t st, const RedTask* tasks_dev, const unsigned short* block_task_dev, int nblocks);
 int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW, int cap);  // partial count of pw_wgrad_f32, at most cap
-int pw_wgrad_f32_small_parts(int N, int Cin, int Cout, int HW);  // the count of a stage that has to fit the static scratch
+int pw_wgrad_f32_compact_parts(int N, int Cin, int Cout, int HW);  // the count of a stage that has to fit the static scratch
 // Backward of a pointwise conv in one launch: dx = W^T g (+ add) with Wp_t the packed W^T, and
 // the weight-gradient partials (then G += their sum, unless G is NULL: left to the caller).
 void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* dx, const float* add, const float* x,

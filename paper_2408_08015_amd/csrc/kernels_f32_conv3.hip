@@ -14,6 +14,7 @@
 // per tap: g is loaded once per pass, x once per tap, shifted, strided and masked.
 // Partials per pixel chunk, layout [chunk][cout][cin][tap] = the layout of the weights.
 #include <algorithm>
+#include <climits>
 
 #include "device_utils.h"
 #include "kernels.h"
@@ -564,6 +565,11 @@ size_t conv_mfma_pack_floats(int Mdim, int Kdim, bool split) {
   return split ? x3_pack_floats(Mdim, Kdim) : pw_pack_floats(Mdim, Kdim);
 }
 
+int conv_mfma_wgrad_compact_parts(int N, int Cin, int Cout, int H, int W, int k, int stride) {
+  const int direct = conv_mfma_wgrad_small_parts(N, Cin, Cout, H, W, k, stride);
+  const int staged = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride, INT_MAX);
+  return staged > 0 ? std::min(direct, staged) : direct;
+}
 int conv_mfma_wgrad_parts(int N, int Cin, int Cout, int H, int W, int k, int stride, int cap) {
   if (const int xp = conv_x3_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) return xp;
   if (const int lp = conv_lds_wgrad_parts(N, Cin, Cout, H, W, k, stride, cap)) return lp;

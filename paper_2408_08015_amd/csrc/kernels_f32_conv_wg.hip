@@ -327,11 +327,8 @@ bool pick_wgx3(int N, int Cin, int Cout, int H, int W, int KS, int S, int cap, W
     it = seen.emplace(key, search_wgx3(W < 64 ? 8 : 16, N, Cin, Cout, H, W)).first;
   }
   p = it->second;
-  if (p.R > 0 && p.chunks > cap) {
-    p.per = cdiv(p.nstage, cap);
-    p.chunks = cdiv(p.nstage, p.per);
-  }
-  return p.R > 0;
+  // (fewer partials would make the chains longer than they are measured for; the staged kernel adds up in between)
+  return p.R > 0 && p.chunks <= cap;
 }
 
 }  // namespace

@@ -678,7 +678,8 @@ void pw_conv_f32(hipStream_t st, const float* Wp, const float* X, float* Y, cons
 // Word c lies at position c ^ (row/2 & 7): the sixteen lanes of one LDS access hit all 64 banks.
 //
 // Chains of additions: a rounding per 16 pixels (the small products have accumulators of their own), and a range is at most
-// WG_CHAIN steps, so no chain grows with the micro-batch; wavefronts and partials are added in 64 bits.
+// WG_CHAIN steps, so no chain grows with the micro-batch; wavefronts and partials are added in 64 bits.  LONG: where there is
+// no room for so many partials, a range is longer, and every WG_CHAIN steps of it go to 64-bit sums in registers.
 template <int TCO, int TCI>
 struct WgTile {
   static constexpr int ROWS = (TCO + TCI) * 32, PLANE = ROWS * 128, LDS = 3 * PLANE / 4;  // bytes, floats
@@ -704,7 +705,8 @@ __device__ __forceinline__ void wg_contract_f32(const WgArgs& w, int co, int ci,
   }
 }
 
-template <int TCO, int TCI, bool VEC>
+constexpr int WG_CHAIN = 32;
+template <int TCO, int TCI, bool VEC, bool LONG>
 __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bci, int bco, char* __restrict__ lds) {
   using T = WgTile<TCO, TCI>;
   constexpr int NI = TCO + TCI;  // a thread stages eight pixels of one row of each 32-row tile
@@ -777,6 +779,15 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
     for (int j = 0; j < TCI; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = acs[i][j][r] = 0.f;
+  double sum[LONG ? TCO : 1][LONG ? TCI : 1][LONG ? 16 : 1];
+  if constexpr (LONG) {
+#pragma unroll
+    for (int i = 0; i < TCO; ++i)
+#pragma unroll
+      for (int j = 0; j < TCI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[i][j][r] = 0.0;
+  }
   if (s0 < s1) load();  // uniform
   for (int s = s0; s < s1; ++s) {
     put();
@@ -799,6 +810,19 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
     mma(acs, 1, 1);
     mma(acs, 1, 0);
     mma(acs, 0, 1);
+    if constexpr (LONG) {
+      if ((s - s0) % WG_CHAIN == WG_CHAIN - 1) {  // uniform
+#pragma unroll
+        for (int i = 0; i < TCO; ++i)
+#pragma unroll
+          for (int j = 0; j < TCI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              sum[i][j][r] += (double)acc[i][j][r] + acs[i][j][r];
+              acc[i][j][r] = acs[i][j][r] = 0.f;
+            }
+      }
+    }
     if (s + 1 < s1) barrier();  // the buffer has been read
   }
   // the four wavefronts' sums of a tile are added in a fixed order; the staging buffer is free by now
@@ -812,7 +836,9 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
       float bad = 0.f, *const own = red + wave * 1024 + lane;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float v = acc[i][j][r] + acs[i][j][r];
+        float v;
+        if constexpr (LONG) v = (float)(sum[i][j][r] + ((double)acc[i][j][r] + acs[i][j][r]));
+        else v = acc[i][j][r] + acs[i][j][r];
         bad = fmaf(v, 0.f, bad);
         own[r * 64] = v;
       }
@@ -837,23 +863,23 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
 
 // The block shapes of the weight gradient: weight tiles (co x ci) per block, wavefronts per tile
 enum { WG_2x2 = 0, WG_2x1 = 1, WG_1x2 = 2, WG_1x1 = 3 };
-template <int SHAPE, bool VEC>
+template <int SHAPE, bool VEC, bool LONG = false>
 __device__ __forceinline__ void pw_wgrad_shape(const WgArgs& w, int split, int bci, int bco, float* lds) {
   constexpr int TCO = SHAPE == WG_2x2 || SHAPE == WG_2x1 ? 2 : 1, TCI = SHAPE == WG_2x2 || SHAPE == WG_1x2 ? 2 : 1;
-  pw_wgrad_body<TCO, TCI, VEC>(w, split, bci, bco, reinterpret_cast<char*>(lds));
+  pw_wgrad_body<TCO, TCI, VEC, LONG>(w, split, bci, bco, reinterpret_cast<char*>(lds));
 }
 template <int SHAPE>
 constexpr int wg_lds_floats() {
   return SHAPE == WG_2x2 ? WgTile<2, 2>::LDS : SHAPE == WG_1x1 ? WgTile<1, 1>::LDS : WgTile<2, 1>::LDS;
 }
 
-template <int SHAPE, bool VEC>
-__global__ __launch_bounds__(256, SHAPE == WG_2x2 ? 2 : 3) void pw_wgrad_f32_kernel(WgArgs w) {
+template <int SHAPE, bool VEC, bool LONG = false>
+__global__ __launch_bounds__(256, SHAPE == WG_2x2 || LONG ? 2 : 3) void pw_wgrad_f32_kernel(WgArgs w) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   int bx, t;
   pw_block_xy((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x, gridDim.y * gridDim.z,
               w.tile_order, bx, t);
-  pw_wgrad_shape<SHAPE, VEC>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, reinterpret_cast<float*>(lds));
+  pw_wgrad_shape<SHAPE, VEC, LONG>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, reinterpret_cast<float*>(lds));
 }
 
 // the wide product's forms in the launch below: more than 32 channels in, an addend
@@ -917,9 +943,9 @@ __global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __re
 //   between: 40 -> 240 at 32 x 30x30 2x1 14.5, 2x2 15.6; 64 -> 64 at 32 x 56x56 14.8, 15.8
 //   little (less than two blocks per compute unit): the smallest blocks with one step upwards
 // A range is at most WG_CHAIN steps: chains of 32 roundings.  Relative error of dW against 64 bits 5e-8 to 9e-8 over these
-// sizes (the fp32 matrix instructions with their sums in two levels: 8e-8 to 1.3e-7).
-static constexpr int WG_CHAIN = 32;
-struct WgPick { int shape; dim3 grid; };
+// sizes (the fp32 matrix instructions with their sums in two levels: 8e-8 to 1.3e-7).  A cap on the number of ranges that makes
+// them longer (chained) takes a shape with registers for 64-bit sums.
+struct WgPick { int shape; dim3 grid; bool chained; };
 static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
   const int a = cdiv(Cout, 32), b = cdiv(Cin, 32);
   static const int tco[4] = {2, 2, 1, 1}, tci[4] = {2, 1, 2, 1}, blocks[4] = {512, 768, 768, 1024};
@@ -936,15 +962,15 @@ static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
   if (a == 1 || b == 1) splits(WG_1x1, 64);
   else if (NQ * a * b >= 600000 || (NQ < 2048 && a * b >= 256)) splits(WG_2x2, 128);
   else if (splits(a % 2 && b % 2 == 0 ? WG_1x2 : WG_2x1, 128) < 512) splits(WG_1x1, 64);
+  p.chained = cdiv(cdiv(NQ, 64), p.grid.x) > WG_CHAIN;
+  if (p.chained && p.shape == WG_2x2) splits(a % 2 && b % 2 == 0 ? WG_1x2 : WG_2x1, 128);
   return p;
 }
 int pw_wgrad_f32_parts(int N, int Cin, int Cout, int HW, int cap) { return (int)wg_pick(N, Cin, Cout, HW, cap).grid.x; }
-// four wavefronts of 256, 128, 64 or 32 pixels of one sample per chunk, the most that leave 768 tiles and chunks
-int pw_wgrad_f32_small_parts(int N, int Cin, int Cout, int HW) {
-  const long tiles = (long)cdiv(Cin, 32) * cdiv(Cout, 32);
-  int px = 256;
-  while (px > 32 && (long)N * cdiv(HW, 4 * px) * tiles < 768) px /= 2;
-  return N * cdiv(HW, 4 * px);
+// The fewest that a stage is held to where more would not fit the static workspace: one wavefront per SIMD and tile.
+int pw_wgrad_f32_compact_parts(int N, int Cin, int Cout, int HW) {
+  const long fill = std::min((long)cdiv(768, (long)cdiv(Cin, 32) * cdiv(Cout, 32)), (long)N * HW / 128);
+  return (int)std::max(1L, fill);
 }
 size_t pw_wgrad_f32_ws(int N, int Cin, int Cout, int HW, int cap) {
   return (size_t)pw_wgrad_f32_parts(N, Cin, Cout, HW, cap) * Cin * Cout;
@@ -963,8 +989,19 @@ static void launch_wgrad(hipStream_t st, const WgArgs& w, dim3 grid, bool vec) {
   if (vec) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true>), grid, dim3(256), 0, st, w);
   else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false>), grid, dim3(256), 0, st, w);
 }
+template <int SHAPE>
+static void launch_chained(hipStream_t st, const WgArgs& w, dim3 grid, bool vec) {
+  if (vec) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true, true>), grid, dim3(256), 0, st, w);
+  else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false, true>), grid, dim3(256), 0, st, w);
+}
 static void launch_wgrad(hipStream_t st, const WgArgs& w, const WgPick& p) {
   const bool vec = w.HW % 4 == 0;
+  if (p.chained) {
+    if (p.shape == WG_2x1) launch_chained<WG_2x1>(st, w, p.grid, vec);
+    else if (p.shape == WG_1x2) launch_chained<WG_1x2>(st, w, p.grid, vec);
+    else launch_chained<WG_1x1>(st, w, p.grid, vec);
+    return;
+  }
   switch (p.shape) {
     case WG_2x2: launch_wgrad<WG_2x2>(st, w, p.grid, vec); break;
     case WG_2x1: launch_wgrad<WG_2x1>(st, w, p.grid, vec); break;
@@ -1013,7 +1050,10 @@ void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* d
   const WgPick wp = wg_pick(N, Cin, Cout, HW, cap);
   const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
   const unsigned nA = p.gx * p.gy;
-  switch (p.var) {
+  if (wp.chained) {  // rare: not worth the forms of the common launch
+    pw_conv_f32(st, Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW, nullptr);
+    launch_wgrad(st, w, wp);
+  } else switch (p.var) {
     case PW_1x1: launch_dual<PW_1x1>(st, a, w, nA, wp); break;
     case PW_1x2: launch_dual<PW_1x2>(st, a, w, nA, wp); break;
     case PW_2x1: launch_dual<PW_2x1>(st, a, w, nA, wp); break;
@@ -1110,14 +1150,15 @@ void reduce_parts_acc_f32(hipStream_t st, const float* part, float* G, size_t n,
 }  // namespace ast
 
 // The choices above, for tests: out = {product's form (PwVar), pixel blocks, row tiles of a block's wavefront walk, wavefronts}
-// of a forward product without bias or of an input gradient, and {block shape, ranges} of a weight gradient.
+// of a forward product without bias or of an input gradient, and {block shape, ranges, 64-bit sums} of a
+// weight gradient.
 extern "C" void ast_pw_choice(int dgrad, int N, int Cin, int Cout, int HW, int out[4]) {
   using namespace ast;
   const PwPick p = dgrad ? bwd_pick(N, Cin, Cout, HW) : pw_pick((long)N * HW, HW, Cin, Cout, true);
   out[0] = p.var; out[1] = p.gx; out[2] = p.mper; out[3] = p.waves;
 }
-extern "C" void ast_pw_wgrad_choice(int N, int Cin, int Cout, int HW, int cap, int out[2]) {
+extern "C" void ast_pw_wgrad_choice(int N, int Cin, int Cout, int HW, int cap, int out[3]) {
   using namespace ast;
   const WgPick p = wg_pick(N, Cin, Cout, HW, cap);
-  out[0] = p.shape; out[1] = (int)p.grid.x;
+  out[0] = p.shape; out[1] = (int)p.grid.x; out[2] = p.chained;
 }

@@ -10,8 +10,8 @@
 // piece product that is not finite, so the sum is not finite either: a wavefront that holds such sums forms them again on
 // the fp32 matrix instructions from the operands themselves, and takes those.  Where every value is NaN that is the time of
 // both and of loads that nothing hides: forward and backward of 24 -> 144 channels at 8 x 56x56 31 us finite, 59 us NaN; 64 ->
-// 64 3x3 at 16 x 56x56 130 and 480; 256 -> 256 3x3 at 2 x 14x14 56 and 126.  (By their definition, element by element, they
-// took 490, 5000 and 2950 us.)
+// 64 3x3 at 4 x 56x56 63 and 155; 256 -> 256 3x3 at 2 x 14x14 56 and 126.  (By their definition, element by element, they
+// took 490, 2070 and 2950 us.)
 #pragma once
 #include "device_utils.h"
 

@@ -575,21 +575,51 @@ ast_status build_plan(Stage& s, std::string& err) {
     s.ws_bytes = s.fscratch_off + align_up(fsc, 256) + 256;
   };
   lay_out_scratch();
-  // The kernels choose the number of weight-gradient partials for speed alone.  A stage that this takes past the static
-  // scratch array, and that fits it with fewer, takes fewer.
+  // The kernels choose the number of weight-gradient partials, and the convolutions in front of a BatchNorm the number of
+  // statistics partials that they leave, for speed alone.  Where these take a stage past the static scratch array, the
+  // convolutions that can give most of it back take fewer weight-gradient partials, one after the other until the stage fits,
+  // and then the BatchNorms a statistics pass of their own; a stage that does not fit all the same keeps the fast counts.
   if (s.ws_bytes > (size_t)AST_STATIC_SCRATCH_BYTES) {
-    auto set_caps = [&](bool small) {
-      for (Op& op : s.ops) {
-        const Act& I = s.acts[op.in];
-        op.wg_cap = INT_MAX;
-        if (small && op.kind == OP_CONV_PW) op.wg_cap = pw_wgrad_f32_small_parts(I.n, op.cin, op.cout, I.h * I.w);
-        if (small && op.kind == OP_CONV_3X3)
-          op.wg_cap = conv_mfma_wgrad_small_parts(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride);
-      }
+    const std::vector<Op> fast = s.ops;
+    auto fits = [&] {
       lay_out_scratch();
+      return s.ws_bytes <= (size_t)AST_STATIC_SCRATCH_BYTES;
     };
-    set_caps(true);
-    if (s.ws_bytes > (size_t)AST_STATIC_SCRATCH_BYTES) set_caps(false);
+    struct Fewer { size_t saved; Op* op; int cap; };
+    std::vector<Fewer> list;
+    for (Op& op : s.ops) {
+      const Act& I = s.acts[op.in];
+      if (op.kind == OP_CONV_PW) {
+        const int HW = I.h * I.w, cap = pw_wgrad_f32_compact_parts(I.n, op.cin, op.cout, HW);
+        list.push_back({pw_wgrad_f32_ws(I.n, op.cin, op.cout, HW, INT_MAX) - pw_wgrad_f32_ws(I.n, op.cin, op.cout, HW, cap), &op, cap});
+      } else if (op.kind == OP_CONV_3X3) {
+        const int cap = conv_mfma_wgrad_compact_parts(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride);
+        list.push_back({conv_mfma_wgrad_ws(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride, INT_MAX) -
+                            conv_mfma_wgrad_ws(I.n, op.cin, op.cout, I.h, I.w, op.k, op.stride, cap), &op, cap});
+      }
+    }
+    std::stable_sort(list.begin(), list.end(), [](const Fewer& a, const Fewer& b) { return a.saved > b.saved; });
+    bool ok = false;
+    for (size_t i = 0; i < list.size() && !ok && list[i].saved > 0; ++i) {
+      list[i].op->wg_cap = list[i].cap;
+      ok = fits();
+    }
+    if (!ok) {
+      for (Op& pw : s.ops) {
+        if (pw.kind != OP_CONV_PW || pw.stats_op < 0) continue;
+        Op& bn = s.ops[pw.stats_op];
+        const Act& I = s.acts[bn.in];
+        if (bn.given_parts <= bn_parts(I.n, I.h * I.w)) continue;
+        bn.bn_stats_given = false;
+        bn.given_parts = 0;
+        pw.stats_op = -1;
+      }
+      ok = fits();
+    }
+    if (!ok) {
+      s.ops = fast;
+      lay_out_scratch();
+    }
   }
   return AST_OK;
 }

@@ -4,6 +4,7 @@ import ctypes
 import pytest
 
 import paper_2408_08015_amd as A
+from asteroid_workloads.configs import bn, conv, irb, simple
 
 FWD, DGRAD, WGRAD = 0, 1, 2
 
@@ -97,3 +98,35 @@ def test_size_limit_of_the_staged_convolutions(what, n, cin, cout, h, k, s, read
     assert (n * cout * ((h - 1) // s + 1) ** 2 * 4 < 2 ** 31) == reads_g
     want = {FWD: reads_x, DGRAD: reads_g, WGRAD: reads_x and reads_g}[what]
     assert (choice(what, n, cin, cout, h, h, k, s) is not None) == want
+
+
+# Stages whose workspace with the counts that are fastest is past the static scratch array (33.6 MB), and with fewer is not:
+# backward_static takes them.
+BN_PAIR = lambda c, m: [conv(c, m, 1), bn(m), simple("relu6"), conv(m, c, 1), bn(c)]
+FIT_WITH_FEWER = [
+    ([conv(64, 128, 1), simple("relu"), conv(128, 64, 1)], 64, 40, 16),     # one pointwise weight gradient is enough
+    ([conv(256, 192, 1), simple("relu"), conv(192, 256, 1)], 256, 54, 5),
+    (BN_PAIR(16, 384), 16, 18, 29),                                         # statistics partials as well
+    (BN_PAIR(48, 64), 48, 32, 37),
+    ([conv(64, 384, 3, 1, 1), bn(384), simple("relu")], 64, 35, 11),        # dense weight gradients
+    ([conv(256, 144, 3, 1, 1), bn(144), simple("relu")], 256, 45, 17),
+    (irb(8, 24, 1, 6), 8, 36, 28),
+    (irb(128, 16, 1, 6), 128, 12, 14),
+]
+
+
+@pytest.mark.parametrize("layers,c,hw,n", FIT_WITH_FEWER)
+def test_workspace_fits_the_static_array(layers, c, hw, n):
+    assert A.plan_memory(layers, n, 1, 1, (c, hw, hw))[3] <= 32 << 20
+
+
+def test_weight_gradient_ranges():
+    """Chains of additions: at most 32 steps of 64 pixels to a range, or 64-bit sums in between."""
+    lib = ctypes.CDLL(A.lib_path())
+    out = (ctypes.c_int * 3)()
+    for cin, cout, hw, n in ((512, 512, 3136, 22), (1024, 96, 3025, 60), (2048, 32, 3136, 85), (24, 144, 3136, 128)):
+        steps = -(-n * hw // 64)
+        lib.ast_pw_wgrad_choice(n, cin, cout, hw, 2 ** 31 - 1, out)
+        assert not out[2] and -(-steps // out[1]) <= 32
+        lib.ast_pw_wgrad_choice(n, cin, cout, hw, 5, out)
+        assert out[2] and out[1] == 5 and out[0] != 0   # (not the block shape that has no registers left)

@@ -345,3 +345,46 @@ def test_dense_weight_gradient_of_operands_that_are_not_finite(A, cin, cout, h, 
     big = np.abs(want) > 1e6
     np.testing.assert_allclose(G[fin & ~big], want[fin & ~big], rtol=1e-5, atol=1e-4)
     np.testing.assert_allclose(G[fin & big], want[fin & big], rtol=1e-5)
+
+
+# One pointwise convolution whose weight gradient has few, long ranges so that its stage fits the static workspace: every block
+# shape that adds up in 64 bits, with loads of four and single words
+@pytest.mark.parametrize("cin,cout,h,B,shape", [(512, 512, 56, 22, 1), (520, 512, 55, 24, 1), (1024, 96, 55, 60, 2),
+                                                (1024, 90, 56, 60, 2), (2048, 32, 56, 85, 3), (2048, 31, 55, 90, 3)])
+def test_pointwise_weight_gradient_of_few_ranges(A, cin, cout, h, B, shape):
+    import ctypes
+    import torch
+    lib, out = ctypes.CDLL(A.lib_path()), (ctypes.c_int * 3)()
+    parts = max(1, min(-(-768 // (-(-cin // 32) * -(-cout // 32))), B * h * h // 128))
+    lib.ast_pw_wgrad_choice(B, cin, cout, h * h, parts, out)
+    assert tuple(out) == (shape, parts, 1)
+    st = A.Stage([conv(cin, cout, 1)], B, 1, 1, (cin, h, h), "f32", "nchw", True,
+                 stream=torch.cuda.current_stream().cuda_stream)
+    assert st.memory()[3] <= 32 << 20
+    gen_ = torch.Generator(device="cuda")
+    gen_.manual_seed(9)
+    w = torch.randn(cout, cin, generator=gen_, device="cuda")
+    st.set_params(w.cpu().numpy().ravel())
+    x = torch.randn(B, cin, h, h, generator=gen_, device="cuda").clamp_(min=0)
+    g = torch.randn(B, cout, h, h, generator=gen_, device="cuda")
+    y, dx, dx2 = torch.empty_like(g), torch.empty_like(x), torch.empty_like(x)
+    st.forward(0, x, None, y, None)
+    st.backward(0, g, dx)
+    G = st.get_grads()
+    st.step(0.0, 0.0)
+    st.forward(0, x, None, y, None)
+    st.backward_static(0, g, dx2)
+    np.testing.assert_array_equal(G, st.get_grads())
+    assert torch.equal(dx, dx2)
+    st.close()
+    ref = torch.zeros(cout, cin, dtype=torch.float64, device="cuda")
+    err = tot = 0.0
+    for n in range(B):
+        gn, xn = g[n].reshape(cout, -1).double(), x[n].reshape(cin, -1).double()
+        ref += gn @ xn.t().contiguous()
+        d = w.double().t().contiguous() @ gn
+        err += float((dx[n].reshape(cin, -1).double() - d).pow(2).sum())
+        tot += float(d.pow(2).sum())
+    G = torch.from_numpy(G).cuda().reshape(cout, cin).double()
+    assert float((G - ref).norm() / ref.norm()) <= BOUND_W
+    assert (err / tot) ** 0.5 <= bound(cout)
