@@ -31,7 +31,6 @@ struct PackTask {
 };
 void pw_pack_all_f32(hipStream_t st, const PackTask* tasks_dev, const unsigned short* block_task_dev, float* arena,
                      int nblocks);
-bool pw_conv_supported(int Cin, int Cout, int HW);  // else (planes of hundreds of MiB) the generic kernels apply
 // stats (may be NULL; needs bias == add == NULL and pw_conv_stats_parts() > 0): the kernel also
 // leaves (sum, sum of squares) of Y per channel and pixel block, stats[Mdim][pw_conv_stats_parts()][2],
 // for a BatchNorm behind the convolution.

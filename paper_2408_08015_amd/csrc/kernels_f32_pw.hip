@@ -509,6 +509,31 @@ __global__ __launch_bounds__(512, G <= 2 ? 4 : 2) void pw_conv_f32_wide_kernel(P
   if (a.stats) block_stats(sd, waves, rows, a.stats, by * rows, a.Mdim, bx, gridDim.x / a.gy);
 }
 
+// Planes that 32-bit offsets from a wavefront's first sample do not reach (pw_far): 64-bit addresses, one 32 x 32 tile per
+// wavefront on the fp32 matrix instructions, five and more wavefronts per SIMD to hide its loads.
+// One sample of 2048x2048, us (the generic kernels): 16 -> 96 channels forward 625 (9060), backward with the weight gradient 900
+// (27200); 96 -> 24 950 (13700) and 1160 (42000); 64 -> 128 1590 (47500) and 2570 (126000).
+__global__ __launch_bounds__(256, 5) void pw_conv_f32_far_kernel(PwArgs a) {
+  int bx, by;
+  pw_product_xy(blockIdx.x, gridDim.x, a, bx, by);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned q = ((unsigned)bx * 4u + wave) * 32u + (lane & 31), HW = (unsigned)a.HW;
+  const bool valid = q < a.NQ;
+  const unsigned n = valid ? q / HW : 0, p = valid ? q - n * HW : 0;
+  floatx16 acc = zero16();
+  pw_contract_f32(a.Wp + (size_t)by * a.KG * 192 + lane, a.X + (size_t)n * a.Kdim * HW + p, valid, HW, a.Kdim, 0, a.KG, acc);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int m = by * 32 + acc_row(i) + 4 * (lane >> 5);
+    if (!valid || m >= a.Mdim) continue;
+    const size_t o = ((size_t)n * a.Mdim + m) * HW + p;
+    float v = acc[i];
+    if (a.bias) v += a.bias[m];
+    if (a.add) v += a.add[o];
+    a.Y[o] = v;
+  }
+}
+
 // Split copy of A[m][k] = W[m*lda_m + k*lda_k]: for tile t of 32 rows, group g of 16 columns and piece i, lane l finds
 // A[32t + l%32][16g + 8*(l/32) + 0..7] as one 16-byte word at Wp[((t*KG + g)*3 + i)*64 + l]; zero outside.
 size_t x3_pack_floats(int Mdim, int Kdim) { return (size_t)cdiv(Mdim, 32) * cdiv(Kdim, 16) * 768; }
@@ -562,13 +587,20 @@ void pw_pack_f32(hipStream_t st, const float* W, int lda_m, int lda_k, float* Wp
 }
 
 // ---- which product kernel serves a shape, and its grid
-enum PwVar { PW_1x1, PW_1x2, PW_2x1, PW_2x2, PW_KS4, PW_KS4x2, PW_KS8, PW_WIDE };
+enum PwVar { PW_1x1, PW_1x2, PW_2x1, PW_2x2, PW_KS4, PW_KS4x2, PW_KS8, PW_WIDE, PW_FAR };
 struct PwPick { PwVar var; int waves, gx, gy, mper; };
+// A wavefront's offsets from its first sample are 32-bit: two samples and the rows of a tile past them have to be in reach.
+static bool pw_far(int Cin, int Cout, int HW) { return ((size_t)HW + 64) * (std::max(Cin, Cout) + 64) * 4 >= ((size_t)1 << 30); }
 // Measured over the layers of MobileNetV2, EfficientNet-B1 and ResNet50 at 1 to 32 samples; `tiles` counts 32 x 32 tiles.
 static PwPick pw_pick(long NQ, int HW, int Kdim, int Mdim, bool wide) {
   const int mt = cdiv(Mdim, 32), KG = cdiv(Kdim, 16);
   const long tiles = (long)cdiv(NQ, 32) * mt;
   PwPick p = {PW_1x1, 4, 0, mt, 0};
+  if (pw_far(Kdim, Mdim, HW)) {
+    p.var = PW_FAR;
+    p.gx = cdiv(NQ, 128);
+    return p;
+  }
   if (tiles < 1024 && KG >= 6) {
     // under one wavefront per SIMD: K is split.  Two row tiles per wavefront where that leaves K long (512 -> 2048 at
     // 8 x 7x7 11.6 us, one tile 13.2), eight shares where there are few tiles (960 -> 160 at 8 x 7x7 7.4 us, four 7.7).
@@ -598,9 +630,6 @@ static PwPick pw_pick(long NQ, int HW, int Kdim, int Mdim, bool wide) {
   return p;
 }
 
-// A wavefront's offsets from its first sample are 32-bit; operands that they do not reach go to the generic kernels.
-bool pw_conv_supported(int Cin, int Cout, int HW) { return ((size_t)HW + 64) * (std::max(Cin, Cout) + 64) * 4 < ((size_t)1 << 30); }
-
 static PwArgs pw_args(const float* Wp, const float* X, float* Y, const float* bias, const float* add, int N, int Kdim,
                       int Mdim, int HW, const PwPick& p) {
   PwArgs a;
@@ -622,7 +651,7 @@ static PwArgs pw_args(const float* Wp, const float* X, float* Y, const float* bi
 // 32 x 56x56 as 392 blocks of eight wavefronts 19.5 us, as 196 of sixteen 25.9 us: one block on a compute unit, and its loads
 // and stores take turns.)
 static bool pw_stats_blocks(PwPick& p, long NQ) {
-  if (p.var == PW_KS4 || p.var == PW_KS4x2 || p.var == PW_KS8) return false;
+  if (p.var == PW_KS4 || p.var == PW_KS4x2 || p.var == PW_KS8 || p.var == PW_FAR) return false;
   if (p.gx > 256) {
     p.waves = 8;
     p.gx = cdiv(NQ, 256L * (p.var == PW_2x1 || p.var == PW_2x2 ? 2 : 1));
@@ -654,6 +683,7 @@ static void launch_product(hipStream_t st, const PwArgs& a, const PwPick& p) {
       else if (a.KG == 2) launch_wide<2>(st, a, p);
       else launch_wide<4>(st, a, p);
       break;
+    case PW_FAR: KLAUNCH(pw_conv_f32_far_kernel, grid, block, 0, st, a); break;
   }
 }
 
@@ -706,7 +736,7 @@ __device__ __forceinline__ void wg_contract_f32(const WgArgs& w, int co, int ci,
 }
 
 constexpr int WG_CHAIN = 32;
-template <int TCO, int TCI, bool VEC, bool LONG>
+template <int TCO, int TCI, bool VEC, bool LONG, bool FAR>
 __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bci, int bco, char* __restrict__ lds) {
   using T = WgTile<TCO, TCI>;
   constexpr int NI = TCO + TCI;  // a thread stages eight pixels of one row of each 32-row tile
@@ -721,7 +751,37 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
   const unsigned row_bytes = HW * 4u;
   float rv[NI][8];
   unsigned q0 = (unsigned)s0 * 64u, n0 = __builtin_amdgcn_readfirstlane(q0 / HW), p0 = q0 - n0 * HW;  // of the step to load
+  // (FAR: planes that 32-bit offsets do not reach)
+  auto load_far = [&]() __attribute__((always_inline)) {
+    constexpr int NV = VEC ? 2 : 8;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const unsigned d = VEC ? 32 * j + 4 * sc : 32 * (j >> 2) + 4 * sc + (j & 3);
+      const unsigned k = plane_of(p0 + d, HW, w.rHW), p = p0 + d - k * HW;
+      const float* const gp = w.g + ((size_t)(n0 + k) * Cout + co_base + sr) * HW + p;
+      const float* const xp = w.x + ((size_t)(n0 + k) * Cin + ci_base + sr) * HW + p;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const bool isg = i < TCO;
+        const int row = (isg ? i : i - TCO) * 32;
+        const bool in = q0 + d < Q && (isg ? co_base + row + sr < Cout : ci_base + row + sr < Cin);
+        const float* const s = (isg ? gp : xp) + (size_t)row * HW;
+        if constexpr (VEC) {
+          const float4 v = in ? *reinterpret_cast<const float4*>(s) : make_float4(0.f, 0.f, 0.f, 0.f);
+          rv[i][4 * j] = v.x; rv[i][4 * j + 1] = v.y; rv[i][4 * j + 2] = v.z; rv[i][4 * j + 3] = v.w;
+        } else {
+          rv[i][j] = in ? *s : 0.f;
+        }
+      }
+    }
+    q0 += 64;
+    for (p0 += 64; p0 >= HW; p0 -= HW) ++n0;  // uniform
+  };
   auto load = [&]() __attribute__((always_inline)) {
+    if constexpr (FAR) {
+      load_far();
+      return;
+    }
     const size_t go = ((size_t)n0 * Cout + co_base) * HW, xo = ((size_t)n0 * Cin + ci_base) * HW;
     const __amdgpu_buffer_rsrc_t rg = rsrc_words(w.g + go, (size_t)Q * Cout - go), rx = rsrc_words(w.x + xo, (size_t)Q * Cin - xo);
     constexpr int NV = VEC ? 2 : 8;  // words of four pixels (HW % 4 == 0: they never leave their sample) or single ones
@@ -863,27 +923,27 @@ __device__ __forceinline__ void pw_wgrad_body(const WgArgs& w, int split, int bc
 
 // The block shapes of the weight gradient: weight tiles (co x ci) per block, wavefronts per tile
 enum { WG_2x2 = 0, WG_2x1 = 1, WG_1x2 = 2, WG_1x1 = 3 };
-template <int SHAPE, bool VEC, bool LONG = false>
+template <int SHAPE, bool VEC, bool LONG = false, bool FAR = false>
 __device__ __forceinline__ void pw_wgrad_shape(const WgArgs& w, int split, int bci, int bco, float* lds) {
   constexpr int TCO = SHAPE == WG_2x2 || SHAPE == WG_2x1 ? 2 : 1, TCI = SHAPE == WG_2x2 || SHAPE == WG_1x2 ? 2 : 1;
-  pw_wgrad_body<TCO, TCI, VEC, LONG>(w, split, bci, bco, reinterpret_cast<char*>(lds));
+  pw_wgrad_body<TCO, TCI, VEC, LONG, FAR>(w, split, bci, bco, reinterpret_cast<char*>(lds));
 }
 template <int SHAPE>
 constexpr int wg_lds_floats() {
   return SHAPE == WG_2x2 ? WgTile<2, 2>::LDS : SHAPE == WG_1x1 ? WgTile<1, 1>::LDS : WgTile<2, 1>::LDS;
 }
 
-template <int SHAPE, bool VEC, bool LONG = false>
+template <int SHAPE, bool VEC, bool LONG = false, bool FAR = false>
 __global__ __launch_bounds__(256, SHAPE == WG_2x2 || LONG ? 2 : 3) void pw_wgrad_f32_kernel(WgArgs w) {
   __shared__ float4 lds[wg_lds_floats<SHAPE>() / 4];
   int bx, t;
   pw_block_xy((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x, gridDim.y * gridDim.z,
               w.tile_order, bx, t);
-  pw_wgrad_shape<SHAPE, VEC, LONG>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, reinterpret_cast<float*>(lds));
+  pw_wgrad_shape<SHAPE, VEC, LONG, FAR>(w, bx, t % (int)gridDim.y, t / (int)gridDim.y, reinterpret_cast<float*>(lds));
 }
 
 // the wide product's forms in the launch below: more than 32 channels in, an addend
-constexpr int PW_WIDE4 = PW_WIDE + 1, PW_WIDE_ADD = PW_WIDE + 2, PW_WIDE4_ADD = PW_WIDE + 3;
+constexpr int PW_WIDE4 = PW_FAR + 1, PW_WIDE_ADD = PW_FAR + 2, PW_WIDE4_ADD = PW_FAR + 3;
 
 // Input gradient and weight-gradient partials of one pointwise conv in ONE launch: the two products only share their input
 // g, and each alone is too short to fill the chip, so their blocks are dealt from one grid: block ids [0, nA) are those of
@@ -944,8 +1004,8 @@ __global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __re
 //   little (less than two blocks per compute unit): the smallest blocks with one step upwards
 // A range is at most WG_CHAIN steps: chains of 32 roundings.  Relative error of dW against 64 bits 5e-8 to 9e-8 over these
 // sizes (the fp32 matrix instructions with their sums in two levels: 8e-8 to 1.3e-7).  A cap on the number of ranges that makes
-// them longer (chained) takes a shape with registers for 64-bit sums.
-struct WgPick { int shape; dim3 grid; bool chained; };
+// them longer (chained) takes a shape with registers for 64-bit sums.  far: planes that 32-bit offsets do not reach.
+struct WgPick { int shape; dim3 grid; bool chained, far; };
 static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
   const int a = cdiv(Cout, 32), b = cdiv(Cin, 32);
   static const int tco[4] = {2, 2, 1, 1}, tci[4] = {2, 1, 2, 1}, blocks[4] = {512, 768, 768, 1024};
@@ -962,6 +1022,7 @@ static WgPick wg_pick(int N, int Cin, int Cout, int HW, int cap) {
   if (a == 1 || b == 1) splits(WG_1x1, 64);
   else if (NQ * a * b >= 600000 || (NQ < 2048 && a * b >= 256)) splits(WG_2x2, 128);
   else if (splits(a % 2 && b % 2 == 0 ? WG_1x2 : WG_2x1, 128) < 512) splits(WG_1x1, 64);
+  p.far = pw_far(Cin, Cout, HW);
   p.chained = cdiv(cdiv(NQ, 64), p.grid.x) > WG_CHAIN;
   if (p.chained && p.shape == WG_2x2) splits(a % 2 && b % 2 == 0 ? WG_1x2 : WG_2x1, 128);
   return p;
@@ -984,30 +1045,27 @@ static WgArgs wg_args(const float* g, const float* x, float* part, int N, int Ci
   w.tile_order = p.grid.y * p.grid.z > 1;
   return w;
 }
-template <int SHAPE>
-static void launch_wgrad(hipStream_t st, const WgArgs& w, dim3 grid, bool vec) {
-  if (vec) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true>), grid, dim3(256), 0, st, w);
-  else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false>), grid, dim3(256), 0, st, w);
+template <int SHAPE, bool LONG, bool FAR>
+static void launch_wgrad(hipStream_t st, const WgArgs& w, dim3 grid) {
+  if (w.HW % 4 == 0) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true, LONG, FAR>), grid, dim3(256), 0, st, w);
+  else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false, LONG, FAR>), grid, dim3(256), 0, st, w);
 }
-template <int SHAPE>
-static void launch_chained(hipStream_t st, const WgArgs& w, dim3 grid, bool vec) {
-  if (vec) KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, true, true>), grid, dim3(256), 0, st, w);
-  else KLAUNCH_NAMED("pw_wgrad_f32_kernel", (pw_wgrad_f32_kernel<SHAPE, false, true>), grid, dim3(256), 0, st, w);
+template <bool LONG, bool FAR>
+static void launch_wgrad(hipStream_t st, const WgArgs& w, const WgPick& p) {
+  switch (p.shape) {
+    case WG_2x2:
+      if constexpr (!LONG) launch_wgrad<WG_2x2, LONG, FAR>(st, w, p.grid);
+      break;
+    case WG_2x1: launch_wgrad<WG_2x1, LONG, FAR>(st, w, p.grid); break;
+    case WG_1x2: launch_wgrad<WG_1x2, LONG, FAR>(st, w, p.grid); break;
+    default: launch_wgrad<WG_1x1, LONG, FAR>(st, w, p.grid); break;
+  }
 }
 static void launch_wgrad(hipStream_t st, const WgArgs& w, const WgPick& p) {
-  const bool vec = w.HW % 4 == 0;
-  if (p.chained) {
-    if (p.shape == WG_2x1) launch_chained<WG_2x1>(st, w, p.grid, vec);
-    else if (p.shape == WG_1x2) launch_chained<WG_1x2>(st, w, p.grid, vec);
-    else launch_chained<WG_1x1>(st, w, p.grid, vec);
-    return;
-  }
-  switch (p.shape) {
-    case WG_2x2: launch_wgrad<WG_2x2>(st, w, p.grid, vec); break;
-    case WG_2x1: launch_wgrad<WG_2x1>(st, w, p.grid, vec); break;
-    case WG_1x2: launch_wgrad<WG_1x2>(st, w, p.grid, vec); break;
-    default: launch_wgrad<WG_1x1>(st, w, p.grid, vec); break;
-  }
+  if (p.chained && p.far) launch_wgrad<true, true>(st, w, p);
+  else if (p.chained) launch_wgrad<true, false>(st, w, p);
+  else if (p.far) launch_wgrad<false, true>(st, w, p);
+  else launch_wgrad<false, false>(st, w, p);
 }
 void pw_wgrad_f32(hipStream_t st, const float* g, const float* x, float* part, float* G, int N,
                   int Cin, int Cout, int HW, int cap) {
@@ -1050,7 +1108,7 @@ void pw_conv_bwd_f32(hipStream_t st, const float* Wp_t, const float* g, float* d
   const WgPick wp = wg_pick(N, Cin, Cout, HW, cap);
   const WgArgs w = wg_args(g, x, part, N, Cin, Cout, HW, wp);
   const unsigned nA = p.gx * p.gy;
-  if (wp.chained) {  // rare: not worth the forms of the common launch
+  if (wp.chained || wp.far) {  // (rare, and not worth the forms of the common launch)
     pw_conv_f32(st, Wp_t, g, dx, nullptr, add, N, Cout, Cin, HW, nullptr);
     launch_wgrad(st, w, wp);
   } else switch (p.var) {

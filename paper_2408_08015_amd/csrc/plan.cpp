@@ -89,7 +89,7 @@ ast_status build_plan(Stage& s, std::string& err) {
           op.sh_off = shadow; shadow += (size_t)Cout * k * k * Cin;   // [Cout][tap][Cin]
           op.sh2_off = shadow; shadow += (size_t)Cout * k * k * Cin;  // [Cin][tap flipped][Cout]
           if (i + 1 < nl && s.layers[i + 1].kind == AST_RELU) { op.act = 1; ++i; }
-        } else if (k == 1 && st == 1 && pad == 0 && g == 1 && pw_conv_supported(Cin, Cout, A.h * A.w)) {
+        } else if (k == 1 && st == 1 && pad == 0 && g == 1) {
           op.kind = OP_CONV_PW;
         } else if (k == 3 && pad == 1 && g == Cin && Cin == Cout && (st == 1 || st == 2) && !hb &&
                    dw3x3_supported(A.h, A.w, st)) {

@@ -388,3 +388,48 @@ def test_pointwise_weight_gradient_of_few_ranges(A, cin, cout, h, B, shape):
     G = torch.from_numpy(G).cuda().reshape(cout, cin).double()
     assert float((G - ref).norm() / ref.norm()) <= BOUND_W
     assert (err / tot) ** 0.5 <= bound(cout)
+
+
+@pytest.mark.parametrize("cin,cout,h,w,B,skip", [(8, 24, 1750, 1750, 2, False), (24, 8, 1747, 1749, 1, False), (33, 40, 1620, 1620, 1, True)])
+def test_pointwise_planes_past_32_bit_offsets(A, cin, cout, h, w, B, skip):
+    """... stay on the matrix cores (a wavefront addresses two samples from its first pixel on)."""
+    import torch
+    assert [pw_choice(d, B, cin, cout, h * w) for d in (0, 1)] == [8, 8]
+    layers = [conv(cin, cout, 1, bias=True)]
+    if skip:   # the skip gradient is added by the input gradient's product
+        layers = [simple("res_begin")] + layers + [conv(cout, cin, 1), simple("res_add")]
+    st = A.Stage(layers, B, 1, 1, (cin, h, w), "f32", "nchw", True, stream=torch.cuda.current_stream().cuda_stream)
+    gen_ = torch.Generator(device="cuda")
+    gen_.manual_seed(2)
+    r = lambda *s: torch.randn(*s, generator=gen_, device="cuda")
+    p = r(st.num_params)
+    st.set_params(p.cpu().numpy())
+    x, g = r(B, cin, h, w), r(B, cin if skip else cout, h, w)
+    y, dx = torch.empty_like(g), torch.empty_like(x)
+    st.profile_begin("conv", 64)
+    st.forward(0, x, None, y, None)
+    st.backward(0, g, dx)
+    names = set(st.profile_end())
+    assert names == {"pw_conv_f32_far_kernel", "pw_wgrad_f32_kernel"} or names == {"pw_conv_f32_far_kernel"}, names
+    G = torch.from_numpy(st.get_grads()).cuda().double()
+    st.close()
+    W, b = p[:cin * cout].view(cout, cin).double(), p[cin * cout:cin * cout + cout].double()
+    V = p[cin * cout + cout:].view(cin, cout).double() if skip else None
+    ref, e = torch.zeros_like(G), np.zeros(4)
+    for n in range(B):
+        xn, gn = x[n].view(cin, -1).double(), g[n].view(g.shape[1], -1).double()
+        z = W @ xn + b[:, None]
+        gz, yn = gn, z
+        if skip:
+            yn = V @ z + xn
+            gz = V.t().contiguous() @ gn
+            ref[cin * cout + cout:] += (gn @ z.t().contiguous()).ravel()
+        dxn = W.t().contiguous() @ gz + (gn if skip else 0)
+        ref[:cin * cout] += (gz @ xn.t().contiguous()).ravel()
+        for i, (got, want) in enumerate(((y, yn), (dx, dxn))):
+            e[2 * i] += float((got[n].view(want.shape).double() - want).pow(2).sum())
+            e[2 * i + 1] += float(want.pow(2).sum())
+    # (fp32 matrix instructions: a rounding per two terms, and two products behind each other)
+    assert max(e[0] / e[1], e[2] / e[3]) ** 0.5 <= 1e-6
+    G[cin * cout:cin * cout + cout] = 0   # (the bias gradient is another kernel's)
+    assert float((G - ref).norm() / ref.norm()) <= 4e-7
