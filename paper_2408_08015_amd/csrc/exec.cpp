@@ -537,40 +537,31 @@ ast_status run_backward(Stage& s, int slot, const void* dy, void* dx, char* stat
   return check_launch(err, "backward");
 }
 
+// the packed copies of an op's weights
+static std::vector<PackTask> pack_tasks_of(const Stage& s, const Op& op) {
+  const float* W = s.W + op.w_off;
+  if (op.kind == OP_CONV_PW)
+    return {pack_task(W, op.cin, 1, op.wp_off, op.cout, op.cin, 1, true), pack_task(W, 1, op.cin, op.wp2_off, op.cin, op.cout, 1, true)};
+  if (op.kind == OP_CONV_GK) {
+    const int kd = op.cin * op.k * op.k;
+    return {pack_task(W, kd, 1, op.wp_off, op.cout, kd, 1, false)};
+  }
+  if (op.kind == OP_CONV_3X3) {  // W[co][ci][tap]: A[co][ci], and of the input gradient A[ci][co]
+    const int kk = op.k * op.k;
+    return {pack_task(W, op.cin * kk, kk, op.wp_off, op.cout, op.cin, kk, op.wp_split),
+            pack_task(W, kk, op.cin * kk, op.wp2_off, op.cin, op.cout, kk, op.wp2_split)};
+  }
+  return {};
+}
 static ast_status build_pack_tasks(Stage& s, std::string& err) {
   std::vector<PackTask> tasks;
   std::vector<unsigned short> block_task;
-  auto add = [&](const float* W, int lda_m, int lda_k, size_t off, int Mdim, int Kdim, bool split) {
-    PackTask t = {};
-    t.W = W; t.lda_m = lda_m; t.lda_k = lda_k; t.Mdim = Mdim; t.Kdim = Kdim; t.split = split;
-    t.KG = split ? (Kdim + 15) / 16 : (Kdim + 7) / 8;
-    t.block0 = (unsigned)block_task.size();
-    if (off != (size_t)t.block0 * 256) return false;  // the arena is laid out in op order: cannot happen
-    for (size_t b = 0; b < (split ? x3_pack_floats(Mdim, Kdim) : pw_pack_floats(Mdim, Kdim)) / 256; ++b) block_task.push_back((unsigned short)tasks.size());
-    tasks.push_back(t);
-    return true;
-  };
   for (const Op& op : s.ops)
-    if (op.kind == OP_CONV_PW) {
-      if (tasks.size() + 2 >= 65535) return AST_OK;  // per-conv launches instead
-      if (!add(s.W + op.w_off, op.cin, 1, op.wp_off, op.cout, op.cin, true) ||
-          !add(s.W + op.w_off, 1, op.cin, op.wp2_off, op.cin, op.cout, true))
-        return AST_OK;
-    } else if (op.kind == OP_CONV_GK) {
-      if (tasks.size() + 1 >= 65535) return AST_OK;
-      const int kd = op.cin * op.k * op.k;
-      if (!add(s.W + op.w_off, kd, 1, op.wp_off, op.cout, kd, false)) return AST_OK;
-    } else if (op.kind == OP_CONV_3X3) {
-      // W[co][ci][tap]: forward copy t is A[co][ci] = W[..][t]; input-gradient copy t is A[ci][co] = W[..][t]
-      const int kk = op.k * op.k;
-      if (tasks.size() + 2 * kk >= 65535) return AST_OK;
-      const float* W = s.W + op.w_off;
-      for (int t = 0; t < kk; ++t)
-        if (!add(W + t, op.cin * kk, kk, op.wp_off + t * conv_mfma_pack_floats(op.cout, op.cin, op.wp_split),
-                 op.cout, op.cin, op.wp_split)) return AST_OK;
-      for (int t = 0; t < kk; ++t)
-        if (!add(W + t, kk, op.cin * kk, op.wp2_off + t * conv_mfma_pack_floats(op.cin, op.cout, op.wp2_split),
-                 op.cin, op.cout, op.wp2_split)) return AST_OK;
+    for (PackTask t : pack_tasks_of(s, op)) {
+      if (tasks.size() >= 65535) return AST_OK;  // per-op launches instead
+      t.block0 = (unsigned)block_task.size();
+      block_task.insert(block_task.end(), pack_blocks(t), (unsigned short)tasks.size());
+      tasks.push_back(t);
     }
   if (tasks.empty()) return AST_OK;
   hipError_t e;
@@ -850,24 +841,9 @@ ast_status refresh_shadow(Stage& s, std::string& err) {
   if (s.lsh_nblocks)
     linear_weight_shadow_all_bf16(s.stream, static_cast<const LinShadowTask*>(s.lsh_tasks), s.lsh_block_task, s.lsh_nblocks);
   for (const Op& op : s.ops) {
-    if (op.kind == OP_CONV_PW) {
+    if (op.kind == OP_CONV_PW || op.kind == OP_CONV_GK || op.kind == OP_CONV_3X3) {
       if (s.pack_nblocks) continue;
-      pw_pack_f32(s.stream, s.W + op.w_off, op.cin, 1, s.wpack + op.wp_off, op.cout, op.cin, true);
-      pw_pack_f32(s.stream, s.W + op.w_off, 1, op.cin, s.wpack + op.wp2_off, op.cin, op.cout, true);
-    } else if (op.kind == OP_CONV_GK) {
-      if (s.pack_nblocks) continue;
-      const int kd = op.cin * op.k * op.k;
-      pw_pack_f32(s.stream, s.W + op.w_off, kd, 1, s.wpack + op.wp_off, op.cout, kd, false);
-    } else if (op.kind == OP_CONV_3X3) {
-      if (s.pack_nblocks) continue;
-      const float* W = s.W + op.w_off;
-      const int kk = op.k * op.k;
-      for (int t = 0; t < kk; ++t) {
-        pw_pack_f32(s.stream, W + t, op.cin * kk, kk, s.wpack + op.wp_off + t * conv_mfma_pack_floats(op.cout, op.cin, op.wp_split),
-                    op.cout, op.cin, op.wp_split);
-        pw_pack_f32(s.stream, W + t, kk, op.cin * kk, s.wpack + op.wp2_off + t * conv_mfma_pack_floats(op.cin, op.cout, op.wp2_split),
-                    op.cin, op.cout, op.wp2_split);
-      }
+      for (const PackTask& t : pack_tasks_of(s, op)) pw_pack_f32(s.stream, t, s.wpack);
     } else if (!s.bf16) {
       continue;  // the remaining copies are bf16 layouts
     } else if (op.kind == OP_CONV_IGEMM) {

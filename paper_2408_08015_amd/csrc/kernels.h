@@ -18,17 +18,18 @@ typedef unsigned short bf16_t;
 // gradient (A = W^T).  The other convolutions on the matrix cores read fp32 copies (pw_pack_floats words).
 size_t x3_pack_floats(int Mdim, int Kdim);
 size_t pw_pack_floats(int Mdim, int Kdim);
-// one copy, of A[m][k] = W[m*lda_m + k*lda_k]
-void pw_pack_f32(hipStream_t st, const float* W, int lda_m, int lda_k, float* Wp, int Mdim, int Kdim, bool split);
-// All packed copies of a stage in one launch.  The copies lie back to back in `arena` in task
-// order (each a whole number of 256-word blocks); block b of the launch writes arena[256*b, +256) for task
-// block_task[b], whose first block is block0.
+// Copies of A[m][k] = W[m*lda_m + k*lda_k + tap], one per tap, back to back at word `dst` of an arena
 struct PackTask {
   const float* W;
+  size_t dst;
   int lda_m, lda_k, Mdim, Kdim, KG;  // KG: groups of 16 (split) or 8 columns
-  unsigned block0;
-  int split;
+  int taps, split;
+  unsigned block0;  // the launch of all tasks: the first of its pack_blocks blocks
 };
+PackTask pack_task(const float* W, int lda_m, int lda_k, size_t dst, int Mdim, int Kdim, int taps, bool split);
+unsigned pack_blocks(const PackTask& t);
+void pw_pack_f32(hipStream_t st, const PackTask& t, float* arena);
+// All packed copies of a stage in one launch; block b works on task block_task[b].
 void pw_pack_all_f32(hipStream_t st, const PackTask* tasks_dev, const unsigned short* block_task_dev, float* arena,
                      int nblocks);
 // stats (may be NULL; needs bias == add == NULL and pw_conv_stats_parts() > 0): the kernel also

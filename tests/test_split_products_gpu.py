@@ -433,3 +433,22 @@ def test_pointwise_planes_past_32_bit_offsets(A, cin, cout, h, w, B, skip):
     assert max(e[0] / e[1], e[2] / e[3]) ** 0.5 <= 1e-6
     G[cin * cout:cin * cout + cout] = 0   # (the bias gradient is another kernel's)
     assert float((G - ref).norm() / ref.norm()) <= 4e-7
+
+
+@pytest.mark.parametrize("cin,mid,k", [(2048, 1024, 1), (512, 1024, 3)])
+def test_time_of_the_packed_copies(A, cin, mid, k):
+    """The update reads and writes 24 bytes a weight, the two split copies are 20: they take about as long."""
+    import torch
+    st = A.Stage([conv(cin, mid, k, 1, k // 2), conv(mid, cin, k, 1, k // 2)], 1, 1, 1, (cin, 4, 4), "f32", "nchw", True,
+                 stream=torch.cuda.current_stream().cuda_stream)
+    x = torch.randn(1, cin, 4, 4, device="cuda")
+    y, dx, best = torch.empty_like(x), torch.empty_like(x), {}
+    for _ in range(6):
+        st.forward(0, x, None, y, None)
+        st.backward(0, x, dx)
+        st.profile_begin("", 64)
+        st.step(0.0, 0.0)
+        for name, (_, ms) in st.profile_end().items():
+            best[name] = min(best.get(name, 1e9), ms)
+    st.close()
+    assert best["pw_pack_all_kernel"] <= 2.5 * best["sgd_kernel"], best
