@@ -1129,14 +1129,16 @@ hipError_t conv_lds_allow() {
 }  // namespace ast
 
 // The choices above, for tests that name one.  what: 0 forward, 1 input gradient, 2 weight gradient of a conv with
-// these sizes (H, W: its input).  0: the direct kernels run.  1: staged; out = {row tiles, pixel groups, shares of the
+// these sizes (H, W: its input); 3: a weight gradient with the partials of a stage that has to fit the static workspace.  0:
+// other kernels run (conv_x3_f32_kernel, conv_wgrad_x3_f32_kernel, the direct ones).  1: staged; out = {row tiles, pixel groups, shares of the
 // contraction, classes of result pixels, 0, 0}, or for a weight gradient {pixels per stage, stages per block, partials,
 // buffers, stages per flush, scratch areas of a flush inside the stage's buffer}.
 extern "C" int ast_conv_lds_choice(int what, int N, int Cin, int Cout, int H, int W, int KS, int S, int out[6]) {
   using namespace ast;
-  if (what == 2) {
+  if (what >= 2) {
+    const int cap = what == 2 ? INT_MAX : conv_mfma_wgrad_compact_parts(N, Cin, Cout, H, W, KS, S);
     LdsWgPick p;
-    if (!pick_wgrad(N, Cin, Cout, H, W, KS, S, INT_MAX, p)) return 0;
+    if (conv_x3_wgrad_parts(N, Cin, Cout, H, W, KS, S, cap) || !pick_wgrad(N, Cin, Cout, H, W, KS, S, cap, p)) return 0;
     out[0] = p.PT; out[1] = p.per; out[2] = p.chunks; out[3] = p.nbuf;
     out[4] = p.flush(p.per);
     out[5] = p.buf >= 8 * kFlush ? 2 : p.buf >= 4 * kFlush ? 1 : 0;
@@ -1145,7 +1147,8 @@ extern "C" int ast_conv_lds_choice(int what, int N, int Cin, int Cout, int H, in
   LdsArgs a;
   LdsPick p;
   int ncls;
-  if (!plan_product(what == 1, N, what ? Cout : Cin, what ? Cin : Cout, H, W, KS, S, a, ncls, p)) return 0;
+  const int Kdim = what ? Cout : Cin, Mdim = what ? Cin : Cout;
+  if (conv_x3_takes(what == 1, N, Kdim, Mdim, H, W, KS, S) || !plan_product(what == 1, N, Kdim, Mdim, H, W, KS, S, a, ncls, p)) return 0;
   out[0] = p.MT; out[1] = p.WN; out[2] = p.WK; out[3] = ncls;
   out[4] = out[5] = 0;
   return 1;

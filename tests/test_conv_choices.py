@@ -6,31 +6,46 @@ import pytest
 import paper_2408_08015_amd as A
 from asteroid_workloads.configs import bn, conv, irb, simple
 
-FWD, DGRAD, WGRAD = 0, 1, 2
+FWD, DGRAD, WGRAD, FEWER = 0, 1, 2, 3   # FEWER: a weight gradient whose stage has to fit the static workspace
 
 
 def choice(what, n, cin, cout, h, w, k, s):
-    """None: the direct kernels; else the words of the staged kernel's block shape."""
+    """None: other kernels; else the words of the staged fp32 kernel's block shape."""
     out = (ctypes.c_int * 6)()
     lib = ctypes.CDLL(A.lib_path())
     return tuple(out) if lib.ast_conv_lds_choice(what, n, cin, cout, h, w, k, s, out) else None
+
+
+def split_choice(what, n, cin, cout, h, w, k, s):
+    """The same for the kernels on the bf16 matrix cores."""
+    out = (ctypes.c_int * 6)()
+    lib = ctypes.CDLL(A.lib_path())
+    if what == WGRAD:
+        return tuple(out) if lib.ast_conv_wgrad_x3_choice(n, cin, cout, h, w, k, s, out) else None
+    return tuple(out) if lib.ast_conv_x3_choice(what, n, cin, cout, h, w, k, s, out) else None
 
 
 # Sizes (cin, cout, k, stride, h, w, B) whose parity is checked on the GPU, each for the form that its choice must be, so
 # that a change of the cost models cannot leave a form untested.
 #   weight gradient: buffers, scratch areas of a flush inside a buffer, stages per block, stages per flush
 WGRAD_FORMS = [
-    ((136, 392, 3, 1, 7, 7, 32), (2, 0, 9, 5)),       # flushes of unequal length, both scratch areas past the buffers
-    ((40, 392, 3, 1, 14, 14, 12), (2, 1, 5, 3)),
-    ((40, 264, 3, 1, 30, 62, 2), (2, 2, 3, 2)),
-    ((40, 72, 3, 1, 5, 90, 12), (2, 2, 3, 3)),        # no flush before the end
-    ((40, 392, 3, 1, 6, 150, 3), (1, 2, 3, 2)),
+    ((40, 392, 3, 1, 6, 150, 3), (1, 2, 3, 2)),       # rows of 128 and more
     ((392, 392, 3, 2, 7, 7, 12), (2, 1, 3, 2)),       # stride 2
     ((40, 392, 3, 2, 28, 28, 12), (2, 2, 5, 3)),
     ((392, 392, 3, 2, 5, 90, 2), (1, 2, 3, 2)),
     ((72, 392, 1, 2, 14, 14, 24), (2, 1, 2, 2)),      # 1x1: 64 x 64 tiles
     ((72, 136, 1, 2, 6, 150, 12), (1, 2, 2, 2)),
 ]
+#   ... of stride 1 and shorter rows: only where the stage has to fit the static workspace
+FEWER_FORMS = [
+    ((256, 392, 3, 1, 63, 8, 22), (2, 0, 25, 13)),    # flushes of unequal length, both scratch areas past the buffers
+    ((192, 392, 3, 1, 34, 16, 13), (2, 1, 19, 7)),
+    ((192, 512, 3, 1, 25, 8, 40), (2, 1, 8, 8)),      # no flush before the end
+    ((192, 392, 3, 1, 9, 78, 10), (2, 2, 37, 13)),
+    ((192, 392, 3, 1, 4, 98, 20), (1, 2, 21, 7)),
+]
+#   ... else these run on the bf16 matrix cores (their forms: test_split_products_gpu.py)
+SPLIT_WGRAD = [(136, 392, 3, 1, 7, 7, 32), (40, 392, 3, 1, 14, 14, 12), (40, 264, 3, 1, 30, 62, 2), (40, 72, 3, 1, 5, 90, 12)]
 
 #   products, forward and input gradient: 32-row tiles of result channels, groups of 32 pixels, shares of the contraction
 PRODUCT_FORMS = [
@@ -70,16 +85,22 @@ def test_rows_too_long_for_the_staged_kernels(sizes, staged):
     assert tuple(choice(what, n, cin, cout, h, w, k, s) is not None for what in (FWD, DGRAD, WGRAD)) == staged
 
 
-@pytest.mark.parametrize("sizes,want", WGRAD_FORMS)
-def test_form_of_the_staged_weight_gradient(sizes, want):
+@pytest.mark.parametrize("what,sizes,want", [(WGRAD,) + f for f in WGRAD_FORMS] + [(FEWER,) + f for f in FEWER_FORMS])
+def test_form_of_the_staged_weight_gradient(what, sizes, want):
     cin, cout, k, s, h, w, n = sizes
-    got = choice(WGRAD, n, cin, cout, h, w, k, s)
+    got = choice(what, n, cin, cout, h, w, k, s)
     assert got is not None and (got[3], got[5], got[1], got[4]) == want
+    assert (split_choice(WGRAD, n, cin, cout, h, w, k, s) is not None) == (what == FEWER)
+
+
+@pytest.mark.parametrize("cin,cout,k,s,h,w,n", SPLIT_WGRAD)
+def test_weight_gradients_on_the_bf16_matrix_cores(cin, cout, k, s, h, w, n):
+    assert choice(WGRAD, n, cin, cout, h, w, k, s) is None and split_choice(WGRAD, n, cin, cout, h, w, k, s) is not None
 
 
 @pytest.mark.parametrize("what", [FWD, DGRAD, WGRAD])
 @pytest.mark.parametrize("n,cin,cout,h,k,s,reads_x,reads_g", [
-    # the staged kernels address a tensor with 32-bit byte offsets below 2 GiB
+    # the kernels that stage through LDS, fp32 or split, address a tensor with 32-bit byte offsets below 2 GiB
     (668, 64, 64, 112, 1, 2, True, True),       # x of 2 145 124 352 bytes
     (669, 64, 64, 112, 1, 2, False, True),      # x of 2 148 335 616
     (1400, 64, 64, 112, 1, 2, False, True),     # x of 4.5 GB, and the subsampled x of 1.1 GB
@@ -97,7 +118,8 @@ def test_size_limit_of_the_staged_convolutions(what, n, cin, cout, h, k, s, read
     assert (n * cin * h * h * 4 < 2 ** 31) == reads_x
     assert (n * cout * ((h - 1) // s + 1) ** 2 * 4 < 2 ** 31) == reads_g
     want = {FWD: reads_x, DGRAD: reads_g, WGRAD: reads_x and reads_g}[what]
-    assert (choice(what, n, cin, cout, h, h, k, s) is not None) == want
+    staged, split = (c(what, n, cin, cout, h, h, k, s) is not None for c in (choice, split_choice))
+    assert (staged or split) == want and not (staged and split)
 
 
 # Stages whose workspace with the counts that are fastest is past the static scratch array (33.6 MB), and with fewer is not:

@@ -7,7 +7,7 @@ import pytest
 import harness
 from asteroid_workloads import gen
 from asteroid_workloads.configs import bn, conv, simple
-from test_conv_choices import DIRECT_FORMS, PRODUCT_FORMS, WGRAD, WGRAD_FORMS, choice
+from test_conv_choices import DIRECT_FORMS, PRODUCT_FORMS, SPLIT_WGRAD, WGRAD, WGRAD_FORMS, choice
 from test_parity_gpu import A, check, one  # noqa: F401  (A: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -30,7 +30,7 @@ def test_dense_conv_tiles(A, cin, cout, k, stride, h, w, B):
     check(one([conv(cin, cout, k, stride, k // 2)], (cin, h, w), B=B), rounds=1)
 
 
-@pytest.mark.parametrize("cin,cout,k,stride,h,w,B", [f[0] for f in PRODUCT_FORMS + WGRAD_FORMS + DIRECT_FORMS])
+@pytest.mark.parametrize("cin,cout,k,stride,h,w,B", [f[0] for f in PRODUCT_FORMS + WGRAD_FORMS + DIRECT_FORMS] + SPLIT_WGRAD)
 def test_dense_conv_forms(A, cin, cout, k, stride, h, w, B):
     check(one([conv(cin, cout, k, stride, k // 2)], (cin, h, w), B=B, M=1), rounds=1)
 
@@ -45,28 +45,37 @@ def test_batchnorm_planes_not_a_multiple_of_16_bytes(A, c, h, w, B):
     check(one([bn(c), simple("relu6")], (c, h, w), B=B), rounds=1)
 
 
-@pytest.mark.parametrize("cin,cout,h,w,B", [
-    (96, 128, 16, 16, 64),   # blocks of 2x2 weight tiles, whole
-    (56, 232, 14, 14, 77),   # 2x2, ragged rows of both operands
-    (24, 144, 19, 20, 60),   # one tile of input channels: 1x1 blocks, four wavefronts a tile
-    (160, 40, 13, 14, 90),   # 2x2 and 1x2 pad the same number of tiles
-    (80, 24, 9, 9, 200),     # 1x2, planes no multiple of 16 bytes
-    (24, 80, 9, 9, 200),     # 2x1, the same
-    (256, 192, 7, 7, 43),    # steps of 32 pixels across samples of 49
-    (33, 65, 7, 7, 3),       # few blocks: one step, rows past both edges
-    (8, 8, 1, 1, 5),         # fewer pixels than a step
-    (1024, 40, 7, 7, 2),     # product split over 16 wavefronts: 64 channels each, in one pass
-    (1032, 40, 7, 7, 2),     # 72 each, pipelined; the last wavefronts have fewer or none
-    (40, 2056, 5, 5, 2),     # the same in the input gradient, 136 each
+# weight-gradient tiles per block (co x ci); the products' forms: test_split_products_gpu.py
+@pytest.mark.parametrize("cin,cout,h,w,B,tiles", [
+    (96, 128, 16, 16, 64, "2x1"),
+    (56, 232, 14, 14, 77, "2x1"),   # ragged rows of both operands
+    (528, 520, 7, 7, 16, "2x2"),    # ... 17 tiles of either
+    (24, 144, 19, 20, 60, "1x1"),   # one tile of input channels
+    (160, 40, 13, 14, 90, "2x1"),   # an odd number of tiles of input channels
+    (64, 96, 14, 14, 130, "1x2"),   # ... of output channels
+    (33, 264, 27, 27, 36, "1x2"),   # planes no multiple of 16 bytes
+    (80, 72, 25, 25, 20, "2x1"),
+    (80, 24, 9, 9, 200, "1x1"),
+    (24, 80, 9, 9, 200, "1x1"),
+    (256, 192, 7, 7, 43, "1x1"),    # steps across samples of 49
+    (33, 65, 7, 7, 3, "1x1"),       # few blocks: two steps, rows past both edges
+    (8, 8, 1, 1, 5, "1x1"),         # fewer pixels than a step
+    (1024, 40, 7, 7, 2, "1x1"),     # product split over eight wavefronts: eight groups of 16 channels each
+    (1032, 40, 7, 7, 2, "1x1"),     # nine each; the last wavefront has two
+    (40, 2056, 5, 5, 2, "1x1"),     # over four in the input gradient, 33 each, the last 30
 ])
-def test_pointwise_conv_tiles(A, cin, cout, h, w, B):
+def test_pointwise_conv_tiles(A, cin, cout, h, w, B, tiles):
+    import ctypes
+    out = (ctypes.c_int * 3)()
+    ctypes.CDLL(A.lib_path()).ast_pw_wgrad_choice(B, cin, cout, h * w, 2 ** 31 - 1, out)
+    assert ("2x2", "2x1", "1x2", "1x1")[out[0]] == tiles
     check(one([conv(cin, cout, 1, 1, 0)], (cin, h, w), B=B), rounds=1)
 
 
 @pytest.mark.parametrize("cin,cout,k,stride,hw,B", [
-    (512, 2048, 1, 1, 7, 128),      # pointwise, 2x2 weight tiles: three ranges of 65 steps
-    (24, 144, 1, 1, 56, 128),       # 1x1 tiles, ranges of 41 steps
-    (960, 160, 1, 1, 7, 512),       # 2x1 tiles, ranges of 64 steps
+    (512, 2048, 1, 1, 7, 128),      # pointwise, 2x2 weight tiles: ranges of 25 steps
+    (24, 144, 1, 1, 56, 128),       # 1x1 tiles, ranges of 31 steps
+    (960, 160, 1, 1, 7, 512),       # 2x2 tiles, ranges of 31 steps
     (512, 512, 3, 1, 7, 128),       # dense
     (64, 64, 3, 1, 56, 64),
     (1024, 2048, 1, 2, 14, 128),    # 64 x 64 tiles
