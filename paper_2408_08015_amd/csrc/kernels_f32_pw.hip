@@ -657,7 +657,10 @@ static PwPick pw_pick(long NQ, int HW, int Kdim, int Mdim, bool wide) {
   }
   // Longer contractions are bound by reading and splitting the pixels once per row tile.
   if (KG > 4 && HW % 2 == 0) {
-    if (mt >= 2 && mt != 3 && tiles >= 3000) { p.var = PW_2x2; p.gy = cdiv(mt, 2); p.gx = cdiv(NQ, 256); }
+    // Two row tiles per wavefront read and split half the pixels, but of an odd count the last pair does nothing for its second
+    // tile, which is too much below seven: forward, two tiles / one, three of them 128 -> 72 at 32 x 56x56 30 / 25 us, five
+    // 256 -> 144 at 32 x 28x28 26.6 / 20.9, seven 256 -> 208 27.0 / 27.4 and 96 -> 200 at 16 x 56x56 24.8 / 23.9.
+    if ((mt % 2 == 0 || mt >= 7) && tiles >= 3000) { p.var = PW_2x2; p.gy = cdiv(mt, 2); p.gx = cdiv(NQ, 256); }
     else { p.var = PW_2x1; p.gx = cdiv(NQ, 256); }
     return p;
   }

@@ -44,8 +44,9 @@ POINTWISE = [
     (1032, 392, 7, 7, 20, KS4X2, KS4),
     (81, 40, 25, 24, 32, PX2, PX1),         # 600 pixels a plane
     (80, 72, 24, 24, 90, PX2, PX2),
-    (104, 136, 24, 24, 35, PX2X2, PX2),     # five row tiles: the last pair has one
-    (136, 136, 24, 26, 33, PX2X2, PX2X2),
+    (104, 136, 24, 24, 35, PX2, PX2),       # five row tiles
+    (104, 200, 24, 24, 25, PX2X2, PX2),     # seven: the last pair has one
+    (200, 200, 24, 26, 25, PX2X2, PX2X2),
     (80, 72, 25, 25, 20, PX1X2, PX1X2),     # odd planes; three row tiles
     (16, 104, 56, 56, 20, WIDE, PX2),       # all row tiles in one wavefront
     (33, 264, 28, 28, 36, WIDE, PX2),       # ... nine tiles in two shares
@@ -120,7 +121,7 @@ def test_pointwise_skip_gradient(A):
 
 @pytest.mark.parametrize("cin,cout,h,B,fwd,dgrad", [
     (24, 40, 6, 3, PX1, PX1), (272, 40, 7, 2, KS8, PX1), (40, 272, 7, 2, PX1, KS4), (528, 520, 7, 16, KS4X2, KS4X2),
-    (72, 72, 24, 90, PX2, PX2), (80, 72, 25, 20, PX1X2, PX1X2), (104, 136, 24, 35, PX2X2, PX2), (24, 104, 56, 20, WIDE, PX2)])
+    (72, 72, 24, 90, PX2, PX2), (80, 72, 25, 20, PX1X2, PX1X2), (104, 200, 24, 25, PX2X2, PX2), (24, 104, 56, 20, WIDE, PX2)])
 def test_pointwise_operands_that_are_not_finite(A, cin, cout, h, B, fwd, dgrad):
     """An infinity or NaN reaches the outputs that its definition gives and no others, with the right sign, and the largest
     finite values are still values."""
@@ -163,7 +164,7 @@ def test_pointwise_operands_that_are_not_finite(A, cin, cout, h, B, fwd, dgrad):
         np.testing.assert_allclose(got[fin], want[fin], rtol=1e-5, atol=2e-3)
 
 
-@pytest.mark.parametrize("cin,cout,h,B,form", [(24, 104, 56, 20, WIDE), (104, 136, 24, 35, PX2X2), (16, 40, 14, 9, PX1)])
+@pytest.mark.parametrize("cin,cout,h,B,form", [(24, 104, 56, 20, WIDE), (104, 200, 24, 25, PX2X2), (16, 40, 14, 9, PX1)])
 def test_statistics_of_operands_that_round_to_infinity(A, cin, cout, h, B, form):
     """The sums that a product leaves for the BatchNorm behind it are those of the values it stored."""
     import torch
@@ -172,7 +173,7 @@ def test_statistics_of_operands_that_round_to_infinity(A, cin, cout, h, B, form)
     x = rng.standard_normal((B, cin, h, h)).astype(np.float32)
     wt = rng.standard_normal((cout, cin)).astype(np.float32)
     x[B - 1, 3, 1, 2] = 3.4e38
-    wt[:, 3] *= 1e-37 ** 0.9
+    wt[:, 3] *= 1e-30            # (a value of 2^-110 is 8e-34; of smaller ones the pieces lose what lies under 2^-133)
     wt[1, 3] = 0                 # (a channel of ordinary values)
     st = A.Stage([conv(cin, cout, 1), bn(cout)], B, 1, 1, (cin, h, h), "f32", "nchw", True,
                  stream=torch.cuda.current_stream().cuda_stream)
