@@ -84,8 +84,8 @@ __device__ __forceinline__ void load8(__amdgpu_buffer_rsrc_t r, unsigned voff, i
 // Block of twelve wavefronts, one per compute unit: 32 x 32 of (cout, cin), all nine taps, over a run of stages of R rows (at
 // most CH chunks).  A wavefront has the three taps of one row and a quarter of the stage's steps of 16 columns: the sums of
 // all nine taps, each with its small products, would leave one wavefront per SIMD.  (One sum per tap, to which a step's six
-// products are added when they are complete, took 69 us below: the additions cost as much as the products, and a matrix
-// instruction rounds what it adds to downwards, so the error of the step grew five times.)  A thread reads a chunk of g or x
+// products are added when they are complete, took 69 us below: the additions cost as much as the products, and a large
+// product that meets a smaller sum cuts it downwards (kernels_f32_x3.h), so the error of the step grew five times.)  A thread reads a chunk of g or x
 // (CH 16: up to two), a stage ahead, splits it and writes its three pieces to LDS while the stage before is multiplied: g to
 // the other of two buffers, x to a ring of 2R + 2 rows, so that no row is split twice.  A third of the wavefronts does that
 // before its products and the others behind them, so that a SIMD's matrix core is not idle meanwhile.  Chunk pitches are

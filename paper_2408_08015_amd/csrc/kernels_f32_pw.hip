@@ -746,7 +746,7 @@ void pw_conv_f32(hipStream_t st, const float* Wp, const float* X, float* Y, cons
 // as long as g and x agree: word c of a row holds pixels 4c..4c+3 and 32+4c..32+4c+3, so that eight lanes load whole runs.
 // Word c lies at position c ^ (row/2 & 7): the sixteen lanes of one LDS access hit all 64 banks.
 //
-// Chains of additions: a rounding per 16 pixels (the small products have accumulators of their own), and a range is at most
+// Chains of additions: two roundings per 16 pixels (the small products have accumulators of their own), and a range is at most
 // WG_CHAIN steps, so no chain grows with the micro-batch; wavefronts and partials are added in 64 bits.  LONG: where there is
 // no room for so many partials, a range is longer, and every WG_CHAIN steps of it go to 64-bit sums in registers.
 template <int TCO, int TCI>
@@ -1041,7 +1041,7 @@ __global__ __launch_bounds__(256) void reduce_parts_acc_kernel(const float* __re
 //     512 -> 2048 at 8 x 7x7 20.5, 24.0; 256 -> 1024 at 8 x 14x14 13.8, 14.8
 //   between: 40 -> 240 at 32 x 30x30 2x1 14.5, 2x2 15.6; 64 -> 64 at 32 x 56x56 14.8, 15.8
 //   little (less than two blocks per compute unit): the smallest blocks with one step upwards
-// A range is at most WG_CHAIN steps: chains of 32 roundings.  Relative error of dW against 64 bits 5e-8 to 9e-8 over these
+// A range is at most WG_CHAIN steps: chains of 64 roundings.  Relative error of dW against 64 bits 5e-8 to 9e-8 over these
 // sizes (the fp32 matrix instructions with their sums in two levels: 8e-8 to 1.3e-7).  A cap on the number of ranges that makes
 // them longer (chained) takes a shape with registers for 64-bit sums.  far: planes that 32-bit offsets do not reach.
 struct WgPick { int shape; dim3 grid; bool chained, far; };

@@ -1,10 +1,17 @@
 // Products of fp32 matrices on the bf16 matrix cores: every operand is split into three bf16 pieces
 // (x = x1 + x2 + x3, each the rounding of what is left), which together hold its 24 bits, and a product keeps the six
-// piece products that reach 32-bit precision.  v_mfma_f32_32x32x16_bf16 takes 32 cycles for a contraction of 16 where
-// v_mfma_f32_32x32x2_f32 takes 512: six of them are 2.7 times faster.  The five small products add up in an accumulator of
-// their own, so the large sum is rounded once per 16 terms.  Relative error of a product of normal matrices against 64
-// bits, fp32 matrix instructions / this: contraction 24 9.0e-8 / 3.6e-8, 256 2.9e-7 / 8.9e-8, 2304 8.6e-7 / 2.9e-7; with one
-// operand behind a ReLU 6.5e-8 / 3.1e-8, 2.1e-7 / 7.0e-8, 6.0e-7 / 2.2e-7.
+// piece products that reach 32-bit precision (the scheme of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019).  v_mfma_f32_32x32x16_bf16 takes 32 cycles for a
+// contraction of 16 where v_mfma_f32_32x32x2_f32 takes 512: six of them are 2.7 times faster.  The five small products add up
+// in an accumulator of their own, so the large sum is rounded twice per 16 terms: the instruction adds the terms 0 to 7 and
+// then 8 to 15, each time rounding to nearest, ties to even.  (Measured.  Where a product is larger than what it is added to,
+// that is first cut downwards to a multiple of half the product's ulp: the large products go straight to the growing sum and
+// are not collected step by step from zero.)  Relative error of a product of normal matrices against 64 bits, fp32
+// matrix instructions / this: contraction 24 9.0e-8 / 3.6e-8, 256 2.9e-7 / 8.9e-8, 2304 8.6e-7 / 2.9e-7; with one operand
+// behind a ReLU 6.5e-8 / 3.1e-8, 2.1e-7 / 7.0e-8, 6.0e-7 / 2.2e-7.
+//
+// The pieces end at 2^-133, the smallest bf16 value: an operand below 2^-110 loses what lies under that, so a product of
+// operands that are all so small has fewer than 24 bits (17 at 2^-117).
 //
 // An infinity or a NaN in an operand, and a value within half a bf16 ulp of the largest finite one, makes a piece or a
 // piece product that is not finite, so the sum is not finite either: a wavefront that holds such sums forms them again on

@@ -465,8 +465,8 @@ ast_status build_plan(Stage& s, std::string& err) {
 
   // A standalone ReLU / ReLU6 behind a BatchNorm that adds a skip, or behind a RES_ADD: its value is written by the pass in
   // front, and its gradient is formed by the statistics pass of the BatchNorm's backward.  (A pass of its own reads what has
-  // just been written: 256 channels of 32 x 56x56, 32 us forward and 46 us backward; without it a round of the bottleneck
-  // stage at 4 x 32 x 56x56 takes 9.11 ms, with it 9.42; ResNet-50 at 8 x 8 x 224x224 38.2, 39.1.)
+  // just been written: 256 channels of 32 x 56x56, 32 us forward and 46 us backward; with one, a round of the bottleneck
+  // stage at 4 x 32 x 56x56 takes 9.42 ms, without 9.11; ResNet-50 at 8 x 8 x 224x224 39.1, 38.2.)
   for (size_t j = 1; !s.bf16 && j < s.ops.size(); ++j) {
     Op& a = s.ops[j];
     Op& f = s.ops[j - 1];

@@ -11,9 +11,11 @@ from test_parity_gpu import A, one  # noqa: F401  (A: the fixture)
 
 pytestmark = pytest.mark.gpu
 
-# Relative error of a product of normal matrices: about 2^-25 from the last rounding plus a random walk of one rounding per
-# 16 terms, 6e-8 + 2^-25 * sqrt(K / 16) / 2; the fp32 matrix instructions, which round every second term, are at
-# 2^-25 * sqrt(K / 2) and more.  Weight gradients: chains of at most 32 roundings, 1e-7 measured.
+# Relative error of a product of normal matrices: at most 2^-24 from the last rounding, 2^-24 from the five small products, and
+# a random walk of one rounding per 8 terms, of which each is 2^-25.3 of the sum so far (root mean square): K / 8 of them are
+# 2^-25.3 * sqrt(K / 16) of the whole sum, and the bound has 2^-24 there.  The fp32 matrix instructions, which round every
+# second term, are at twice that walk.  Weight gradients: chains of at most 64 roundings, 2^-25.3 * sqrt(32) = 1.4e-7, and
+# 0.6e-7 for the last roundings; 1e-7 measured.
 BOUND_W = 2e-7
 
 
@@ -369,8 +371,8 @@ def test_dense_weight_gradient_forms(A, sizes, rows, chunks):
     rng = np.random.default_rng(5)
     x = rng.standard_normal((B, cin, h, w)).astype(np.float32)
     G, ref = weight_gradient(A, x, rng.standard_normal((B, cout, h, w)).astype(np.float32))
-    # at most 32 roundings of a sum in a wavefront, whose errors add up as their root; one more of the sum of the
-    # wavefronts and of the partials each, and of the pieces
+    # a sum in a wavefront is rounded at most 64 times, whose errors (2^-25.3 of the sum so far each) add up to less than
+    # 2^-24 * sqrt(32) of it; one more of the sum of the wavefronts and of the partials each, and of the pieces
     assert np.linalg.norm(G - ref) <= 2.0 ** -24 * (32 ** 0.5 + 3) * np.linalg.norm(ref)
 
 
