@@ -17,6 +17,7 @@ achieved rate against the HBM or MFMA peak, the launches per round, and a step-l
 sample of the same workload.  Prints ONE JSON line.
 """
 import argparse
+import ctypes
 import glob
 import json
 import os
@@ -47,6 +48,17 @@ def _dw_vw(h, w, stride):
     return 1 if (stride == 1 and w <= 64) else 0
 
 
+def _one_launch(L, B, shape, act1, act2):
+    """The depthwise conv L with the BatchNorms and activations around it is one launch per direction."""
+    code = {"relu": 1, "relu6": 2, "swish": 4}
+    if L.get("bias", False) or L["pad"] != L["k"] // 2 or act1 not in code or act2 not in code or \
+            (act1 == "swish") != (act2 == "swish"):
+        return False
+    import paper_2408_08015_amd as A
+    words = (ctypes.c_int * 3)()
+    return bool(ctypes.CDLL(A.lib_path()).ast_dws_choice(0, L["k"], B, shape[0], shape[1], shape[2], L["stride"], code[act1], words))
+
+
 def kernel_model(cfg):
     """Algorithmic work of the kernel classes that can dominate a workload, from the layer list
     and the launch rules of the library (one entry per launch of one micro-batch):
@@ -61,8 +73,17 @@ def kernel_model(cfg):
     # BatchNorm(+ReLU) directly in front, the statistics pass of a BatchNorm directly behind
     lazy_bn, given_bn = set(), set()
     kinds = [L["kind"] for L in cfg.layers]
+    # ... or the whole run BatchNorm, activation, depthwise, BatchNorm, activation in one launch per direction
+    dws, dws_bn = set(), set()
+    shp = tuple(cfg.in_shape)
     for i, L in enumerate(cfg.layers):
-        if L["kind"] == "conv2d" and cfg.dtype == "f32" and L["k"] == 3 and L["groups"] == L["cin"] == L["cout"] \
+        if L["kind"] == "conv2d" and cfg.dtype == "f32" and L["groups"] == L["cin"] == L["cout"] and 2 <= i < len(kinds) - 2 and \
+                kinds[i - 2] == kinds[i + 1] == "batchnorm2d" and _one_launch(L, B, shp, kinds[i - 1], kinds[i + 2]):
+            dws.add(i)
+            dws_bn |= {i - 2, i + 1}
+        shp = gen.layer_shapes(cfg.layers, cfg.in_shape)[i]
+    for i, L in enumerate(cfg.layers):
+        if i not in dws and L["kind"] == "conv2d" and cfg.dtype == "f32" and L["k"] == 3 and L["groups"] == L["cin"] == L["cout"] \
                 and L.get("pad", 1) == 1 and not L.get("bias", False):
             if i >= 1 and kinds[i - 1] == "batchnorm2d":
                 lazy_bn.add(i - 1)
@@ -84,7 +105,7 @@ def kernel_model(cfg):
     outs = gen.layer_shapes(cfg.layers, cfg.in_shape)
     for i, L in enumerate(cfg.layers):
         if L["kind"] == "conv2d" and cfg.dtype == "f32" and L["k"] == 1 and L["groups"] == 1 and not L.get("bias", False) \
-                and i + 1 < len(kinds) and kinds[i + 1] == "batchnorm2d" and (i + 1) not in given_bn:
+                and i + 1 < len(kinds) and kinds[i + 1] == "batchnorm2d" and (i + 1) not in given_bn | dws_bn:
             nq_ = B * shp[1] * shp[2]
             if pw_kernel(nq_, L["cin"], L["cout"], True) != "pw_conv_f32_ks_kernel" and \
                     nq_ <= 512 * (512 if _cdiv(L["cin"], 16) > 4 and shp[1] * shp[2] % 2 == 0 else 256):
@@ -95,6 +116,10 @@ def kernel_model(cfg):
         oshape = outs[i]
         if k == "res_begin":
             res_open = True
+        if i in dws:
+            n_in, n_out = B * shape[0] * shape[1] * shape[2], B * oshape[0] * oshape[1] * oshape[2]
+            out.setdefault("dws_fwd_kernel", []).append(4 * (n_in + 2 * n_out))      # x in, convolution's and BatchNorm's output out
+            out.setdefault("dws_bwd_kernel", []).append(4 * (2 * n_in + 2 * n_out))  # g, convolution's output, x in; dx out
         if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 1 and L["groups"] == 1:
             cin, cout = L["cin"], L["cout"]
             nq = B * shape[1] * shape[2]
@@ -116,20 +141,20 @@ def kernel_model(cfg):
             if not first or cfg.needs_input_grad:
                 out.setdefault("conv3x3_mfma_f32_kernel", []).append(flops)
             out.setdefault("conv3x3_wgrad_mfma_f32_kernel", []).append(flops)
-        if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 5 and L["groups"] == L["cin"] == L["cout"]:
+        if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 5 and L["groups"] == L["cin"] == L["cout"] and i not in dws:
             c, h, w = shape
             oc, oh, ow = oshape
             out.setdefault("dwk_fwd_f32_kernel<s%d>" % L["stride"], []).append(4 * B * (c * h * w + oc * oh * ow))
             # upstream gradient and input in, input gradient out
             out.setdefault("dwk_bwd_f32_kernel<s%d>" % L["stride"], []).append(4 * B * (2 * c * h * w + oc * oh * ow))
-        if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 3 and L["groups"] == L["cin"] == L["cout"]:
+        if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 3 and L["groups"] == L["cin"] == L["cout"] and i not in dws:
             oc, oh, ow = oshape
             if _dw_vw(shape[1], shape[2], L["stride"]):
                 name = "dw3x3_fwd_s%d_f32_kernel" % L["stride"]
             else:
                 name = "dw3x3_fwd_f32_kernel"
             out.setdefault(name, []).append(4 * B * (shape[0] * shape[1] * shape[2] + oc * oh * ow))
-        if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 3 and L["groups"] == L["cin"] == L["cout"]:
+        if k == "conv2d" and cfg.dtype == "f32" and L["k"] == 3 and L["groups"] == L["cin"] == L["cout"] and i not in dws:
             c, h, w = shape
             if _dw_vw(h, w, L["stride"]):
                 oc, oh, ow = oshape
@@ -137,7 +162,7 @@ def kernel_model(cfg):
                 # g, x in; dx out; with a BatchNorm behind also the conv output (that BatchNorm's input)
                 ny = 2 if (i + 1) in given_bn else 1
                 out.setdefault(name, []).append(4 * B * (2 * c * h * w + ny * oc * oh * ow))
-        if k == "batchnorm2d":
+        if k == "batchnorm2d" and i not in dws_bn:
             c, h, w = shape
             vec = "<true>" if (h * w) % 4 == 0 else "<false>"
             n_el = B * c * h * w

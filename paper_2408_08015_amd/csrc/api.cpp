@@ -170,6 +170,12 @@ ast_status asteroid_stage_create(const ast_layer* layers, int32_t n_layers, cons
   bool dense = false;
   for (const ast::Op& op : s.ops) dense |= op.kind == ast::OP_CONV_3X3;
   if (dense && (e = ast::conv_lds_allow()) != hipSuccess) return bail(e, "create: dynamic LDS");
+  for (size_t j = 0; j < s.ops.size(); ++j) {
+    const ast::Op& op = s.ops[j];
+    if (!op.dws || op.kind == ast::OP_BN) continue;
+    const ast::Act& I = s.acts[op.in];
+    if ((e = ast::dws_allow(op.k, I.n, I.c, I.h, I.w, op.stride, s.ops[j - 1].act)) != hipSuccess) return bail(e, "create: dynamic LDS");
+  }
   const size_t pbytes = (s.nparams + 4) * sizeof(float);
   if ((e = hipMalloc((void**)&s.W, pbytes)) != hipSuccess) return bail(e, "create: hipMalloc(W)");
   if ((e = hipMalloc((void**)&s.G, pbytes)) != hipSuccess) return bail(e, "create: hipMalloc(G)");

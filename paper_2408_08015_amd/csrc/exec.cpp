@@ -62,12 +62,26 @@ inline size_t mha_lw_offset(int B, int S, int D, int heads) {
 typedef const float* cf;
 typedef const bf16_t* cb;
 
+// a BatchNorm of a run that is one launch, as that launch reads and records it
+DwsBn dws_bn(Ctx& c, const Op& bn) {
+  Stage& s = c.s;
+  float* aux = reinterpret_cast<float*>(c.slot + bn.aux_off);
+  return {s.W + bn.w_off, s.W + bn.b_off, aux, aux + 2 * s.acts[bn.in].c, s.running + bn.run_off, bn.eps, bn.act};
+}
+
 void fwd_op(Ctx& c, const Op& op, const int32_t* labels, float* loss) {
   Stage& s = c.s;
   hipStream_t st = c.st;
   const Act& I = s.acts[op.in];
   const int HW = I.h * I.w;
   if (op.absorbed) return;
+  if (op.dws) {  // the convolution's launch does the BatchNorms beside it too
+    if (op.kind == OP_BN) return;
+    const Op &b1 = (&op)[-1], &b2 = (&op)[1];
+    dws_fwd_f32(st, (cf)act_ptr(c, b1.in), s.W + op.w_off, (float*)act_ptr(c, op.out), (float*)act_ptr(c, b2.out),
+                dws_bn(c, b1), dws_bn(c, b2), op.k, I.n, I.c, I.h, I.w, op.stride);
+    return;
+  }
   switch (op.kind) {
     case OP_SE_GATE: {  // this op is the first linear layer; swish, the second linear layer and sigmoid follow it
       const Op* q = &op;
@@ -223,6 +237,14 @@ void bwd_op(Ctx& c, const Op& op) {
   const int HW = I.h * I.w;
   void* gin = grad_ptr(c, op.in);  // NULL: not wanted
   if (op.absorbed) return;
+  if (op.dws) {
+    if (op.kind == OP_BN) return;
+    const Op &b1 = (&op)[-1], &b2 = (&op)[1];
+    dws_bwd_f32(st, (cf)grad_ptr(c, b2.out), (cf)act_ptr(c, op.out), (cf)act_ptr(c, b1.in), s.W + op.w_off,
+                (float*)grad_ptr(c, b1.in), s.G + op.w_off, s.G + b1.w_off, s.G + b1.b_off, s.G + b2.w_off, s.G + b2.b_off,
+                dws_bn(c, b1), dws_bn(c, b2), op.k, I.n, I.c, I.h, I.w, op.stride);
+    return;
+  }
   switch (op.kind) {
     case OP_SE_GATE: {
       const Op* q = &op;
@@ -765,6 +787,7 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
     const Act& I = s.acts[op.in];
     char* sc = ws_base + s.scratch_off + op.sc_off;
     float* scf = reinterpret_cast<float*>(sc);
+    if (op.dws) continue;  // a run that is one launch adds to G itself
     switch (op.kind) {
       case OP_CONV_PW: {
         const size_t n = (size_t)op.cin * op.cout;

@@ -167,6 +167,27 @@ struct DwBwdFuse {
 void dw3x3_bwd_f32(hipStream_t st, const float* g, const float* x, const float* w, float* dx, float* part,
                    float* G, int N, int C, int H, int W, int stride, const DwBwdFuse* fuse = nullptr);
 
+// BatchNorm -> act -> depthwise K x K (pad K/2, stride 1 or 2, no bias) -> BatchNorm -> act in one launch per direction, one
+// block per channel (kernels_f32_dws.hip).  Forward: x, the first BatchNorm's input, in; y, the convolution's output, and z
+// out; both BatchNorms' statistics are recorded.  Backward: gz in, dx (may be NULL) out; dW and the gradients of both
+// BatchNorms are added to G.  dws_allow: before the first launch of a size on a device.
+struct DwsBn {
+  const float* gamma;
+  const float* beta;
+  float* stat;
+  float* ss;
+  float* running;
+  float eps;
+  int act;
+};
+bool dws_supported(int K, int N, int C, int H, int W, int stride, int act1, int act2);
+hipError_t dws_allow(int K, int N, int C, int H, int W, int stride, int act);
+void dws_fwd_f32(hipStream_t st, const float* x, const float* w, float* y, float* z, const DwsBn& b1, const DwsBn& b2, int K,
+                 int N, int C, int H, int W, int stride);
+void dws_bwd_f32(hipStream_t st, const float* gz, const float* y, const float* x, const float* w, float* dx, float* Gw,
+                 float* Gg1, float* Gb1, float* Gg2, float* Gb2, const DwsBn& b1, const DwsBn& b2, int K, int N, int C, int H,
+                 int W, int stride);
+
 // Generic direct convolution (any k, stride, pad, groups); the fallback for shapes the
 // specialised kernels do not cover (e.g. a 3-channel stem).
 void conv_direct_fwd_f32(hipStream_t st, const float* x, const float* w, const float* bias, float* y,

@@ -406,19 +406,33 @@ ast_status build_plan(Stage& s, std::string& err) {
   //   2  backward: the first BatchNorm's partial sums (conv backward epilogue); needs 1
   //   4  backward: the second BatchNorm's apply pass (on load of the conv's upstream gradient)
   //   8  see below (pointwise conv -> BatchNorm)
+  //  16  the whole run as one launch per direction, where a channel of the micro-batch fits a block (dws_supported); also
+  //      with swish and 5x5 convolutions.  The other moves are for what is left
   std::vector<char> virtual_act(s.acts.size(), 0);  // activations that are never materialised
   {
     const char* e = getenv("ASTEROID_BN_FUSE");
-    const int fuse = e ? atoi(e) : 15;
+    const int fuse = e ? atoi(e) : 31;
+    for (size_t j = 1; (fuse & 16) && j + 1 < s.ops.size(); ++j) {
+      Op &b1 = s.ops[j - 1], &dw = s.ops[j], &b2 = s.ops[j + 1];
+      if ((dw.kind != OP_CONV_DW && dw.kind != OP_CONV_DWK) || b1.kind != OP_BN || b2.kind != OP_BN || b1.out != dw.in ||
+          b2.in != dw.out || b1.skip >= 0 || b2.skip >= 0 || b1.dws)
+        continue;
+      const Act& I = s.acts[dw.in];
+      if (!dws_supported(dw.k, I.n, I.c, I.h, I.w, dw.stride, b1.act, b2.act)) continue;
+      b1.dws = dw.dws = b2.dws = true;
+      virtual_act[b1.out] = 1;
+      for (int& la : s.layer_act)
+        if (la == b1.out) la = -1;
+    }
     for (size_t j = 0; fuse && j < s.ops.size(); ++j) {
       Op& dw = s.ops[j];
-      if (dw.kind != OP_CONV_DW) continue;
+      if (dw.kind != OP_CONV_DW || dw.dws) continue;
       const Act& DI = s.acts[dw.in];
       const int dparts = dw3x3_parts(DI.n, DI.c, DI.h, DI.w, dw.stride);  // partial sums per channel it leaves
       if (j > 0 && (fuse & 1)) {
         Op& bn = s.ops[j - 1];
         // (the conv's kernels apply ReLU / ReLU6 only, and mask by the recomputed activated value)
-        if (bn.kind == OP_BN && bn.out == dw.in && bn.skip < 0 && bn.act <= 2) {
+        if (bn.kind == OP_BN && bn.out == dw.in && bn.skip < 0 && bn.act <= 2 && !bn.dws) {
           bn.bn_lazy = true;
           bn.bn_bwd_sums_given = (fuse & 2) != 0;
           bn.given_bwd_parts = dparts;
@@ -430,7 +444,7 @@ ast_status build_plan(Stage& s, std::string& err) {
       }
       if (j + 1 < s.ops.size()) {
         Op& bn = s.ops[j + 1];
-        if (bn.kind == OP_BN && bn.in == dw.out) {
+        if (bn.kind == OP_BN && bn.in == dw.out && !bn.dws) {
           if (fuse & 1) {
             bn.bn_stats_given = true;
             bn.given_parts = dparts;
@@ -449,11 +463,11 @@ ast_status build_plan(Stage& s, std::string& err) {
   // BatchNorm's statistics partials in its epilogue, where its launch shape offers them.
   {
     const char* e = getenv("ASTEROID_BN_FUSE");
-    const int fuse = e ? atoi(e) : 15;
+    const int fuse = e ? atoi(e) : 31;
     for (size_t j = 0; (fuse & 8) && j + 1 < s.ops.size(); ++j) {
       Op& pw = s.ops[j];
       Op& bn = s.ops[j + 1];
-      if (pw.kind != OP_CONV_PW || pw.has_bias || bn.kind != OP_BN || bn.in != pw.out || bn.bn_stats_given) continue;
+      if (pw.kind != OP_CONV_PW || pw.has_bias || bn.kind != OP_BN || bn.in != pw.out || bn.bn_stats_given || bn.dws) continue;
       const Act& I = s.acts[pw.in];
       const int parts = pw_conv_stats_parts(I.n, pw.cin, pw.cout, I.h * I.w);
       if (parts <= 0) continue;
@@ -472,7 +486,7 @@ ast_status build_plan(Stage& s, std::string& err) {
     Op& f = s.ops[j - 1];
     if (a.kind != OP_ACT || (a.act != 1 && a.act != 2) || a.in != f.out || (f.kind != OP_BN && f.kind != OP_RES_ADD)) continue;
     Op& b = f.kind == OP_BN ? f : s.ops[j >= 2 ? j - 2 : 0];
-    const bool bn = b.kind == OP_BN && !b.bn_lazy && b.act != 4 && (&b == &f || f.in == b.out);
+    const bool bn = b.kind == OP_BN && !b.bn_lazy && !b.dws && b.act != 4 && (&b == &f || f.in == b.out);
     if (f.kind == OP_RES_ADD ? s.acts[f.out].elems % 4 == 0 : bn) {
       f.act_behind = (int)j;
       a.act_fwd_done = true;
@@ -525,7 +539,7 @@ ast_status build_plan(Stage& s, std::string& err) {
     for (Op& op : s.ops) {
       const Act& I = s.acts[op.in];
       size_t need = 0;
-      switch (op.kind) {
+      if (!op.dws) switch (op.kind) {  // (none where a run of operators is one launch)
         case OP_CONV_PW: need = pw_wgrad_f32_ws(I.n, op.cin, op.cout, I.h * I.w, op.wg_cap) * sizeof(float); break;
         case OP_CONV_DW: need = dw3x3_bwd_f32_ws(I.n, I.c, I.h, I.w, op.stride) * sizeof(float); break;
         case OP_CONV_DWK: need = dwk_bwd_f32_ws(I.n, I.c, op.k) * sizeof(float); break;
@@ -564,7 +578,7 @@ ast_status build_plan(Stage& s, std::string& err) {
     // micro-batch may run beside the backward of another.
     size_t fsc = 0;
     for (Op& op : s.ops) {
-      if (op.kind != OP_BN) continue;
+      if (op.kind != OP_BN || op.dws) continue;
       const Act& I = s.acts[op.in];
       op.fsc_off = fsc;
       fsc += align_up(std::max(bn_ws_doubles(I.c, I.n, I.h * I.w), (size_t)2 * I.c * op.given_parts) * sizeof(double), 256);

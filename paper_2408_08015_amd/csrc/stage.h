@@ -95,6 +95,7 @@ struct Op {
   int bn_in_op = -1;                  // depthwise conv: index of the lazy BatchNorm op in front
   int bn_out_op = -1;                 // depthwise conv: index of the BatchNorm op it writes statistics for
   int bn_bwd_out_op = -1;             // depthwise conv: index of the BatchNorm op whose backward apply it does
+  bool dws = false;                   // BatchNorm, depthwise conv, BatchNorm that run as one launch per direction (the conv's)
   int stats_op = -1;                  // pointwise conv: index of the BatchNorm op it writes statistics for
   // A ReLU / ReLU6 that stands alone at a residual block's end (fp32), done by its neighbours' passes:
   int act_behind = -1;                // BatchNorm or RES_ADD: index of the OP_ACT whose forward it does
