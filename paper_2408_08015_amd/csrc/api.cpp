@@ -78,8 +78,7 @@ void free_stage(ast::Stage& s) {
   s.red_nblocks = 0;
   for (ast::Stage::WgGroup& wg : s.wg_groups) {
     if (wg.tasks) (void)hipFree(wg.tasks);
-    if (wg.block_task) (void)hipFree(wg.block_task);
-    if (wg.task_block0) (void)hipFree(wg.task_block0);
+    if (wg.blocks) (void)hipFree(wg.blocks);
   }
   s.wg_groups.clear();
   s.wg_nblocks = 0;

@@ -21,8 +21,10 @@
 #include "kernels_bf16.h"
 #include "prof.h"
 
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
+#include <vector>
 
 namespace ast {
 
@@ -33,7 +35,7 @@ struct WgArgs {
   const bf16_t* x;   // [P][Cin]
   float* part;       // [splits][taps][Cout][Cin]
   float* bias_part;  // [splits][Cout] or NULL: column sums of dy (the bias gradient) per split
-  float* acc_out;    // grouped launches (one split): [Cout][Cin] that the product is ADDED to, instead of `part`
+  float* acc_out;    // grouped launches, products of one split: [Cout][Cin] that the product is ADDED to, instead of `part`
   float* bias_acc;   // ... and [Cout] that the column sums of dy are added to (or NULL)
   int P, H, W, Cout, Cin;
   int taps;          // 9 (3x3) or 1
@@ -334,15 +336,12 @@ __global__ __launch_bounds__(512) void conv_wgrad_tr_kernel_n128(WgArgs g) {
 }
 
 // Many products in one launch (the weight gradients of all linear layers of a stage: nothing later in
-// a backward pass depends on them): block -> (product, block of that product) through a table;
-// every product runs unsplit and adds its result straight into the gradient arena.
+// a backward pass depends on them): block -> (product, block of that product) through a list.
 __global__ __launch_bounds__(512) void wgrad_grouped_kernel(const WgArgs* __restrict__ tasks,
-                                                            const unsigned short* __restrict__ block_task,
-                                                            const unsigned* __restrict__ task_block0, int block_base) {
-  const int b = block_base + (int)blockIdx.x;  // (a launch may cover a sub-range of the table's blocks)
-  const int t = block_task[b];
-  const WgArgs g = tasks[t];
-  conv_wgrad_tr_body<4>(g, b - (int)task_block0[t]);
+                                                            const unsigned* __restrict__ blocks) {
+  const unsigned b = blocks[blockIdx.x];
+  const WgArgs g = tasks[b >> 16];
+  conv_wgrad_tr_body<4>(g, (int)(b & 0xffffu));
 }
 constexpr size_t wg_lds_bytes(int tn) { return 3 * (size_t)(WG_A_BYTES + (tn == 4 ? WG_BK * 512 : 16 * 1024)); }
 
@@ -419,26 +418,130 @@ bool wgrad_group_supported(size_t rows, int Cin, int Cout) {
   return Cin % 8 == 0 && Cout % 8 == 0 && rows >= (size_t)WG_BK && rows * Cin * 2 < (1ul << 31) && rows * Cout * 2 < (1ul << 31) &&
          wg_attr_ok();
 }
-// Writes the descriptor of GW[Cout][Cin] += dy[rows][Cout]^T x[rows][Cin] (and Gb[Cout] += column sums of dy,
-// if Gb) to `task_out`; returns the number of blocks the product takes.
-int wgrad_group_task(void* task_out, const bf16_t* dy, const bf16_t* x, float* GW, float* Gb, size_t rows, int Cin, int Cout) {
+inline long share_rows(size_t rows, int splits) { return wg_cdiv(wg_cdiv((long)rows, splits), WG_BK) * WG_BK; }
+int wgrad_group_shares(size_t rows, int splits) { return (int)wg_cdiv((long)rows, share_rows(rows, splits)); }
+// Writes the descriptor of GW[Cout][Cin] += dy[rows][Cout]^T x[rows][Cin] (and Gb[Cout] += column sums of dy, if Gb), or of its
+// partials, to `task_out`; returns the number of blocks the product takes.
+int wgrad_group_task(void* task_out, const bf16_t* dy, const bf16_t* x, float* GW, float* Gb, size_t rows, int Cin, int Cout,
+                     int shares, float* part, float* bias_part) {
   WgArgs g = {};
-  g.dy = dy; g.x = x; g.acc_out = GW; g.bias_acc = Gb;
+  g.dy = dy; g.x = x;
+  if (shares > 1) {
+    g.part = part;
+    g.bias_part = Gb ? bias_part : nullptr;
+  } else {
+    g.acc_out = GW;
+    g.bias_acc = Gb;
+  }
   g.P = (int)rows; g.H = 1; g.W = 1; g.Cout = Cout; g.Cin = Cin;
   g.taps = 1;
-  g.k_per_split = (int)(wg_cdiv((long)rows, WG_BK) * WG_BK);
+  g.k_per_split = (int)share_rows(rows, shares);
   g.tiles_m = (int)wg_cdiv(Cout, 256);
   g.tiles_n = (int)wg_cdiv(Cin, 256);
   g.step_q = 0; g.step_r = 0;   // (one tap: no pixel is ever outside the image)
   g.x_bytes = (unsigned)(rows * Cin * 2);
   *static_cast<WgArgs*>(task_out) = g;
-  return g.tiles_m * g.tiles_n;
+  return g.tiles_m * g.tiles_n * shares;
 }
-void wgrad_group_launch(hipStream_t st, const void* tasks_dev, const unsigned short* block_task_dev,
-                        const unsigned* task_block0_dev, int block_base, int nblocks) {
+
+// 288 whole tiles of 4096 rows on 256 compute units, one block on each at a time, take two rounds of 180 us, the second of
+// which only 32 blocks fill.  So some products are formed in shares of their rows.  A K-tile takes 1.78 us; a block's ends, where
+// all blocks of a round read and write their part of the gradient at once, 30 us, and 18 where they only write a partial;
+// the reduction reads the partials and adds them up (0.065 us each, 0.1 per tile).  (Measured: 144 to 216 whole tiles of 864,
+// 4096 and 10240 rows 65, 175 and 410 us.)  Which products, and how many shares of up to two counts, is the shortest time of
+// whole blocks first and shares into the gaps and behind them.
+constexpr double kTileStep = 1.78, kEndsWhole = 30.0, kEndsShare = 18.0, kPartial = 0.065, kSplitTile = 0.1;  // us
+namespace {
+// the time at which kWgBlocks compute units are done, that take blocks as they become free; add(): n blocks of t each, after
+// those before
+struct Schedule {
+  struct Group {
+    long units;
+    double t;
+  };
+  std::vector<Group> groups{{kWgBlocks, 0.0}};  // by time
+  void add(long n, double t) {
+    while (n > 0) {
+      Group g = groups.front();
+      if (n < g.units) {
+        groups.front().units -= n;
+        g.units = n;
+      } else {
+        groups.erase(groups.begin());
+      }
+      n -= g.units;
+      g.t += t;
+      groups.insert(std::upper_bound(groups.begin(), groups.end(), g, [](const Group& a, const Group& b) { return a.t < b.t; }), g);
+    }
+  }
+  double done() const { return groups.back().t; }
+};
+}  // namespace
+void wgrad_group_split(WgradProduct* products, size_t n, int most) {
+  if (!n) return;
+  const size_t rows = products[0].rows;
+  std::vector<long> tiles(1, 0);  // of the first i products
+  for (size_t i = 0; i < n; ++i) {
+    tiles.push_back(tiles.back() + wg_cdiv(products[i].cout, 256) * wg_cdiv(products[i].cin, 256));
+    products[i].splits = 1;
+    if (products[i].rows != rows) return;  // (a stage's layers have the same rows)
+  }
+  std::vector<int> counts;  // that leave no share empty and none below four K-tiles
+  for (int s = 2; s <= most; ++s)
+    if (wgrad_group_shares(rows, s) == s && share_rows(rows, s) >= 4 * WG_BK) counts.push_back(s);
+  auto block_time = [&](int s) { return (s > 1 ? kEndsShare : kEndsWhole) + kTileStep * (share_rows(rows, s) / WG_BK); };
+  auto shares_of = [](double t, long split, int s) { return t + kPartial * split * s + kSplitTile * split; };
+  Schedule whole;
+  whole.add(tiles[n], block_time(1));
+  double best = whole.done();
+  size_t m1 = 0, m2 = 0;  // products [0, m1) in s1 shares, [m1, m2) in s2
+  int s1 = 1, s2 = 1;
+  const size_t step = (n + 15) / 16;  // (long stages: not every product by itself)
+  for (size_t b = step; b < n + step; b += step) {
+    const size_t e2 = std::min(b, n);
+    Schedule first;
+    first.add(tiles[n] - tiles[e2], block_time(1));
+    if (first.done() >= best) continue;
+    for (const int q2 : counts)
+      for (size_t e1 = 0; e1 < e2; e1 += step) {
+        const long t1 = tiles[e1], t2 = tiles[e2] - tiles[e1];
+        Schedule second = first;
+        second.add(t2 * q2, block_time(q2));
+        if (second.done() >= best) continue;
+        for (const int q1 : counts) {
+          if (q1 <= q2 && e1 > 0) continue;
+          Schedule third = second;
+          third.add(t1 * q1, block_time(q1));
+          const double t = shares_of(shares_of(third.done(), t2, q2), t1, q1);
+          if (t < best) {
+            best = t;
+            m1 = e1; m2 = e2; s1 = q1; s2 = q2;
+          }
+          if (e1 == 0) break;
+        }
+      }
+  }
+  for (size_t i = 0; i < m2; ++i) products[i].splits = i < m1 ? s1 : s2;
+}
+void wgrad_group_order(unsigned* blocks, size_t first, size_t n) {
+  // block b of a launch runs on XCD b % 8
+  const std::vector<unsigned> in(blocks + first, blocks + first + n);
+  size_t at = 0;
+  for (size_t x = 0; x < 8; ++x)
+    for (size_t b = (x + 8 - first % 8) % 8; b < n; b += 8) blocks[first + b] = in[at++];
+}
+void wgrad_group_launch(hipStream_t st, const void* tasks_dev, const unsigned* blocks_dev, int nblocks) {
   if (nblocks <= 0) return;
   KLAUNCH(wgrad_grouped_kernel, dim3((unsigned)nblocks), dim3(512), wg_lds_bytes(4), st,
-          static_cast<const WgArgs*>(tasks_dev), block_task_dev, task_block0_dev, block_base);
+          static_cast<const WgArgs*>(tasks_dev), blocks_dev);
 }
 
 }  // namespace ast
+
+// The shares of a group's products, for tests: n layers of cin[i] -> cout[i] features on the same rows.
+extern "C" void ast_wgrad_shares(long rows, int n, const int* cin, const int* cout, int* shares) {
+  std::vector<ast::WgradProduct> p;
+  for (int i = 0; i < n; ++i) p.push_back({(size_t)rows, cin[i], cout[i], 1});
+  ast::wgrad_group_split(p.data(), p.size(), ast::kWgradMostShares);
+  for (int i = 0; i < n; ++i) shares[i] = p[i].splits;
+}

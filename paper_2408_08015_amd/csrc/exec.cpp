@@ -2,6 +2,7 @@
 // on the stage's stream.  No allocation, no host synchronisation.
 #include <cstdint>
 #include <cstdlib>
+#include <map>
 #include <vector>
 
 #include "kernels.h"
@@ -473,7 +474,7 @@ void bwd_op(Ctx& c, const Op& op) {
       float* dsum = reinterpret_cast<float*>(sc + align256(R * 4 * D * sizeof(bf16_t)));
       // partials of the two projections' weight gradients: output projection, then qkv
       char* lw_o = sc + mha_lw_offset(I.n, I.h, D, op.heads);
-      char* lw_q = lw_o + align256(linear_bf16_ws_bytes(R, D, D));
+      char* lw_q = lw_o + align256(linear_bf16_ws_bytes(R, D, D, op.wg_splits[0]));
       const bool defer = s.red_nblocks != 0;
       cb g = (cb)grad_ptr(c, op.out);
       hipStream_t sw = op.wg_grouped ? st : fork_side(c);
@@ -534,20 +535,17 @@ ast_status run_backward(Stage& s, int slot, const void* dy, void* dx, char* stat
   s.cur_y = nullptr;
   s.cur_dy = dy;
   s.cur_dx = dx;
-  // the weight (and bias) gradients of all grouped linear layers: two launches on the second stream, each
-  // adding its products into G (every entry of G belongs to one block of one launch)
-  const Stage::WgGroup* wg = s.wg_nblocks ? &s.wg_groups[2 * slot + (static_ws ? 1 : 0)] : nullptr;
-  for (int j = (int)s.ops.size() - 1; j >= 0; --j) {
-    bwd_op(c, s.ops[j]);
-    if (wg && j == s.wg_split_op)
-      wgrad_group_launch(fork_side(c), wg->tasks, wg->block_task, wg->task_block0, 0, s.wg_first_blocks);
+  for (int j = (int)s.ops.size() - 1; j >= 0; --j) bwd_op(c, s.ops[j]);
+  // The weight (and bias) gradients of all grouped linear layers.  Here, on the pass's own stream: beside the pass on the
+  // second stream they slowed its kernels by as much as they gained (a block fills a compute unit), and the hand-over between
+  // the queues at the end cost 30 us (six layers of 512, 4096 rows: 350 us a pass as two launches, 235 so).
+  if (s.wg_nblocks) {
+    const Stage::WgGroup& wg = s.wg_groups[2 * slot + (static_ws ? 1 : 0)];
+    wgrad_group_launch(s.stream, wg.tasks, wg.blocks, s.wg_nblocks);
   }
-  if (wg)
-    wgrad_group_launch(fork_side(c), wg->tasks, wg->block_task, wg->task_block0, s.wg_first_blocks,
-                       s.wg_nblocks - s.wg_first_blocks);
   if (s.red_nblocks)  // every layer's partials -> G, one launch (behind all of this pass's kernels)
-    reduce_tasks_f32(fork_side(c), static_cast<const RedTask*>(static_ws ? s.red_tasks_static : s.red_tasks), s.red_block_task,
-                     s.red_nblocks);
+    reduce_tasks_f32(c.forked ? fork_side(c) : s.stream, static_cast<const RedTask*>(static_ws ? s.red_tasks_static : s.red_tasks),
+                     s.red_block_task, s.red_nblocks);
   if (c.forked) {  // join: whatever follows on the main stream sees every gradient
     (void)hipEventRecord(s.join_ev, s.side);
     (void)hipStreamWaitEvent(s.stream, s.join_ev, 0);
@@ -657,7 +655,10 @@ static ast_status build_wgrad_groups(Stage& s, char* static_ws, std::string& err
     if (id == 0 || (id == s.final_act && !s.loss_tail)) return nullptr;  // the caller's dx / dy
     return ws + s.acts[id].grad_off;
   };
-  struct Prod { const bf16_t* dy; const bf16_t* x; float* GW; float* Gb; size_t rows; int cin, cout; };
+  struct Prod {
+    const bf16_t* dy; const bf16_t* x; float* GW; float* Gb; size_t rows; int cin, cout, splits;
+    char* part;
+  };
   auto products = [&](const Op& op, char* slot, char* ws, std::vector<Prod>& out) -> bool {
     const Act& I = s.acts[op.in];
     char* sc = ws + s.scratch_off + op.sc_off;
@@ -666,7 +667,8 @@ static ast_status build_wgrad_groups(Stage& s, char* static_ws, std::string& err
       char* g = (op.act == 3 && !op.gelu_bwd_fused) ? sc : grad_at(ws, op.out);  // the GELU-masked gradient lies in the scratch
       char* x = act_at(slot, op.in);
       if (!g || !x || !wgrad_group_supported(R, op.cin, op.cout)) return false;
-      out.push_back({(const bf16_t*)g, (const bf16_t*)x, s.G + op.w_off, op.has_bias ? s.G + op.b_off : nullptr, R, op.cin, op.cout});
+      out.push_back({(const bf16_t*)g, (const bf16_t*)x, s.G + op.w_off, op.has_bias ? s.G + op.b_off : nullptr, R, op.cin, op.cout,
+                     op.wg_splits[0], sc + align256(s.acts[op.out].bytes)});
       return true;
     }
     if (op.kind == OP_MHA) {
@@ -682,8 +684,10 @@ static ast_status build_wgrad_groups(Stage& s, char* static_ws, std::string& err
       char* g = grad_at(ws, op.out);
       char* x = act_at(slot, op.in);
       if (!g || !x || !wgrad_group_supported(R, D, 3 * D)) return false;
-      out.push_back({(const bf16_t*)g, o, Go, Gbo, R, D, D});
-      out.push_back({dqkv, (const bf16_t*)x, Gq, Gbq, R, D, 3 * D});
+      char* const lw_o = sc + mha_lw_offset(I.n, I.h, D, op.heads);
+      out.push_back({(const bf16_t*)g, o, Go, Gbo, R, D, D, op.wg_splits[0], lw_o});
+      out.push_back({dqkv, (const bf16_t*)x, Gq, Gbq, R, D, 3 * D, op.wg_splits[1],
+                     lw_o + align256(linear_bf16_ws_bytes(R, D, D, op.wg_splits[0]))});
       return true;
     }
     return false;
@@ -701,47 +705,40 @@ static ast_status build_wgrad_groups(Stage& s, char* static_ws, std::string& err
   for (size_t k = 0; k < s.slots.size(); ++k)
     for (int v = 0; v < (static_ws ? 2 : 1); ++v) {
       std::vector<Prod> prods;
-      std::vector<int> prod_op;
       for (int j = (int)s.ops.size() - 1; j >= 0; --j)  // the order of the backward pass
-        if (s.ops[j].wg_grouped) {
-          products(s.ops[j], s.slots[k], v ? static_ws : s.ws, prods);
-          prod_op.resize(prods.size(), j);
-        }
+        if (s.ops[j].wg_grouped) products(s.ops[j], s.slots[k], v ? static_ws : s.ws, prods);
       std::vector<char> tasks(prods.size() * tb);
-      std::vector<unsigned short> block_task;
-      std::vector<unsigned> block0;
-      for (size_t t = 0; t < prods.size(); ++t) {
+      std::map<int, std::vector<unsigned>> by_shares;  // the longest blocks first
+      bool fits = prods.size() < 65536;
+      for (size_t t = 0; t < prods.size() && fits; ++t) {
         const Prod& p = prods[t];
-        const int nb = wgrad_group_task(tasks.data() + t * tb, p.dy, p.x, p.GW, p.Gb, p.rows, p.cin, p.cout);
-        block0.push_back((unsigned)block_task.size());
-        for (int b = 0; b < nb; ++b) block_task.push_back((unsigned short)t);
+        const WgradParts wp = linear_bf16_group_parts(p.rows, p.cin, p.cout, p.splits);
+        float* const part = reinterpret_cast<float*>(p.part);
+        const int nb = wgrad_group_task(tasks.data() + t * tb, p.dy, p.x, p.GW, p.Gb, p.rows, p.cin, p.cout, p.splits, part,
+                                        part + wp.bias_off);
+        fits = nb < 65536;
+        for (int b = 0; b < nb; ++b) by_shares[p.splits].push_back((unsigned)(t << 16 | b));
       }
-      if (prods.size() >= 65535) {  // (absurdly long stage) back to per-layer launches
+      if (!fits) {  // (absurdly long stage) back to per-layer launches
         for (Op& op : s.ops) op.wg_grouped = false;
         s.wg_groups.clear();
         return AST_OK;
       }
+      std::vector<unsigned> blocks;
+      for (const auto& c : by_shares) {
+        blocks.insert(blocks.end(), c.second.begin(), c.second.end());
+        wgrad_group_order(blocks.data(), blocks.size() - c.second.size(), c.second.size());
+      }
       Stage::WgGroup& wg = s.wg_groups[2 * k + v];
       hipError_t e;
       if ((e = hipMalloc(&wg.tasks, tasks.size())) != hipSuccess ||
-          (e = hipMalloc((void**)&wg.block_task, block_task.size() * sizeof(unsigned short))) != hipSuccess ||
-          (e = hipMalloc((void**)&wg.task_block0, block0.size() * sizeof(unsigned))) != hipSuccess ||
+          (e = hipMalloc((void**)&wg.blocks, blocks.size() * sizeof(unsigned))) != hipSuccess ||
           (e = hipMemcpy(wg.tasks, tasks.data(), tasks.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-          (e = hipMemcpy(wg.block_task, block_task.data(), block_task.size() * sizeof(unsigned short), hipMemcpyHostToDevice)) != hipSuccess ||
-          (e = hipMemcpy(wg.task_block0, block0.data(), block0.size() * sizeof(unsigned), hipMemcpyHostToDevice)) != hipSuccess) {
+          (e = hipMemcpy(wg.blocks, blocks.data(), blocks.size() * sizeof(unsigned), hipMemcpyHostToDevice)) != hipSuccess) {
         err = std::string("grouped weight-gradient table: ") + hipGetErrorString(e);
         return e == hipErrorOutOfMemory ? AST_ENOMEM : AST_EHIP;
       }
-      s.wg_nblocks = (int)block_task.size();
-      // first launch: the products of the ops the pass reaches first, up to about half of the blocks
-      s.wg_first_blocks = 0;
-      s.wg_split_op = -1;
-      for (size_t t = 0; t + 1 < prods.size(); ++t)
-        if (prod_op[t + 1] != prod_op[t] && (int)block0[t + 1] * 2 >= s.wg_nblocks) {
-          s.wg_first_blocks = (int)block0[t + 1];
-          s.wg_split_op = prod_op[t];
-          break;
-        }
+      s.wg_nblocks = (int)blocks.size();
     }
   return AST_OK;
 }
@@ -783,6 +780,14 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
     add(base, GW, taps * mn, wp.splits, taps * mn, taps, mn);
     if (Gb) add(base + wp.bias_off, Gb, cout, wp.bias_parts, cout, 1, cout);
   };
+  // a linear layer's product: partials of its own launch, or of the grouped one where that forms it in shares
+  auto add_linear = [&](char* base, const Op& op, int i, float* GW, float* Gb, int cin, int cout) {
+    const Act& I = s.acts[op.in];
+    const size_t R = (size_t)I.n * I.h * I.w;
+    if (op.wg_grouped && op.wg_splits[i] == 1) return;  // added to G by its blocks
+    add_wgrad(reinterpret_cast<float*>(base), op.wg_grouped ? linear_bf16_group_parts(R, cin, cout, op.wg_splits[i])
+                                                            : linear_bf16_wgrad_parts(R, cin, cout), GW, Gb, cout, cin, 1);
+  };
   for (const Op& op : s.ops) {
     const Act& I = s.acts[op.in];
     char* sc = ws_base + s.scratch_off + op.sc_off;
@@ -813,10 +818,7 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
                   op.has_bias ? s.G + op.b_off : nullptr, op.cout, op.cin, op.k * op.k);
         break;
       case OP_LINEAR:
-        if (s.bf16 && !op.wg_grouped)
-          add_wgrad(reinterpret_cast<float*>(sc + align256(s.acts[op.out].bytes)),
-                    linear_bf16_wgrad_parts((size_t)I.n * I.h * I.w, op.cin, op.cout), s.G + op.w_off,
-                    op.has_bias ? s.G + op.b_off : nullptr, op.cout, op.cin, 1);
+        if (s.bf16) add_linear(sc + align256(s.acts[op.out].bytes), op, 0, s.G + op.w_off, op.has_bias ? s.G + op.b_off : nullptr, op.cin, op.cout);
         break;
       case OP_MHA: {
         const int D = op.cin;
@@ -826,10 +828,9 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
         float* Go = Gbq + 3 * D;
         float* Gbo = Go + (size_t)D * D;
         char* lw_o = sc + mha_lw_offset(I.n, I.h, D, op.heads);
-        char* lw_q = lw_o + align256(linear_bf16_ws_bytes(R, D, D));
-        if (op.wg_grouped) break;
-        add_wgrad(reinterpret_cast<float*>(lw_o), linear_bf16_wgrad_parts(R, D, D), Go, Gbo, D, D, 1);
-        add_wgrad(reinterpret_cast<float*>(lw_q), linear_bf16_wgrad_parts(R, D, 3 * D), Gq, Gbq, (size_t)3 * D, D, 1);
+        char* lw_q = lw_o + align256(linear_bf16_ws_bytes(R, D, D, op.wg_splits[0]));
+        add_linear(lw_o, op, 0, Go, Gbo, D, D);
+        add_linear(lw_q, op, 1, Gq, Gbq, D, 3 * D);
         break;
       }
       case OP_LAYERNORM: {

@@ -935,8 +935,17 @@ void conv_bf16_wgrad(hipStream_t st, const bf16_t* gy, const bf16_t* x, float* G
                   (long)N * H * W, Cout);
 }
 
-size_t linear_bf16_ws_bytes(size_t R, int Cin, int Cout) {
-  return (align64f(wgrad_ws_floats(Cout, Cin, (long)R, 1)) + colsum_ws_floats(Cout)) * sizeof(float) + 256;
+// splits: the shares that a product of the grouped launch is formed in (its partials may be more than those of a launch of its
+// own, whose layout they have)
+static size_t linear_part_floats(size_t R, int Cin, int Cout, int splits) {
+  const size_t grouped = splits > 1 ? (size_t)splits * Cout * Cin : 0;
+  return align64f(std::max(wgrad_ws_floats(Cout, Cin, (long)R, 1), grouped));
+}
+size_t linear_bf16_ws_bytes(size_t R, int Cin, int Cout, int splits) {
+  return (linear_part_floats(R, Cin, Cout, splits) + colsum_ws_floats(Cout)) * sizeof(float) + 256;
+}
+WgradParts linear_bf16_group_parts(size_t R, int Cin, int Cout, int splits) {
+  return {splits, linear_part_floats(R, Cin, Cout, splits), splits};
 }
 WgradParts linear_bf16_wgrad_parts(size_t R, int Cin, int Cout) {
   WgradParts p;

@@ -59,16 +59,22 @@ int conv_wgrad_tr_splits(long P, int Cin, int Cout, int taps);
 bool conv_wgrad_tr_supported(int N, int H, int W, int Cin, int Cout, int k);
 void conv_wgrad_tr_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* x, float* part, float* bias_part, int N, int H,
                         int W, int Cin, int Cout, int k);
-// Grouped weight gradients of linear layers (same kernel, one launch for many products, no split-K:
-// each product is added straight into its gradient): the caller builds one descriptor per product on
-// the host (wgrad_group_task returns the product's block count), a block -> product table and the
-// first block of each product, copies the three arrays to the device once, and launches them together
-// (or a contiguous range of the table's blocks: block_base, nblocks).
+// Grouped weight gradients of linear layers: the same kernel, one launch for many products.  A product is formed in one share of
+// its rows and added straight into its gradient, or in several, whose partials part[share][Cout][Cin], bias_part[share][Cout]
+// are left to the caller.  The caller builds one descriptor per product on the host (wgrad_group_task returns the product's
+// block count) and a list of blocks, product << 16 | block of the product, and copies both to the device once.
 size_t wgrad_group_task_bytes();
 bool wgrad_group_supported(size_t rows, int Cin, int Cout);
-int wgrad_group_task(void* task_out, const bf16_t* dy, const bf16_t* x, float* GW, float* Gb, size_t rows, int Cin, int Cout);
-void wgrad_group_launch(hipStream_t st, const void* tasks_dev, const unsigned short* block_task_dev,
-                        const unsigned* task_block0_dev, int block_base, int nblocks);
+int wgrad_group_shares(size_t rows, int splits);  // the shares that a wish for `splits` makes
+int wgrad_group_task(void* task_out, const bf16_t* dy, const bf16_t* x, float* GW, float* Gb, size_t rows, int Cin, int Cout,
+                     int shares, float* part, float* bias_part);
+void wgrad_group_launch(hipStream_t st, const void* tasks_dev, const unsigned* blocks_dev, int nblocks);
+// The shares of every product of a group, at most `most`, so that its blocks fill the chip evenly (each product: rows, Cin, Cout).
+struct WgradProduct { size_t rows; int cin, cout, splits; };
+constexpr int kWgradMostShares = 12;
+void wgrad_group_split(WgradProduct* products, size_t n, int most);
+// Rearranges n blocks from `first` on in a launch's list so that neighbours run on one XCD.
+void wgrad_group_order(unsigned* blocks, size_t first, size_t n);
 // Scratch layout of a weight-gradient call: `splits` partial copies of the weight gradient at
 // ws[0, ...), `bias_parts` partial bias gradients ([bias_parts][Cout]) from float offset bias_off.
 struct WgradParts { int splits; size_t bias_off; int bias_parts; };
@@ -85,7 +91,9 @@ void conv_bf16_wgrad(hipStream_t st, const bf16_t* g, const bf16_t* x, float* GW
 bool linear_dl_supported(size_t R, int K, int N);
 void linear_dl_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, const float* bias, bf16_t* c, bf16_t* pre,
                     const bf16_t* add, const bf16_t* gmul, size_t R, int K, int N, int act);
-size_t linear_bf16_ws_bytes(size_t R, int Cin, int Cout);
+size_t linear_bf16_ws_bytes(size_t R, int Cin, int Cout, int splits = 1);
+// ... of a product of the grouped launch in `splits` shares
+WgradParts linear_bf16_group_parts(size_t R, int Cin, int Cout, int splits);
 // y = act(x W^T + b) (+ add); with act == GELU the pre-activation goes to `pre` as well
 // `add` (may be NULL): residual input [R][Cout] added to the rounded output.
 void linear_bf16_fwd(hipStream_t st, const bf16_t* x, const bf16_t* sh, const float* bias, bf16_t* y,

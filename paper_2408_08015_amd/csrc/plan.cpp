@@ -560,14 +560,15 @@ ast_status build_plan(Stage& s, std::string& err) {
           break;
         case OP_LINEAR:
           if (s.bf16)
-            need = align_up(s.acts[op.out].bytes, 256) + linear_bf16_ws_bytes((size_t)I.n * I.h * I.w, op.cin, op.cout);
+            need = align_up(s.acts[op.out].bytes, 256) +
+                   linear_bf16_ws_bytes((size_t)I.n * I.h * I.w, op.cin, op.cout, op.wg_splits[0]);
           break;
         case OP_LAYERNORM: need = layernorm_bf16_ws_bytes((size_t)I.n * I.h, I.c); break;
         case OP_MHA:  // d_o and dqkv, the row sums, then the split-K partials of each projection
           need = align_up((size_t)I.n * I.h * 4 * op.cin * 2, 256) +
                  align_up(mha_bf16_ws_bytes(I.n, I.h, op.cin, op.heads), 256) +
-                 align_up(linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, op.cin), 256) +
-                 linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, 3 * op.cin);
+                 align_up(linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, op.cin, op.wg_splits[0]), 256) +
+                 linear_bf16_ws_bytes((size_t)I.n * I.h, op.cin, 3 * op.cin, op.wg_splits[1]);
           break;
         default: break;
       }
@@ -588,7 +589,33 @@ ast_status build_plan(Stage& s, std::string& err) {
     s.fscratch_off = s.scratch_off + s.scratch_bytes;
     s.ws_bytes = s.fscratch_off + align_up(fsc, 256) + 256;
   };
-  lay_out_scratch();
+  // Weight gradients of the linear layers and attention projections of a bf16 stage are formed by one launch at the end of a
+  // backward pass: some of them in shares of their rows, so that it fills the chip evenly.
+  if (s.bf16) {
+    std::vector<WgradProduct> products;
+    std::vector<int*> splits;
+    for (size_t j = s.ops.size(); j-- > 0;) {
+      Op& op = s.ops[j];
+      if (op.kind != OP_LINEAR && op.kind != OP_MHA) continue;
+      const Act& I = s.acts[op.in];
+      const size_t rows = (size_t)I.n * I.h * I.w;
+      if (rows < 48) continue;
+      products.push_back({rows, op.cin, op.cout, 1});
+      splits.push_back(&op.wg_splits[0]);
+      if (op.kind != OP_MHA) continue;
+      products.push_back({rows, op.cin, 3 * op.cin, 1});
+      splits.push_back(&op.wg_splits[1]);
+    }
+    // (fewer where the partials alone would take the stage past the static scratch array)
+    for (const int most : {kWgradMostShares, 8, 5, 3, 2, 1, kWgradMostShares}) {
+      wgrad_group_split(products.data(), products.size(), most);
+      for (size_t i = 0; i < products.size(); ++i) *splits[i] = products[i].splits;
+      lay_out_scratch();
+      if (s.ws_bytes <= (size_t)AST_STATIC_SCRATCH_BYTES) break;
+    }
+  } else {
+    lay_out_scratch();
+  }
   // The kernels choose the number of weight-gradient partials, and the convolutions in front of a BatchNorm the number of
   // statistics partials that they leave, for speed alone.  Where these take a stage past the static scratch array, the
   // convolutions that can give most of it back take fewer weight-gradient partials, one after the other until the stage fits,

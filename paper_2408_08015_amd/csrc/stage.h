@@ -103,6 +103,8 @@ struct Op {
   bool act_fwd_done = false, act_bwd_done = false;  // OP_ACT: by them
   bool wg_grouped = false;            // bf16 linear / attention projections: the weight (and bias) gradient is part of
                                       // the stage's one grouped weight-gradient launch at the end of the backward pass
+  int wg_splits[2] = {1, 1};          // ... and shares of the rows that it is formed in (attention: output, qkv projection):
+                                      // one is added into G, several are partials for the reduction behind it
 };
 
 struct Stage {
@@ -151,13 +153,9 @@ struct Stage {
 
   // Grouped weight gradients of the bf16 linear layers: descriptor tables on the device, one per stash
   // slot (the layer inputs live there) and workspace (the stage's own, the static array), index 2*slot + static
-  struct WgGroup { void* tasks = nullptr; unsigned short* block_task = nullptr; unsigned* task_block0 = nullptr; };
+  struct WgGroup { void* tasks = nullptr; unsigned* blocks = nullptr; };  // blocks: product << 16 | block of it
   std::vector<WgGroup> wg_groups;
   int wg_nblocks = 0;
-  // the products are launched in two halves on the second stream: the first as soon as the backward pass has
-  // gone through op `wg_split_op` (the gradients its products read exist then) and overlaps the rest of the
-  // pass, the second at the end
-  int wg_first_blocks = 0, wg_split_op = -1;
 
   // Second stream for the weight-gradient kernels, which no later kernel of the same
   // backward pass depends on (NULL: everything runs on `stream`).
