@@ -191,6 +191,9 @@ def kernel_model(cfg):
             halo = lambda kc, nn: L["k"] == 3 and kc % 64 == 0 and shape[2] <= 63   # the LDS-halo kernel's shapes
 
             def gcls(mm, nn, kc):
+                few = mm < (42000 if kc <= 128 else 32000 if kc <= 192 else 26000) or (128 < nn <= 192 and kc <= 192)
+                if L["k"] == 3 and (few or not halo(kc, nn)):      # (rows short enough for a block's LDS, here)
+                    return "conv_res_kernel_p64"
                 if halo(kc, nn):
                     return "conv3x3_halo_kernel_n256" if nn > 128 else "conv3x3_halo_kernel_n128"
                 return "gemm_bf16_kernel<128x128,im2col>" if _cdiv(mm, 128) * _cdiv(nn, 128) >= 256 \
@@ -235,7 +238,7 @@ def kernel_model(cfg):
 
 
 def kernel_bound(name):
-    return "mfma" if name.startswith(("gemm_bf16", "attention", "conv3x3_", "conv_wgrad", "wgrad_grouped", "linear_dl")) else "hbm"
+    return "mfma" if name.startswith(("gemm_bf16", "attention", "conv3x3_", "conv_res", "conv_wgrad", "wgrad_grouped", "linear_dl")) else "hbm"
 
 
 def family(name):

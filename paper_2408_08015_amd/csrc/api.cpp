@@ -169,6 +169,15 @@ ast_status asteroid_stage_create(const ast_layer* layers, int32_t n_layers, cons
   bool dense = false;
   for (const ast::Op& op : s.ops) dense |= op.kind == ast::OP_CONV_3X3;
   if (dense && (e = ast::conv_lds_allow()) != hipSuccess) return bail(e, "create: dynamic LDS");
+  bool resident = false;
+  for (ast::Op& op : s.ops) {
+    if (op.kind != ast::OP_CONV_IGEMM) continue;
+    const ast::Act& I = s.acts[op.in];
+    op.kernel = ast::conv_bf16_kernel(I.n, I.h, I.w, op.cin, op.cout, op.k);
+    op.kernel2 = ast::conv_bf16_kernel(I.n, I.h, I.w, op.cout, op.cin, op.k);
+    resident |= op.kernel == ast::CONV_RESIDENT || op.kernel2 == ast::CONV_RESIDENT;
+  }
+  if (resident && (e = ast::conv_res_allow()) != hipSuccess) return bail(e, "create: dynamic LDS");
   for (size_t j = 0; j < s.ops.size(); ++j) {
     const ast::Op& op = s.ops[j];
     if (!op.dws || op.kind == ast::OP_BN) continue;
@@ -203,6 +212,7 @@ ast_status asteroid_stage_create(const ast_layer* layers, int32_t n_layers, cons
   }
   if ((e = hipMemset(s.G, 0, pbytes)) != hipSuccess) return bail(e, "create: memset");
   if ((e = hipMemset(s.V, 0, pbytes)) != hipSuccess) return bail(e, "create: memset");
+  if (s.shadow && (e = hipMemset(s.shadow, 0, s.shadow_elems * 2 + 16)) != hipSuccess) return bail(e, "create: memset");
   if ((e = hipMemset(s.ws, 0, s.ws_bytes)) != hipSuccess) return bail(e, "create: memset");
   if (s.running) {
     std::vector<float> rs(s.running_floats, 0.f);

@@ -137,7 +137,7 @@ void fwd_op(Ctx& c, const Op& op, const int32_t* labels, float* loss) {
       break;
     case OP_CONV_IGEMM:
       conv_bf16_fwd(st, (cb)act_ptr(c, op.in), s.shadow + op.sh_off, op.has_bias ? s.W + op.b_off : nullptr,
-                    (bf16_t*)act_ptr(c, op.out), I.n, I.h, I.w, op.cin, op.cout, op.k, op.act);
+                    (bf16_t*)act_ptr(c, op.out), I.n, I.h, I.w, op.cin, op.cout, op.k, op.act, op.kernel);
       break;
     case OP_BN: {
       float* aux = reinterpret_cast<float*>(c.slot + op.aux_off);
@@ -351,7 +351,8 @@ void bwd_op(Ctx& c, const Op& op) {
       hipStream_t sw = fork_side(c);
       if (gin)
         conv_bf16_dgrad(st, g, s.shadow + op.sh2_off, (bf16_t*)gin,
-                        op.relu_from >= 0 ? (cb)act_ptr(c, op.relu_from) : nullptr, I.n, I.h, I.w, op.cin, op.cout, op.k);
+                        op.relu_from >= 0 ? (cb)act_ptr(c, op.relu_from) : nullptr, I.n, I.h, I.w, op.cin, op.cout, op.k,
+                        op.kernel2);
       conv_bf16_wgrad(sw, g, (cb)act_ptr(c, op.in), s.G + op.w_off, s.G + op.b_off, op.has_bias != 0, s.red_nblocks != 0,
                       sc, I.n, I.h, I.w, op.cin, op.cout, op.k);
       break;
@@ -871,10 +872,8 @@ ast_status refresh_shadow(Stage& s, std::string& err) {
     } else if (!s.bf16) {
       continue;  // the remaining copies are bf16 layouts
     } else if (op.kind == OP_CONV_IGEMM) {
-      const Act& I = s.acts[op.in];  // the kernel each direction will run decides the layout of its copy
       conv_weight_shadow_bf16(s.stream, s.W + op.w_off, s.shadow + op.sh_off, s.shadow + op.sh2_off, op.cout,
-                              op.cin, op.k, conv_bf16_uses_halo(I.n, I.h, I.w, op.cin, op.cout, op.k),
-                              conv_bf16_uses_halo(I.n, I.h, I.w, op.cout, op.cin, op.k));
+                              op.cin, op.k, op.kernel, op.kernel2);
     } else if (s.lsh_nblocks) {
       continue;  // the dense-layer copies went out in one launch above
     } else if (op.kind == OP_LINEAR) {

@@ -869,18 +869,28 @@ WgradParts conv_bf16_wgrad_parts(int N, int H, int W, int Cin, int Cout, int k) 
   return p;
 }
 
-// experiment switch: ASTEROID_CONV_HALO=0 keeps the 3x3 products on the generic implicit-GEMM kernel
-bool conv_bf16_uses_halo(int N, int H, int W, int Cin, int Cout, int k) {
-  static const bool on = env_int("ASTEROID_CONV_HALO") != 0;
-  return on && k == 3 && conv3x3_halo_supported(N, H, W, Cin, Cout);
+// Which kernel a 3x3 product runs on (CONV_*): the persistent halo kernel for whole 64-channel slices over many pixels, else the
+// one with the whole halo resident, else the general implicit GEMM.  Between the first two (halo / resident, us, 416 sizes):
+// below 26000 pixels the resident one is 1.3 to 5 times as fast (256 -> 256 at 14 x 14x14 47.5 / 12.9, 192 -> 192 at 32 x 23x23
+// 38.6 / 22.4), from 45000 on the halo kernel leads where its tiles of 128 or 256 channels are filled (256 -> 256 at 32 x 56x56 108 /
+// 133, 128 -> 128 35 / 41), not where a quarter of them is empty (128 -> 192 at 40 x 50x50 1.12 times).
+// ASTEROID_CONV_KERNEL (read at create): the best of those named that there is, 0 general, 1 halo, 2 resident.
+int conv_bf16_kernel(int N, int H, int W, int Cin, int Cout, int k) {
+  if (k != 3) return CONV_GENERAL;
+  const char* e = getenv("ASTEROID_CONV_KERNEL");
+  const int want = e && e[0] ? atoi(e) : -1;
+  const bool res = want != CONV_GENERAL && want != CONV_HALO && conv_res_supported(N, H, W, Cin, Cout);
+  const bool halo = want != CONV_GENERAL && want != CONV_RESIDENT && conv3x3_halo_supported(N, H, W, Cin, Cout);
+  if (!halo || !res) return halo ? CONV_HALO : res ? CONV_RESIDENT : CONV_GENERAL;
+  const long M = (long)N * H * W;
+  const bool part = Cout > 128 && Cout <= 192 && Cin <= 192;
+  return part || M < (Cin <= 128 ? 42000 : Cin <= 192 ? 32000 : 26000) ? CONV_RESIDENT : CONV_HALO;
 }
 
 void conv_bf16_fwd(hipStream_t st, const bf16_t* x, const bf16_t* sh_fwd, const float* bias, bf16_t* y, int N,
-                   int H, int W, int Cin, int Cout, int k, int act) {
-  if (conv_bf16_uses_halo(N, H, W, Cin, Cout, k)) {  // sh_fwd is the tiled copy then
-    conv3x3_halo_bf16(st, x, sh_fwd, bias, nullptr, y, N, H, W, Cin, Cout, act);
-    return;
-  }
+                   int H, int W, int Cin, int Cout, int k, int act, int kernel) {
+  if (kernel == CONV_HALO) return conv3x3_halo_bf16(st, x, sh_fwd, bias, nullptr, y, N, H, W, Cin, Cout, act);
+  if (kernel == CONV_RESIDENT) return conv_res_bf16(st, x, sh_fwd, bias, nullptr, y, N, H, W, Cin, Cout, act);
   GemmArgs g = {};
   g.A = x; g.B = sh_fwd;
   g.M = (long)N * H * W; g.N = Cout; g.K = (long)k * k * Cin;
@@ -891,12 +901,10 @@ void conv_bf16_fwd(hipStream_t st, const bf16_t* x, const bf16_t* sh_fwd, const 
 }
 
 void conv_bf16_dgrad(hipStream_t st, const bf16_t* gy, const bf16_t* sh_dgrad, bf16_t* dx, const bf16_t* relu_out,
-                     int N, int H, int W, int Cin, int Cout, int k) {
+                     int N, int H, int W, int Cin, int Cout, int k, int kernel) {
   // the input gradient is the same product with the roles of the channel counts exchanged
-  if (conv_bf16_uses_halo(N, H, W, Cout, Cin, k)) {
-    conv3x3_halo_bf16(st, gy, sh_dgrad, nullptr, relu_out, dx, N, H, W, Cout, Cin, 0);
-    return;
-  }
+  if (kernel == CONV_HALO) return conv3x3_halo_bf16(st, gy, sh_dgrad, nullptr, relu_out, dx, N, H, W, Cout, Cin, 0);
+  if (kernel == CONV_RESIDENT) return conv_res_bf16(st, gy, sh_dgrad, nullptr, relu_out, dx, N, H, W, Cout, Cin, 0);
   GemmArgs g = {};
   g.gmul = relu_out;
   g.gmul_relu = 1;

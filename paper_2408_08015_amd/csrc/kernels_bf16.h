@@ -11,11 +11,13 @@ namespace ast {
 typedef unsigned short bf16_t;
 
 // ---- weight copies (refreshed by the optimizer step from the fp32 master weights)
-// conv: master [Cout][Cin][k][k] -> fwd operand [Cout][tap][Cin] and input-gradient operand
-// [Cin][tap'][Cout] with tap' the point-reflected tap.  With tiled_fwd / tiled_dgrad the copy is
-// laid out for the LDS-halo kernel instead: [Cin/64][tap][Cout][64] / [Cout/64][tap'][Cin][64].
+// conv: master [Cout][Cin][k][k] -> fwd operand [Cout][tap][Cin] and input-gradient operand [Cin][tap'][Cout] with tap' the
+// point-reflected tap; or in the layout of the kernel that reads it (CONV_*): halo [Cin/64][tap][Cout][64] /
+// [Cout/64][tap'][Cin][64], resident the fragments [Cout/32][Cin/16][tap][64 lanes][8] / [Cin/32][Cout/16][tap'][64][8] (padded
+// with zeros, conv_res_pack_elems).
+enum : int { CONV_GENERAL = 0, CONV_HALO = 1, CONV_RESIDENT = 2 };
 void conv_weight_shadow_bf16(hipStream_t st, const float* w, bf16_t* sh_fwd, bf16_t* sh_dgrad, int Cout,
-                             int Cin, int k, bool tiled_fwd, bool tiled_dgrad);
+                             int Cin, int k, int kernel_fwd, int kernel_dgrad);
 // linear: master [Cout][Cin] -> copy [Cout][Cin] and transpose [Cin][Cout]
 void linear_weight_shadow_bf16(hipStream_t st, const float* w, bf16_t* sh, bf16_t* sh_t, int Cout, int Cin,
                                bool tiled, bool tiled_t);
@@ -36,18 +38,22 @@ void linear_weight_shadow_all_bf16(hipStream_t st, const LinShadowTask* tasks_de
 size_t conv_bf16_ws_bytes(int N, int H, int W, int Cin, int Cout, int k);
 // y = act(conv(x) + bias)
 void conv_bf16_fwd(hipStream_t st, const bf16_t* x, const bf16_t* sh_fwd, const float* bias, bf16_t* y,
-                   int N, int H, int W, int Cin, int Cout, int k, int act);
+                   int N, int H, int W, int Cin, int Cout, int k, int act, int kernel);
 // dx = conv^T(g); with `relu_out` ([N][H][W][Cin], may be NULL: the output of a ReLU that feeds this
 // conv) dx is zeroed where relu_out <= 0: that ReLU's backward, folded into the epilogue.
 void conv_bf16_dgrad(hipStream_t st, const bf16_t* g, const bf16_t* sh_dgrad, bf16_t* dx, const bf16_t* relu_out,
-                     int N, int H, int W, int Cin, int Cout, int k);
+                     int N, int H, int W, int Cin, int Cout, int k, int kernel);
 // The same 3x3 product with the input tile and its halo staged in LDS once per 64-channel slice
-// (conv_bf16_halo.hip).  conv_bf16_uses_halo(N, H, W, Cin, Cout, k): conv_bf16_fwd takes that
-// kernel for this shape and expects the tiled weight copy [Cin/64][tap][Cout][64]; the input
-// gradient asks with Cin and Cout exchanged.  The answer is fixed for the life of the process
-// (it needs a device: the kernel's LDS size has to be granted).
+// (conv_bf16_halo.hip), or once for all channels (conv_bf16_res.hip).  conv_bf16_kernel(N, H, W, Cin, Cout, k): the kernel
+// (CONV_*) for this shape, which expects its layout of the weight copy; the input gradient asks with Cin and Cout
+// exchanged.  Asked once, at create (it needs a device: the halo kernel's LDS size has to be granted).
 // conv3x3_halo_bf16: act is 0 or ReLU; the output is zeroed where mask <= 0 (mask may be NULL).
-bool conv_bf16_uses_halo(int N, int H, int W, int Cin, int Cout, int k);
+int conv_bf16_kernel(int N, int H, int W, int Cin, int Cout, int k);
+bool conv_res_supported(int N, int H, int W, int Cin, int Cout);
+size_t conv_res_pack_elems(int Cin, int Cout);
+hipError_t conv_res_allow();  // before the first launch on a device
+void conv_res_bf16(hipStream_t st, const bf16_t* x, const bf16_t* w, const float* bias, const bf16_t* mask, bf16_t* y, int N,
+                   int H, int W, int Cin, int Cout, int act);
 bool conv3x3_halo_supported(int N, int H, int W, int Cin, int Cout);
 void conv3x3_halo_bf16(hipStream_t st, const bf16_t* x, const bf16_t* w, const float* bias, const bf16_t* mask,
                        bf16_t* y, int N, int H, int W, int Cin, int Cout, int act);

@@ -31,9 +31,17 @@ __device__ __forceinline__ float gelu_val(float x) { return gelu_fast(x); }
 }  // namespace
 
 // ------------------------------------------------------------------ weight copies
+// Where the weight of output channel m, contracted channel c (of Mdim, Kdim) and tap t lies in a copy for kernel `kernel`
+__device__ __forceinline__ size_t conv_shadow_at(int kernel, int m, int c, int t, int Mdim, int Kdim, int kk) {
+  if (kernel == CONV_HALO) return (((size_t)(c >> 6) * kk + t) * Mdim + m) * 64 + (c & 63);
+  if (kernel == CONV_RESIDENT)
+    return (((size_t)(m >> 5) * ((Kdim + 15) >> 4) + (c >> 4)) * kk + t) * 512 + ((m & 31) + ((c >> 3) & 1) * 32) * 8 + (c & 7);
+  return ((size_t)m * kk + t) * Kdim + c;
+}
+// (the padding of the fragments' layout is zero from create on)
 __global__ void conv_shadow_kernel(const float* __restrict__ w, bf16_t* __restrict__ fwd,
-                                   bf16_t* __restrict__ dgr, int Cout, int Cin, int kk, int tiled_fwd, int tiled_dgrad) {
-  // master [co][ci][t]; fwd [co][t][ci]; dgrad [ci][kk-1-t][co]; tiled: [slice of 64][tap][row][64]
+                                   bf16_t* __restrict__ dgr, int Cout, int Cin, int kk, int kernel_fwd, int kernel_dgrad) {
+  // master [co][ci][t]
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t total = (size_t)Cout * Cin * kk;
   if (i >= total) return;
@@ -42,16 +50,14 @@ __global__ void conv_shadow_kernel(const float* __restrict__ w, bf16_t* __restri
   int ci = (int)(r % Cin);
   int co = (int)(r / Cin);
   bf16_t v = f2bf(w[i]);
-  if (tiled_fwd) fwd[(((size_t)(ci >> 6) * kk + t) * Cout + co) * 64 + (ci & 63)] = v;
-  else fwd[((size_t)co * kk + t) * Cin + ci] = v;
-  if (tiled_dgrad) dgr[(((size_t)(co >> 6) * kk + (kk - 1 - t)) * Cin + ci) * 64 + (co & 63)] = v;
-  else dgr[((size_t)ci * kk + (kk - 1 - t)) * Cout + co] = v;
+  fwd[conv_shadow_at(kernel_fwd, co, ci, t, Cout, Cin, kk)] = v;
+  dgr[conv_shadow_at(kernel_dgrad, ci, co, kk - 1 - t, Cin, Cout, kk)] = v;
 }
 void conv_weight_shadow_bf16(hipStream_t st, const float* w, bf16_t* sh_fwd, bf16_t* sh_dgrad, int Cout, int Cin,
-                             int k, bool tiled_fwd, bool tiled_dgrad) {
+                             int k, int kernel_fwd, int kernel_dgrad) {
   size_t total = (size_t)Cout * Cin * k * k;
-  KLAUNCH(conv_shadow_kernel, dim3(cdivu(total, 256)), dim3(256), 0, st, w, sh_fwd, sh_dgrad, Cout, Cin, k * k,
-          tiled_fwd ? 1 : 0, tiled_dgrad ? 1 : 0);
+  KLAUNCH(conv_shadow_kernel, dim3(cdivu(total, 256)), dim3(256), 0, st, w, sh_fwd, sh_dgrad, Cout, Cin, k * k, kernel_fwd,
+          kernel_dgrad);
 }
 
 // sh [Cout][Cin] and sht [Cin][Cout]; tiled: [K/64][rows][64] with K the contraction index of the

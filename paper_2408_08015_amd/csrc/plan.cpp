@@ -27,6 +27,12 @@ static int new_act(Stage& s, int n, int c, int h, int w, int rank, int layer, in
   return (int)s.acts.size() - 1;
 }
 
+// elements of a bf16 conv's weight copy, in whichever layout its kernel reads (a multiple of 16 bytes)
+static size_t conv_shadow_elems(int k, int Cin, int Cout) {
+  const size_t plain = (size_t)Cout * k * k * Cin;
+  return k == 3 ? std::max(plain, conv_res_pack_elems(Cin, Cout)) : plain;
+}
+
 ast_status build_plan(Stage& s, std::string& err) {
   const ast_stage_cfg& cfg = s.cfg;
   const int B = cfg.B;
@@ -86,8 +92,8 @@ ast_status build_plan(Stage& s, std::string& err) {
             err = fmt("layer %d: bf16 conv2d tensors must stay below 2^30 elements", i);
             return AST_EUNSUPPORTED; }
           op.kind = OP_CONV_IGEMM;
-          op.sh_off = shadow; shadow += (size_t)Cout * k * k * Cin;   // [Cout][tap][Cin]
-          op.sh2_off = shadow; shadow += (size_t)Cout * k * k * Cin;  // [Cin][tap flipped][Cout]
+          op.sh_off = shadow; shadow += conv_shadow_elems(k, Cin, Cout);
+          op.sh2_off = shadow; shadow += conv_shadow_elems(k, Cout, Cin);
           if (i + 1 < nl && s.layers[i + 1].kind == AST_RELU) { op.act = 1; ++i; }
         } else if (k == 1 && st == 1 && pad == 0 && g == 1) {
           op.kind = OP_CONV_PW;
