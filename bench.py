@@ -201,7 +201,9 @@ def kernel_model(cfg):
             out.setdefault(gcls(m, cout, cin), []).append(2 * m * cout * kk * cin)
             if not first or cfg.needs_input_grad:
                 out.setdefault(gcls(m, cin, cout), []).append(2 * m * cin * kk * cout)
-            wg = "conv_wgrad_tr_kernel_n256" if cin > 128 else "conv_wgrad_tr_kernel_n128"
+            tiles = _cdiv(cin, 32) * _cdiv(cout, 32)
+            wg = "conv_wgrad_taps_kernel" if L["k"] == 3 and (tiles <= 16 or tiles * m <= 2600000) else \
+                "conv_wgrad_tr_kernel_n256" if cin > 128 else "conv_wgrad_tr_kernel_n128"
             out.setdefault(wg if m >= 48 else "gemm_bf16_kernel<128x128,wgrad_conv>", []).append(2 * m * cout * kk * cin)
         if cfg.dtype == "bf16" and k in ("linear", "mha"):
             rows = B * shape[0]

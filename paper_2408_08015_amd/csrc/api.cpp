@@ -169,15 +169,17 @@ ast_status asteroid_stage_create(const ast_layer* layers, int32_t n_layers, cons
   bool dense = false;
   for (const ast::Op& op : s.ops) dense |= op.kind == ast::OP_CONV_3X3;
   if (dense && (e = ast::conv_lds_allow()) != hipSuccess) return bail(e, "create: dynamic LDS");
-  bool resident = false;
+  bool resident = false, taps = false;
   for (ast::Op& op : s.ops) {
     if (op.kind != ast::OP_CONV_IGEMM) continue;
     const ast::Act& I = s.acts[op.in];
     op.kernel = ast::conv_bf16_kernel(I.n, I.h, I.w, op.cin, op.cout, op.k);
     op.kernel2 = ast::conv_bf16_kernel(I.n, I.h, I.w, op.cout, op.cin, op.k);
+    taps |= op.wg_taps != 0;
     resident |= op.kernel == ast::CONV_RESIDENT || op.kernel2 == ast::CONV_RESIDENT;
   }
   if (resident && (e = ast::conv_res_allow()) != hipSuccess) return bail(e, "create: dynamic LDS");
+  if (taps && (e = ast::conv_wgrad_taps_allow()) != hipSuccess) return bail(e, "create: dynamic LDS");
   for (size_t j = 0; j < s.ops.size(); ++j) {
     const ast::Op& op = s.ops[j];
     if (!op.dws || op.kind == ast::OP_BN) continue;

@@ -348,13 +348,16 @@ void bwd_op(Ctx& c, const Op& op) {
         g = gm;
       }
       sc += align256(O.bytes);
-      hipStream_t sw = fork_side(c);
+      // (A weight gradient with all taps in a wavefront fills the chip and is short: on this stream, where it costs no hand-over
+      // between queues.  Backward and step of two products, us, beside / behind the input gradient: 64 -> 64 at 2 x 14x14 526 / 313,
+      // 24 -> 40 at 32 x 50x50 457 / 398, 192 -> 192 at 16 x 56x56 1621 / 1521; the other kernels: 128 -> 256 at 32 x 56x56 4054 / 4180.)
+      hipStream_t sw = op.wg_taps ? st : fork_side(c);
       if (gin)
         conv_bf16_dgrad(st, g, s.shadow + op.sh2_off, (bf16_t*)gin,
                         op.relu_from >= 0 ? (cb)act_ptr(c, op.relu_from) : nullptr, I.n, I.h, I.w, op.cin, op.cout, op.k,
                         op.kernel2);
       conv_bf16_wgrad(sw, g, (cb)act_ptr(c, op.in), s.G + op.w_off, s.G + op.b_off, op.has_bias != 0, s.red_nblocks != 0,
-                      sc, I.n, I.h, I.w, op.cin, op.cout, op.k);
+                      sc, I.n, I.h, I.w, op.cin, op.cout, op.k, op.wg_taps);
       break;
     }
     case OP_BN: {
@@ -815,7 +818,7 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
         break;
       case OP_CONV_IGEMM:
         add_wgrad(reinterpret_cast<float*>(sc + align256(s.acts[op.out].bytes)),
-                  conv_bf16_wgrad_parts(I.n, I.h, I.w, op.cin, op.cout, op.k), s.G + op.w_off,
+                  conv_bf16_wgrad_parts(I.n, I.h, I.w, op.cin, op.cout, op.k, op.wg_taps), s.G + op.w_off,
                   op.has_bias ? s.G + op.b_off : nullptr, op.cout, op.cin, op.k * op.k);
         break;
       case OP_LINEAR:

@@ -17,6 +17,7 @@
 // so that every lane stores 16 contiguous bytes.
 #include "device_utils.h"
 #include "kernels_bf16.h"
+#include <climits>
 #include <cstdlib>
 
 #include "prof.h"
@@ -857,11 +858,28 @@ static size_t conv_wgrad_part_floats(int N, int H, int W, int Cin, int Cout, int
   const size_t b = (size_t)conv_wgrad_tr_splits(P, Cin, Cout, k * k) * k * k * Cout * Cin;
   return a > b ? a : b;
 }
-size_t conv_bf16_ws_bytes(int N, int H, int W, int Cin, int Cout, int k) {
-  return (align64f(conv_wgrad_part_floats(N, H, W, Cin, Cout, k)) + colsum_ws_floats(Cout)) * sizeof(float) + 256;
+static size_t conv_bias_off(int N, int H, int W, int Cin, int Cout, int k, int taps) {
+  return align64f(std::max(conv_wgrad_part_floats(N, H, W, Cin, Cout, k), (size_t)taps * 9 * Cout * Cin));
 }
-WgradParts conv_bf16_wgrad_parts(int N, int H, int W, int Cin, int Cout, int k) {
+size_t conv_bf16_ws_bytes(int N, int H, int W, int Cin, int Cout, int k, int taps) {
+  return (conv_bias_off(N, H, W, Cin, Cout, k, taps) + std::max(colsum_ws_floats(Cout), (size_t)taps * Cout)) * sizeof(float) + 256;
+}
+// The partials of the kernel with all taps in a wavefront, where that runs, else 0 (ASTEROID_CONV_WGRAD=0 at create: never).  Its
+// time goes with the 32 x 32 tiles of weights times the pixels; that of the tiles of 256 channels is less for many of
+// these, but they leave three times the partials then and have too few blocks for few pixels.  us, tiles of 256 (128) channels / all
+// taps: 96 -> 96 (9 tiles) at 6 x 45x45 20 / 11, at 32 x 56x56 74 / 32; 64 -> 256 (16) there 76 / 46; 128 -> 256 (32) at 20 x 45x45
+// 41 / 39, at 20 x 60x60 61 / 64; 256 -> 256 (64) at 10 x 45x45 44 / 39, at 20 x 40x40 55 / 58.
+int conv_bf16_wgrad_taps(int N, int H, int W, int Cin, int Cout, int k, int most) {
+  const char* e = getenv("ASTEROID_CONV_WGRAD");
+  const long tiles = cdivl(Cout, 32) * cdivl(Cin, 32);
+  if (k != 3 || (e && e[0] == '0') || !conv_wgrad_taps_supported(N, H, W, Cin, Cout) ||
+      (tiles > 16 && tiles * ((long)N * H * W) > 2600000))
+    return 0;
+  return conv_wgrad_taps_splits(N, H, W, Cin, Cout, most);
+}
+WgradParts conv_bf16_wgrad_parts(int N, int H, int W, int Cin, int Cout, int k, int taps) {
   WgradParts p;
+  if (taps) return {taps, conv_bias_off(N, H, W, Cin, Cout, k, taps), taps};
   p.splits = conv_wgrad_uses_tr(N, H, W, Cin, Cout, k) ? conv_wgrad_tr_splits((long)N * H * W, Cin, Cout, k * k)
                                                       : wgrad_splits(Cout, Cin, (long)N * H * W, k * k);
   p.bias_off = align64f(conv_wgrad_part_floats(N, H, W, Cin, Cout, k));
@@ -917,11 +935,12 @@ void conv_bf16_dgrad(hipStream_t st, const bf16_t* gy, const bf16_t* sh_dgrad, b
 }
 
 void conv_bf16_wgrad(hipStream_t st, const bf16_t* gy, const bf16_t* x, float* GW, float* Gb, bool has_bias,
-                     bool defer, void* ws, int N, int H, int W, int Cin, int Cout, int k) {
-  if (conv_wgrad_uses_tr(N, H, W, Cin, Cout, k)) {  // the bias gradient's partials come from the same launch
-    float* bias_ws = reinterpret_cast<float*>(ws) + align64f(conv_wgrad_part_floats(N, H, W, Cin, Cout, k));
-    const int splits = conv_wgrad_tr_splits((long)N * H * W, Cin, Cout, k * k);
-    conv_wgrad_tr_bf16(st, gy, x, reinterpret_cast<float*>(ws), has_bias ? bias_ws : nullptr, N, H, W, Cin, Cout, k);
+                     bool defer, void* ws, int N, int H, int W, int Cin, int Cout, int k, int taps) {
+  if (taps || conv_wgrad_uses_tr(N, H, W, Cin, Cout, k)) {  // the bias gradient's partials come from the same launch
+    float* bias_ws = reinterpret_cast<float*>(ws) + conv_bias_off(N, H, W, Cin, Cout, k, taps);
+    const int splits = taps ? taps : conv_wgrad_tr_splits((long)N * H * W, Cin, Cout, k * k);
+    if (taps) conv_wgrad_taps_bf16(st, gy, x, reinterpret_cast<float*>(ws), has_bias ? bias_ws : nullptr, N, H, W, Cin, Cout, taps);
+    else conv_wgrad_tr_bf16(st, gy, x, reinterpret_cast<float*>(ws), has_bias ? bias_ws : nullptr, N, H, W, Cin, Cout, k);
     if (!defer) {
       const long total = (long)k * k * Cout * Cin;
       KLAUNCH(reduce_wgrad_kernel, dim3((unsigned)cdivl(total, 64)), dim3(256), 0, st, reinterpret_cast<const float*>(ws), GW,
@@ -1005,3 +1024,8 @@ void linear_bf16_wgrad(hipStream_t st, const bf16_t* gy, const bf16_t* x, float*
 }
 
 }  // namespace ast
+
+// The partials of a convolution's weight gradient with all taps in a wavefront; 0: another kernel runs.
+extern "C" int ast_conv_wgrad_taps_choice(int N, int H, int W, int Cin, int Cout) {
+  return ast::conv_bf16_wgrad_taps(N, H, W, Cin, Cout, 3, INT_MAX);
+}

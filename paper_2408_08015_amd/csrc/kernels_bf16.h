@@ -35,7 +35,10 @@ void linear_weight_shadow_all_bf16(hipStream_t st, const LinShadowTask* tasks_de
                                    int nblocks);
 
 // ---- dense 'same' convolution, stride 1, NHWC, k in {1,3}
-size_t conv_bf16_ws_bytes(int N, int H, int W, int Cin, int Cout, int k);
+// taps (of these and of conv_bf16_wgrad): the partials of the kernel with all taps in a wavefront, conv_bf16_wgrad_taps() of them
+// as asked for at create; 0: another kernel runs.
+int conv_bf16_wgrad_taps(int N, int H, int W, int Cin, int Cout, int k, int most);
+size_t conv_bf16_ws_bytes(int N, int H, int W, int Cin, int Cout, int k, int taps);
 // y = act(conv(x) + bias)
 void conv_bf16_fwd(hipStream_t st, const bf16_t* x, const bf16_t* sh_fwd, const float* bias, bf16_t* y,
                    int N, int H, int W, int Cin, int Cout, int k, int act, int kernel);
@@ -65,6 +68,13 @@ int conv_wgrad_tr_splits(long P, int Cin, int Cout, int taps);
 bool conv_wgrad_tr_supported(int N, int H, int W, int Cin, int Cout, int k);
 void conv_wgrad_tr_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* x, float* part, float* bias_part, int N, int H,
                         int W, int Cin, int Cout, int k);
+// ... with all nine taps of a 32 x 32 tile in one wavefront (conv_bf16_wgrad_taps.hip): the same partials, `splits` =
+// conv_wgrad_taps_splits(.., most) of them, at most `most`.
+int conv_wgrad_taps_splits(int N, int H, int W, int Cin, int Cout, int most);
+hipError_t conv_wgrad_taps_allow();  // before the first launch on a device
+bool conv_wgrad_taps_supported(int N, int H, int W, int Cin, int Cout);
+void conv_wgrad_taps_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* x, float* part, float* bias_part, int N, int H, int W,
+                          int Cin, int Cout, int splits);
 // Grouped weight gradients of linear layers: the same kernel, one launch for many products.  A product is formed in one share of
 // its rows and added straight into its gradient, or in several, whose partials part[share][Cout][Cin], bias_part[share][Cout]
 // are left to the caller.  The caller builds one descriptor per product on the host (wgrad_group_task returns the product's
@@ -84,11 +94,11 @@ void wgrad_group_order(unsigned* blocks, size_t first, size_t n);
 // Scratch layout of a weight-gradient call: `splits` partial copies of the weight gradient at
 // ws[0, ...), `bias_parts` partial bias gradients ([bias_parts][Cout]) from float offset bias_off.
 struct WgradParts { int splits; size_t bias_off; int bias_parts; };
-WgradParts conv_bf16_wgrad_parts(int N, int H, int W, int Cin, int Cout, int k);
+WgradParts conv_bf16_wgrad_parts(int N, int H, int W, int Cin, int Cout, int k, int taps);
 // GW[Cout][Cin][k][k] += conv weight gradient, Gb[Cout] += sum of g (if has_bias).  With
 // `defer` only the partials are written and the caller reduces them (reduce_tasks_f32).
 void conv_bf16_wgrad(hipStream_t st, const bf16_t* g, const bf16_t* x, float* GW, float* Gb, bool has_bias,
-                     bool defer, void* ws, int N, int H, int W, int Cin, int Cout, int k);
+                     bool defer, void* ws, int N, int H, int W, int Cin, int Cout, int k, int taps);
 
 // ---- linear on [R][Cin] rows
 // Whether the product of [R][K] rows with an [N][K] weight matrix runs in the direct-to-LDS kernel,

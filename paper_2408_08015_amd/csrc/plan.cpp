@@ -562,7 +562,7 @@ ast_status build_plan(Stage& s, std::string& err) {
                           (size_t)2 * I.c * std::max(op.given_parts, op.given_bwd_parts)) * sizeof(double);
           break;
         case OP_CONV_IGEMM:  // masked upstream gradient + split-K partials
-          need = align_up(s.acts[op.out].bytes, 256) + conv_bf16_ws_bytes(I.n, I.h, I.w, op.cin, op.cout, op.k);
+          need = align_up(s.acts[op.out].bytes, 256) + conv_bf16_ws_bytes(I.n, I.h, I.w, op.cin, op.cout, op.k, op.wg_taps);
           break;
         case OP_LINEAR:
           if (s.bf16)
@@ -612,10 +612,17 @@ ast_status build_plan(Stage& s, std::string& err) {
       products.push_back({rows, op.cin, 3 * op.cin, 1});
       splits.push_back(&op.wg_splits[1]);
     }
-    // (fewer where the partials alone would take the stage past the static scratch array)
+    // (Fewer partials where these alone would take the stage past the static scratch array; those of a convolution then no more
+    // than other kernels leave.)
     for (const int most : {kWgradMostShares, 8, 5, 3, 2, 1, kWgradMostShares}) {
       wgrad_group_split(products.data(), products.size(), most);
       for (size_t i = 0; i < products.size(); ++i) *splits[i] = products[i].splits;
+      for (Op& op : s.ops) {
+        if (op.kind != OP_CONV_IGEMM) continue;
+        const Act& I = s.acts[op.in];
+        const int other = conv_wgrad_tr_splits((long)I.n * I.h * I.w, op.cin, op.cout, op.k * op.k);
+        op.wg_taps = conv_bf16_wgrad_taps(I.n, I.h, I.w, op.cin, op.cout, op.k, most < kWgradMostShares ? other : INT_MAX);
+      }
       lay_out_scratch();
       if (s.ws_bytes <= (size_t)AST_STATIC_SCRATCH_BYTES) break;
     }

@@ -80,6 +80,7 @@ struct Op {
                                       // gradient is added to the one OP_SE_SCALE has already written
   size_t sh_off = 0, sh2_off = 0;     // bf16 weight copies (elements) in the shadow arena
   int kernel = 0, kernel2 = 0;        // bf16 conv: the kernels (CONV_*) that read them
+  int wg_taps = 0;                    // ... and the weight gradient's partials (conv_bf16_wgrad_taps)
   size_t wp_off = 0, wp2_off = 0;     // fp32 conv on the matrix cores: packed forward / dgrad operands (words)
   bool wp_split = false, wp2_split = false;  // ... of a dense conv: split copies (conv_x3_takes)
   size_t sc_off = 0;                  // this op's private scratch region (bytes past scratch_off)
