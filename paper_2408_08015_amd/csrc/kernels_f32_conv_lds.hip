@@ -416,13 +416,21 @@ namespace {
 //
 // Block: WM row tiles x WN groups of 32 * NT pixels x WK shares of the contraction, one wavefront each.  A wavefront's weights
 // (3 KB per tap and group) come from L2 and are its largest stream: 64 bytes per clock and compute unit with NT = 1 at the full
-// matrix rate, 32 with 2.  They are requested up to two taps ahead (one with NT = 4), in front of that tap's share of the pixel
-// loads: vector memory returns in order, so weights requested behind the pixels of a chunk would wait for them.
+// matrix rate, 32 with 2.  They are requested up to three taps ahead (two with NT = 4).
+//
+// What bounds it is that the reads of a wavefront and its products take turns: 256 -> 256 at 8 x 14x14 spends 28 % of its cycles in
+// products, 35 % in vector memory and 27 % in LDS, and takes their sum, with eight wavefronts on a compute unit as with
+// sixteen.  So the reads of the next 32 pixels and of the weights to come stand between the six products of these (behind
+// them in one go: 21.5 us where this takes 20.4; 64 -> 64 at 32 x 56x56 54.9 / 52.4, 128 -> 128 at 4 x 28x28 14.9 / 14.2).
+//
+// The blocks of an XCD that share weights run through them side by side, so every line would be waited for once by all of
+// them, with no more in flight than one of them asks for.  At its start each block reads a word of each line of a share of
+// them: 256 -> 256 at 8 x 14x14 in a pass over ResNet50 21.6 / 20.1 us, its strided products 42.7 / 37.8.
 struct X3Shape { int NT, NI, WM, WN, WK, rows, NP; size_t lds; double cost; };
 struct X3Args {
   LdsArgs p;
   int WM;
-  size_t x_words, y_words;
+  unsigned shares;  // blocks of an XCD that read the same weights
 };
 
 // acc += a wavefront's share (groups g0, g0 + gstep, ...) for one row tile and pixel (n, i, j) of each lane, on the fp32
@@ -452,7 +460,8 @@ __device__ __forceinline__ void x3_contract_f32(const LdsArgs& a, const LdsClass
 }
 
 template <int NT, int TAPS, int NI>
-__device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c, char* lds, int tile0, unsigned q0) {
+__device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c, char* lds, int tile0, unsigned q0,
+                                             unsigned share) {
   const LdsArgs& a = xa.p;
   const int tid = threadIdx.x, lane = tid & 63, T = blockDim.x, waves = T >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
@@ -476,12 +485,12 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
     voff[i] = g8 < G8 && v != kOutside ? v + (unsigned)(g8 * 8) * a.XHW * 4u : kOutside;
   }
   float xr[NI][8];
-  auto fetch = [&](int i, int ch) __attribute__((always_inline)) {
+  auto fetch = [&](int i, int ch, int j0, int j1) __attribute__((always_inline)) {
     const unsigned k0 = (unsigned)(ch * 16 * WK);
     unsigned vo = voff[i];
     if ((ch + 1) * WK > KG) vo = k0 + (unsigned)((tid + i * T) / NP * 8) < (unsigned)a.Kdim ? vo : kOutside;  // uniform: a short chunk
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = j0; j < j1; ++j)
       xr[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, vo, (k0 + j) * a.XHW * 4u, 0));
   };
   auto put = [&](int i, int buf) __attribute__((always_inline)) {
@@ -525,39 +534,17 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
   constexpr int AHEAD = RING == 3 && NT == 4 ? 2 : RING;  // (NT = 4 takes all registers: 64 -> 64 at 32 x 56x56 49 us, 3 ahead 54 to 57)
   const uint4* const wl = reinterpret_cast<const uint4*>(a.Wp) + (size_t)min(tile, (a.Mdim - 1) / 32) * KG * 192 + lane;
   uint4 A[RING][3];
-  auto ldA = [&](int t, int ch) __attribute__((always_inline)) {
-    const uint4* w = wl + (woff[t] + (unsigned)min(ch * WK + wk, KG - 1) * 192u);
-#pragma unroll
-    for (int p = 0; p < 3; ++p) A[t % RING][p] = w[p * 64];
+  auto ldA = [&](int t, int ch, int p) __attribute__((always_inline)) {
+    A[t % RING][p] = wl[woff[t] + (unsigned)min(ch * WK + wk, KG - 1) * 192u + p * 64u];
   };
   floatx16 acc[NT], acs[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[n][r] = acs[n][r] = 0.f;
-  auto tap = [&](int t, int buf) __attribute__((always_inline)) {
-    constexpr int NB = NT == 1 ? 1 : 2;
-    const uint4(&w)[3] = A[t % RING];
-#pragma unroll
-    for (int n0 = 0; n0 < NT; n0 += NB) {
-      uint4 x[NB][3];
-#pragma unroll
-      for (int n = 0; n < NB; ++n)
-#pragma unroll
-        for (int p = 0; p < 3; ++p) x[n][p] = *reinterpret_cast<const uint4*>(bl[n0 + n] + boff[t] + buf * BS + p * PS);
-#pragma unroll
-      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[2], x[n][0], acs[n0 + n]);
-#pragma unroll
-      for (int n = 0; n < NB; ++n) acc[n0 + n] = mfma_bf16(w[0], x[n][0], acc[n0 + n]);
-#pragma unroll
-      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[1], x[n][0], acs[n0 + n]);
-#pragma unroll
-      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[1], x[n][1], acs[n0 + n]);
-#pragma unroll
-      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[0], x[n][1], acs[n0 + n]);
-#pragma unroll
-      for (int n = 0; n < NB; ++n) acs[n0 + n] = mfma_bf16(w[0], x[n][2], acs[n0 + n]);
-    }
+  uint4 xb[2][3];  // pixel operands of a step (tap, group of 32 pixels), and of the next
+  auto rdX = [&](int step, int buf, int p) __attribute__((always_inline)) {
+    xb[step & 1][p] = *reinterpret_cast<const uint4*>(bl[step % NT] + boff[step / NT] + buf * BS + p * PS);
   };
   auto barrier = [&]() __attribute__((always_inline)) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (loads to registers stay in flight)
@@ -565,9 +552,28 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
     asm volatile("" ::: "memory");
   };
 #pragma unroll
-  for (int i = 0; i < NI; ++i) fetch(i, 0);
+  for (int i = 0; i < NI; ++i) fetch(i, 0, 0, 8);
 #pragma unroll
-  for (int t = 0; t < AHEAD; ++t) ldA(t, 0);
+  for (int t = 0; t < AHEAD; ++t)
+#pragma unroll
+    for (int p = 0; p < 3; ++p) ldA(t, 0, p);
+  constexpr int NW = 2;
+  uint32_t warm[NW];
+  {  // the block's share of its row tiles' weights, one word of each line of 128 bytes
+    const unsigned per = (unsigned)min(WM, a.Mdim / 32 - tile0) * KG * 24u, lines = per * TAPS;
+    const char* const w0 = reinterpret_cast<const char*>(a.Wp) + (size_t)tile0 * KG * 3072;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      const unsigned l = (k * xa.shares + share) * T + tid;
+      warm[k] = 0;
+      if (l < lines) {
+        const unsigned t = l / per;
+        const unsigned rc = c.rows >> (8 * (t / c.nc)), cc = c.cols >> (8 * (t % c.nc));
+        const size_t tap = ((rc >> 4 & 15) * (unsigned)a.KS + (cc >> 4 & 15)) * a.tap_stride;
+        warm[k] = *reinterpret_cast<const uint32_t*>(w0 + tap * 16 + (size_t)(l - t * per) * 128);
+      }
+    }
+  }
 #pragma unroll
   for (int i = 0; i < NI; ++i) put(i, 0);
   barrier();
@@ -576,18 +582,49 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
   auto chunk = [&](int ch, auto more_c) __attribute__((always_inline)) {
     constexpr bool more = decltype(more_c)::value;
     const int buf = ch & 1;
-    const bool on = more || ch * WK + wk < KG;  // uniform per wavefront; only the last chunk can be short
+    if (more || ch * WK + wk < KG) {  // uniform per wavefront; only the last chunk can be short
 #pragma unroll
-    for (int t = 0; t < TAPS; ++t) {
-      if (on) tap(t, buf);
-      if (t + AHEAD < TAPS) ldA(t + AHEAD, ch);
-      else if constexpr (more) ldA(t + AHEAD - TAPS, ch + 1);
-      if constexpr (more) {
-#pragma unroll
-        for (int i = t * PER; i < (t + 1) * PER; ++i)
-          if (i < NI) fetch(i, ch + 1);
-      }
+      for (int p = 0; p < 3; ++p) rdX(0, buf, p);
       __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < TAPS * NT; ++s) {
+        const int t = s / NT, n = s % NT;
+        const uint4(&w)[3] = A[t % RING];
+        const uint4(&x)[3] = xb[s & 1];
+        auto weights = [&](int p) __attribute__((always_inline)) {
+          if (t + AHEAD < TAPS) ldA(t + AHEAD, ch, p);
+          else if constexpr (more) ldA(t + AHEAD - TAPS, ch + 1, p);
+        };
+        auto beside = [&](int k) __attribute__((always_inline)) {  // behind the k-th product
+          if (k < 3 && s + 1 < TAPS * NT) rdX(s + 1, buf, k);
+          if (AHEAD < RING) {
+            if (n == 0 && k < 3) weights(2 - k);
+          } else if (n == NT - 1) {
+            if (k == 0) weights(2);
+            if (k == 2) weights(1);
+            if (k == 5) weights(0);
+          }
+          if constexpr (more) {
+            if (n == NT - 1 && (k == 3 || k == 4))
+#pragma unroll
+              for (int i = t * PER; i < (t + 1) * PER; ++i)
+                if (i < NI) fetch(i, ch + 1, k == 3 ? 0 : 4, k == 3 ? 4 : 8);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        acs[n] = mfma_bf16(w[2], x[0], acs[n]);
+        beside(0);
+        acs[n] = mfma_bf16(w[1], x[0], acs[n]);
+        beside(1);
+        acs[n] = mfma_bf16(w[1], x[1], acs[n]);
+        beside(2);
+        acc[n] = mfma_bf16(w[0], x[0], acc[n]);
+        beside(3);
+        acs[n] = mfma_bf16(w[0], x[1], acs[n]);
+        beside(4);
+        acs[n] = mfma_bf16(w[0], x[2], acs[n]);
+        beside(5);
+      }
     }
     if constexpr (more) {
 #pragma unroll
@@ -597,6 +634,8 @@ __device__ __forceinline__ void conv_x3_body(const X3Args& xa, const LdsClass& c
   };
   for (int ch = 0; ch + 1 < nchunk; ++ch) chunk(ch, std::true_type{});
   chunk(nchunk - 1, std::false_type{});
+#pragma unroll
+  for (int k = 0; k < NW; ++k) asm volatile("" ::"v"(warm[k]));  // (their only use)
 
   const size_t OHW = (size_t)a.OH * a.OW;
   auto row = [&](int r) { return tile * 32 + 8 * (r >> 2) + 4 * half + (r & 3); };
@@ -689,13 +728,14 @@ __global__ __launch_bounds__(512, 2) void conv_x3_f32_kernel(X3Args xa) {
   const int tile0 = __builtin_amdgcn_readfirstlane((int)(a.CH ? lo : hi)) * xa.WM;
   const unsigned q0 = __builtin_amdgcn_readfirstlane(a.CH ? hi : lo) * (unsigned)(32 * NT * a.WN);
   if (q0 >= c.npix) return;  // uniform: a smaller parity class
+  const unsigned share = (a.CH ? hi : lo) % xa.shares;
   if constexpr (ALL) {
-    conv_x3_body<NT, 9, NI>(xa, c, xlds, tile0, q0);
+    conv_x3_body<NT, 9, NI>(xa, c, xlds, tile0, q0, share);
   } else {
     const int nt = c.nr * c.nc;
-    if (nt == 4) conv_x3_body<NT, 4, NI>(xa, c, xlds, tile0, q0);
-    else if (nt == 2) conv_x3_body<NT, 2, NI>(xa, c, xlds, tile0, q0);
-    else if (nt == 1) conv_x3_body<NT, 1, NI>(xa, c, xlds, tile0, q0);
+    if (nt == 4) conv_x3_body<NT, 4, NI>(xa, c, xlds, tile0, q0, share);
+    else if (nt == 2) conv_x3_body<NT, 2, NI>(xa, c, xlds, tile0, q0, share);
+    else if (nt == 1) conv_x3_body<NT, 1, NI>(xa, c, xlds, tile0, q0, share);
     else {
       const unsigned PHW = (unsigned)(c.PH * c.PW), P = 32 * NT * a.WN;
       for (unsigned i = threadIdx.x; i < P * 32u * xa.WM; i += blockDim.x) {
@@ -751,6 +791,9 @@ void run_x3(hipStream_t st, const char* name, const LdsArgs& sizes, int ncls, co
   // (6 bytes a weight)
   a.p.CH = (size_t)sizes.Mdim * sizes.KS * sizes.KS * 3 < (size_t)sizes.N * sizes.XH * sizes.XW * 2;
   const dim3 grid((unsigned)cdiv(most, 32 * p.NT * p.WN), (unsigned)cdiv(sizes.Mdim / 32, p.WM), (unsigned)ncls);
+  // (grid.x * grid.y / 8: the blocks of an XCD)
+  const unsigned here = std::max(1u, grid.x * grid.y / 8);
+  a.shares = std::max(1u, std::min(grid.x, a.p.CH ? here / grid.y : here));
   const bool all = ncls == 1 && a.p.cls[0].nr * a.p.cls[0].nc == 9;
   if (p.NT == 1) launch_x3<1>(st, name, a, p, grid, all);
   else if (p.NT == 2) launch_x3<2>(st, name, a, p, grid, all);
@@ -761,8 +804,8 @@ void run_x3(hipStream_t st, const char* name, const LdsArgs& sizes, int ncls, co
 // instead only where there are fewer), and more pixels per wavefront where there is plenty of work; of the shapes that fit, the
 // nearest.
 // Measured at ResNet50's layers (us, fp32 matrix instructions / best shape / this one's neighbours): 64 -> 64 at 32 x 56x56 104 /
-// 54 (4 pixel groups) / 59 (2) / 75 (1); 128 -> 128 at 8 x 28x28 32.5 / 20.2 (2 shares, 4 row tiles) / 20.6 (2 row tiles); 256 ->
-// 256 at 8 x 14x14 33.2 / 20.9 (4 shares) / 22.7 (2); 512 -> 512 at 8 x 7x7 36.8 / 24.0 (8 shares) / 26.3 (4).
+// 52 (4 pixel groups) / 57 (2) / 57 (1); 128 -> 128 at 8 x 28x28 32.5 / 19.8 (2 shares, 4 row tiles) / 20.1 (2 row tiles); 256 ->
+// 256 at 8 x 14x14 33.2 / 20.4 (4 shares) / 21.1 (2); 512 -> 512 at 8 x 7x7 36.8 / 22.6 (8 shares) / 24.0 (4).
 bool search_x3(const LdsArgs& sizes, int ncls, X3Shape& best) {
   LdsArgs a = sizes;
   a.KG = cdiv(sizes.Kdim, 16);
@@ -772,8 +815,16 @@ bool search_x3(const LdsArgs& sizes, int ncls, X3Shape& best) {
   const bool all = ncls == 1 && sizes.cls[0].nr * sizes.cls[0].nc == 9;
   int wk = 1;
   while (wk < 8 && wk * tiles < (all && a.KG >= 16 * wk ? 2000 : 1200) && wk * 2 <= std::max(1, a.KG / 2)) wk *= 2;
-  const int wm = std::min(mt, std::max(1, std::min(4, 8 / wk))), wn = wk == 1 && (wm < 4 || (!all && sizes.KS == 3)) ? 8 / wm : 1;
-  const int nt = all && tiles >= 6000 ? 4 : tiles >= 3000 && sizes.KS == 1 && ncls == 1 ? 2 : 1;
+  const int wm = std::min(mt, std::max(1, std::min(4, 8 / wk)));
+  // four row tiles: every wavefront reads weights of its own, so two groups of pixels share each read once that leaves the compute
+  // units their blocks (128 -> 128 at 32 x 28x28 57.7 us with one, 48.0 with two, 51.0 with four; 256 -> 256 at 32 x 14x14
+  // 58.7 / 50.1; half as many tiles: 128 -> 128 at 8 x 28x28 19.8 / 21.0)
+  // Four row tiles: every wavefront reads weights of its own, so two groups of pixels share each read as soon as that leaves most
+  // compute units a block (128 -> 128 at 32 x 28x28 57.7 us with one, 49 with two, 51 with four; 256 -> 256 at 32 x 14x14, two
+  // shares of the contraction, 58.7 / 50.2; at half as many pixels, 128 -> 128 at 16 x 28x28, two take 44 and one 32)
+  const bool one = sizes.KS == 1 && ncls == 1;
+  const int nt = all && tiles >= 6000 ? 4 : (all && wm == 4 && wk * tiles >= 3000) || (tiles >= 3000 && one) ? 2 : 1;
+  const int wn = wk == 1 && (wm < 4 || (all && nt == 2) || (!all && sizes.KS == 3)) ? 8 / wm : 1;
   best.cost = 1e30;
   for (int NT = 1; NT <= 4; NT *= 2)
     for (int WM = 1; WM <= 8; ++WM)

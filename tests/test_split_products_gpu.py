@@ -247,6 +247,9 @@ DENSE = [
     ((64, 128, 1, 2, 14, 14, 3), (1, 4, 1, 2), (1, 2, 1, 4)),      # 1x1: three of four classes are zeros
     ((512, 512, 3, 1, 7, 7, 3), (1, 1, 1, 8), (1, 1, 1, 8)),
     ((48, 64, 3, 1, 11, 11, 2), (1, 2, 4, 1), None),               # forward alone: 48 is no multiple of 32
+    ((16, 128, 3, 1, 39, 39, 16), (2, 4, 2, 1), None),             # two pixel groups for four row tiles: 24336 pixels
+    ((16, 128, 3, 1, 38, 39, 16), (1, 4, 1, 1), None),             # ... and one, of 23712
+    ((256, 128, 3, 1, 20, 31, 20), (2, 4, 1, 2), (2, 4, 2, 1)),    # ... beside two shares of the contraction
 ]
 
 
