@@ -1,5 +1,6 @@
 // C ABI of the stage-training library (see include/asteroid.h): argument checks, the
 // 1F1B call discipline (Sec. 3.2), allocation in create, and the flat-vector accessors.
+#include <cmath>
 #include <cstring>
 #include <new>
 #include <cstdlib>
@@ -424,7 +425,29 @@ ast_status asteroid_stage_debug_activation(asteroid_stage* h, int32_t mb, int32_
   if (n_out) *n_out = A.elems;
   if (!host_out) return AST_OK;
   HIPCHK(sync_stage(s), "debug_activation");
-  const char* src = s.slots[s.mb_slot[mb]] + A.slot_off;
+  const char* const slot = s.slots[s.mb_slot[mb]];
+  const char* src = slot + A.slot_off;
+  for (const ast::Op& op : s.ops) {
+    if (op.out != id || op.act_behind < 0 || !s.ops[op.act_behind].in_unwritten) continue;
+    // (a sum in front of an activation, which the forward pass does not keep: once more, as the kernels form it)
+    std::vector<float> x(A.elems), k(op.skip >= 0 ? A.elems : 0), ss(2 * (size_t)A.c);
+    HIPCHK(hipMemcpy(x.data(), slot + s.acts[op.in].slot_off, A.bytes, hipMemcpyDeviceToHost), "debug_activation");
+    if (op.skip >= 0) HIPCHK(hipMemcpy(k.data(), slot + s.acts[op.skip].slot_off, A.bytes, hipMemcpyDeviceToHost), "debug_activation");
+    const bool bn = op.kind == ast::OP_BN;
+    if (bn) HIPCHK(hipMemcpy(ss.data(), slot + op.aux_off + 2 * (size_t)A.c * 4, 8 * (size_t)A.c, hipMemcpyDeviceToHost), "debug_activation");
+    const size_t HW = (size_t)A.h * A.w;
+    for (size_t i = 0; i < A.elems; ++i) {
+      float v = x[i];
+      if (bn) {
+        const size_t c = i / HW % A.c;
+        v = std::fmaf(v, ss[c], ss[A.c + c]);
+        if (op.act == 1 || op.act == 2) v = std::fmax(v, 0.f);
+        if (op.act == 2) v = std::fmin(v, 6.f);
+      }
+      host_out[i] = op.skip >= 0 ? v + k[i] : v;
+    }
+    return AST_OK;
+  }
   if (A.esize == 4) {
     HIPCHK(hipMemcpy(host_out, src, A.bytes, hipMemcpyDeviceToHost), "debug_activation");
   } else {

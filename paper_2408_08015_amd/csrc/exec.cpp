@@ -145,18 +145,18 @@ void fwd_op(Ctx& c, const Op& op, const int32_t* labels, float* loss) {
       cf x = (cf)act_ptr(c, op.in);
       const Op* a = op.act_behind >= 0 ? &s.ops[op.act_behind] : nullptr;
       float* const y2 = a ? (float*)act_ptr(c, a->out) : nullptr;
+      float* const y = a && a->in_unwritten ? nullptr : (float*)act_ptr(c, op.out);
       const int act2 = a ? a->act : 0;
       if (!op.bn_stats_given && !op.bn_lazy && op.act != 4 && bn_onepass_fits(I.n, HW)) {  // small tensor: one launch
         bn_fwd_onepass_f32(st, x, s.W + op.w_off, s.W + op.b_off, op.skip >= 0 ? (cf)act_ptr(c, op.skip) : nullptr,
-                           (float*)act_ptr(c, op.out), aux, aux + 2 * I.c, s.running + op.run_off, I.n, I.c, HW, op.eps,
-                           op.act, y2, act2);
+                           y, aux, aux + 2 * I.c, s.running + op.run_off, I.n, I.c, HW, op.eps, op.act, y2, act2);
         break;
       }
       // statistics: from the depthwise conv in front (one partial pair per plane) or a pass of its own
       if (!op.bn_stats_given) bn_stats_f32(st, x, ws, I.n, I.c, HW);
       if (!op.bn_lazy)  // else the depthwise conv behind normalises on load
         bn_apply_f32(st, x, s.W + op.w_off, s.W + op.b_off, op.skip >= 0 ? (cf)act_ptr(c, op.skip) : nullptr,
-                     (float*)act_ptr(c, op.out), aux, aux + 2 * I.c, s.running + op.run_off, ws,
+                     y, aux, aux + 2 * I.c, s.running + op.run_off, ws,
                      op.bn_stats_given ? op.given_parts : bn_parts(I.n, HW), I.n, I.c, HW, op.eps, op.act, y2, act2);
       break;
     }
@@ -177,7 +177,8 @@ void fwd_op(Ctx& c, const Op& op, const int32_t* labels, float* loss) {
     case OP_RES_ADD:
       if (s.bf16) add_bf16(st, (cb)act_ptr(c, op.in), (cb)act_ptr(c, op.skip), (bf16_t*)act_ptr(c, op.out), I.elems);
       else if (op.act_behind >= 0)
-        add_act_f32(st, (cf)act_ptr(c, op.in), (cf)act_ptr(c, op.skip), (float*)act_ptr(c, op.out),
+        add_act_f32(st, (cf)act_ptr(c, op.in), (cf)act_ptr(c, op.skip),
+                    s.ops[op.act_behind].in_unwritten ? nullptr : (float*)act_ptr(c, op.out),
                     (float*)act_ptr(c, s.ops[op.act_behind].out), I.elems, s.ops[op.act_behind].act);
       else add_f32(st, (cf)act_ptr(c, op.in), (cf)act_ptr(c, op.skip), (float*)act_ptr(c, op.out), I.elems);
       break;
@@ -368,7 +369,7 @@ void bwd_op(Ctx& c, const Op& op) {
       // a pass of its own; input gradient: formed by the depthwise conv in front on load, or a pass of its own
       const bool given = op.bn_bwd_sums_given;
       const Op* a = op.act_bwd_behind >= 0 ? &s.ops[op.act_bwd_behind] : nullptr;
-      cf pre = a ? (cf)act_ptr(c, a->in) : nullptr, gy = a ? (cf)grad_ptr(c, a->out) : g;
+      cf pre = a ? (cf)act_ptr(c, a->in_unwritten ? a->out : a->in) : nullptr, gy = a ? (cf)grad_ptr(c, a->out) : g;
       float* const gp = a ? (float*)grad_ptr(c, a->in) : nullptr;  // (where g is)
       const int act2 = a ? a->act : 0;
       if (!given && !op.bn_bwd_apply_fused && op.act != 4 && bn_onepass_fits(I.n, HW)) {  // small tensor: one launch
@@ -388,7 +389,7 @@ void bwd_op(Ctx& c, const Op& op) {
         act_bwd_bf16(st, (cb)grad_ptr(c, op.out), op.act == 3 ? (cb)act_ptr(c, op.in) : (cb)act_ptr(c, op.out),
                      (bf16_t*)gin, I.elems, op.act);
       else
-        act_bwd_f32(st, (cf)grad_ptr(c, op.out), (cf)act_ptr(c, op.in), (float*)gin, I.elems, op.act);
+        act_bwd_f32(st, (cf)grad_ptr(c, op.out), (cf)act_ptr(c, op.in_unwritten ? op.out : op.in), (float*)gin, I.elems, op.act);
       break;
     case OP_SE_BEGIN:  // both gradients of the tensor are already in its buffer (OP_SE_SCALE, then the pool)
     case OP_RES_SWAP:

@@ -344,13 +344,13 @@ __global__ void act_bwd4_kernel(const float4* __restrict__ g, const float4* __re
   d.x *= act_slope(v.x, act); d.y *= act_slope(v.y, act); d.z *= act_slope(v.z, act); d.w *= act_slope(v.w, act);
   dx[i] = d;
 }
-// y = a + b and the ReLU / ReLU6 behind it (bound by memory; as two launches y is read again)
+// y = a + b, if wanted, and the ReLU / ReLU6 behind it (bound by memory; as two launches y is read again)
 __global__ void add_act4_kernel(const float4* __restrict__ a, const float4* __restrict__ b, float4* __restrict__ y,
                                 float4* __restrict__ y2, size_t n4, int act) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
   const float4 u = a[i], v = b[i], r = make_float4(u.x + v.x, u.y + v.y, u.z + v.z, u.w + v.w);
-  y[i] = r;
+  if (y) y[i] = r;
   y2[i] = apply_act4(r, act);
 }
 // y may alias a (in-place accumulation of a skip gradient): no __restrict__ here

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void bn_stats_partial_kernel(const float* __re
   }
 }
 
-// y = act(x*scale + shift) (+ skip); y2, if there: act2(y), the activation behind a residual block's end; grid (planes, chunks)
+// y, if there: act(x*scale + shift) (+ skip); y2, if there: act2(that), the activation behind a residual block's end; grid (planes, chunks)
 template <bool VEC, bool SW = false>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const float* __restrict__ x,
                                                        const double* __restrict__ ws,
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const float* __restrict__
         if (skip) {
           v.x += kv[u].x; v.y += kv[u].y; v.z += kv[u].z; v.w += kv[u].w;
         }
-        *reinterpret_cast<float4*>(y + base + e) = v;
+        if (y) *reinterpret_cast<float4*>(y + base + e) = v;
         if (y2) *reinterpret_cast<float4*>(y2 + base + e) = apply_act4(v, act2);
       }
     }
@@ -179,14 +179,14 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const float* __restrict__
         float4 k = *reinterpret_cast<const float4*>(skip + base + e);
         v.x += k.x; v.y += k.y; v.z += k.z; v.w += k.w;
       }
-      *reinterpret_cast<float4*>(y + base + e) = v;
+      if (y) *reinterpret_cast<float4*>(y + base + e) = v;
       if (y2) *reinterpret_cast<float4*>(y2 + base + e) = apply_act4(v, act2);
     }
   } else {
     for (int e = e0 + threadIdx.x; e < e1; e += 256) {
       float v = apply_act_sw<SW>(x[base + e] * sc + sf, act);
       if (skip) v += skip[base + e];
-      y[base + e] = v;
+      if (y) y[base + e] = v;
       if (y2) y2[base + e] = apply_act(v, act2);
     }
   }
@@ -235,7 +235,7 @@ void bn_fwd_f32(hipStream_t st, const float* x, const float* gamma, const float*
 }
 
 // PRE: g comes from behind an activation that stands alone at a residual block's end; the pass writes the gradient in front
-// of it, g * act2'(pre), to gp and goes on with that.
+// of it, g * act2'(pre), to gp and goes on with that.  (pre: the activation's input, or its output, which has the same mask.)
 template <bool VEC, bool SW = false, bool PRE = false>
 __global__ __launch_bounds__(256) void bn_bwd_partial_kernel(const float* __restrict__ g,
                                                              const float* __restrict__ x,
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(T) void bn_fwd_onepass_kernel(const float* __restri
   for (int k = 0; k < 8; ++k)
     if (threadIdx.x + k * T < E) {
       const float r = apply_act(v[k] * sc + sf, act) + kv[k];
-      y[off[k]] = r;
+      if (y) y[off[k]] = r;
       if (y2) y2[off[k]] = apply_act(r, act2);
     }
 }

@@ -103,6 +103,7 @@ struct Op {
   int act_behind = -1;                // BatchNorm or RES_ADD: index of the OP_ACT whose forward it does
   int act_bwd_behind = -1;            // BatchNorm: ... whose backward it does
   bool act_fwd_done = false, act_bwd_done = false;  // OP_ACT: by them
+  bool in_unwritten = false;          // OP_ACT: nothing but it reads its input, which is not written (the mask comes from its output)
   bool wg_grouped = false;            // bf16 linear / attention projections: the weight (and bias) gradient is part of
                                       // the stage's one grouped weight-gradient launch at the end of the backward pass
   int wg_splits[2] = {1, 1};          // ... and shares of the rows that it is formed in (attention: output, qkv projection):

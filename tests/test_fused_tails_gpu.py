@@ -1,5 +1,6 @@
 """Short passes that ride with their neighbours: a ReLU or ReLU6 that stands alone at a residual block's end with the
 BatchNorm or the addition in front, and the sum of a few rows' losses with their softmax."""
+import numpy as np
 import pytest
 
 import harness
@@ -37,6 +38,22 @@ def test_activation_behind_a_residual_block(A, two, act, c, mid, hw, B):
     # stands on it
     for name, err in sc["r0.G_all"]:
         assert err <= 1e-3, (name, err)
+
+
+# the sum in front of that activation is written only where something else reads it; asked for, it is formed again
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("act,hw,B", [("relu", 8, 3), ("relu6", 7, 3), ("relu", 56, 4)])
+def test_sum_in_front_of_that_activation(A, two, act, hw, B):
+    layers = layers_of(two, act, 16, 24) + layers_of(False, act, 16, 24)
+    at = len(layers_of(two, act, 16, 24)) - 2   # the addition; the activation behind it
+    cfg = one(layers, (16, hw, hw), B=B, M=1)
+    inp = gen.make_inputs(cfg)
+    _, dbg, _ = harness.run_hip(cfg, inp, rounds=1, debug_layers=[at, at + 1])
+    pre, post = dbg[at], dbg[at + 1]
+    assert pre.min() < 0
+    want = np.clip(pre, 0, 6 if act == "relu6" else None)
+    # (one rounding of a fused multiply-add and one of the addition)
+    np.testing.assert_allclose(post, want, rtol=2.4e-7, atol=2.4e-7 * np.abs(pre).max())
 
 
 # on either side of sixteen rows and 64 classes, the largest heads that one block takes
