@@ -77,12 +77,7 @@ void free_stage(ast::Stage& s) {
   s.red_tasks = nullptr;
   s.red_block_task = nullptr;
   s.red_nblocks = 0;
-  for (ast::Stage::WgGroup& wg : s.wg_groups) {
-    if (wg.tasks) (void)hipFree(wg.tasks);
-    if (wg.blocks) (void)hipFree(wg.blocks);
-  }
-  s.wg_groups.clear();
-  s.wg_nblocks = 0;
+  ast::drop_wgrad_groups(s);
   if (s.wpack) (void)hipFree(s.wpack);
   s.wpack = nullptr;
   if (s.ws) (void)hipFree(s.ws);

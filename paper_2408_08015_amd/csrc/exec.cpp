@@ -748,6 +748,15 @@ static ast_status build_wgrad_groups(Stage& s, char* static_ws, std::string& err
   return AST_OK;
 }
 
+void drop_wgrad_groups(Stage& s) {
+  for (Stage::WgGroup& wg : s.wg_groups) {
+    if (wg.tasks) (void)hipFree(wg.tasks);
+    if (wg.blocks) (void)hipFree(wg.blocks);
+  }
+  s.wg_groups.clear();
+  s.wg_nblocks = 0;
+}
+
 ast_status build_reduce_tasks(Stage& s, std::string& err) {
   if (ast_status r = build_pack_tasks(s, err)) return r;
   if (ast_status r = build_linear_shadow_tasks(s, err)) return r;
@@ -847,7 +856,12 @@ ast_status build_reduce_tasks(Stage& s, std::string& err) {
       default: break;
     }
   }
-  if (tasks.empty() || overflow) return AST_OK;  // (absurdly long stage: per-layer launches)
+  if (overflow) {  // (absurdly long stage: per-layer launches, and nothing that would add up the shares of a grouped product)
+    for (Op& op : s.ops) op.wg_splits[0] = op.wg_splits[1] = 1;
+    drop_wgrad_groups(s);
+    return build_wgrad_groups(s, static_ws, err);
+  }
+  if (tasks.empty()) return AST_OK;
   hipError_t e;
   void** table = pass == 0 ? &s.red_tasks : &s.red_tasks_static;
   if ((e = hipMalloc(table, tasks.size() * sizeof(RedTask))) != hipSuccess ||

@@ -198,5 +198,6 @@ ast_status run_backward(Stage& s, int slot, const void* dy, void* dx, char* stat
 ast_status run_step(Stage& s, float lr, float mu, std::string& err);
 ast_status refresh_shadow(Stage& s, std::string& err);
 ast_status build_reduce_tasks(Stage& s, std::string& err);  // after the workspace is allocated
+void drop_wgrad_groups(Stage& s);
 
 }  // namespace ast

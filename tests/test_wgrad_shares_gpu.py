@@ -2,6 +2,7 @@
 counts, against the oracle; and a stage that the partials of the shares would take past the static workspace."""
 import ctypes
 
+import numpy as np
 import pytest
 
 import harness
@@ -74,3 +75,31 @@ def test_layers_at_the_ends_of_a_stage(A):
     hip, _, _ = harness.run_hip(cfg, inp, rounds=1)
     for name, err in harness.score(cfg, hip, ora)["r0.G_all"]:
         assert err <= 1e-2, (name, err)
+
+
+# more sums than the reduction's table holds: nothing adds up partials there, and the product behind it is formed whole
+@pytest.mark.gpu
+def test_stage_longer_than_the_reduction_table(A, monkeypatch):
+    import torch
+    d, S, B, n = 64, 16, 24, 32768   # two sums to a normalisation, 65535 in the table
+    assert shares(B * S, [(d, d)]) == [2]
+    ln = dict(kind="layernorm", d=d, eps=1e-5)
+    layers = [ln] * (n - 1) + [linear(d, d), ln]
+    g = torch.Generator().manual_seed(3)
+    x, dy = (torch.randn(B, S, d, generator=g).bfloat16().cuda() for _ in range(2))
+    got = []
+    for group in ("1", "0"):
+        monkeypatch.setenv("ASTEROID_WGRAD_GROUP", group)
+        st = A.Stage(layers, B, 1, 1, (S, d), "bf16", "bsd", stream=torch.cuda.current_stream().cuda_stream)
+        p = np.tile(np.repeat(np.float32([1, 0]), d), n)
+        at = 2 * d * (n - 1)
+        w = torch.randn(d * d + d, generator=torch.Generator().manual_seed(4)).mul(0.1).numpy()
+        st.set_params(np.concatenate([p[:at], w, p[:2 * d]]))
+        y, dx = torch.empty_like(dy), torch.empty_like(x)
+        st.forward(0, x, None, y)
+        st.backward(0, dy, dx)
+        torch.cuda.synchronize()
+        got.append(st.get_grads()[at:at + d * d + d])
+        st.close()
+    # the same products in another order of fp32 additions: 384 of them
+    assert np.linalg.norm(got[1]) > 0 and harness.rel_l2(got[0], got[1]) < 1e-5
