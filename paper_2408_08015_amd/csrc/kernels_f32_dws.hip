@@ -172,6 +172,12 @@ __device__ __forceinline__ double swap_add16(double v) {
 __device__ __forceinline__ double lane_value(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
+// f(AT) + .. + f(AT + N - 1) as a tree: the rounding of a chain of 32 additions is 2 to 3 times that of the separate launches, whose
+// threads add up 16 values in pairs
+template <int N, int AT = 0, typename F> __device__ __forceinline__ float tree_sum(F f) {
+  if constexpr (N == 1) return f(AT);
+  else return tree_sum<N / 2, AT>(f) + tree_sum<N - N / 2, AT + N / 2>(f);
+}
 // Both sums over the block, in 64 bits and a fixed order, the same in every thread; red: 2 * T / 64 words of their own.  The
 // halves of a wavefront take a sum each, and so do they over the block's wavefronts: an eighth of the 64-bit additions of two
 // sums one after the other in every lane.
@@ -296,15 +302,11 @@ __global__ __launch_bounds__(T) void dws_fwd_kernel(FwdArgs a, Geom g) {
   have(gamma1); have(beta1); have(gamma2); have(beta2);
   const float rm1 = a.b1.running[c], rv1 = a.b1.running[g.C + c], rm2 = a.b2.running[c], rv2 = a.b2.running[g.C + c];
   for (int i = threadIdx.x; i < g.p.words4; i += T) reinterpret_cast<float4*>(sh)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-  for (int k = 0; k < V; ++k) {
+  for (int k = 0; k < V; ++k)
     if (!holds<Q, T>(k, E)) v[k] = 0.f;
-    s1 += v[k];
-    s2 += v[k] * v[k];
-  }
-  double d1, d2;
-  block_sums<T>(s1, s2, red, d1, d2);  // (its barrier is behind the zeros)
+  double d1, d2;  // (the barrier in it is behind the zeros)
+  block_sums<T>(tree_sum<V>([&](int k) { return v[k]; }), tree_sum<V>([&](int k) { return v[k] * v[k]; }), red, d1, d2);
   const Coef k1 = coefficients(d1, d2, g.inv, gamma1, beta1, a.b1.eps);
 #pragma unroll
   for (int k = 0; k < V; ++k) v[k] = act_value<SW>(v[k] * k1.scale + k1.shift, hi1);
@@ -323,18 +325,14 @@ __global__ __launch_bounds__(T) void dws_fwd_kernel(FwdArgs a, Geom g) {
   };
   constexpr int RM = V / Q;
   const Strip st = strip_of<Q>(g);
-  float o[RM][Q];
-  s1 = s2 = 0.f;
+  float o[RM][Q] = {};
   each_window<K, S, Q, V>(sh, g, st, [&](int r, bool live, auto win) {
     conv(win, o[r]);
 #pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      const float w = live ? o[r][j] : 0.f;
-      s1 += w;
-      s2 += w * w;
-    }
+    for (int j = 0; j < Q; ++j) o[r][j] = live ? o[r][j] : 0.f;
   });
-  block_sums<T>(s1, s2, red + 2 * (T / 64), d1, d2);
+  block_sums<T>(tree_sum<V>([&](int k) { return o[k / Q][k % Q]; }),
+                tree_sum<V>([&](int k) { return o[k / Q][k % Q] * o[k / Q][k % Q]; }), red + 2 * (T / 64), d1, d2);
   const Coef k2 = coefficients(d1, d2, g.inv_o, gamma2, beta2, a.b2.eps);
   const size_t at = ((size_t)st.n * g.C + c) * HWo + __mul24(st.r0, g.Wo) + st.col;
 #pragma unroll
@@ -460,25 +458,24 @@ __global__ __launch_bounds__(T) void dws_bwd_kernel(BwdArgs a, Geom g) {
     for (int t = 0; t < KK; ++t) wk[t] = a.w[(size_t)c * KK + t];
     have(mean1); have(istd1); have(sc1); have(sf1); have(mean2); have(istd2); have(sc2); have(sf2); have(gamma1); have(gamma2);
     for (int i = threadIdx.x; i < g.p.words4; i += T) reinterpret_cast<float4*>(sh)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int k = 0; k < V; ++k) {
       float val, slope;
       act_both<SW>(xh[k] * sc2 + sf2, hi2, val, slope);
       gm[k] = holds<Q, T>(k, Eo) ? gm[k] * slope : 0.f;
       xh[k] = holds<Q, T>(k, Eo) ? (xh[k] - mean2) * istd2 : 0.f;
-      s1 += gm[k];
-      s2 += gm[k] * xh[k];
     }
     double d1, d2;
-    block_sums<T>(s1, s2, red, d1, d2);
+    block_sums<T>(tree_sum<V>([&](int k) { return gm[k]; }), tree_sum<V>([&](int k) { return gm[k] * xh[k]; }), red, d1, d2);
     if (threadIdx.x == 0) {
       a.Gb2[c] = gb2 + (float)d1;
       a.Gg2[c] = gg2 + (float)d2;
     }
+    // (m1 by itself off a rounded product loses the same part of m1 in every value: the next BatchNorm's sums, in which the
+    // values cancel, came out 3 to 5 times as far off as with the term of xh added to it first)
     const float k2 = gamma2 * istd2, m1 = (float)(d1 * g.inv_o), m2 = (float)(d2 * g.inv_o);
 #pragma unroll
-    for (int k = 0; k < V; ++k) gm[k] = k2 * (gm[k] - m1 - xh[k] * m2);
+    for (int k = 0; k < V; ++k) gm[k] = k2 * (gm[k] - fmaf(xh[k], m2, m1));
     store_padded<Q, T, V>(sh, g.p, Eo, gm);
   }
   if (LATE) load_x();
@@ -486,10 +483,17 @@ __global__ __launch_bounds__(T) void dws_bwd_kernel(BwdArgs a, Geom g) {
 
   // input gradient of the convolution in front of the first activation, the weight gradient's sums, and those of the first
   // BatchNorm
-  float d[RM][XN], acc[KK];
+  // The sums: a tree over all values where they are all held at once; for 5x5, which has no registers for that, trees over the
+  // rows of a batch, added up (planes of 28x28, forward and backward: 3x3 4 % less time by the first, 5x5 9 % by the second)
+  constexpr bool AT_END = K == 3;
+  constexpr int R = kGradRows<K, S, Q, V>;
+  float d[RM][XN], acc[KK], s1 = 0.f, s2 = 0.f, t1 = 0.f, t2 = 0.f;
+  if (AT_END) {
+#pragma unroll
+    for (int k = 0; k < RM * XN; ++k) d[k / XN][k % XN] = 0.f;
+  }
 #pragma unroll
   for (int t = 0; t < KK; ++t) acc[t] = 0.f;
-  float s1 = 0.f, s2 = 0.f;
   // the pixel of strip entry j that tap (u, v) joins
   auto pixel = [](int u, int v, int j) { return S == 1 ? j : dws_parity(K, u) * 2 * Q + 2 * j + dws_parity(K, v); };
   // (stride 2, odd planes: the quads of the last row and column reach past them)
@@ -513,10 +517,16 @@ __global__ __launch_bounds__(T) void dws_bwd_kernel(BwdArgs a, Geom g) {
           acc[u * K + q] += xt[pixel(u, q, j)] * w;
         }
 #pragma unroll
-    for (int k = 0; k < XN; ++k) {
-      d[r][k] = o[k] * sl[k];
-      s1 += d[r][k];
-      s2 += d[r][k] * ((xs[r][k] - mean1) * istd1);
+    for (int k = 0; k < XN; ++k) d[r][k] = o[k] * sl[k];
+    if (!AT_END) {
+      const float a1 = tree_sum<XN>([&](int k) { return d[r][k]; });
+      const float a2 = tree_sum<XN>([&](int k) { return d[r][k] * ((xs[r][k] - mean1) * istd1); });
+      t1 = r % R ? t1 + a1 : a1;
+      t2 = r % R ? t2 + a2 : a2;
+      if (r % R == R - 1) {
+        s1 += t1;
+        s2 += t2;
+      }
     }
   });
 #pragma unroll
@@ -524,6 +534,10 @@ __global__ __launch_bounds__(T) void dws_bwd_kernel(BwdArgs a, Geom g) {
   if ((threadIdx.x & 15) == 0) {
 #pragma unroll
     for (int t = 0; t < KK; ++t) wsum[(threadIdx.x >> 4) * KK + t] = acc[t];
+  }
+  if (AT_END) {
+    s1 = tree_sum<RM * XN>([&](int k) { return d[k / XN][k % XN]; });
+    s2 = tree_sum<RM * XN>([&](int k) { return d[k / XN][k % XN] * ((xs[k / XN][k % XN] - mean1) * istd1); });
   }
   double d1, d2;
   block_sums<T>(s1, s2, red + 2 * (T / 64), d1, d2);
@@ -534,7 +548,7 @@ __global__ __launch_bounds__(T) void dws_bwd_kernel(BwdArgs a, Geom g) {
     for (int r = 0; r < RM; ++r) {
       if (r < st.rows) {
 #pragma unroll
-        for (int k = 0; k < XN; ++k) d[r][k] = k1 * (d[r][k] - m1 - ((xs[r][k] - mean1) * istd1) * m2);
+        for (int k = 0; k < XN; ++k) d[r][k] = k1 * (d[r][k] - fmaf((xs[r][k] - mean1) * istd1, m2, m1));
 #pragma unroll
         for (int b = 0; b < S * S; ++b) {
           float* const p = dp + (r * S + b / S) * g.W + b % S * Q;
