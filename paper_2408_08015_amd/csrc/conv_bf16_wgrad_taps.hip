@@ -21,6 +21,7 @@
 #include "prof.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ast {
 
@@ -59,7 +60,7 @@ __device__ __forceinline__ bf16x8 taps_read(const unsigned char* smem, int off) 
 
 __global__ __launch_bounds__(64 * kTapsWaves, 2) void conv_wgrad_taps_kernel(TapsArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int bid = (int)xcd_grouped(blockIdx.x, gridDim.x);
   const int tile_ci = bid % g.tiles_ci; bid /= g.tiles_ci;
   const int tile_co = bid % g.tiles_co, split = bid / g.tiles_co;
@@ -70,20 +71,19 @@ __global__ __launch_bounds__(64 * kTapsWaves, 2) void conv_wgrad_taps_kernel(Tap
   // two buffers of [xrows][64 bytes], whose first row is virtual pixel q - halo, and [kTapsChunk][64 bytes] of dy
   const int xrows = g.xrows, buffer = (xrows + kTapsChunk) * 64;
 
+  // the pixel of the tensors that virtual pixel q is, or -1
+  auto pixel = [&](int q) __attribute__((always_inline)) -> int {
+    const int row = (int)__umulhi((unsigned)q, g.m_w), col = q - row * V;
+    const int img = (int)__umulhi((unsigned)row, g.m_h), r = row - img * (g.H + 1);
+    return q >= 0 && q < g.Q && col < g.W && r < g.H ? (img * g.H + r) * g.W + col : -1;
+  };
   // byte offset of virtual pixel q's chunk c in a tensor of C channels whose tile begins at channel t0; beyond the extent where
   // there is no such pixel or channel
   auto source = [&](int q, int c, int C, int t0) __attribute__((always_inline)) -> unsigned {
-    const int row = (int)__umulhi((unsigned)q, g.m_w), col = q - row * V;
-    const int img = (int)__umulhi((unsigned)row, g.m_h), r = row - img * (g.H + 1);
-    const bool ok = q >= 0 && q < g.Q && col < g.W && r < g.H && t0 + c * 8 < C;
-    return ok ? (unsigned)((((img * g.H + r) * g.W + col) * C + t0 + c * 8) * 2) : TAPS_OOB;
+    const int p = pixel(q);
+    return p >= 0 && t0 + c * 8 < C ? (unsigned)((p * C + t0 + c * 8) * 2) : TAPS_OOB;
   };
 
-  floatx16 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
   float bsum = 0.f;
   const bool do_bias = g.bias_part != nullptr && tile_ci == 0;
 
@@ -105,46 +105,81 @@ __global__ __launch_bounds__(64 * kTapsWaves, 2) void conv_wgrad_taps_kernel(Tap
       }
     }
   };
-  issue(q_begin, 0);
-  __syncthreads();  // (waits for the copies too)
-  int at = 0;
-  for (int q0 = q_begin; q0 < q_end; q0 += kTapsChunk, at = buffer - at) {
-    if (q0 + kTapsChunk < q_end) issue(q0 + kTapsChunk, buffer - at);
-    const unsigned char* const sx = smem + at;
-    const unsigned char* const sdy = sx + xrows * 64;
-#pragma unroll 1
-    for (int s = wave; s < kTapsChunk / 16; s += kTapsWaves) {
-      const bf16x8 a = taps_read(sdy, s * 16 * 64 + lane_off);
-      if (do_bias) {
-        const taps_u32x4 w = __builtin_bit_cast(taps_u32x4, a);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bsum += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
-      }
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const bf16x8 b = taps_read(sx, (s * 16 + (t / 3) * V + t % 3) * 64 + lane_off);
-        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[t], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-
-  // ---- the wavefronts' tiles, tap by tap, through LDS: [wavefront][32 co][32 ci], two areas in turn
-  float* const sums = reinterpret_cast<float*>(smem);
+  // The products of the range and the partials.  A zero of the virtual order times an infinity or a NaN of the other operand is a
+  // NaN in a weight that this pair of pixels has no part in: with `pairs`, both operands are zero where either pixel is none.
+  // Returns whether a partial is no finite number.
   const int row = tid >> 3, col = (tid & 7) * 4;
+  float* const sums = reinterpret_cast<float*>(smem);
+  auto form = [&](auto pairs_c) __attribute__((always_inline)) -> bool {
+    constexpr bool pairs = decltype(pairs_c)::value;
+    floatx16 acc[9];
 #pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    float* const area = sums + (t & 1) * (kTapsWaves * 1024);
+    for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int r = 0; r < 16; ++r)  // register r of lane l is D[8*(r/4) + 4*(l/32) + r%4][l%32]
-      area[wave * 1024 + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)] = acc[t][r];
-    __syncthreads();
-    floatx4 s = {0.f, 0.f, 0.f, 0.f};
+      for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    issue(q_begin, 0);
+    __syncthreads();  // (waits for the copies too)
+    int at = 0;
+    for (int q0 = q_begin; q0 < q_end; q0 += kTapsChunk, at = buffer - at) {
+      if (q0 + kTapsChunk < q_end) issue(q0 + kTapsChunk, buffer - at);
+      const unsigned char* const sx = smem + at;
+      const unsigned char* const sdy = sx + xrows * 64;
+#pragma unroll 1
+      for (int s = wave; s < kTapsChunk / 16; s += kTapsWaves) {
+        const bf16x8 a = taps_read(sdy, s * 16 * 64 + lane_off);
+        const int q = q0 + s * 16 + 8 * (lane >> 5);  // (of the lane's first k)
+        unsigned have = 0;                            // ... and which of its eight are pixels of dy
+        if constexpr (pairs) {
 #pragma unroll
-    for (int w = 0; w < kTapsWaves; ++w) s += *reinterpret_cast<const floatx4*>(area + w * 1024 + row * 32 + col);
-    if (co0 + row < g.Cout && ci0 + col < g.Cin)
-      *reinterpret_cast<floatx4*>(g.part + ((size_t)(split * 9 + t) * g.Cout + co0 + row) * g.Cin + ci0 + col) = s;
-  }
+          for (int e = 0; e < 8; ++e) have |= (unsigned)(pixel(q + e) >= 0 && q + e < q_end) << e;
+        }
+        if (do_bias && !pairs) {
+          const taps_u32x4 w = __builtin_bit_cast(taps_u32x4, a);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bsum += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
+        }
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          bf16x8 b = taps_read(sx, (s * 16 + (t / 3) * V + t % 3) * 64 + lane_off);
+          if constexpr (pairs) {
+            bf16x8 ap = a;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const bool both = (have >> e & 1) && pixel(q + e + (t / 3 - 1) * V + t % 3 - 1) >= 0;
+              ap[e] = both ? ap[e] : (__bf16)0.f;
+              b[e] = both ? b[e] : (__bf16)0.f;
+            }
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap, b, acc[t], 0, 0, 0);
+          } else {
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[t], 0, 0, 0);
+          }
+        }
+      }
+      __syncthreads();
+    }
+
+    // ---- the wavefronts' tiles, tap by tap, through LDS: [wavefront][32 co][32 ci], two areas in turn
+    float none = 0.f;  // 0 as long as all partials are finite
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      float* const area = sums + (t & 1) * (kTapsWaves * 1024);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)  // register r of lane l is D[8*(r/4) + 4*(l/32) + r%4][l%32]
+        area[wave * 1024 + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)] = acc[t][r];
+      __syncthreads();
+      floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kTapsWaves; ++w) s += *reinterpret_cast<const floatx4*>(area + w * 1024 + row * 32 + col);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) none = fmaf(s[e], 0.f, none);
+      if (co0 + row < g.Cout && ci0 + col < g.Cin)
+        *reinterpret_cast<floatx4*>(g.part + ((size_t)(split * 9 + t) * g.Cout + co0 + row) * g.Cin + ci0 + col) = s;
+    }
+    return none != 0.f;
+  };
+  unsigned* const again = reinterpret_cast<unsigned*>(smem) + 2 * kTapsWaves * 1024;  // behind both areas, in what held the operands
+  if (__any(form(std::false_type{}))) again[wave] = 1;
+  else again[wave] = 0;
   if (do_bias) {  // (uniform) lane l holds channel l % 32 over its half of the pixels
     __syncthreads();
     sums[tid] = bsum;
@@ -155,6 +190,13 @@ __global__ __launch_bounds__(64 * kTapsWaves, 2) void conv_wgrad_taps_kernel(Tap
       for (int w = 0; w < 2 * kTapsWaves; ++w) s += sums[w * 32 + tid];
       g.bias_part[(size_t)split * g.Cout + co0 + tid] = s;
     }
+  }
+  if (!do_bias) __syncthreads();
+  const taps_u32x4 w = *reinterpret_cast<const taps_u32x4*>(again);
+  static_assert(kTapsWaves == 4, "one word each");
+  if (w[0] | w[1] | w[2] | w[3]) {  // (uniform)
+    __syncthreads();
+    (void)form(std::true_type{});
   }
 }
 

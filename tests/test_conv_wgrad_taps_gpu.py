@@ -80,3 +80,43 @@ def test_whole_numbers(A, monkeypatch, sizes):
     want = np.concatenate([want.permute(1, 2, 0).reshape(-1).numpy(), dy.sum((0, 1, 2)).float().numpy()])
     for have in got:
         assert np.array_equal(have, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("of", ["x", "dy"])
+@pytest.mark.parametrize("sizes", [(24, 40, 9, 7, 3), (64, 64, 1, 50, 33), (64, 64, 50, 1, 33), (40, 64, 15, 31, 8), (32, 32, 2, 300, 3)])
+def test_values_that_are_not_finite(A, sizes, of):
+    """An infinity or a NaN reaches the weights whose products it is part of, and no others: pixels in the corners and at the
+    edges of images, and at the ends of what a block works on."""
+    import torch
+    cin, cout, h, w, B = sizes
+    assert partials(B, h, w, cin, cout)
+    g = torch.Generator().manual_seed(5)
+    x, dy = (torch.randint(1, 3, (B, h, w, c), generator=g).float() for c in (cin, cout))
+    t, n = (x, cin) if of == "x" else (dy, cout)
+    t = t.view(B * h * w, n)
+    at = [0, w - 1, (h - 1) * w, h * w - 1, B * h * w - 1]
+    for q in range(255, B * (h + 1) * (w + 1), 256):   # on either side of every 256th pixel of the order that the kernel walks
+        row, col = divmod(q, w + 1)
+        img, r = divmod(row, h + 1)
+        at.append((img * h + min(r, h - 1)) * w + min(col, w - 1))
+    for i, p in enumerate(at):   # (each in a channel of its own, as far as there are)
+        t[min(p + i % 2, B * h * w - 1), (3 * i) % n] = float("nan") if i % 4 == 2 else float("inf")
+    dev = torch.device("cuda:0")
+    st = A.Stage([conv(cin, cout, 3, 1, 1)], B, 1, 1, (cin, h, w), "bf16", "nhwc")
+    st.set_params(np.zeros(st.num_params, np.float32))
+    xd, gd = x.to(dev, torch.bfloat16), dy.to(dev, torch.bfloat16)
+    y, dx = torch.empty_like(gd), torch.empty_like(xd)
+    torch.cuda.synchronize()
+    st.forward(0, xd, None, y)
+    st.backward(0, gd, dx)
+    have = st.get_grads().reshape(cout, cin, 3, 3)
+    st.close()
+    want = np.zeros((cout, cin, 3, 3), np.float32)
+    for u in range(3):
+        for v in range(3):   # the pairs of pixels that there are
+            a = x[:, max(u - 1, 0):h + min(u - 1, 0), max(v - 1, 0):w + min(v - 1, 0)].reshape(-1, cin)
+            b = dy[:, max(1 - u, 0):h + min(1 - u, 0), max(1 - v, 0):w + min(1 - v, 0)].reshape(-1, cout)
+            want[:, :, u, v] = (b.t() @ a).numpy()
+    assert 0 < np.isfinite(want).sum() < want.size
+    assert np.array_equal(have, want, equal_nan=True)
