@@ -423,8 +423,9 @@ ast_status asteroid_stage_debug_activation(asteroid_stage* h, int32_t mb, int32_
   const char* const slot = s.slots[s.mb_slot[mb]];
   const char* src = slot + A.slot_off;
   for (const ast::Op& op : s.ops) {
-    if (op.out != id || op.act_behind < 0 || !s.ops[op.act_behind].in_unwritten) continue;
-    // (a sum in front of an activation, which the forward pass does not keep: once more, as the kernels form it)
+    if (!A.unwritten || op.out != id) continue;
+    // (a sum in front of an activation, or a BatchNorm in front of a depthwise convolution, which the forward pass does not keep:
+    // once more, as the kernels form it)
     std::vector<float> x(A.elems), k(op.skip >= 0 ? A.elems : 0), ss(2 * (size_t)A.c);
     HIPCHK(hipMemcpy(x.data(), slot + s.acts[op.in].slot_off, A.bytes, hipMemcpyDeviceToHost), "debug_activation");
     if (op.skip >= 0) HIPCHK(hipMemcpy(k.data(), slot + s.acts[op.skip].slot_off, A.bytes, hipMemcpyDeviceToHost), "debug_activation");
@@ -438,6 +439,7 @@ ast_status asteroid_stage_debug_activation(asteroid_stage* h, int32_t mb, int32_
         v = std::fmaf(v, ss[c], ss[A.c + c]);
         if (op.act == 1 || op.act == 2) v = std::fmax(v, 0.f);
         if (op.act == 2) v = std::fmin(v, 6.f);
+        if (op.act == 4) v = v / (1.f + std::exp(-v));
       }
       host_out[i] = op.skip >= 0 ? v + k[i] : v;
     }

@@ -428,7 +428,7 @@ ast_status build_plan(Stage& s, std::string& err) {
       b1.dws = dw.dws = b2.dws = true;
       virtual_act[b1.out] = 1;
       for (int& la : s.layer_act)
-        if (la == b1.out) la = -1;
+        if (la == b1.out && b1.act <= 2) la = -1;  // (as where the convolution normalises on load)
     }
     for (size_t j = 0; fuse && j < s.ops.size(); ++j) {
       Op& dw = s.ops[j];
@@ -523,8 +523,10 @@ ast_status build_plan(Stage& s, std::string& err) {
     for (const Op& o : s.ops) read |= &o != &a && (o.in == a.in || o.skip == a.in || o.res_in == a.in);
     for (const Act& t : s.acts) read |= t.data_alias == a.in;
     a.in_unwritten = !read;
+    s.acts[a.in].unwritten |= !read;
   }
   for (size_t a = 0; a < s.acts.size(); ++a) {
+    s.acts[a].unwritten |= virtual_act[a] != 0;
     if ((int)a == final_act && !s.loss_tail && a != 0 && !s.final_in_slot) continue;
     if (virtual_act[a] || s.acts[a].data_alias >= 0) continue;
     s.acts[a].slot_off = off;

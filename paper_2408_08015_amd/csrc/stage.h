@@ -49,6 +49,7 @@ struct Act {
   int grad_alias = -1;             // gradient buffer shared with this activation's
   int data_alias = -1;             // same tensor as this activation (own gradient buffer): the input of a shortcut branch
   int layer = -1;                  // layer index whose output this is (-1: stage input)
+  bool unwritten = false;          // no kernel writes it: the kernels that need it form it from what they read
 };
 
 struct Op {

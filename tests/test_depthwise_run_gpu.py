@@ -94,3 +94,20 @@ def test_run(A, monkeypatch, sizes, grad, fuse):
         assert sc["r0.dx"] <= 1e-5
     for name, err in sc["r0.G_all"]:
         assert err <= 1e-4, (name, err)
+
+
+# the activation in front of the convolution is formed inside the launch; asked for, it is formed again (with ReLU and ReLU6 it
+# cannot be asked for, as where the run is taken apart)
+@pytest.mark.gpu
+@pytest.mark.parametrize("sizes", [f[0] for f in FORMS if f[0][:2] != (3, 2) and f[1]][::4])
+def test_activation_in_front(A, sizes):
+    k, s, c, h, w, B = sizes
+    for act in ("swish", "relu6") if k == 3 else ("swish",):
+        layers = [bn(c), simple(act), conv(c, c, k, s, k // 2, groups=c), bn(c), simple(act)]
+        cfg = one(layers, (c, h, w), B=B, M=1)
+        inp = gen.make_inputs(cfg, randomize_affine=True)
+        _, st = harness.run_oracle(cfg, inp, rounds=1, keep_acts=True)
+        _, dbg, _ = harness.run_hip(cfg, inp, rounds=1, debug_layers=[0, 1])
+        assert list(dbg) == ([1] if act == "swish" else [])
+        if dbg:   # (a BatchNorm in fp32 from statistics in 64 bits)
+            assert harness.rel_l2(dbg[1], st.acts[0][1]) <= 5e-7
