@@ -56,7 +56,7 @@ def _one_launch(L, B, shape, act1, act2):
         return False
     import paper_2408_08015_amd as A
     words = (ctypes.c_int * 3)()
-    return bool(ctypes.CDLL(A.lib_path()).ast_dws_choice(0, L["k"], B, shape[0], shape[1], shape[2], L["stride"], code[act1], words))
+    return ctypes.CDLL(A.lib_path()).ast_dws_choice(0, L["k"], B, shape[0], shape[1], shape[2], L["stride"], code[act1], words) == 2
 
 
 def kernel_model(cfg):

@@ -181,6 +181,7 @@ struct DwsBn {
   int act;
 };
 bool dws_supported(int K, int N, int C, int H, int W, int stride, int act1, int act2);
+bool dws_faster(int K, int N, int C, int H, int W, int stride, int act);  // than the launches that it replaces
 hipError_t dws_allow(int K, int N, int C, int H, int W, int stride, int act);
 void dws_fwd_f32(hipStream_t st, const float* x, const float* w, float* y, float* z, const DwsBn& b1, const DwsBn& b2, int K,
                  int N, int C, int H, int W, int stride);

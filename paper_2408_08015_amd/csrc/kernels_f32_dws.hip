@@ -16,7 +16,7 @@
 //   192 of 32 x 28x28           17.7 / 23     30 / 50        58 and 77 MB
 //   144 of 8 x 56x56            16.0 / 21.4   26 / 36
 //   240 of 32 x 30x30, 5x5      30 / 54       52 / 76
-// A whole inverted-residual block, forward and backward, takes 0.57 to 0.85 of its time before, at every size tried.
+// (dws_faster: where the one launch is not taken.)
 #include <algorithm>
 #include <climits>
 
@@ -650,6 +650,23 @@ bool dws_supported(int K, int N, int C, int H, int W, int S, int act1, int act2)
   return pick(false, K, N, C, H, W, S).T && pick(true, K, N, C, H, W, S).T;
 }
 
+// Blocks of up to 16 values a thread are always the faster form (936 sizes: 1.05 times and more).  Those of 32, one to a compute
+// unit, take a round of t = 14 us + their rows' time, filled or not, and spill registers in the 5x5 backward; the separate
+// launches cost 27 us more at their start (20 where they read words of 16 bytes and these blocks single ones) and more for every
+// value.  us of both directions, one launch / separate: 5x5, 31x31 x 27: 8 channels 72 / 44, 240 channels 109 / 149, 272
+// 175 / 160; 3x3 with ReLU6 there: 8 channels 46 / 37, 96 57 / 67.  Fitted to 2048 sizes of such blocks, of which 206 are faster
+// apart, down to 0.6; by this rule a call takes 0.14 % more than by the faster form of each.
+bool dws_faster(int K, int N, int C, int H, int W, int S, int act) {
+  const Pick p = pick(false, K, N, C, H, W, S);
+  if (p.V < 32 || (S == 2 && p.Q > 1)) return true;
+  const int kind = K == 5 ? 2 : act == ACT_SWISH ? 1 : 0;  // of ReLU, swish, 5x5:
+  constexpr double row1[] = {0.9, 0.9, 1.6}, row[] = {0.4, 0.62, 0.95}, row2[] = {1.0, 1.0, 1.9};  // us per value in a strip's column
+  constexpr double gain[] = {24, 28, 32}, gain2[] = {10, 12, 22};  // us per 256 channels of 10000 values
+  const double t = 14 + p.g.it.rows * p.Q * (S == 2 ? row2 : p.Q == 1 ? row1 : row)[kind];
+  const double apart = p.Q == 1 && H * W % 4 == 0 ? 20 : 27;
+  return apart + (S == 2 ? gain2 : gain)[kind] * ((double)N * H * W / 1e4) * C / 256 >= cdiv(C, 256) * t;
+}
+
 hipError_t dws_allow(int K, int N, int C, int H, int W, int S, int act) {
   hipError_t e = hipSuccess;
   for (const bool bwd : {false, true}) {
@@ -690,11 +707,11 @@ void dws_bwd_f32(hipStream_t st, const float* gz, const float* y, const float* x
 }  // namespace ast
 
 // The choice above, for tests that name one: strip, threads and values per thread of the forward (bwd: backward) block.
-// 0: the run has no such launch.
+// 0: the run has no such launch; 1: it has one that the separate launches are faster than; 2: it runs so.
 extern "C" int ast_dws_choice(int bwd, int K, int N, int C, int H, int W, int S, int act, int out[3]) {
   using namespace ast;
   if (!dws_supported(K, N, C, H, W, S, act, act)) return 0;
   const Pick p = pick(bwd != 0, K, N, C, H, W, S);
   out[0] = p.Q; out[1] = p.T; out[2] = p.V;
-  return 1;
+  return dws_faster(K, N, C, H, W, S, act) ? 2 : 1;
 }

@@ -406,7 +406,7 @@ ast_status build_plan(Stage& s, std::string& err) {
   }
 
   // fp32 inverted-residual pattern BN(+act) -> depthwise 3x3 -> BN: BatchNorm passes move into the
-  // convolution.  ASTEROID_BN_FUSE is a bit mask of the moves to make (default: all):
+  // convolution.  ASTEROID_BN_FUSE is a bit mask of the moves to make (default: all, 16 where it is the faster form):
   //   1  forward: the first BatchNorm's apply pass (normalise on load, also in the conv's backward)
   //      and the second one's statistics pass (conv epilogue)
   //   2  backward: the first BatchNorm's partial sums (conv backward epilogue); needs 1
@@ -425,6 +425,7 @@ ast_status build_plan(Stage& s, std::string& err) {
         continue;
       const Act& I = s.acts[dw.in];
       if (!dws_supported(dw.k, I.n, I.c, I.h, I.w, dw.stride, b1.act, b2.act)) continue;
+      if (!e && !dws_faster(dw.k, I.n, I.c, I.h, I.w, dw.stride, b1.act)) continue;
       b1.dws = dw.dws = b2.dws = true;
       virtual_act[b1.out] = 1;
       for (int& la : s.layer_act)

@@ -61,7 +61,30 @@ def test_forms_that_stay_apart():
     assert choice(0, 3, 4, 8, 14, 14, 1, 0) is None and choice(0, 5, 4, 8, 14, 14, 1, RELU6) is None
 
 
-# fuse: the bit mask of ASTEROID_BN_FUSE; without 16 the run is taken apart
+# Blocks of 32 values a thread: one launch where their channels fill rounds of 256 well enough, on either side of that line
+@pytest.mark.parametrize("sizes,taken", [
+    ((5, 1, 8, 31, 31, 27), False), ((5, 1, 64, 31, 31, 27), False), ((5, 1, 240, 31, 31, 27), True), ((5, 1, 272, 31, 31, 27), False),
+    ((5, 1, 8, 28, 28, 32), False), ((5, 1, 96, 28, 28, 32), True), ((3, 1, 8, 31, 31, 27), False), ((3, 1, 96, 31, 31, 27), True),
+    ((3, 1, 8, 28, 28, 32), True), ((5, 2, 8, 30, 30, 32), False), ((5, 2, 240, 30, 30, 32), True), ((5, 2, 8, 56, 56, 9), True),
+    ((5, 1, 8, 14, 14, 64), True), ((3, 1, 8, 7, 7, 64), True),          # 16 values and fewer: always
+])
+def test_one_launch_where_it_is_faster(monkeypatch, sizes, taken):
+    k, s, c, h, w, B = sizes
+    act = "swish" if k == 5 else "relu6"
+    layers = [bn(c), simple(act), conv(c, c, k, s, k // 2, groups=c), bn(c), simple(act)]
+
+    def workspace():   # (a run in one launch has no partials in it)
+        return lib.plan_memory(layers, B, 1, 1, (c, h, w), "f32", "nchw", True)[3]
+
+    monkeypatch.delenv("ASTEROID_BN_FUSE", raising=False)
+    got = workspace()
+    monkeypatch.setenv("ASTEROID_BN_FUSE", "31" if taken else "15")
+    assert got == workspace()
+    monkeypatch.setenv("ASTEROID_BN_FUSE", "15" if taken else "31")
+    assert got != workspace()
+
+
+# fuse: the bit mask of ASTEROID_BN_FUSE; without 16 the run is taken apart, with it it is one launch wherever a channel fits
 @pytest.mark.gpu
 @pytest.mark.parametrize("fuse", [31, 15])
 @pytest.mark.parametrize("grad", [True, False])
