@@ -816,14 +816,19 @@ bool search_x3(const LdsArgs& sizes, int ncls, X3Shape& best) {
   int wk = 1;
   while (wk < 8 && wk * tiles < (all && a.KG >= 16 * wk ? 2000 : 1200) && wk * 2 <= std::max(1, a.KG / 2)) wk *= 2;
   const int wm = std::min(mt, std::max(1, std::min(4, 8 / wk)));
-  // four row tiles: every wavefront reads weights of its own, so two groups of pixels share each read once that leaves the compute
-  // units their blocks (128 -> 128 at 32 x 28x28 57.7 us with one, 48.0 with two, 51.0 with four; 256 -> 256 at 32 x 14x14
-  // 58.7 / 50.1; half as many tiles: 128 -> 128 at 8 x 28x28 19.8 / 21.0)
-  // Four row tiles: every wavefront reads weights of its own, so two groups of pixels share each read as soon as that leaves most
-  // compute units a block (128 -> 128 at 32 x 28x28 57.7 us with one, 49 with two, 51 with four; 256 -> 256 at 32 x 14x14, two
-  // shares of the contraction, 58.7 / 50.2; at half as many pixels, 128 -> 128 at 16 x 28x28, two take 44 and one 32)
+  // Four row tiles: every wavefront reads weights of its own, so two groups of pixels share each read where that takes fewer rounds
+  // of blocks.  Four wavefronts with one group run three to a compute unit, eight wavefronts one; a round with two groups
+  // takes 1.1 times a round with one, beside two shares of the contraction 1.4 to 1.5 times.  us, one group / two: 128 -> 128 at
+  // 32 x 28x28 (two rounds, one) 57.7 / 49; 256 -> 256 at 32 x 14x14, two shares, 58.7 / 50.2; 64 -> 256 at 13 x 36x36 (two
+  // rounds each, the second of the 264 blocks of two groups nearly empty) 38.5 / 51.4; 128 -> 128 at 16 x 28x28 (one each) 32 / 44.
   const bool one = sizes.KS == 1 && ncls == 1;
-  const int nt = all && tiles >= 6000 ? 4 : (all && wm == 4 && wk * tiles >= 3000) || (tiles >= 3000 && one) ? 2 : 1;
+  auto rounds = [&](int NT) {  // of the whole chip (three times 256, full to a hundredth: the next size has a second round)
+    const int wn = wk == 1 ? NT : 1;
+    const long blocks = (long)cdiv(sizes.cls[0].npix, 32 * NT * wn) * cdiv(mt, 4);
+    return cdiv(blocks, wk * wn == 1 ? 760 : 256);
+  };
+  const bool two = all && wm == 4 && wk * tiles >= 3000 && rounds(1) > (wk == 1 ? 1.1 : 1.5) * rounds(2);
+  const int nt = all && tiles >= 6000 ? 4 : two || (tiles >= 3000 && one) ? 2 : 1;
   const int wn = wk == 1 && (wm < 4 || (all && nt == 2) || (!all && sizes.KS == 3)) ? 8 / wm : 1;
   best.cost = 1e30;
   for (int NT = 1; NT <= 4; NT *= 2)

@@ -152,3 +152,19 @@ def test_weight_gradient_ranges():
         assert not out[2] and -(-steps // out[1]) <= 32
         lib.ast_pw_wgrad_choice(n, cin, cout, hw, 5, out)
         assert out[2] and out[1] == 5 and out[0] != 0   # (not the block shape that has no registers left)
+
+
+# Four row tiles: two groups of 32 pixels to a wavefront where that takes fewer rounds of blocks than one (three blocks of one group
+# run on a compute unit, one of two), at sizes on either side of a whole round
+@pytest.mark.parametrize("sizes,groups", [
+    ((64, 128, 3, 1, 28, 28, 32), 2), ((64, 128, 3, 1, 28, 28, 31), 1),     # 784 blocks of one group; 760
+    ((64, 256, 3, 1, 36, 36, 12), 2), ((64, 256, 3, 1, 36, 36, 13), 1),     # 244 blocks of two groups; 264
+    ((128, 512, 3, 1, 14, 14, 41), 2), ((128, 512, 3, 1, 14, 14, 44), 1),   # 252; 272
+    ((96, 384, 3, 1, 28, 28, 15), 1), ((64, 384, 3, 1, 20, 20, 33), 1),     # 276; 312: a second round that is nearly empty
+    ((256, 384, 3, 1, 14, 14, 22), 2),                                      # two shares: 204 blocks of two groups for 405
+    ((256, 160, 3, 1, 20, 20, 24), 1),                                      # ... 300 for 600: two rounds for three
+    ((32, 128, 3, 1, 56, 56, 32), 4),
+])
+def test_pixel_groups_by_rounds(sizes, groups):
+    cin, cout, k, s, h, w, B = sizes
+    assert split_choice(FWD, B, cin, cout, h, w, k, s)[:2] == (groups, 4)
