@@ -8,13 +8,13 @@
 // tap (u, v) is the same LDS tile read u*W + v rows further down; a pixel whose neighbour lies outside the image reads a row
 // of zeros.  Rows are an odd number of 16-byte chunks apart, so the reads of 16 rows fall into different banks.  The weights
 // come from a copy in the order of the matrix instruction's operand ([32 channels][16 contracted][tap]: 1 KB per fragment),
-// straight from L2 into registers; the nine fragments of the next 16 contracted channels are requested as those of the present
-// ones are used up, 9 * PG matrix instructions
-// ahead.
+// straight from L2 into registers.  (The nine fragments of the next 16 contracted channels are written as requested one by one,
+// as those of the present ones are used up; in the code as built the requests stand behind the last products of a step,
+// and each pixel operand is waited for where it is read.)
 //
-// Bound by latency where blocks are few (6 x 45x45 pixels, 96 -> 96 channels: 7.4 us, the general product kernel 14), by LDS and
-// L2 operand traffic where there are many (32 x 56x56, 96 -> 96: 26 and 50 us; 160 -> 224: 73 and 132, 0.89 PFLOP/s).  Four groups of
-// pixels, or two tiles of channels, per wavefront leave fewer blocks and were slower nearly everywhere (28 and 37 us for 26).
+// Bound by those waits, for L2 and for LDS, with few blocks (6 x 45x45 pixels, 96 -> 96 channels: 7.4 us, the general product
+// kernel 14) and with many (32 x 56x56, 96 -> 96: 26 and 50 us, where products, LDS and L2 take about 7 each; 160 -> 224: 73
+// and 132, 0.89 PFLOP/s).  Four groups of pixels, or two tiles of channels, per wavefront leave fewer blocks and were slower nearly everywhere (28 and 37 us for 26).
 #include "device_utils.h"
 #include "kernels_bf16.h"
 #include "prof.h"
@@ -178,7 +178,7 @@ struct ResPick {
   size_t lds = 0;
   ResArgs g{};
 };
-// us of the launch: a group's step costs a lone wavefront 41 ns, and w of them on a SIMD 28 ns each where a weight fragment
+// us of the launch, with those waits in it: a group's step costs a lone wavefront 41 ns, and w of them on a SIMD 28 ns each where a weight fragment
 // serves one group of pixels (it comes from L2), 18 where it serves two.  Fitted to 416 sizes (16 to 256 channels, 400 to
 // 144000 pixels): the choice by it costs 0.2 % over the faster one of both, 18 % at most.
 double res_cost(const ResPick& p) {

@@ -13,7 +13,10 @@
 // Block = 8 wavefronts (4 x 2) = 256 output channels x 64*TN input channels of ONE tap over a
 // range of pixels (split-K: taps x splits blocks fill the chip); K-tile = 48 pixels, three LDS
 // stages, loads issued two to three K-tiles ahead and waited for with explicit vmcnt counts; one
-// s_barrier per K-tile, placed before the last third of its MFMAs.  The x operand of a tap is the
+// s_barrier per K-tile, placed before the last third of its MFMAs.  (The compiler takes a transposed
+// read for one that may see any copy in flight and waits for all of them in front of the first one
+// behind a K-tile's issue: in the code as built a K-tile's copies are hidden by nothing but the
+// other wavefront of the SIMD, and the three stages gain little.)  The x operand of a tap is the
 // tile shifted by the tap's offset; rows whose shifted pixel lies outside the image are requested
 // beyond the buffer's extent, which the hardware turns into zeros.  Every block writes its fp32
 // partial [co][ci]; a reduction kernel adds the splits into G in a fixed order.
@@ -262,7 +265,7 @@ __device__ __forceinline__ void conv_wgrad_tr_body(const WgArgs& g, int bid) {  
     wg_fence();
     __builtin_amdgcn_s_barrier();
     wg_fence();
-    issue(st);  // three K-tiles ahead, into the stage this K-tile has released
+    issue(st);  // three K-tiles ahead, into the stage this K-tile has released (waited for by the read below: see the top)
     read_frags(P0 ^ 1, st_next, 0);
     __builtin_amdgcn_sched_barrier(0);
     mma(P0);
@@ -445,7 +448,8 @@ int wgrad_group_task(void* task_out, const bf16_t* dy, const bf16_t* x, float* G
 }
 
 // 288 whole tiles of 4096 rows on 256 compute units, one block on each at a time, take two rounds of 180 us, the second of
-// which only 32 blocks fill.  So some products are formed in shares of their rows.  A K-tile takes 1.78 us; a block's ends, where
+// which only 32 blocks fill.  So some products are formed in shares of their rows.  A K-tile takes 1.78 us (its products 0.64 at 2.4 GHz, its
+// transposed reads 1.0 in a loop of nothing else, the rest waits for its copies); a block's ends, where
 // all blocks of a round read and write their part of the gradient at once, 30 us, and 18 where they only write a partial;
 // the reduction reads the partials and adds them up (0.065 us each, 0.1 per tile).  (Measured: 144 to 216 whole tiles of 864,
 // 4096 and 10240 rows 65, 175 and 410 us.)  Which products, and how many shares of up to two counts, is the shortest time of

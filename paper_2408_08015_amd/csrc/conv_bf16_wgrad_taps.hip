@@ -11,10 +11,12 @@
 //
 // A block owns one 32 x 32 tile and a range of the order; its four wavefronts take every fourth step of 16 pixels, and are added
 // through LDS in a fixed order.  Partials [range][tap][co][ci], and the column sums of dy [range][co] from the blocks of the
-// first input-channel tile.  The next chunk of both operands is copied to LDS while this one is multiplied: with 256 pixels to
-// a chunk, 52 KB a block and two blocks on a compute unit, the copies of one hide behind the products of both.
+// first input-channel tile.  The next chunk of both operands (256 pixels, 52 KB of LDS a block) is requested before this one is
+// multiplied, but the compiler takes a transposed read for one that may see any copy in flight and waits for all of them
+// before the first: a block's copies hide behind the products of the other block on its compute unit, not behind its own.
 //
-// Bound by the LDS reads: one 16-pixel step reads 9 + 1 operands of 1 KB for nine products of 32 cycles.  96 -> 96 at 32 x 56x56: 32 us
+// Bound by that wait and by operand reads and products taking turns.  (The reads alone: one 16-pixel step reads 9 + 1 operands of
+// 1 KB for nine products of 32 cycles, 8 us of the 32 below at 128 bytes a clock.)  96 -> 96 at 32 x 56x56: 32 us
 // in 51 ranges, 520 TFLOP/s (tiles of 256 channels 74 us), at 6 x 45x45 10.8 us (20); 16 -> 32 at 32 x 56x56 9.8 us (57).
 #include "device_utils.h"
 #include "kernels_bf16.h"

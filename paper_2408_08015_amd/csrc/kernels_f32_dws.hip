@@ -6,16 +6,18 @@
 // both BatchNorms' statistics with block sums instead of partials in memory.  Forward: x (the first BatchNorm's input) in,
 // y (the convolution's output, kept for the backward) and z (the second activation's output) out.  Backward: g = dz, y, x in,
 // dx out; dW, dgamma and dbeta of both BatchNorms are added into G by the one block that owns the channel.  Results wait for
-// the sums in registers.
+// the sums in registers, or where those of a 1024-thread block (128) do not hold them, in scratch: in the build 14 of the 90
+// backward forms spill, most of them 5x5 (32 values, Q = 1 / 2 / 4: 88, 43 and 55 registers; stride 2 21 to 55), 3x3 of 32 values up to 13.
 //
 // Bound by memory where channels are large (3 and 4 passes over a tensor, where the launches that it replaces make 5 and 9), by
-// one chain of load, sum, multiply, sum, store where they are small, and for 5x5 backward by the 50 multiply-adds of a
-// pixel.  In the stages, us per launch, against the launches that it replaces (forward / backward):
-//   384 channels of 8 x 14x14   6.7 / 7.5     14.6 / 21      (before: statistics, convolution, normalisation; sums, convolution,
+// one chain of load, sum, multiply, sum, store where they are small, and for 5x5 backward by that scratch: 240 channels of 32 x
+// 30x30 read 121 MB and write 68 where the operands are 83 and 28, and take 47 us where those bytes are 22 and the multiply-adds 9.
+// In the stages, us per launch, against the launches that it replaces (forward / backward):
+//   384 channels of 8 x 14x14   7.3 / 7.8     14.6 / 21      (before: statistics, convolution, normalisation; sums, convolution,
 //   960 of 8 x 7x7              6.9 / 7.0     15 / 22         input gradient of the first BatchNorm)
-//   192 of 32 x 28x28           17.7 / 23     30 / 50        58 and 77 MB
-//   144 of 8 x 56x56            16.0 / 21.4   26 / 36
-//   240 of 32 x 30x30, 5x5      30 / 54       52 / 76
+//   192 of 32 x 28x28           18.1 / 23.7   30 / 50        58 and 77 MB
+//   144 of 8 x 56x56            16.3 / 22.5   26 / 36
+//   240 of 32 x 30x30, 5x5      30 / 47       52 / 76
 // (dws_faster: where the one launch is not taken.)
 #include <algorithm>
 #include <climits>
@@ -422,7 +424,7 @@ __global__ __launch_bounds__(T) void dws_bwd_kernel(BwdArgs a, Geom g) {
   float mean1, istd1, sc1, sf1, gamma1, gb1, gg1, gw, wk[KK];
 
   // x as the strips need it, held to the end (past the end of a band or a plane: some row or column of it, not used).
-  // Requested with y and g, or, where that would spill registers, as soon as theirs are free.
+  // Requested with y and g, or, where that would spill (more) registers, as soon as theirs are free.
   constexpr bool LATE = V >= 16 && (K == 5 || (V == 32 && Q < 4));
   auto load_x = [&] {
     const int last = max(st.rows, 1) - 1;
