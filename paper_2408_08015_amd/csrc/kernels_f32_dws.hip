@@ -584,8 +584,9 @@ Pick pick(bool bwd, int K, int N, int C, int H, int W, int S) {
   const long E = (long)N * H * W, Eo = (long)N * Ho * Wo, held = (long)N * h * w;
   Pick p;
   if (E > 32768) return p;
-  // strips: whole ones in every row, words of planes aligned
-  const bool even = W == S * Wo && (Ho * Wo) % 4 == 0 && (H * W) % 4 == 0;
+  // strips: whole ones in every row, words of planes aligned, and (stride 2) no quad that reaches past the last row or column:
+  // single ones check for that, wider strips would write the row behind a plane
+  const bool even = H == S * Ho && W == S * Wo && (Ho * Wo) % 4 == 0 && (H * W) % 4 == 0;
   p.Q = even && Wo % 4 == 0 ? 4 : even && Wo % 2 == 0 ? 2 : 1;
   p.g = {N, C, H, W, Ho, Wo, div_by(H * W), 1.0 / (double)E, 1.0 / (double)Eo, (float)(E > 1 ? (double)E / (E - 1) : 1.0),
          (float)(Eo > 1 ? (double)Eo / (Eo - 1) : 1.0), padded(N, h, w, pad, p.Q), {}};

@@ -44,6 +44,11 @@ FORMS = [
     ((5, 2, 4, 15, 15, 8), (1, 512, 4), (1, 256, 4)),
     ((5, 2, 2, 60, 60, 8), (2, 1024, 32), (2, 1024, 8)),
     ((5, 2, 2, 24, 32, 40), (4, 1024, 32), (4, 1024, 8)),
+    ((3, 2, 4, 7, 28, 8), (1, 512, 4), (1, 256, 4)),        # an odd number of rows of an even number of columns: single ones,
+    ((5, 2, 3, 5, 24, 6), (1, 256, 4), (1, 256, 4)),        # as the quads of the last row reach past it
+    ((3, 2, 2, 47, 56, 9), (1, 1024, 32), (1, 1024, 8)),
+    ((3, 2, 3, 28, 8, 9), (4, 512, 4), (4, 256, 4)),
+    ((3, 1, 3, 9, 28, 11), (4, 512, 8), (4, 512, 8)),
     ((3, 1, 2, 45, 45, 16), None, None),                    # no thread for every strip
     ((3, 1, 2, 56, 56, 11), None, None),                    # a channel larger than a block
 ]
